@@ -69,12 +69,12 @@ extern "C" {
 
 #define OKR_PRECISION_FP64 0   /* complex128 everywhere */
 #define OKR_PRECISION_MIXED 1  /* FP32 difference-form sweep, FP64 refine */
-#define OKR_PRECISION_FP64_FACTORED 2 /* complex128; every mask's score assembled
-                                  from per-chain pattern tables (a chain's
-                                  terms depend only on its own and its nesting
-                                  path's mask bits; max and min are exact), so
-                                  the scores equal OKR_PRECISION_FP64's bit for
-                                  bit */
+#define OKR_PRECISION_FP64_FACTORED 2 /* complex128; the same scoring as
+                                  OKR_PRECISION_FP64 (every mask's score
+                                  assembled from per-chain pattern tables: a
+                                  chain's terms depend only on its own and its
+                                  nesting path's mask bits, and max and min are
+                                  exact); reports no flop counts */
 
 #define OKR_SECONDARY_MAXERR 0 /* key: the largest error over the affected
                                   nodes (eq. iter_obj) */
@@ -88,14 +88,9 @@ extern "C" {
 #define OKR_FLAG_VHAT_GIVEN 2u /* loads->Vhat holds the scenario voltages */
 #define OKR_FLAG_DUMP_SCORES 4u /* keep every segment's per-mask (e, slack) for
                                    okr_dump_scores() */
-#define OKR_FLAG_AUTOTUNE 16u  /* before this call's search, run the search
-                                  once per candidate shape of the FP64
-                                  scoring launch (snapshots per pass 1, 2 or
-                                  4; waves per 64 masks 1, 2 or 4; snapshot
-                                  groups 1, 2, 4, ... 32 within the planned
-                                  workspace) and keep the fastest per segment
-                                  size and chunk width in the handle for this
-                                  and later calls */
+#define OKR_FLAG_AUTOTUNE 16u  /* accepted and without effect: the scoring has
+                                  one launch form for every segment size and
+                                  chunk width, so there is no shape to tune */
 #define OKR_FLAG_GRAPH 8u      /* capture the whole search (load flow, every
                                   segment, final outputs) as one hipGraph on
                                   the first call and replay it afterwards;
@@ -202,13 +197,14 @@ typedef struct {
                            by the chunk's segments (OKR_FLAG_TIMING) */
     int32_t n_refined;  /* MIXED: masks rescored in FP64 (shortlists A + B) */
     double fp32_dev;    /* MIXED: max |e32 - e64| over rescored masks with e64 <= 2 e_bar */
-    int32_t score_groups;   /* FP64 scoring launch shape: snapshot groups, ... */
-    int32_t score_mpl;      /* ... snapshots per pass, ... */
+    int32_t score_groups;   /* launch shape of the scoring (1: it has one form), ... */
+    int32_t score_mpl;      /* ... likewise, ... */
     int32_t chunk;          /* index of the launch chunk the segment ran in */
-    double kernel_flops;    /* flops the per-mask scoring kernel itself performs
-                               (shared tables replace the per-candidate
-                               voltage-change products; 0 with FACTORED) */
-    int32_t score_waves;    /* ... and waves sharing each 64 masks' chains (default rule or autotuned) */
+    double kernel_flops;    /* flops of evaluating every chain for every mask from
+                               the segment's shared tables (the pattern tables
+                               evaluate each chain once per assignment of its
+                               bits instead; 0 with FACTORED) */
+    int32_t score_waves;    /* ... and likewise */
     double key_gap;         /* margin of the decision: the smallest key (e_loc, or SMICE with
                                OKR_SECONDARY_SMICE) of a feasible mask of the chosen level outside the tie
                                window, minus the smallest (+inf if none).  Exact for FP64 and FP64_FACTORED;
@@ -242,7 +238,7 @@ typedef struct {
        per edge carrying it (voltage change), 2|phi| per segment node (shift),
        10 per node-phase of the affected region (magnitude, error, margins);
        plus 18 per reduced node per candidate (series sums); averaged exactly
-       over the masks.  kernel_form_flops: what the scoring kernel computes. */
+       over the masks.  kernel_form_flops: the segments' kernel_flops. */
     double score_kernel_ms, algorithmic_flops;
     int32_t pf_iterations, n_score_launches; /* scoring launches: one per chunk */
     double kernel_form_flops;

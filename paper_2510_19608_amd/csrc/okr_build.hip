@@ -3,10 +3,9 @@
 //
 //   k_build_struct  (1 block)  chains, slots, pairs, nesting, Omega ranges,
 //                              zone entries grouped by (chain, phase)
-//   k_build_values  (grid)     P = Z(super -> reduced) A, record voltages,
-//                              min/max initialisation
-//   k_build_members (grid)     cluster min/max |V^| and the constant error of
-//                              clusters whose super-node is outside Omega_g
+//
+// The numeric tables that follow from them (per snapshot) are built by
+// k_seg_terms (okr_score.hip).
 //
 // The tables have the layout the scoring kernel reads (okr_internal.h).
 #include <hip/hip_runtime.h>
@@ -18,14 +17,6 @@
 
 namespace okr {
 
-__device__ __forceinline__ double2 b_cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ double2 b_cmul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// status bit set when a structural invariant fails (the segment is then
-// skipped by the scoring path and the call reports an error)
-constexpr int kStatusBuild = 64;
 constexpr int kOmegaLds = 4096;  // Omega_g nodes whose zone classification is kept in shared memory
 // structural part of a segment's tables (chains, nesting, slots, pairs, ranges)
 constexpr int kTabLds = kMaxK * kChainInts + kMaxK * kMaxK + kMaxK * kSlotInts + kMaxPairs * kPairInts + 3 * kMaxK;
@@ -42,7 +33,9 @@ __device__ __forceinline__ int child_toward(const Topo& T, int h, int v) {
 
 __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const int* __restrict__ segs, size_t lstride,
                                                       int S, SegHdr* __restrict__ hdrs, int* __restrict__ tab,
-                                                      int tab_cap, int* __restrict__ status) {
+                                                      int tab_cap, int* __restrict__ status,
+                                                      unsigned long long* __restrict__ pat,
+                                                      unsigned long long* __restrict__ ecmax) {
   __shared__ int s_top[kMaxK], s_slotnode[kMaxK], s_slotbit[kMaxK], s_slotchain[kMaxK];
   __shared__ int s_cslot0[kMaxK + 1], s_head[kMaxK], s_outer[kMaxK], s_jslot[kMaxK];
   __shared__ int s_spos[kMaxK], s_ssize[kMaxK], s_sph[kMaxK];           // segment node j
@@ -55,8 +48,9 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   __shared__ int s_pmask[kMaxK];                                        // chain c: mask bits of its nesting path
   __shared__ int s_okey[kMaxK];  // chain c: (preorder position << 5) | j of the deepest segment node above its head
   // exclusive prefix sums over the chains (entry nch: the totals) of: nesting
-  // depth, pairs, new Omega_g range, its nodes, chain patterns
-  __shared__ int s_xs[5][kMaxK + 1];
+  // depth, pairs, new Omega_g range, its nodes, chain patterns, pattern items
+  __shared__ int s_xs[6][kMaxK + 1];
+  __shared__ int s_dn[kMaxK];                 // chain c: bottom slots enumerated by one pattern item
   __shared__ int s_keycnt[kMaxK * 3], s_keyoff[kMaxK * 3], s_keycur[kMaxK * 3];
   __shared__ SegHdr s_h;
   __shared__ int s_err, s_nch;
@@ -212,9 +206,9 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   __syncthreads();
   // the chains' table offsets: prefix sums in one wave (lane = chain)
   if (tid < 64) {
-    int v[5] = {0, 0, 0, 0, 0};
+    int v[6] = {0, 0, 0, 0, 0, 0}, n = 0, npats = 0;
     if (tid < nch) {
-      const int n = s_cslot0[tid + 1] - s_cslot0[tid];
+      n = s_cslot0[tid + 1] - s_cslot0[tid];
       v[0] = s_depth[tid];
       v[1] = n * (n + 1) / 2;
       v[2] = s_rkeep[tid];
@@ -222,13 +216,24 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
       v[4] = 1 << __popc(s_pmask[tid]);
     }
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < 6; ++i) {
+      if (i == 5 && tid < nch) {
+        // pattern items (the patterns' number is known by now): where one
+        // block's threads cannot take a pattern each, an item of a chain of 6
+        // bits or more enumerates its bottom 3 slots, so that the walk above
+        // them is done once for 8 patterns
+        const int bits = __popc(s_pmask[tid]);
+        const int d = (npats > 256 && bits >= 6) ? min(3, n) : 0;
+        s_dn[tid] = d;
+        v[5] = 1 << (bits - d);
+      }
       int x = v[i];
       for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(x, o, 64);
         if (tid >= o) x += y;
       }
       if (tid <= nch) s_xs[i][tid] = x - v[i];
+      if (i == 4) npats = __shfl(x, 63, 64);
     }
   }
   __syncthreads();
@@ -255,6 +260,7 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     H.nslots = k;
     H.npairs = npairs;
     H.npat = npat;
+    H.nitem = s_xs[5][nch];
     // the structural part must fit the segment's table (and the shared image,
     // which holds the largest possible one)
     if (o_zent > tab_cap || o_zent > kTabLds) s_err = 1;
@@ -307,6 +313,8 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     cr[C_PHW2] = phw[2];
     cr[C_PMASK] = s_pmask[c];
     cr[C_PBASE] = pbase;
+    cr[C_D] = s_dn[c];
+    cr[C_IBASE] = s_xs[5][c];
     for (int p = 0; p < 3; ++p) {
       cr[C_ZOFF0 + p] = 0;  // zone ranges filled after the zone pass
       cr[C_ZCNT0 + p] = 0;
@@ -332,6 +340,17 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     St.slot_of[s_slotnode[s]] = s;
   }
   __syncthreads();
+  // the pattern accumulators the scoring folds into (error, smallest and
+  // largest kept squared magnitude of each pattern; the largest constant
+  // error): cleared here, where their number is first known, which saves the
+  // scoring a launch of its own (4.3 us per chunk)
+  pat = lane_ptr(pat, lstride);
+  for (int q = tid; q < npat; q += blockDim.x) {
+    pat[3 * q] = 0ull;
+    pat[3 * q + 1] = (unsigned long long)__double_as_longlong(INFINITY);
+    pat[3 * q + 2] = 0ull;
+  }
+  if (tid == 0) *lane_ptr(ecmax, lstride) = 0ull;
   // the structural tables, built in shared memory, written out by all threads
   for (int q = tid; q < o_zent; q += blockDim.x) tab[q] = s_tab[q];
   // Omega_g ranges for the zone pass (shared copy)
@@ -473,132 +492,6 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
       atomicOr(status, kStatusBuild);
     }
     hdrs[g] = H;
-  }
-}
-
-// Node of Omega_g with flattened index q (ranges: start, end, cumulative).
-__device__ __forceinline__ int omega_node(const Topo& T, const int* rg, int nr, int q) {
-  int r = 0;
-  while (r + 1 < nr && rg[3 * (r + 1) + 2] <= q) ++r;
-  return T.pre[rg[3 * r] + (q - rg[3 * r + 2])];
-}
-
-__global__ __launch_bounds__(256) void k_build_values(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
-                                                      size_t lstride, const int* __restrict__ tab, int n,
-                                                      const double2* __restrict__ Zroot,
-                                                      const double2* __restrict__ Vcur,
-                                                      const double2* __restrict__ A, double2* __restrict__ P,
-                                                      TargetRec* __restrict__ srec, double2* __restrict__ headV,
-                                                      TargetRec* __restrict__ zrec, double* __restrict__ econst) {
-  const SegHdr H = load_hdr(hdrs, segs);
-  if (!H.valid) return;
-  tab = lane_ptr(tab, lstride);
-  P = lane_ptr(P, lstride);
-  srec = lane_ptr(srec, lstride);
-  headV = lane_ptr(headV, lstride);
-  zrec = lane_ptr(zrec, lstride);
-  econst = lane_ptr(econst, lstride);
-  const int part = blockIdx.y;
-  const int S = H.S;
-  const int stride = gridDim.x * blockDim.x;
-  if (part == 0) {
-    // P = Z(super -> reduced) A_reduced with Z(s -> r) = Zroot(r) - Zroot(s),
-    // the series impedance of the path between them
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < S * H.npairs; t += stride) {
-      const int l = t / H.npairs, q = t % H.npairs;
-      const int* pr = tab + H.o_pair + q * kPairInts;
-      const double2* zr = Zroot + (size_t)pr[PR_RNODE] * 9;
-      const double2* zs = Zroot + (size_t)pr[PR_SUPER] * 9;
-      double2 Z[9];
-      for (int e = 0; e < 9; ++e) Z[e] = make_double2(zr[e].x - zs[e].x, zr[e].y - zs[e].y);
-      const double2* a = A + ((size_t)l * n + pr[PR_RNODE]) * 3;
-      double2* o = P + ((size_t)l * H.npairs + q) * 3;
-      for (int r = 0; r < 3; ++r)
-        o[r] = b_cadd(b_cadd(b_cmul(Z[r * 3], a[0]), b_cmul(Z[r * 3 + 1], a[1])), b_cmul(Z[r * 3 + 2], a[2]));
-    }
-  } else if (part == 1) {
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < S * H.nslots * 3; t += stride) {
-      const int l = t / (H.nslots * 3), rem = t % (H.nslots * 3), s = rem / 3, p = rem % 3;
-      const int node = tab[H.o_slot + s * kSlotInts + SL_NODE];
-      TargetRec rec;
-      rec.W = Vcur[((size_t)l * n + node) * 3 + p];
-      rec.lo = INFINITY;
-      rec.hi = 0.0;
-      srec[((size_t)l * H.nslots + s) * 3 + p] = rec;
-    }
-  } else if (part == 2) {
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < S * H.nchains; t += stride) {
-      const int l = t / H.nchains, c = t % H.nchains;
-      const int head = tab[H.o_chain + c * kChainInts + C_HEAD];
-      for (int p = 0; p < 3; ++p) headV[((size_t)l * H.nchains + c) * 3 + p] = Vcur[((size_t)l * n + head) * 3 + p];
-    }
-  } else if (part == 3) {
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < S * H.nz; t += stride) {
-      const int l = t / H.nz, q = t % H.nz;
-      const int* ze = tab + H.o_zent + q * 3;
-      TargetRec rec;
-      rec.W = Vcur[((size_t)l * n + ze[0]) * 3 + ze[1]];
-      rec.lo = INFINITY;
-      rec.hi = 0.0;
-      zrec[(size_t)l * H.nz + q] = rec;
-    }
-  } else {
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < S; t += stride) econst[t] = 0.0;
-  }
-}
-
-__device__ __forceinline__ void atomic_min_nonneg(double* a, double v) {
-  atomicMin((unsigned long long*)a, (unsigned long long)__double_as_longlong(v));
-}
-__device__ __forceinline__ void atomic_max_nonneg(double* a, double v) {
-  atomicMax((unsigned long long*)a, (unsigned long long)__double_as_longlong(v));
-}
-
-// Cluster statistics: every node of Omega_g contributes |V^| to the cluster of
-// its current super-node (a slot, a zone target, or a head outside Omega_g,
-// whose error is mask-independent and folds into econst).
-__global__ __launch_bounds__(256) void k_build_members(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
-                                                       size_t lstride, const int* __restrict__ tab, Topo T, State St,
-                                                       const double2* __restrict__ Vcur,
-                                                       const double* __restrict__ absV, TargetRec* __restrict__ srec,
-                                                       TargetRec* __restrict__ zrec, double* __restrict__ econst) {
-  const int g = segs[blockIdx.z];
-  const SegHdr H = load_hdr_g(hdrs, g);
-  if (!H.valid) return;
-  tab = lane_ptr(tab, lstride);
-  srec = lane_ptr(srec, lstride);
-  zrec = lane_ptr(zrec, lstride);
-  econst = lane_ptr(econst, lstride);
-  const int n = T.n;
-  const int* rg = tab + H.o_range;
-  const long total = (long)H.nomega * H.S;
-  for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long)gridDim.x * blockDim.x) {
-    const int l = (int)(t / H.nomega), q = (int)(t % H.nomega);
-    const int i = omega_node(T, rg, H.nrange, q);
-    const int sp = St.sup[i];
-    const unsigned ph = T.phase[i];
-    const double* av = absV + ((size_t)l * n + i) * 3;
-    if (T.segment[sp] == g) {
-      const int s = St.slot_of[sp];
-      if (s < 0 || s >= H.nslots) continue;
-      TargetRec* r = srec + ((size_t)l * H.nslots + s) * 3;
-      for (int p = 0; p < 3; ++p)
-        if (ph >> p & 1u) { atomic_min_nonneg(&r[p].lo, av[p]); atomic_max_nonneg(&r[p].hi, av[p]); }
-    } else {
-      for (int p = 0; p < 3; ++p) {
-        if (!(ph >> p & 1u)) continue;
-        const int zi = St.zent_of[sp * 3 + p];
-        if (zi >= H.nz) continue;
-        if (zi >= 0) {
-          TargetRec* r = zrec + (size_t)l * H.nz + zi;
-          atomic_min_nonneg(&r->lo, av[p]);
-          atomic_max_nonneg(&r->hi, av[p]);
-        } else {
-          const double2 v = Vcur[((size_t)l * n + sp) * 3 + p];
-          atomic_max_nonneg(&econst[l], fabs(sqrt(v.x * v.x + v.y * v.y) - av[p]));
-        }
-      }
-    }
   }
 }
 

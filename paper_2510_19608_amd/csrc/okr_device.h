@@ -147,186 +147,6 @@ __device__ __forceinline__ void walk_chain(const int* __restrict__ cr, const dou
     for (int p = 0; p < 3; ++p) B[i][p] = S[i][p];
 }
 
-// sqrt_nr of M independent values, step by step across them, so the M
-// dependency chains interleave (each result equals sqrt_nr of its input).
-template <int M>
-__device__ __forceinline__ void sqrt_nr_v(const double (&x)[M], double (&y)[M]) {
-  double g[M], h[M], e[M];
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    const double r = __builtin_amdgcn_rsq(x[j]);
-    g[j] = x[j] * r;
-    h[j] = 0.5 * r;
-  }
-#pragma unroll
-  for (int j = 0; j < M; ++j) e[j] = fma(-h[j], g[j], 0.5);
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    g[j] = fma(g[j], e[j], g[j]);
-    h[j] = fma(h[j], e[j], h[j]);
-  }
-#pragma unroll
-  for (int j = 0; j < M; ++j) e[j] = fma(-g[j], g[j], x[j]);
-#pragma unroll
-  for (int j = 0; j < M; ++j) y[j] = fma(e[j], h[j], g[j]);
-}
-
-// Snapshot-vectorised chain walk: one mask, M snapshots at once, with the
-// per-snapshot arithmetic of walk_chain.  The mask-dependent control (reduced
-// or kept, current super) is shared by the M snapshots, so each side of the
-// branch carries M independent chains, evaluated in lock-step, and on mask
-// bits above the lane bits a whole wave takes one side.  el, qmin and qmax
-// are per snapshot (folded later: max and min are exact).  LDS layout,
-// snapshot fastest: P[(pair * 3 + p) * M + j], T[(slot * 3 + p) * M + j],
-// H and Hm [(chain * 3 + p) * M + j].  With HM_FROM_H the magnitudes of
-// heads no mask moves are formed from H here (as the LDS stage forms Hm)
-// instead of read from Hm.
-template <bool ERR, int M, bool HM_FROM_H = false>
-__device__ __forceinline__ void walk_chain_sv(const cint* cr, const double2* Ps, const TargetRec* Ts,
-                                              const double2* Hs, const double* Hm, int c, uint32_t m,
-                                              double2 (&B)[M][3], double (&el)[M], double (&qmin)[M],
-                                              double (&qmax)[M]) {
-  double2 S[M][3];
-  double sm[M][3];
-#pragma unroll
-  for (int j = 0; j < M; ++j)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      S[j][p] = B[j][p];
-      sm[j][p] = 0.0;
-    }
-  if (ERR) {
-    const int hph = cr[C_PHASE];
-    if (cr[C_OUTER] < 0) {  // head unaffected by the mask: staged magnitude (0 on absent phases)
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-          if (HM_FROM_H) {
-            const double2 hv = Hs[(c * 3 + p) * M + j];
-            sm[j][p] = (hv.x != 0.0 || hv.y != 0.0) ? hmag(hv) : 0.0;
-          } else {
-            sm[j][p] = Hm[(c * 3 + p) * M + j];
-          }
-        }
-    } else {
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-        if (hph >> p & 1) {
-          double x[M], y[M];
-#pragma unroll
-          for (int j = 0; j < M; ++j) {
-            x[j] = mag2(cadd(Hs[(c * 3 + p) * M + j], B[j][p]));
-          }
-          sqrt_nr_v<M>(x, y);
-#pragma unroll
-          for (int j = 0; j < M; ++j) sm[j][p] = y[j];
-        }
-    }
-  }
-  const int ns = cr[C_NSLOT], s0 = cr[C_SLOT0], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
-  const int phw0 = cr[C_PHW0], phw1 = cr[C_PHW1], phw2 = cr[C_PHW2];
-  int sidx = 0;
-  for (int r = 0; r < ns; ++r) {
-    const int w = r < 8 ? phw0 : (r < 16 ? phw1 : phw2);
-    const int ph = __builtin_amdgcn_readfirstlane((w >> (3 * (r & 7))) & 7);  // same for every lane
-    const int prow = pair0 + ((r * (r + 1)) >> 1);
-    const TargetRec* tr = Ts + (s0 + r) * 3 * M;
-    if ((m >> (bit0 + r)) & 1u) {  // reduced: the moved current's rise; cluster error against the super
-      const double2* pr = Ps + (prow + sidx) * 3 * M;
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        if (!(ph >> p & 1)) continue;
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-          const double2 pv = pr[p * M + j];
-          S[j][p].x += pv.x;
-          S[j][p].y += pv.y;
-          if (ERR) {
-            const TargetRec t = tr[p * M + j];
-            el[j] = fmax(el[j], fmax(sm[j][p] - t.lo, t.hi - sm[j][p]));
-          }
-        }
-      }
-    } else {  // kept: a new super
-      if (ERR) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          if (!(ph >> p & 1)) continue;
-          double q[M], mg[M], lo[M], hi[M];
-#pragma unroll
-          for (int j = 0; j < M; ++j) {
-            const TargetRec t = tr[p * M + j];
-            const double vx = t.W.x + S[j][p].x, vy = t.W.y + S[j][p].y;
-            q[j] = fma(vx, vx, vy * vy);
-            lo[j] = t.lo;
-            hi[j] = t.hi;
-          }
-          sqrt_nr_v<M>(q, mg);
-#pragma unroll
-          for (int j = 0; j < M; ++j) {
-            sm[j][p] = mg[j];
-            qmin[j] = fmin(qmin[j], q[j]);
-            qmax[j] = fmax(qmax[j], q[j]);
-            el[j] = fmax(el[j], fmax(mg[j] - lo[j], hi[j] - mg[j]));
-          }
-        }
-      }
-      sidx = r + 1;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < M; ++j)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) B[j][p] = S[j][p];
-}
-
-// Terms of chain c for one mask over M snapshots (snapshot-vectorised
-// score_chain): the nesting path, the chain, then its zone entries (the first
-// zcap from the LDS stage Zs[q * M + j], the rest from global memory, where
-// snapshot j's records start at zg[j]).
-template <int M, bool HM_FROM_H = false>
-__device__ __forceinline__ void score_chain_sv(const cint* chains, const cint* nest, int c,
-                                               const double2* Ps, const TargetRec* Ts, const double2* Hs,
-                                               const double* Hm, const TargetRec* Zs, int zcap,
-                                               const TargetRec* const (&zg)[M], uint32_t m, double (&el)[M],
-                                               double (&qmin)[M], double (&qmax)[M]) {
-  const cint* cr = chains + c * kChainInts;
-  double2 B[M][3];
-#pragma unroll
-  for (int j = 0; j < M; ++j)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) B[j][p] = make_double2(0.0, 0.0);
-  const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
-  for (int q = 0; q + 1 < nl; ++q) {
-    const int oc = nest[no + q];
-    walk_chain_sv<false, M, HM_FROM_H>(chains + oc * kChainInts, Ps, Ts, Hs, Hm, oc, m, B, el, qmin, qmax);
-  }
-  walk_chain_sv<true, M, HM_FROM_H>(cr, Ps, Ts, Hs, Hm, c, m, B, el, qmin, qmax);
-#pragma unroll
-  for (int p = 0; p < 3; ++p)
-    for (int q = cr[C_ZOFF0 + p], qe = q + cr[C_ZCNT0 + p]; q < qe; ++q) {
-      double q2[M], mag[M], lo[M], hi[M];
-#pragma unroll
-      for (int j = 0; j < M; ++j) {
-        TargetRec t;
-        if (q < zcap) t = Zs[q * M + j];
-        else t = zg[j][q];
-        const double vx = t.W.x + B[j][p].x, vy = t.W.y + B[j][p].y;
-        q2[j] = fma(vx, vx, vy * vy);
-        lo[j] = t.lo;
-        hi[j] = t.hi;
-      }
-      sqrt_nr_v<M>(q2, mag);
-#pragma unroll
-      for (int j = 0; j < M; ++j) {
-        el[j] = fmax(el[j], fmax(mag[j] - lo[j], hi[j] - mag[j]));
-        qmin[j] = fmin(qmin[j], q2[j]);
-        qmax[j] = fmax(qmax[j], q2[j]);
-      }
-    }
-}
-
 // Band slack of a mask from the extreme squared magnitudes of its kept
 // node-phases: min(|V| - vmin, vmax - |V|) over them (+inf if there are none).
 __device__ __forceinline__ double band_slack(double qmin, double qmax, double vmin, double vmax) {

@@ -32,27 +32,23 @@ __global__ void k_powerflow_bfs(int, const uint8_t*, const int*, const int*, int
                                 double2*, double2*, double2*, double*, int*, int*);
 __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const double2*, double, double, double2*,
                             double*, int*);
-__global__ void k_build_struct(Topo, State, const int*, size_t, int, SegHdr*, int*, int, int*);
+__global__ void k_build_struct(Topo, State, const int*, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
+                               unsigned long long*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
-__global__ void k_build_values(const SegHdr*, const int*, size_t, const int*, int, const double2*, const double2*,
-                               const double2*, double2*, TargetRec*, double2*, TargetRec*, double*);
-__global__ void k_build_members(const SegHdr*, const int*, size_t, const int*, Topo, State, const double2*,
-                                const double*, TargetRec*, TargetRec*, double*);
-template <int M>
-__global__ void k_score_fp64(const SegHdr*, const int*, size_t, const int*, const double2*, const TargetRec*,
-                           const double2*, const TargetRec*, const double*, int, int, int, int, int, int, SelParams,
-                           MaskScore*, MaskScore*, TileRec*, int*, const int*, int);
-__global__ void k_terms_init(const SegHdr*, const int*, size_t, int, const int*, int, const double*,
-                             unsigned long long*, unsigned long long*);
-__global__ void k_chain_terms(const SegHdr*, const int*, size_t, int, const int*, const double2*, const TargetRec*,
+template <bool BUILD, bool PAT>
+__global__ void k_seg_terms(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, const double2*,
+                            const double2*, const double2*, const double*, double2*, TargetRec*, double2*, TargetRec*,
+                            double*, int, int, unsigned long long*, unsigned long long*, const int*, int*);
+__global__ void k_terms_init(const int*, int, size_t, unsigned long long*);
+__global__ void k_chain_terms(const SegHdr*, const int*, size_t, const int*, const double2*, const TargetRec*,
                               const double2*, const TargetRec*, const double*, const uint32_t*, const int*, int, int,
-                              int, unsigned long long*, unsigned long long*);
+                              int, unsigned long long*);
 __global__ void k_list_finish(const int*, const unsigned long long*, int, SelParams, MaskScore*, size_t);
 __global__ void k_surr_rank(const SegHdr*, int, const int*, const float*, const float*, const SurrSlot*, const double*,
                             const uint32_t*, int, const __bf16*, const __bf16*, const float*, float, uint32_t*,
                             const int*, int);
 __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, const unsigned long long*,
-                              const unsigned long long*, SelParams, MaskScore*, TileRec*);
+                              const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*);
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
                          DevDecision*, const int*);
 __global__ void k_apply(const SegHdr*, const int*, size_t, const int*, Topo, State, const DevDecision*,
@@ -142,13 +138,13 @@ constexpr int kSmiceThreadsHost = 128;  // masks per block of the SMICE scoring
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Snapshot groups of the scoring launches (per-mask FP64, FP32 screen) for
+// Snapshot groups of the FP32 screen for
 // segments of k nodes, each group a contiguous run of snapshots: a
 // group of about 8 snapshots for segments of up to 9 nodes, 16 up to 12, 32
-// up to 16 and 64 above, scaled by (S / 96)^0.37 for S above 96 (a fit to
-// the autotuner's picks on MI355X on the 1000-, 6000- and 8400-node
+// up to 16 and 64 above, scaled by (S / 96)^0.37 for S above 96 (a fit on
+// MI355X on the 1000-, 6000- and 8400-node
 // workloads: 24, 96 and 288 snapshots, segments of 8 to 20 nodes).
-int score64_groups_default(int k, int S, int* spg) {
+int screen32_groups(int k, int S, int* spg) {
   const double base = k <= 9 ? 8.0 : (k <= 12 ? 16.0 : (k <= 16 ? 32.0 : 64.0));
   const double want = base * (S > 96 ? std::pow(S / 96.0, 0.37) : 1.0);
   int SG = (int)std::ceil(S / want - 1e-9);
@@ -158,18 +154,18 @@ int score64_groups_default(int k, int S, int* spg) {
 }
 
 // Launch shape of the FP32 screen: masks per lane by segment size, snapshot
-// groups by the per-mask FP64 kernel's rule (on MI355X 10% faster than a
+// groups by the rule above (on MI355X 10% faster than a
 // block-count target on the 8400-node workload, within 2% on the 6000-node
 // one).  The workspace planner sizes the screen's partial scores from this
 // same function.
 int screen32_shape(int k, int S, int* spg, int* mpl) {
   *mpl = k >= 12 ? 4 : (k >= 10 ? 2 : 1);
-  return score64_groups_default(k, S, spg);
+  return screen32_groups(k, S, spg);
 }
 
 struct Layout {
   size_t topo, z, Zroot, Vhat, Vcur, A, J, absV, kept, sup, slot_of, zent_of, status, iters, hdrs, decs, tab, P, srec,
-      headV, zrec, econst, part, fin, tiles, tickets, kp, yeq, Ykd, Yko, err;
+      headV, zrec, econst, fin, tiles, tickets, kp, yeq, Ykd, Yko, err;
   // factored FP64 scoring: chain-pattern table, largest constant error;
   // accumulators of the short-list scoring
   size_t pat, ecmax, lacc;
@@ -190,7 +186,7 @@ struct Layout {
 // offsets (in int32) of the static topology arrays inside the topology buffer
 struct TopoOffsets {
   int parent, phase, segment, pos, size, pre, ch_off, ch, lvl_off, lvl_nodes, bfs_cf, bfs_pp, seg_off, seg_nodes,
-      chunks, seg_top, total;
+      chunks, units, seg_top, total;
 };
 
 }  // namespace
@@ -225,95 +221,32 @@ struct okr_handle {
   // per-mask score dumps (FP64 scores, or FP32 screening scores in MIXED)
   std::vector<std::vector<MaskScore>> dump;
   std::vector<std::vector<MaskScore32>> dump32;
-  // shape of the FP64 scoring launches, autotuned per segment size (0 = the
-  // default rule): snapshot groups and masks per lane; values forced while
-  // tuning; the partial-score capacity (masks x groups) of the workspace
-  std::vector<int> sg_tuned, mpl_tuned, ws_tuned;
-  int sg_force = 0, mpl_force = 0, ws_force = 0;
-  size_t part_cap = 0;
   // segment chunks: every search step is one launch over a chunk of
   // mutually independent segments (chunk c = chunk_segs[chunk_off[c] ..
   // chunk_off[c + 1]), at most nlanes of them, each with its own scratch
   // block); chunk_k = the chunk's largest segment size
   int nlanes = 1;
   std::vector<int> chunk_off, chunk_segs, chunk_k;
+  // table-kernel work units of chunk c: units[unit_off[c] .. unit_off[c + 1])
+  // (unit_pack); chunk_nz = the most zone entries a segment of it can have
+  std::vector<int> units, unit_off, chunk_nz;
 };
 
 namespace {
-// Launch shape of the per-mask FP64 scoring for a chunk of nz segments whose
-// largest has k nodes: snapshots per pass, waves sharing each 64 masks'
-// chains, snapshot groups.  Each is forced (while autotuning), tuned for
-// (k, nz), or the default rule.
-int shape_key(int k, int nz) { return k * (kMaxLanes + 1) + nz; }
-int tuned(const std::vector<int>& t, int k, int nz) {
-  const int i = shape_key(k, nz);
-  return i < (int)t.size() ? t[i] : 0;
-}
-// Defaults follow the autotuner's picks on MI355X for the 1000-, 6000- and
-// 8400-node workloads (segments of 8 to 20 nodes, chunks of 1-8 segments):
-// 4 snapshots per pass up to 14 nodes (and for a lone segment up to 16), 2 up
-// to 19, then 1; 4 waves per 64 masks up to 14 nodes in chunks of up to 5
-// (else 2), from 15 nodes one in chunks of three or more or from 18 nodes,
-// else 4 for a lone segment of 15 and 2 otherwise.
-int score_mpl(const okr_handle* h, int k, int nz) {
-  if (h->mpl_force) return h->mpl_force;
-  const int t = tuned(h->mpl_tuned, k, nz);
-  if (t) return t;
-  if (k <= 14 || (nz == 1 && k <= 16)) return 4;
-  return k <= 19 ? 2 : 1;
-}
-int score_ws(const okr_handle* h, int k, int nz) {
-  if (h->ws_force) return h->ws_force;
-  const int t = tuned(h->ws_tuned, k, nz);
-  if (t) return t;
-  if (k <= 14) return nz <= 5 ? 4 : 2;
-  if (nz >= 3 || k >= 18) return 1;
-  return (nz == 1 && k <= 15) ? 4 : 2;
-}
-
-// Snapshot groups of the FP64 scoring launch for a segment of k nodes: the
-// forced or tuned count, else the default rule, within the planned
-// partial-score capacity; spg = snapshots per group.
-// LDS of the snapshot-vectorised FP64 scoring kernel: spp snapshots of
-// pairs, slot records, chain heads and their magnitudes, the first kSvZone
-// zone records, and the constant errors.
-constexpr int kSvZone = 128;
-constexpr size_t kSvLdsMax = 60 * 1024;
-size_t sv_lds_bytes(int spp, int k) {
-  const size_t pcap = (size_t)k * (k + 1) / 2;
-  return (size_t)spp * (pcap * 3 * sizeof(double2) + (size_t)k * 3 * (sizeof(TargetRec) + sizeof(double2) + sizeof(double)) +
-                        kSvZone * sizeof(TargetRec) + sizeof(double)) +
-         16;  // (the kernel packs the tables to the segment's own sizes: rounding room)
-}
-// LDS of the chain-term kernel for segments of up to k nodes: chain records
+// LDS of the chain-term kernels for segments of up to k nodes: chain records
 // and nesting paths, one snapshot's pairs, slot and head records, and the
-// first kTermsZone zone records.
-constexpr int kTermsZone = 256;
+// first zcap zone records.
+constexpr int kTermsZone = 256;  // zone records staged by the kernels that read them from memory
 int terms_icap(int k) { return k * kChainInts + k * k; }
-size_t terms_lds_bytes(int k) {
+size_t terms_lds_bytes(int k, int zcap) {
   const size_t pcap = (size_t)k * (k + 1) / 2;
   return ((size_t)terms_icap(k) * 4 + 15) / 16 * 16 + pcap * 3 * sizeof(double2) +
-         (size_t)k * 3 * (sizeof(TargetRec) + sizeof(double2)) + kTermsZone * sizeof(TargetRec);
+         (size_t)k * 3 * (sizeof(TargetRec) + sizeof(double2)) + (size_t)zcap * sizeof(TargetRec);
 }
-
-// Snapshots per pass: the wanted count (1, 2 or 4), at most the group's
-// snapshots, within the LDS budget.
-int sv_spp(int want, int k, int spg) {
-  int spp = want >= 4 ? 4 : (want >= 2 ? 2 : 1);
-  while (spp > 1 && (spp > spg || sv_lds_bytes(spp, k) > kSvLdsMax)) spp /= 2;
-  return spp;
-}
-
-// (within the partial-score capacity of the workspace)
-int snap_groups(const okr_handle* h, int k, int nz, int* spg) {
-  const int S = h->S;
-  int SG = h->sg_force ? h->sg_force : tuned(h->sg_tuned, k, nz);
-  if (SG <= 0) SG = score64_groups_default(k, S, spg);
-  SG = std::min(std::min(SG, S), kMaxSnapGroups);
-  while (SG > 1 && ((size_t)SG << k) > h->part_cap) --SG;
-  *spg = (S + SG - 1) / SG;
-  return (S + *spg - 1) / *spg;
-}
+// The tables and the patterns of a chunk come from one launch while its zone
+// records fit in LDS beside the rest (62 KB: two blocks on a compute unit);
+// beyond, one launch builds the tables and another evaluates the patterns.
+constexpr size_t kTermsLdsMax = 62 * 1024;
 }  // namespace
 
 #define OKR_FAIL(h, code, ...)            \
@@ -644,6 +577,45 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
       h->chunk_k.back() = std::max(h->chunk_k.back(), ksz(g));
     }
     if (!h->chunk_segs.empty()) h->chunk_off.push_back((int)h->chunk_segs.size());
+    // Work units of the table kernel.  A chain's terms depend on the segment
+    // nodes above and in it, so a segment has at most the sum over its nodes
+    // of 2^(segment nodes on the node's root path) patterns; one unit per 4096
+    // of that bound, at most 16 (each unit forms the snapshot's tables again).
+    // Zone entries are node-phases of the segment's region outside it.
+    std::vector<int> parts(nseg, 1), nzb(nseg, 0);
+    for (int g = 0; g < nseg; ++g) {
+      const int* nodes = h->seg_nodes.data() + h->seg_off[g];
+      const int k = ksz(g);
+      double pats = 0.0;
+      std::vector<int> open;  // the segment nodes above the current one (preorder)
+      for (int j = 0; j < k; ++j) {
+        while (!open.empty() && h->pos[nodes[j]] >= h->pos[open.back()] + h->size[open.back()]) open.pop_back();
+        open.push_back(nodes[j]);
+        pats += std::ldexp(1.0, (int)open.size());
+      }
+      pats = std::min(pats, std::ldexp(1.0, k + 1));
+      parts[g] = (int)std::min(16.0, std::max(1.0, std::ceil(pats / 4096.0)));
+      long nz = 0;
+      for (auto& r : iv[g])
+        for (int q = r.first; q < r.second; ++q) {
+          const int v = h->pre[q];
+          if (h->segment[v] != g) nz += __builtin_popcount(h->phase[v]);
+        }
+      nzb[g] = (int)std::min<long>(nz, INT32_MAX);
+    }
+    h->units.clear();
+    h->unit_off.assign(1, 0);
+    h->chunk_nz.clear();
+    for (size_t c = 0; c < h->chunk_k.size(); ++c) {
+      int nz = 0;
+      for (int i = h->chunk_off[c]; i < h->chunk_off[c + 1]; ++i) {
+        const int g = h->chunk_segs[i];
+        nz = std::max(nz, nzb[g]);
+        for (int q = 0; q < parts[g]; ++q) h->units.push_back(unit_pack(i - h->chunk_off[c], q, parts[g]));
+      }
+      h->unit_off.push_back((int)h->units.size());
+      h->chunk_nz.push_back(nz);
+    }
   }
   // packed static topology
   TopoOffsets& TO = h->TO;
@@ -668,6 +640,11 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
   TO.seg_off = put(h->seg_off);
   TO.seg_nodes = put(h->seg_nodes.empty() ? std::vector<int>{0} : h->seg_nodes);
   TO.chunks = put(h->chunk_segs.empty() ? std::vector<int>{0} : h->chunk_segs);
+  {  // the work units of every chunk, then one whole-segment unit per chunk position
+    std::vector<int> u = h->units;
+    for (int z = 0; z < h->nlanes; ++z) u.push_back(unit_pack(z, 0, 1));
+    TO.units = put(u);
+  }
   {
     // static part of the chain-top climb: through nodes of the same segment
     // (preorder: a parent's entry is final before its children's)
@@ -716,21 +693,6 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
   L.zrec = take(sizeof(TargetRec) * (size_t)S * 3 * n);
   L.econst = take(sizeof(double) * S);
   {
-    // partial scores: every default shape, and room to tune up to 32 groups
-    // for segments of up to 16 nodes
-    size_t most = (size_t)std::min(S, kMaxSnapGroups) << std::min(h->kmax, 16);
-    for (int k = 1; k <= h->kmax; ++k) {
-      int spg;
-      most = std::max(most, (size_t)score64_groups_default(k, S, &spg) << k);
-    }
-    L.part = take(sizeof(MaskScore) * most);
-    h->part_cap = most;
-    const size_t nkey = (size_t)shape_key(h->kmax + 1, 0);
-    if (h->sg_tuned.size() != nkey) {  // tuning survives a re-plan of the same sizes
-      h->sg_tuned.assign(nkey, 0);
-      h->mpl_tuned.assign(nkey, 0);
-      h->ws_tuned.assign(nkey, 0);
-    }
     const size_t nm = (size_t)1 << h->kmax, nt = (nm + 63) / 64;
     L.fin = take(sizeof(MaskScore) * nm);
     L.tiles = take(sizeof(TileRec) * nt);
@@ -817,14 +779,14 @@ namespace {
 struct Ptrs {
   Topo T;
   State St;
-  const int *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks;
+  const int *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks, *units;
   double2 *z, *Zroot, *Vhat, *Vcur, *A, *J, *P, *headV, *yeq, *Ykd, *Yko;
   double *absV, *econst, *err;
   int *status, *iters, *tab, *tickets, *kp;
   SegHdr* hdrs;
   DevDecision* decs;
   TargetRec *srec, *zrec;
-  MaskScore *part, *fin;
+  MaskScore* fin;
   TileRec* tiles;
   unsigned long long *pat, *ecmax, *lacc;
   Pair32* P32;
@@ -875,6 +837,7 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.bfs_cf = tp + TO.bfs_cf;
   p.bfs_pp = tp + TO.bfs_pp;
   p.chunks = tp + TO.chunks;
+  p.units = tp + TO.units;
   p.St.kept = (uint8_t*)at(L.kept);
   p.St.sup = (int*)at(L.sup);
   p.St.slot_of = (int*)at(L.slot_of);
@@ -896,7 +859,6 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.headV = (double2*)at(L.headV);
   p.zrec = (TargetRec*)at(L.zrec);
   p.econst = (double*)at(L.econst);
-  p.part = (MaskScore*)at(L.part);
   p.fin = (MaskScore*)at(L.fin);
   p.tiles = (TileRec*)at(L.tiles);
   p.pat = (unsigned long long*)at(L.pat);
@@ -951,19 +913,61 @@ void list_score(const okr_handle* h, const Ptrs& w, const int* segp, int nz, int
                 const int* count, int cap, MaskScore* out, const SelParams& sp, hipStream_t st) {
   const size_t ls = h->L.lane_stride;
   const int fb = std::max(1, std::min(64, (cap + 255) / 256));
-  hipLaunchKernelGGL(k_terms_init, dim3(fb, 1, nz), dim3(256), 0, st, (const SegHdr*)w.hdrs, segp, ls, (int)0, count,
-                     cap, (const double*)w.econst, w.lacc, (unsigned long long*)nullptr);
+  hipLaunchKernelGGL(k_terms_init, dim3(fb, 1, nz), dim3(256), 0, st, count, cap, ls, w.lacc);
   // blocks per (segment, snapshot): each stages the snapshot's records, so
   // as few as fill the chip (about 1024 blocks in all), at most one per 256
   // items and 16
   const size_t pairs = (size_t)h->S * nz;
   const int cb = std::max(1, std::min({16, (int)(((size_t)cap * k + 255) / 256), (int)((1024 + pairs - 1) / pairs)}));
-  hipLaunchKernelGGL(k_chain_terms, dim3(cb, h->S, nz), dim3(256), terms_lds_bytes(k), st, (const SegHdr*)w.hdrs,
-                     segp, ls, (int)0, (const int*)w.tab, (const double2*)w.P, (const TargetRec*)w.srec,
-                     (const double2*)w.headV, (const TargetRec*)w.zrec, (const double*)w.econst, list, count, cap,
-                     terms_icap(k), kTermsZone, w.lacc, (unsigned long long*)nullptr);
+  hipLaunchKernelGGL(k_chain_terms, dim3(cb, h->S, nz), dim3(256), terms_lds_bytes(k, kTermsZone), st,
+                     (const SegHdr*)w.hdrs, segp, ls, (const int*)w.tab, (const double2*)w.P,
+                     (const TargetRec*)w.srec, (const double2*)w.headV, (const TargetRec*)w.zrec,
+                     (const double*)w.econst, list, count, cap, terms_icap(k), kTermsZone, w.lacc);
   hipLaunchKernelGGL(k_list_finish, dim3(fb, 1, nz), dim3(256), 0, st, count, (const unsigned long long*)w.lacc, cap,
                      sp, out, ls);
+}
+
+// One launch of the table kernel over chunk c: the segments' numeric tables
+// (build) and their chain patterns (pats).
+void launch_terms(const okr_handle* h, const Ptrs& q, int c, bool build, bool pats, const int* gates, hipStream_t st) {
+  const int kc = h->chunk_k[c], c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
+  // building alone takes one unit per segment: the pattern parts' first units
+  // (part 0 of each segment) are not contiguous, so such a launch passes the
+  // plain list of positions
+  const int u0 = pats ? h->unit_off[c] : 0, nu = pats ? h->unit_off[c + 1] - u0 : nz;
+  const int* units = pats ? q.units + u0 : q.units + h->units.size();
+  const int zcap = build && pats ? h->chunk_nz[c] : kTermsZone;
+  const size_t lds = terms_lds_bytes(kc, zcap);
+#define OKR_SEG_TERMS(B_, P_)                                                                                          \
+  hipLaunchKernelGGL((k_seg_terms<B_, P_>), dim3(nu, h->S), dim3(256), lds, st, (const SegHdr*)q.hdrs, q.chunks + c0,  \
+                     h->L.lane_stride, units, (const int*)q.tab, q.T, q.St, (const double2*)q.Zroot,                   \
+                     (const double2*)q.Vcur, (const double2*)q.A, (const double*)q.absV, q.P, q.srec, q.headV, q.zrec, \
+                     q.econst, terms_icap(kc), zcap, q.pat, q.ecmax, gates, q.status)
+  if (build && pats) OKR_SEG_TERMS(true, true);
+  else if (build) OKR_SEG_TERMS(true, false);
+  else OKR_SEG_TERMS(false, true);
+#undef OKR_SEG_TERMS
+}
+
+// Every mask's FP64 score for the segments of chunk c: each chain's terms for
+// every assignment of the mask bits they depend on (at most 2^(k+1) patterns
+// in all), then one table entry per chain for every mask, its score and the
+// tile records.  Exact, since max and min are: the scores are those of
+// walking every chain for every mask, which took 1.8x (1000 nodes, 24
+// snapshots) to 19x (8400 nodes, 288) as long per search and was no faster on
+// single chains of 16 to 20 nodes, where the patterns are as many as the masks
+// (163 against 85 ms, 610 against 445 ms).  With build, the segments' tables
+// are formed too.  With gates, only segments whose entry is nonzero are
+// scored.
+void pattern_score(const okr_handle* h, const Ptrs& q, int c, bool build, const SelParams& sp, const int* gates,
+                   hipStream_t st) {
+  const int kc = h->chunk_k[c], c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
+  const bool fused = build && terms_lds_bytes(kc, h->chunk_nz[c]) <= kTermsLdsMax;
+  if (build && !fused) launch_terms(h, q, c, true, false, nullptr, st);
+  launch_terms(h, q, c, fused, true, gates, st);
+  hipLaunchKernelGGL(k_fac_combine, dim3(((1u << kc) + 255) / 256, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs,
+                     q.chunks + c0, h->L.lane_stride, (const int*)q.tab, (const unsigned long long*)q.pat,
+                     (const unsigned long long*)q.ecmax, sp, q.fin, q.tiles, gates);
 }
 
 void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loads* loads,
@@ -1020,7 +1024,6 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   sp.amb = mg->amb_tol;
   sp.delta = mg->mixed_delta > 0.0 ? mg->mixed_delta : kMixedDelta;
   const bool mixed = mg->precision == OKR_PRECISION_MIXED;
-  const bool factored = mg->precision == OKR_PRECISION_FP64_FACTORED;
   const bool surr = mg->top_k > 0 && mg->top_k <= h->topk && mg->surrogate != nullptr &&
                     mg->precision == OKR_PRECISION_FP64;
   if (surr)
@@ -1032,32 +1035,17 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   for (int g = 0; g < h->nseg; ++g) foff[g + 1] = foff[g] + ((size_t)1 << (h->seg_off[g + 1] - h->seg_off[g]));
   const size_t lstride = h->L.lane_stride;
   const int nchunk = (int)h->chunk_k.size();
-  // every mask's final FP64 score is stored only when it is read back
-  const int full_fin = (dump || feat_out) ? 1 : 0;
   for (int c = 0; c < nchunk; ++c) {
     const int c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
     const int* segs = p.chunks + c0;  // device copy of this chunk's segment ids
     const int kc = h->chunk_k[c];
     const Ptrs& q = lp[0];  // scratch of chunk position 0; position z is z * lstride further
     hipLaunchKernelGGL(k_build_struct, dim3(1, 1, nz), dim3(256), 0, st, q.T, q.St, segs, lstride, S, q.hdrs, q.tab,
-                       h->tab_cap, q.status);
-    hipLaunchKernelGGL(k_build_values, dim3(256, 5, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                       (const int*)q.tab, n, (const double2*)q.Zroot, (const double2*)q.Vcur, (const double2*)q.A, q.P,
-                       q.srec, q.headV, q.zrec, q.econst);
-    hipLaunchKernelGGL(k_build_members, dim3(members_blocks, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs,
-                       lstride, (const int*)q.tab, q.T, q.St, (const double2*)q.Vcur, (const double*)q.absV, q.srec,
-                       q.zrec, q.econst);
+                       h->tab_cap, q.status, q.pat, q.ecmax);
+    // the tables come with the scoring, or first where something reads them before
+    const bool tables_first = mixed || surr || feat_out;
+    if (tables_first) launch_terms(h, q, c, true, false, nullptr, st);
     const uint32_t nmask = 1u << kc;
-    int spg;
-    const int SG = snap_groups(h, kc, nz, &spg);
-    // per-mask FP64 launch: one mask per lane, groups of ws waves sharing the
-    // chains of 64 masks, spp snapshots per pass, LDS for spp snapshots
-    const int sws = score_ws(h, kc, nz);
-    const uint32_t bmask = kScoreBlock * (kScoreThreads / 64 / sws);
-    const int mblocks = (int)((nmask + bmask - 1) / bmask);
-    const int pcap = kc * (kc + 1) / 2;
-    const int spp = sv_spp(score_mpl(h, kc, nz), kc, spg);
-    const size_t lds = sv_lds_bytes(spp, kc);
     const int* gates = surr ? q.sgates : nullptr;
     for (int z = 0; z < nz; ++z) {
       const int g = h->chunk_segs[c0 + z];
@@ -1120,42 +1108,10 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
                          (const MaskScore*)w.sscore, w.decs, w.sgates + g);
     }
     if (!mixed) {
-      // timing: the factored form's three launches between two recorded
-      // events; the per-mask kernel's own start and end through its launch
-      // (no marker packets around it)
-      if (ev && factored) (void)hipEventRecord((*ev)[2 * c], st);
-      hipEvent_t e0 = (ev && !factored) ? (*ev)[2 * c] : nullptr;
-      hipEvent_t e1 = (ev && !factored) ? (*ev)[2 * c + 1] : nullptr;
-      if (factored) {
-        // pattern table (up to 2^(k+1) patterns), then every mask.  The
-        // chain terms take one block per (segment, snapshot), looping over
-        // all patterns: each block stages the snapshot's records once (with
-        // 16 blocks per snapshot, each staging them, the launch took 2.7x
-        // as long on the 8400-node feeder and 2.0x on the 6000-node one)
-        const int pb = (int)std::min<uint64_t>(16, std::max<uint64_t>(1, ((uint64_t)2 << kc) / 256));
-        hipLaunchKernelGGL(k_terms_init, dim3(pb, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride, (int)1,
-                           (const int*)nullptr, 0, (const double*)q.econst, q.pat, q.ecmax);
-        hipLaunchKernelGGL(k_chain_terms, dim3(1, S, nz), dim3(256), terms_lds_bytes(kc), st, (const SegHdr*)q.hdrs,
-                           segs, lstride, (int)1, (const int*)q.tab, (const double2*)q.P, (const TargetRec*)q.srec,
-                           (const double2*)q.headV, (const TargetRec*)q.zrec, (const double*)q.econst,
-                           (const uint32_t*)nullptr, (const int*)nullptr, 0, terms_icap(kc), kTermsZone, q.pat,
-                           q.ecmax);
-        hipLaunchKernelGGL(k_fac_combine, dim3((nmask + 255) / 256, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs,
-                           segs, lstride, (const int*)q.tab, (const unsigned long long*)q.pat,
-                           (const unsigned long long*)q.ecmax, sp, q.fin, q.tiles);
-      } else {
-#define OKR_SCORE64(M_)                                                                                             \
-  hipExtLaunchKernelGGL(k_score_fp64<M_>, dim3(mblocks, SG, nz), dim3(kScoreThreads), lds, st, e0, e1, 0,            \
-                        (const SegHdr*)q.hdrs, segs, lstride, (const int*)q.tab, (const double2*)q.P,              \
-                        (const TargetRec*)q.srec, (const double2*)q.headV, (const TargetRec*)q.zrec,               \
-                        (const double*)q.econst, spg, SG, pcap, kc, kSvZone, sws, sp, q.part, q.fin, q.tiles,      \
-                        q.tickets, gates, full_fin)
-        if (spp == 4) OKR_SCORE64(4);
-        else if (spp == 2) OKR_SCORE64(2);
-        else OKR_SCORE64(1);
-#undef OKR_SCORE64
-      }
-      if (ev && factored) (void)hipEventRecord((*ev)[2 * c + 1], st);
+      // timing: the scoring launches between two recorded events
+      if (ev) (void)hipEventRecord((*ev)[2 * c], st);
+      pattern_score(h, q, c, !tables_first, sp, gates, st);
+      if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
       hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates);
       if (mg->secondary == OKR_SECONDARY_SMICE && !surr) {
@@ -1232,15 +1188,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
                          (const MaskScore*)q.scoreB, q.decs, q.sgates);
       {
         const int* redo = q.sgates;
-#define OKR_SCORE64(M_)                                                                                             \
-  hipLaunchKernelGGL(k_score_fp64<M_>, dim3(mblocks, SG, nz), dim3(kScoreThreads), lds, st, (const SegHdr*)q.hdrs, segs, \
-                     lstride, (const int*)q.tab, (const double2*)q.P, (const TargetRec*)q.srec,                      \
-                     (const double2*)q.headV, (const TargetRec*)q.zrec, (const double*)q.econst, spg, SG, pcap, kc,   \
-                     kSvZone, sws, sp, q.part, q.fin, q.tiles, q.tickets, redo, full_fin)
-        if (spp == 4) OKR_SCORE64(4);
-        else if (spp == 2) OKR_SCORE64(2);
-        else OKR_SCORE64(1);
-#undef OKR_SCORE64
+        pattern_score(h, q, c, false, sp, redo, st);
         hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                            (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, redo);
       }
@@ -1394,68 +1342,6 @@ static int reduce_feeder_impl(okr_handle* h, const okr_yblocks* Y, const okr_top
     h->ev.resize(2 * std::max(nseg, 1), nullptr);
     for (auto& e : h->ev) OKR_HIP(h, hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
   }
-  if (mg->flags & OKR_FLAG_AUTOTUNE) {
-    // time the scoring launches of a whole search once per candidate group
-    // count; keep the fastest per segment size
-    if ((int)h->ev.size() < 2 * nseg) {
-      drop_events(h);
-      h->ev.resize(2 * std::max(nseg, 1), nullptr);
-      for (auto& e : h->ev) OKR_HIP(h, hipEventCreateWithFlags(&e, hipEventDisableSystemFence));
-    }
-    // (the FP64 scoring kernel is tuned whatever the call's precision)
-    okr_margins mt = *mg;
-    mt.precision = OKR_PRECISION_FP64;
-    mt.top_k = 0;
-    mt.surrogate = nullptr;
-    // tsum[k][mpl index][waves index][groups]
-    const int NG = kMaxSnapGroups + 1;
-    const int nkey = shape_key(h->kmax + 1, 0);
-    std::vector<double> tsum((size_t)nkey * 3 * 3 * NG, 0.0);
-    auto T_ = [&](int key, int mi, int wi, int c) -> double& {
-      return tsum[(((size_t)key * 3 + mi) * 3 + wi) * NG + c];
-    };
-    for (int mi = 0; mi < 3; ++mi)
-      for (int wi = 0; wi < 3; ++wi)
-        for (int c = 1; c <= std::min(S, kMaxSnapGroups); c *= 2) {
-          h->sg_force = c;
-          h->mpl_force = 1 << mi;
-          h->ws_force = 1 << wi;
-          enqueue_search(h, d_workspace, Y, loads, &mt, st, &h->ev, nullptr, nullptr, nullptr, nullptr);
-          const hipError_t e1 = hipGetLastError(), e2 = hipStreamSynchronize(st);
-          if (e1 != hipSuccess || e2 != hipSuccess) {
-            h->sg_force = h->mpl_force = h->ws_force = 0;
-            OKR_FAIL(h, OKR_E_HIP, "autotune run failed: %s", hipGetErrorString(e1 != hipSuccess ? e1 : e2));
-          }
-          for (int cc = 0; cc < (int)h->chunk_k.size(); ++cc) {
-            const int k = h->chunk_k[cc], nzc = h->chunk_off[cc + 1] - h->chunk_off[cc];
-            int spg;
-            const int used = snap_groups(h, k, nzc, &spg);
-            float ms = 0.f;
-            const hipError_t ee = hipEventElapsedTime(&ms, h->ev[2 * cc], h->ev[2 * cc + 1]);
-            if (ee != hipSuccess) {
-              h->sg_force = h->mpl_force = h->ws_force = 0;
-              OKR_FAIL(h, OKR_E_HIP, "autotune timing failed: %s", hipGetErrorString(ee));
-            }
-            if (used == c) T_(shape_key(k, nzc), mi, wi, c) += ms;
-          }
-          h->sg_force = h->mpl_force = h->ws_force = 0;
-        }
-    for (int key = 0; key < nkey; ++key) {
-      int bc = 0, bm = 0, bw = 0;
-      for (int mi = 0; mi < 3; ++mi)
-        for (int wi = 0; wi < 3; ++wi)
-          for (int c = 1; c <= kMaxSnapGroups; c *= 2)
-            if (T_(key, mi, wi, c) > 0.0 && (bc == 0 || T_(key, mi, wi, c) < T_(key, bm, bw, bc))) {
-              bc = c;
-              bm = mi;
-              bw = wi;
-            }
-      h->sg_tuned[key] = bc;
-      h->mpl_tuned[key] = bc ? 1 << bm : 0;
-      h->ws_tuned[key] = bc ? 1 << bw : 0;
-    }
-    drop_graph(h);  // a captured search used the earlier group counts
-  }
   if (graph && st == nullptr) OKR_FAIL(h, OKR_E_ARG, "OKR_FLAG_GRAPH needs a non-null stream (the null stream cannot be captured)");
   if (graph) {
     const double2* V0 = (const double2*)loads->V0;
@@ -1577,17 +1463,9 @@ static int reduce_feeder_impl(okr_handle* h, const okr_yblocks* Y, const okr_top
     R.key_gap = decs[g].key_gap;
     R.smice_rise = mg->secondary == OKR_SECONDARY_SMICE ? decs[g].smice_rise : NAN;
     R.n_scored = 1 << k;
-    {
-      // launch shape of the segment's chunk (set by its largest segment)
-      const int kc = h->chunk_k[chunk_of[g]];
-      int spg;
-      const int nzc = h->chunk_off[chunk_of[g] + 1] - h->chunk_off[chunk_of[g]];
-      R.score_groups = snap_groups(h, kc, nzc, &spg);
-      R.score_mpl = sv_spp(score_mpl(h, kc, nzc), kc, spg);
-      R.score_waves = score_ws(h, kc, nzc);
-      R.chunk = chunk_of[g];
-    }
-    // the scoring kernel's own FP64 work: per slot and mask, reduced ->
+    R.score_groups = R.score_mpl = R.score_waves = 1;
+    R.chunk = chunk_of[g];
+    // evaluating every chain for every mask: per slot and mask, reduced ->
     // 6 + 4|phi|, kept -> 14|phi| (half the masks each); per zone entry 14
     double fl = 0.0;
     for (int q = h->seg_off[g]; q < h->seg_off[g + 1]; ++q) {

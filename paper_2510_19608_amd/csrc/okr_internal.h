@@ -11,6 +11,10 @@ constexpr int kMaxPairs = kMaxK * (kMaxK + 1) / 2;  // (super slot, reduced slot
 constexpr int kScoreBlock = 64;              // masks per tile record (one wave)
 constexpr int kScoreThreads = 256;           // scoring block: 4 waves, one mask per lane
 
+// status bit set when a structural invariant of a segment's tables fails (the
+// segment is then skipped by the scoring path and the call reports an error)
+constexpr int kStatusBuild = 64;
+
 // Header of one segment's tables (one per segment, in device memory), written
 // by the device-side builder; offsets index the int32 table buffer.
 struct SegHdr {
@@ -32,6 +36,7 @@ struct SegHdr {
   int o_zent;     // [nz][3]: node, phase, chain
   int total_ints;
   int npat;       // chain patterns: sum over chains of 2^popcount(C_PMASK)
+  int nitem;      // work items of the pattern table: sum over chains of 2^(popcount(C_PMASK) - C_D)
   int lanebits;   // the mask bits that vary across a scoring wave's 64 lanes
                   // (6 of them, all k when k < 6); a tile is the 64 masks
                   // sharing every other bit (tile_mask)
@@ -62,6 +67,16 @@ template <typename T>
 __device__ __forceinline__ T* lane_ptr(T* p, size_t lstride) {
   return p ? (T*)((char*)p + (size_t)blockIdx.z * lstride) : p;
 }
+
+// (the same with the chunk position given)
+template <typename T>
+__device__ __forceinline__ T* lane_ptr_z(T* p, size_t lstride, int z) {
+  return p ? (T*)((char*)p + (size_t)z * lstride) : p;
+}
+
+// Work unit of the table kernel (k_seg_terms): chunk position, part and part
+// count of its segment's pattern items, one int32 per unit.
+__host__ __device__ __forceinline__ int unit_pack(int z, int part, int parts) { return z | part << 8 | parts << 16; }
 
 // Read-only int tables (segment structure) in the constant address space:
 // kernels never write them while reading, so wave-uniform reads compile to
@@ -114,6 +129,8 @@ enum { C_HEAD = 0, C_NSLOT, C_SLOT0, C_NEST_OFF, C_NEST_LEN,
        C_PHW0, C_PHW1, C_PHW2,  // phase masks of slots 8w..8w+7, 3 bits each
        C_PMASK,  // mask bits the chain's terms depend on: its slots and those of its nesting path
        C_PBASE,  // first entry of the chain's patterns in the segment's pattern table
+       C_D,      // bottom slots whose bits one work item of the pattern table enumerates
+       C_IBASE,  // first work item of the chain
        kChainInts };
 // slot record
 enum { SL_NODE = 0, SL_BIT, SL_PHASE, SL_PAIRBASE, SL_CHAIN, kSlotInts };

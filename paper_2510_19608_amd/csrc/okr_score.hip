@@ -12,8 +12,6 @@
 namespace okr {
 
 // ---------------------------------------------------------------- scoring --
-constexpr int kStageBatch = 2;  // LDS-stage chunks each thread loads before it stores any
-
 // Tile record of one wave's 64 masks (lane q holds mask
 // tile_mask(lanebits, tile, q, k), final score r): highest feasible level,
 // smallest error at that level, highest level of a mask near the e_bar /
@@ -40,348 +38,364 @@ __device__ __forceinline__ int tile_record(const MaskScore& r, uint32_t m, uint3
   return best;
 }
 
-// Whether a mask's final score is stored: every mask when all are wanted
-// (dumps, surrogate targets), else only the masks the arg-min can read -- a
-// tile's masks at its best feasible level (no mask of a lower level of the
-// tile can be at the chosen level) and mask 0 (the decision's error when no
-// mask is feasible).
-__device__ __forceinline__ bool keep_score(bool full, uint32_t m, int tile_best) {
-  return full || __popc(m) == tile_best || m == 0;
-}
-
-// LDS stage of one pass of the per-mask kernel, in 16-byte chunks: chunk i
-// of one index space over the pair rows, slot records (2 chunks each), chain
-// heads and the first zone records (2 chunks each) of the pass's M snapshots
-// (element r * M + j of each table, snapshot j fastest, M a power of two, so
-// the LDS writes are contiguous).  stage_issue loads kStageBatch chunks per
-// thread, from chunk b on (past the end the last chunk is loaded again and
-// not stored); stage_store writes them to the buffer at chunk bb of the LDS,
-// a chain head's magnitude too.
-struct StageMap {
-  int nP, nT, nH, nst;  // chunks of the pair, slot, head tables; all chunks
-  int oT, oH, oZ, oHm;  // their offsets in a buffer (pairs at 0), head magnitudes
-};
-template <int M>
-__device__ __forceinline__ void stage_issue(const StageMap& S, int b, int l, int l1, const SegHdr& H,
-                                            const double2* __restrict__ P, const TargetRec* __restrict__ srec,
-                                            const double2* __restrict__ headV, const TargetRec* __restrict__ zrec,
-                                            uint4 (&v)[kStageBatch], int (&dst)[kStageBatch]) {
-  constexpr int LM = M == 4 ? 2 : (M == 2 ? 1 : 0);
-#pragma unroll
-  for (int u = 0; u < kStageBatch; ++u) {
-    const int i0 = b + u * kScoreThreads + (int)threadIdx.x;
-    const int i = min(i0, S.nst - 1);
-    // its table by selects, no branches, so the loads issue back to back
-    const int iT = i - S.nP, iH = iT - S.nT, iZ = iH - S.nH;
-    const bool isP = i < S.nP, isT = !isP && iT < S.nT, isH = !isP && !isT && iH < S.nH;
-    const bool rec = !isP && !isH;  // slot and zone records: 2 chunks each
-    const int ii = isP ? i : (isT ? iT : (isH ? iH : iZ));
-    const int j = rec ? (ii >> 1) & (M - 1) : ii & (M - 1);
-    const int chunk = rec ? ((ii >> (LM + 1)) << 1) + (ii & 1) : ii >> LM;
-    const uint4* base =
-        isP ? (const uint4*)P : (isT ? (const uint4*)srec : (isH ? (const uint4*)headV : (const uint4*)zrec));
-    const int per = isP ? H.npairs * 3 : (isT ? H.nslots * 6 : (isH ? H.nchains * 3 : H.nz * 2));  // per snapshot
-    dst[u] = i0 < S.nst ? (isP ? 0 : (isT ? S.oT : (isH ? S.oH : S.oZ))) + ii : -1;
-    v[u] = base[(size_t)min(l + j, l1 - 1) * per + chunk];
-  }
-}
-__device__ __forceinline__ void stage_store(const StageMap& S, unsigned char* lds, int bb,
-                                            const uint4 (&v)[kStageBatch], const int (&dst)[kStageBatch]) {
-  uint4* buf = (uint4*)lds + bb;
-  double* Hm = (double*)(buf + S.oHm);
-#pragma unroll
-  for (int u = 0; u < kStageBatch; ++u) {
-    if (dst[u] < 0) continue;
-    buf[dst[u]] = v[u];
-    if (dst[u] >= S.oH && dst[u] < S.oZ) {  // a chain head: its magnitude too
-      const double2 hv =
-          make_double2(__hiloint2double((int)v[u].y, (int)v[u].x), __hiloint2double((int)v[u].w, (int)v[u].z));
-      Hm[dst[u] - S.oH] = (hv.x != 0.0 || hv.y != 0.0) ? hmag(hv) : 0.0;
-    }
-  }
-}
-
-// Per-mask FP64 scoring, snapshot-vectorised: one mask per lane; a block's 4
-// waves form groups of ws waves (1, 2 or 4) over 64 consecutive masks each,
-// the waves of a group splitting the segment's chains (each chain's terms,
-// nesting path and zone entries included, are independent of the others')
-// and folding their maxima and minima in LDS at the end.  The block's
-// snapshot group is walked in passes of M snapshots staged together in LDS
-// (snapshot fastest), every chain's terms for the M snapshots at once
-// (score_chain_sv).  A pass past the group's last snapshot repeats it.  With
-// one snapshot group the block writes the final per-mask scores and tile
-// records itself; with several, the last block of a tile to finish (ticket
-// counter) folds the groups.  Final per-mask scores are stored for every
-// mask only with full_fin (keep_score).  Dynamic LDS per snapshot: pcap pairs, kcap
-// slots and chains, zcap zone records (later zone records are read from
-// global memory).
-template <int M>
-__global__ __launch_bounds__(kScoreThreads) void k_score_fp64(
-    const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ tab,
-    const double2* __restrict__ P, const TargetRec* __restrict__ srec, const double2* __restrict__ headV,
-    const TargetRec* __restrict__ zrec, const double* __restrict__ econst, int snaps_per_group, int SG, int pcap,
-    int kcap, int zcap, int ws, SelParams sp, MaskScore* __restrict__ part, MaskScore* __restrict__ fin,
-    TileRec* __restrict__ tiles, int* __restrict__ tickets, const int* __restrict__ gates, int full_fin) {
-  constexpr int NW = kScoreThreads / 64;
-  extern __shared__ __align__(16) unsigned char sv_lds[];
-  __shared__ double f_e[NW][64], f_qn[NW][64], f_qx[NW][64];
-  const int g = *as_cint(segs + blockIdx.z);
-  const SegHdr H = load_hdr(hdrs, segs);
-  if (!H.valid || (gates && gates[g] == 0)) return;
-  // blocks past this segment's masks (a chunk's launch covers its largest segment)
-  const uint32_t nmask = 1u << H.k;
-  const uint32_t bmasks = kScoreBlock * (NW / ws);
-  if ((uint64_t)blockIdx.x * bmasks >= nmask) return;
-  tab = lane_ptr(tab, lstride);
-  P = lane_ptr(P, lstride);
-  srec = lane_ptr(srec, lstride);
-  headV = lane_ptr(headV, lstride);
-  zrec = lane_ptr(zrec, lstride);
-  econst = lane_ptr(econst, lstride);
-  part = lane_ptr(part, lstride);
-  fin = lane_ptr(fin, lstride);
-  tiles = lane_ptr(tiles, lstride);
-  tickets = lane_ptr(tickets, lstride);
-  const int tid = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63;
-  const int c0 = w % ws;  // this wave's first chain within its group
-  // this wave's tile and this lane's mask (the lane bits vary across the wave)
-  const uint32_t L = (uint32_t)H.lanebits;
-  const uint32_t tile = blockIdx.x * (NW / ws) + (uint32_t)(w / ws);
-  const uint32_t m = tile_mask(L, tile, (uint32_t)lane, H.k);
-  const bool tile_ok = (tile << __popc(L)) < nmask;  // (a block's last waves can lie past the masks)
-  const bool valid = tile_ok && ((uint32_t)lane >> __popc(L)) == 0;
-  const int sg = blockIdx.y;
-  const int l0 = sg * snaps_per_group;
-  const int l1 = min(H.S, l0 + snaps_per_group);
-  const cint* chains = as_cint(tab + H.o_chain);
-  const cint* nest = as_cint(tab + H.o_nest);
-  const int zst = min(H.nz, zcap);
-  const int cP = H.npairs * 3, cT = H.nslots * 6, cH = H.nchains * 3, cZ = zst * 2;  // 16-byte chunks per snapshot
-  double e = 0.0, qmn[M], qmx[M];
-#pragma unroll
-  for (int j = 0; j < M; ++j) {
-    qmn[j] = INFINITY;
-    qmx[j] = -INFINITY;
-  }
-  // LDS: the pass's tables packed to this segment's own sizes.  The launch
-  // allocates the layout of the capacities (pcap pairs, kcap slots and
-  // chains, zcap zone records per snapshot, for the chunk's largest
-  // segment); when two packed buffers fit in it, the next pass is staged
-  // while this one is computed (its first loads in flight during the
-  // compute, one barrier per pass), else passes stage and compute in turn.
-  constexpr int LM = M == 4 ? 2 : (M == 2 ? 1 : 0);
-  StageMap SM;
-  SM.nP = cP << LM;
-  SM.nT = cT << LM;
-  SM.nH = cH << LM;
-  SM.nst = SM.nP + SM.nT + SM.nH + (cZ << LM);
-  SM.oT = SM.nP;
-  SM.oH = SM.oT + SM.nT;
-  SM.oZ = SM.oH + SM.nH;
-  SM.oHm = SM.nst;  // then doubles: the head magnitudes (nchains * 3 * M), the constant errors (M)
-  const int nEc = H.nchains * 3 * M;             // (index of the first constant error among them)
-  const int ubuf = SM.oHm + (nEc + M + 1) / 2;  // chunks per buffer
-  // (the allocation: the capacities' layout and 16 bytes, which covers the
-  // rounding of the packed one)
-  const size_t cap_bytes = (size_t)M * ((size_t)pcap * 3 * sizeof(double2) +
-                                        (size_t)kcap * 3 * (sizeof(TargetRec) + sizeof(double2) + sizeof(double)) +
-                                        (size_t)zcap * sizeof(TargetRec) + sizeof(double)) +
-                           16;
-  const bool dbl = (size_t)2 * ubuf * 16 <= cap_bytes;
-  const int npass = (l1 - l0 + M - 1) / M;
-  uint4 sv[kStageBatch];
-  int sd[kStageBatch];
-  auto stage_all = [&](int l, int bb, int from) {  // chunks from `from` on, issued and stored in turn
-    for (int b = from; b < SM.nst; b += kStageBatch * kScoreThreads) {
-      stage_issue<M>(SM, b, l, l1, H, P, srec, headV, zrec, sv, sd);
-      stage_store(SM, sv_lds, bb, sv, sd);
-    }
-    if (tid < M) ((double*)((uint4*)sv_lds + bb + SM.oHm))[nEc + tid] = econst[min(l + tid, l1 - 1)];
-  };
-  if (npass > 0) stage_all(l0, 0, 0);
-  __syncthreads();
-  for (int pi = 0; pi < npass; ++pi) {
-    const int l = l0 + pi * M;
-    const int cb = dbl ? (pi & 1) * ubuf : 0;  // this pass's buffer
-    const int nb = dbl ? ubuf - cb : 0;        // the next pass's
-    const bool ahead = dbl && pi + 1 < npass;
-    if (ahead) stage_issue<M>(SM, 0, l + M, l1, H, P, srec, headV, zrec, sv, sd);
-    uint4* buf = (uint4*)sv_lds + cb;
-    const double2* Ps = (const double2*)buf;
-    const TargetRec* Ts = (const TargetRec*)(buf + SM.oT);
-    const double2* Hv = (const double2*)(buf + SM.oH);
-    const TargetRec* Zs = (const TargetRec*)(buf + SM.oZ);
-    const double* Hm = (const double*)(buf + SM.oHm);
-    const double* Ec = Hm + nEc;
-    double el[M];
-    const TargetRec* zg[M];
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      el[j] = Ec[j];
-      zg[j] = zrec + (size_t)min(l + j, l1 - 1) * H.nz;
-    }
-    for (int c = c0; c < H.nchains; c += ws)
-      if (chains[c * kChainInts + C_PMASK] & L)  // (the others below)
-        score_chain_sv<M>(chains, nest, c, Ps, Ts, Hv, Hm, Zs, zst, zg, m, el, qmn, qmx);
-#pragma unroll
-    for (int j = 0; j < M; ++j) e = fmax(e, el[j]);
-    if (ahead) {
-      stage_store(SM, sv_lds, nb, sv, sd);
-      stage_all(l + M, nb, kStageBatch * kScoreThreads);
-      __syncthreads();
-    } else if (pi + 1 < npass) {
-      __syncthreads();  // every wave is done with the buffer
-      stage_all(l + M, 0, 0);
-      __syncthreads();
-    }
-  }
-  double qmin = qmn[0], qmax = qmx[0];
-#pragma unroll
-  for (int j = 1; j < M; ++j) {
-    qmin = fmin(qmin, qmn[j]);
-    qmax = fmax(qmax, qmx[j]);
-  }
-  // Chains whose terms depend on no lane bit (none of their own and their
-  // nesting path's mask bits among the 6 that vary across the wave) are the same
-  // for the wave's 64 masks: the wave evaluates each once, one snapshot per
-  // lane, from the tables in global memory, and every lane takes the maxima
-  // and minima over the snapshots.
-  {
-    const uint32_t mu = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
-    double ue = 0.0, uqn = INFINITY, uqx = -INFINITY;
-    bool any = false;
-    for (int c = c0; c < H.nchains; c += ws) {
-      if (chains[c * kChainInts + C_PMASK] & L) continue;
-      any = true;
-      for (int l = l0 + lane; l < l1; l += 64) {
-        double e1[1] = {0.0}, qn1[1] = {INFINITY}, qx1[1] = {-INFINITY};
-        const TargetRec* zl = zrec + (size_t)l * H.nz;
-        const TargetRec* const zg1[1] = {zl};
-        score_chain_sv<1, true>(chains, nest, c, P + (size_t)l * H.npairs * 3, srec + (size_t)l * H.nslots * 3,
-                                headV + (size_t)l * H.nchains * 3, nullptr, zl, H.nz, zg1, mu, e1, qn1, qx1);
-        ue = fmax(ue, e1[0]);
-        uqn = fmin(uqn, qn1[0]);
-        uqx = fmax(uqx, qx1[0]);
-      }
-    }
-    if (any) {
-      for (int o = 32; o > 0; o >>= 1) {
-        ue = fmax(ue, __shfl_xor(ue, o, 64));
-        uqn = fmin(uqn, __shfl_xor(uqn, o, 64));
-        uqx = fmax(uqx, __shfl_xor(uqx, o, 64));
-      }
-      e = fmax(e, ue);
-      qmin = fmin(qmin, uqn);
-      qmax = fmax(qmax, uqx);
-    }
-  }
-  // fold the chains of a group's waves into its first wave (max and min are
-  // exact in any order)
-  if (ws > 1) {
-    f_e[w][lane] = e;
-    f_qn[w][lane] = qmin;
-    f_qx[w][lane] = qmax;
-    __syncthreads();
-    if (c0 != 0) return;
-    for (int q = 1; q < ws; ++q) {
-      e = fmax(e, f_e[w + q][lane]);
-      qmin = fmin(qmin, f_qn[w + q][lane]);
-      qmax = fmax(qmax, f_qx[w + q][lane]);
-    }
-  }
-  if (!tile_ok) return;
-  MaskScore r;
-  r.e = e;
-  r.slack = band_slack(qmin, qmax, sp.vmin, sp.vmax);
-  if (SG == 1) {  // the block holds every snapshot: final scores and tile record directly
-    const int tb = tile_record(r, m, tile, valid, sp, tiles);
-    if (valid && keep_score(full_fin, m, tb)) fin[m] = r;
-    return;
-  }
-  if (valid) part[(size_t)sg * nmask + m] = r;
-  __threadfence();
-  int t = 0;
-  if (lane == 0) t = atomicAdd(&tickets[tile], 1);
-  t = __shfl(t, 0, 64);
-  if (t != SG - 1) return;
-  __threadfence();
-  // last block of this tile: combine the snapshot groups
-  r.e = 0.0;
-  r.slack = INFINITY;
-  if (valid) {
-    for (int q = 0; q < SG; ++q) {
-      const volatile MaskScore* x = part + (size_t)q * nmask + m;
-      r.e = fmax(r.e, x->e);
-      r.slack = fmin(r.slack, x->slack);
-    }
-  }
-  const int tb = tile_record(r, m, tile, valid, sp, tiles);
-  if (valid && keep_score(full_fin, m, tb)) fin[m] = r;
-  if (lane == 0) tickets[tile] = 0;  // ready for the next launch
-}
-
-#define OKR_SCORE64_INST(M_)                                                                                               \
-  template __global__ void k_score_fp64<M_>(const SegHdr*, const int*, size_t, const int*, const double2*,              \
-                                          const TargetRec*, const double2*, const TargetRec*, const double*, int, int, \
-                                          int, int, int, int, SelParams, MaskScore*, MaskScore*, TileRec*, int*,       \
-                                          const int*, int);
-OKR_SCORE64_INST(1)
-OKR_SCORE64_INST(2)
-OKR_SCORE64_INST(4)
-#undef OKR_SCORE64_INST
-
 // ------------------------------------------------- chain-term kernels --
-// Exact FP64 terms of chains for given mask bits, one lane per (item,
-// snapshot), folded into per-item accumulators by 64-bit atomics on the IEEE
-// bit patterns.  Items are either (listed mask, chain) pairs -- the scores of
-// a short mask list -- or chain patterns -- the factored form's table: for
-// chain c and assignment u of its C_PMASK bits (bit j of u at the j-th lowest
-// set bit), the chain's terms.  Every folded value is a non-negative double
-// (errors max(|V| - lo, hi - |V|) with lo <= hi, squared magnitudes), and for
-// those the bit patterns order like the values; max and min are exact, so the
-// results equal the per-mask kernel's.  qmax starts at +0 instead of -inf:
-// band_slack treats both alike (no kept node-phase).
+// Exact FP64 terms of chains for given mask bits, folded into per-item
+// accumulators by 64-bit atomics on the IEEE bit patterns.  Items are either
+// (listed mask, chain) pairs -- the scores of a short mask list -- or chain
+// patterns: for chain c and assignment u of its C_PMASK bits (bit j of u at
+// the j-th lowest set bit), the chain's terms.  Every folded value is a
+// non-negative double (errors max(|V| - lo, hi - |V|) with lo <= hi, squared
+// magnitudes), and for those the bit patterns order like the values; max and
+// min are exact, so any grouping of the folds gives the same scores.  qmax
+// starts at +0 instead of -inf: band_slack treats both alike (no kept
+// node-phase).
+
+// ---- a segment's numeric tables and its chain patterns, per snapshot ----
 //
-// A block serves one snapshot (blockIdx.y) of one segment (blockIdx.z of a
-// chunk): it first stages the chain records and nesting paths and the
-// snapshot's pair, slot, head and first zcap zone records in LDS (one
-// coalesced round trip), then walks every item's chain from there.
-enum { kTermsList = 0, kTermsPatterns = 1 };
+// A block serves one snapshot (blockIdx.y) of one unit (a segment of the
+// chunk, or a part of its pattern items).  With BUILD it forms the snapshot's
+// tables in LDS from the search state -- P = Z(super -> reduced) A_reduced
+// with Z(s -> r) = Zroot(r) - Zroot(s), the records' voltages, every
+// cluster's smallest and largest |V^| over its members, the constant error of
+// clusters outside Omega_g -- and writes them out (part 0) for the kernels
+// that read them later (state update, SMICE, short lists, the FP32 screen);
+// without, it stages the tables an earlier launch wrote.  With PAT it then
+// folds every pattern's terms into the segment's pattern table.
+//
+// Building where the patterns are evaluated saves two launches and the
+// tables' round trip through memory.  An item walks its chain's upper slots
+// once and enumerates the bottom C_D of them by nested loops whose branch is
+// the same for the whole wave: about 2.75 slot evaluations per pattern of a
+// chain of 11 bits instead of 11.
+struct ChainState {
+  double2 S[3];   // voltage shift
+  double sm[3];   // magnitude of the current super
+  int sidx;       // its slot + 1 (0: the head)
+  double e, qn, qx;
+};
+
+// Slot r of the chain reduced: the moved current's rise, the slot's cluster
+// against the current super.
+__device__ __forceinline__ void slot_reduced(ChainState& s, int ph, const double2* pr, const TargetRec* tr) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+    if (ph >> p & 1) {
+      s.S[p].x += pr[p].x;
+      s.S[p].y += pr[p].y;
+      s.e = fmax(s.e, fmax(s.sm[p] - tr[p].lo, tr[p].hi - s.sm[p]));
+    }
+}
+// Slot r kept: it becomes the super of the slots below.
+__device__ __forceinline__ void slot_kept(ChainState& s, int ph, int r, const TargetRec* tr) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+    if (ph >> p & 1) {
+      const TargetRec t = tr[p];
+      const double vx = t.W.x + s.S[p].x, vy = t.W.y + s.S[p].y;
+      const double q = fma(vx, vx, vy * vy);
+      s.sm[p] = sqrt_nr(q);
+      s.qn = fmin(s.qn, q);
+      s.qx = fmax(s.qx, q);
+      s.e = fmax(s.e, fmax(s.sm[p] - t.lo, t.hi - s.sm[p]));
+    }
+  s.sidx = r + 1;
+}
+
 constexpr int kTermsBlock = 256;  // threads of a chain-term block
 
-__device__ __forceinline__ int terms_count(int mode, const SegHdr& H, const int* count, int cap) {
-  return mode == kTermsList ? min(*count, cap) * H.nchains : H.npat;
+template <bool BUILD, bool PAT>
+__global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
+    const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ units,
+    const int* __restrict__ tab, Topo T, State St, const double2* __restrict__ Zroot,
+    const double2* __restrict__ Vcur, const double2* __restrict__ A, const double* __restrict__ absV,
+    double2* __restrict__ P, TargetRec* __restrict__ srec, double2* __restrict__ headV,
+    TargetRec* __restrict__ zrec, double* __restrict__ econst, int icap, int zcap,
+    unsigned long long* __restrict__ pat, unsigned long long* __restrict__ ecmax, const int* __restrict__ gates,
+    int* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char ct_lds[];
+  __shared__ double s_ec;
+  const int u = *as_cint(units + blockIdx.x);
+  const int uz = u & 255, part = (u >> 8) & 255, parts = u >> 16;
+  const int g = *as_cint(segs + uz);
+  const SegHdr H = load_hdr_g(hdrs, g);
+  if (!H.valid || (gates && gates[g] == 0)) return;
+  const int tid = threadIdx.x;
+  if (PAT && part > 0 && part * kTermsBlock >= H.nitem) return;  // (parts come from the plan's bound)
+  if (BUILD && PAT && H.nz > zcap) {  // the plan's bound failed: never in a consistent plan
+    if (tid == 0) atomicOr(status, kStatusBuild);
+    return;
+  }
+  tab = lane_ptr_z(tab, lstride, uz);
+  P = lane_ptr_z(P, lstride, uz);
+  srec = lane_ptr_z(srec, lstride, uz);
+  headV = lane_ptr_z(headV, lstride, uz);
+  zrec = lane_ptr_z(zrec, lstride, uz);
+  econst = lane_ptr_z(econst, lstride, uz);
+  const int l = blockIdx.y, n = T.n;
+  const int nint = H.o_slot;  // chain records and nesting paths
+  const int zst = min(H.nz, zcap);
+  int* si = (int*)ct_lds;
+  double2* sP = (double2*)(ct_lds + (size_t)((icap * 4 + 15) / 16) * 16);
+  TargetRec* sS = (TargetRec*)(sP + (size_t)H.npairs * 3);
+  double2* sH = (double2*)(sS + (size_t)H.nslots * 3);
+  TargetRec* sZ = (TargetRec*)(sH + (size_t)H.nchains * 3);
+  double2* gP = P + (size_t)l * H.npairs * 3;
+  TargetRec* gS = srec + (size_t)l * H.nslots * 3;
+  double2* gH = headV + (size_t)l * H.nchains * 3;
+  TargetRec* gZ = zrec + (size_t)l * H.nz;
+  for (int i = tid; i < nint; i += kTermsBlock) si[i] = tab[i];
+  const double2* Vl = Vcur + (size_t)l * n * 3;
+  if (BUILD) {
+    const double2* Al = A + (size_t)l * n * 3;
+    const double* av = absV + (size_t)l * n * 3;
+    if (tid == 0) s_ec = 0.0;
+    // one index space over pairs, slot-phases, chains and zone entries
+    const int nP = H.npairs, nS = H.nslots * 3, nC = H.nchains * 3;
+    for (int x = tid; x < nP + nS + nC + H.nz; x += kTermsBlock) {
+      if (x < nP) {
+        const int* pr = tab + H.o_pair + x * kPairInts;
+        const int rn = pr[PR_RNODE], sn = pr[PR_SUPER];
+        const double2 *zr = Zroot + (size_t)rn * 9, *zs = Zroot + (size_t)sn * 9;
+        const double2* a = Al + (size_t)rn * 3;
+        double2 Z[9];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) Z[e] = csub(zr[e], zs[e]);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          sP[x * 3 + r] = cadd(cadd(cmul(Z[r * 3], a[0]), cmul(Z[r * 3 + 1], a[1])), cmul(Z[r * 3 + 2], a[2]));
+      } else if (x < nP + nS) {
+        const int y = x - nP, s = y / 3, p = y - s * 3;
+        TargetRec rec;
+        rec.W = Vl[(size_t)tab[H.o_slot + s * kSlotInts + SL_NODE] * 3 + p];
+        rec.lo = INFINITY;
+        rec.hi = 0.0;
+        sS[y] = rec;
+      } else if (x < nP + nS + nC) {
+        const int y = x - nP - nS, c = y / 3, p = y - c * 3;
+        sH[y] = Vl[(size_t)tab[H.o_chain + c * kChainInts + C_HEAD] * 3 + p];
+      } else {
+        const int q = x - nP - nS - nC;
+        const int* ze = tab + H.o_zent + q * 3;
+        TargetRec rec;
+        rec.W = Vl[(size_t)ze[0] * 3 + ze[1]];
+        rec.lo = INFINITY;
+        rec.hi = 0.0;
+        if (q < zst) sZ[q] = rec;
+        else gZ[q] = rec;
+      }
+    }
+    __syncthreads();
+    // members: every node of Omega_g contributes |V^| to the cluster of its
+    // current super-node (a slot, a zone target, or a head outside Omega_g,
+    // whose error is mask-independent and folds into the constant error)
+    const int* rg = tab + H.o_range;
+    auto fold = [](TargetRec* r, double v) {
+      atomicMin((unsigned long long*)&r->lo, (unsigned long long)__double_as_longlong(v));
+      atomicMax((unsigned long long*)&r->hi, (unsigned long long)__double_as_longlong(v));
+    };
+    for (int q = tid; q < H.nomega; q += kTermsBlock) {
+      int r = 0;
+      while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
+      const int i = T.pre[rg[3 * r] + (q - rg[3 * r + 2])];
+      const int sp = St.sup[i];
+      const unsigned ph = T.phase[i];
+      if (T.segment[sp] == g) {
+        const int s = St.slot_of[sp];
+        if (s < 0 || s >= H.nslots) continue;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+          if (ph >> p & 1u) fold(&sS[s * 3 + p], av[(size_t)i * 3 + p]);
+      } else {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          if (!(ph >> p & 1u)) continue;
+          const double a = av[(size_t)i * 3 + p];
+          const int zi = St.zent_of[sp * 3 + p];
+          if (zi >= H.nz) continue;
+          if (zi >= 0) {
+            if (zi < zst) fold(&sZ[zi], a);
+            else fold(&gZ[zi], a);
+          } else {
+            const double2 v = Vl[(size_t)sp * 3 + p];
+            atomicMax((unsigned long long*)&s_ec,
+                      (unsigned long long)__double_as_longlong(fabs(sqrt(v.x * v.x + v.y * v.y) - a)));
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (part == 0) {
+      uint4 *dP = (uint4*)gP, *dS = (uint4*)gS, *dH = (uint4*)gH, *dZ = (uint4*)gZ;
+      for (int i = tid; i < H.npairs * 3; i += kTermsBlock) dP[i] = ((const uint4*)sP)[i];
+      for (int i = tid; i < H.nslots * 6; i += kTermsBlock) dS[i] = ((const uint4*)sS)[i];
+      for (int i = tid; i < H.nchains * 3; i += kTermsBlock) dH[i] = ((const uint4*)sH)[i];
+      for (int i = tid; i < zst * 2; i += kTermsBlock) dZ[i] = ((const uint4*)sZ)[i];
+      if (tid == 0) econst[l] = s_ec;
+    }
+  } else {
+    const int cP = H.npairs * 3, cS = H.nslots * 6, cH = H.nchains * 3, cZ = zst * 2;
+    for (int i = tid; i < cP + cS + cH + cZ; i += kTermsBlock) {
+      if (i < cP) ((uint4*)sP)[i] = ((const uint4*)gP)[i];
+      else if (i < cP + cS) ((uint4*)sS)[i - cP] = ((const uint4*)gS)[i - cP];
+      else if (i < cP + cS + cH) ((uint4*)sH)[i - cP - cS] = ((const uint4*)gH)[i - cP - cS];
+      else ((uint4*)sZ)[i - cP - cS - cH] = ((const uint4*)gZ)[i - cP - cS - cH];
+    }
+    if (tid == 0) s_ec = econst[l];
+    __syncthreads();
+  }
+  if (!PAT) return;
+  pat = lane_ptr_z(pat, lstride, uz);
+  if (part == 0 && tid == 0)
+    atomicMax(lane_ptr_z(ecmax, lstride, uz), (unsigned long long)__double_as_longlong(s_ec));
+  const int* chains = si + H.o_chain;
+  const int* nest = si + H.o_nest;
+  const int nch = H.nchains;
+  int c = 0;  // (a thread's items increase, so its chain index only moves forward)
+  for (int it = part * kTermsBlock + tid; it < H.nitem; it += parts * kTermsBlock) {
+    while (c + 1 < nch && chains[(c + 1) * kChainInts + C_IBASE] <= it) ++c;
+    const int* cr = chains + c * kChainInts;
+    const uint32_t ulow = (uint32_t)(it - cr[C_IBASE]);
+    uint32_t pm = (uint32_t)cr[C_PMASK], mask = 0;
+    const int d = cr[C_D], ub = __popc(pm) - d;  // the item's own bits; the d bits above them are enumerated
+    for (int j = 0; pm; ++j) {  // deposit bit j of ulow at the j-th lowest bit of C_PMASK
+      const uint32_t low = pm & (0u - pm);
+      if (ulow >> j & 1u) mask |= low;
+      pm ^= low;
+    }
+    ChainState s0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      s0.S[p] = make_double2(0.0, 0.0);
+      s0.sm[p] = 0.0;
+    }
+    s0.sidx = 0;
+    s0.e = 0.0;
+    s0.qn = INFINITY;
+    s0.qx = 0.0;
+    const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
+    {  // the nesting path down to the chain's head: voltage shifts only
+      double2 B[1][3];
+      double e1[1], q1[1], q2[1];
+      const uint32_t mm[1] = {mask};
+#pragma unroll
+      for (int p = 0; p < 3; ++p) B[0][p] = make_double2(0.0, 0.0);
+      for (int q = 0; q + 1 < nl; ++q) {
+        const int oc = nest[no + q];
+        walk_chain<false, 1>(chains + oc * kChainInts, sP, sS, sH, (const double*)nullptr, oc, mm, B, e1, q1, q2);
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p) s0.S[p] = B[0][p];
+    }
+    {  // the head's magnitude (0 on absent phases), moved by the outer chains when it lies below one
+      const int hph = cr[C_PHASE];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        if (hph >> p & 1) s0.sm[p] = vmag(nl > 1 ? cadd(sH[c * 3 + p], s0.S[p]) : sH[c * 3 + p]);
+    }
+    const int ns = cr[C_NSLOT], slot0 = cr[C_SLOT0], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
+    const int phw0 = cr[C_PHW0], phw1 = cr[C_PHW1], phw2 = cr[C_PHW2];
+    auto phase_of = [&](int r) { return ((r < 8 ? phw0 : (r < 16 ? phw1 : phw2)) >> (3 * (r & 7))) & 7; };
+    auto pair_row = [&](int r, int sidx) { return sP + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3; };
+    for (int r = 0; r < ns - d; ++r) {  // the item's own slots: lanes differ, both sides by selects
+      const int ph = phase_of(r);
+      const TargetRec* tr = sS + (slot0 + r) * 3;
+      const bool red = (mask >> (bit0 + r)) & 1u;
+      const double rf = red ? 1.0 : 0.0;
+      const double2* pp = pair_row(r, s0.sidx);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        if (!(ph >> p & 1)) continue;
+        const TargetRec t = tr[p];
+        s0.S[p].x = fma(rf, pp[p].x, s0.S[p].x);
+        s0.S[p].y = fma(rf, pp[p].y, s0.S[p].y);
+        const double vx = t.W.x + s0.S[p].x, vy = t.W.y + s0.S[p].y;
+        const double q = fma(vx, vx, vy * vy);
+        if (!red) s0.sm[p] = sqrt_nr(q);
+        s0.qn = fmin(s0.qn, red ? INFINITY : q);
+        s0.qx = fmax(s0.qx, red ? 0.0 : q);
+        s0.e = fmax(s0.e, fmax(s0.sm[p] - t.lo, t.hi - s0.sm[p]));
+      }
+      s0.sidx = red ? s0.sidx : r + 1;
+    }
+    auto step = [&](ChainState& s, int r, int red) {
+      const int ph = phase_of(r);
+      const TargetRec* tr = sS + (slot0 + r) * 3;
+      if (red) slot_reduced(s, ph, pair_row(r, s.sidx), tr);
+      else slot_kept(s, ph, r, tr);
+    };
+    const int pb = cr[C_PBASE] + (int)ulow;
+#pragma unroll 1
+    for (int b0 = 0; b0 < (d > 2 ? 2 : 1); ++b0) {
+      ChainState s1 = s0;
+      if (d > 2) step(s1, ns - 3, b0);
+#pragma unroll 1
+      for (int b1 = 0; b1 < (d > 1 ? 2 : 1); ++b1) {
+        ChainState s2 = s1;
+        if (d > 1) step(s2, ns - 2, b1);
+#pragma unroll 1
+        for (int b2 = 0; b2 < (d > 0 ? 2 : 1); ++b2) {
+          ChainState s3 = s2;
+          if (d > 0) step(s3, ns - 1, b2);
+          // the zone entries anchored below the chain, shifted by its exit value
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            for (int q = cr[C_ZOFF0 + p], qe = q + cr[C_ZCNT0 + p]; q < qe; ++q) {
+              TargetRec t;
+              if (q < zst) t = sZ[q];
+              else t = gZ[q];
+              const double vx = t.W.x + s3.S[p].x, vy = t.W.y + s3.S[p].y;
+              const double q2 = fma(vx, vx, vy * vy);
+              const double mag = sqrt_nr(q2);
+              s3.e = fmax(s3.e, fmax(mag - t.lo, t.hi - mag));
+              s3.qn = fmin(s3.qn, q2);
+              s3.qx = fmax(s3.qx, q2);
+            }
+          const int x = pb + (((b0 | b1 << 1 | b2 << 2) >> (3 - d)) << ub);
+          atomicMax(&pat[3 * x], (unsigned long long)__double_as_longlong(s3.e));
+          if (s3.qn < INFINITY) atomicMin(&pat[3 * x + 1], (unsigned long long)__double_as_longlong(s3.qn));
+          if (s3.qx > 0.0) atomicMax(&pat[3 * x + 2], (unsigned long long)__double_as_longlong(s3.qx));
+        }
+      }
+    }
+  }
 }
 
-__global__ void k_terms_init(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, int mode,
-                             const int* __restrict__ count, int cap, const double* __restrict__ econst,
-                             unsigned long long* __restrict__ acc, unsigned long long* __restrict__ ecmax) {
-  const SegHdr H = load_hdr(hdrs, segs);
-  if (!H.valid) return;
+#define OKR_SEG_TERMS_INST(B_, P_)                                                                                    \
+  template __global__ void k_seg_terms<B_, P_>(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, \
+                                               const double2*, const double2*, const double2*, const double*, double2*, \
+                                               TargetRec*, double2*, TargetRec*, double*, int, int,                    \
+                                               unsigned long long*, unsigned long long*, const int*, int*);
+OKR_SEG_TERMS_INST(true, true)
+OKR_SEG_TERMS_INST(true, false)
+OKR_SEG_TERMS_INST(false, true)
+#undef OKR_SEG_TERMS_INST
+
+// ---- terms of a short mask list ----
+
+// Clears the list's accumulators (the pattern table's are cleared by
+// k_build_struct).
+__global__ void k_terms_init(const int* __restrict__ count, int cap, size_t lstride,
+                             unsigned long long* __restrict__ acc) {
   count = lane_ptr(count, lstride);
-  econst = lane_ptr(econst, lstride);
   acc = lane_ptr(acc, lstride);
-  ecmax = lane_ptr(ecmax, lstride);
-  const int n = mode == kTermsList ? min(*count, cap) : H.npat;
-  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-  for (int q = t0; q < n; q += stride) {
+  const int n = min(*count, cap);
+  for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < n; q += gridDim.x * blockDim.x) {
     acc[3 * q] = 0ull;
     acc[3 * q + 1] = (unsigned long long)__double_as_longlong(INFINITY);
     acc[3 * q + 2] = 0ull;
   }
-  if (mode == kTermsPatterns && ecmax) {
-    if (t0 == 0) *ecmax = 0ull;
-  }
 }
 
+// One lane per (listed mask, chain, snapshot).  A block serves one snapshot
+// (blockIdx.y) of one segment (blockIdx.z of a chunk): it first stages the
+// chain records and nesting paths and the snapshot's pair, slot, head and
+// first zcap zone records in LDS (one coalesced round trip), then walks every
+// item's chain from there.
 __global__ __launch_bounds__(kTermsBlock) void k_chain_terms(
-    const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, int mode,
-    const int* __restrict__ tab, const double2* __restrict__ P, const TargetRec* __restrict__ srec,
-    const double2* __restrict__ headV, const TargetRec* __restrict__ zrec, const double* __restrict__ econst,
-    const uint32_t* __restrict__ list, const int* __restrict__ count, int cap, int icap, int zcap,
-    unsigned long long* __restrict__ acc, unsigned long long* __restrict__ ecmax) {
+    const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ tab,
+    const double2* __restrict__ P, const TargetRec* __restrict__ srec, const double2* __restrict__ headV,
+    const TargetRec* __restrict__ zrec, const double* __restrict__ econst, const uint32_t* __restrict__ list,
+    const int* __restrict__ count, int cap, int icap, int zcap, unsigned long long* __restrict__ acc) {
   extern __shared__ __align__(16) unsigned char ct_lds[];
   const SegHdr H = load_hdr(hdrs, segs);
   if (!H.valid) return;
@@ -394,11 +408,8 @@ __global__ __launch_bounds__(kTermsBlock) void k_chain_terms(
   list = lane_ptr(list, lstride);
   count = lane_ptr(count, lstride);
   acc = lane_ptr(acc, lstride);
-  ecmax = lane_ptr(ecmax, lstride);
-  const int items = terms_count(mode, H, count, cap);
+  const int items = min(*count, cap) * H.nchains;
   const int l = blockIdx.y;
-  if (mode == kTermsPatterns && ecmax && blockIdx.x == 0 && threadIdx.x == 0)
-    atomicMax(ecmax, (unsigned long long)__double_as_longlong(econst[l]));
   if ((int)(blockIdx.x * blockDim.x) >= items) return;  // whole block idle
   // stage: chain records and nesting paths (ints [0, o_slot)), then this
   // snapshot's pairs, slot records, heads and first zone records
@@ -426,59 +437,38 @@ __global__ __launch_bounds__(kTermsBlock) void k_chain_terms(
   const int* nest = si + H.o_nest;
   const int nch = H.nchains;
   const double ec = econst[l];
-  if (mode == kTermsList) {
-    // a block's items cover consecutive listed masks (each with all its
-    // chains): fold them in LDS first, then one global atomic per mask
-    __shared__ unsigned long long s_acc[3 * (kTermsBlock + 2)];
-    for (int base = blockIdx.x * blockDim.x; base < items; base += gridDim.x * blockDim.x) {
-      const int q0 = base / nch, q1 = min(items - 1, base + (int)blockDim.x - 1) / nch;
-      for (int i = threadIdx.x; i <= q1 - q0; i += blockDim.x) {
-        s_acc[3 * i] = 0ull;
-        s_acc[3 * i + 1] = (unsigned long long)__double_as_longlong(INFINITY);
-        s_acc[3 * i + 2] = 0ull;
-      }
-      __syncthreads();
-      const int it = base + threadIdx.x;
-      if (it < items) {
-        const int q = it / nch, c = it - q * nch;
-        const uint32_t mm[1] = {list[q]};
-        double el[1] = {ec}, qn[1] = {INFINITY}, qx[1] = {0.0};
-        score_chain<true, 1>(chains, nest, c, sP, sS, sH, (const double*)nullptr, sZ, zst, zrec + (size_t)l * H.nz,
-                             mm, el, qn, qx);
-        unsigned long long* a = s_acc + 3 * (q - q0);
-        atomicMax(&a[0], (unsigned long long)__double_as_longlong(el[0]));
-        if (qn[0] < INFINITY) atomicMin(&a[1], (unsigned long long)__double_as_longlong(qn[0]));
-        if (qx[0] > 0.0) atomicMax(&a[2], (unsigned long long)__double_as_longlong(qx[0]));
-      }
-      __syncthreads();
-      for (int i = threadIdx.x; i <= q1 - q0; i += blockDim.x) {
-        const int q = q0 + i;
-        atomicMax(&acc[3 * q], s_acc[3 * i]);
-        if (s_acc[3 * i + 1] != (unsigned long long)__double_as_longlong(INFINITY))
-          atomicMin(&acc[3 * q + 1], s_acc[3 * i + 1]);
-        if (s_acc[3 * i + 2] != 0ull) atomicMax(&acc[3 * q + 2], s_acc[3 * i + 2]);
-      }
-      __syncthreads();
+  // a block's items cover consecutive listed masks (each with all its
+  // chains): fold them in LDS first, then one global atomic per mask
+  __shared__ unsigned long long s_acc[3 * (kTermsBlock + 2)];
+  for (int base = blockIdx.x * blockDim.x; base < items; base += gridDim.x * blockDim.x) {
+    const int q0 = base / nch, q1 = min(items - 1, base + (int)blockDim.x - 1) / nch;
+    for (int i = threadIdx.x; i <= q1 - q0; i += blockDim.x) {
+      s_acc[3 * i] = 0ull;
+      s_acc[3 * i + 1] = (unsigned long long)__double_as_longlong(INFINITY);
+      s_acc[3 * i + 2] = 0ull;
     }
-    return;
-  }
-  int c = 0;  // (a thread's items increase, so its chain index only moves forward)
-  for (int it = blockIdx.x * blockDim.x + threadIdx.x; it < items; it += gridDim.x * blockDim.x) {
-    while (c + 1 < nch && chains[(c + 1) * kChainInts + C_PBASE] <= it) ++c;
-    const uint32_t u = (uint32_t)(it - chains[c * kChainInts + C_PBASE]);
-    uint32_t pm = (uint32_t)chains[c * kChainInts + C_PMASK], mask = 0;
-    for (int j = 0; pm; ++j) {  // deposit bit j of u at the j-th lowest bit of C_PMASK
-      const uint32_t low = pm & (0u - pm);
-      if (u >> j & 1u) mask |= low;
-      pm ^= low;
+    __syncthreads();
+    const int it = base + threadIdx.x;
+    if (it < items) {
+      const int q = it / nch, c = it - q * nch;
+      const uint32_t mm[1] = {list[q]};
+      double el[1] = {ec}, qn[1] = {INFINITY}, qx[1] = {0.0};
+      score_chain<true, 1>(chains, nest, c, sP, sS, sH, (const double*)nullptr, sZ, zst, zrec + (size_t)l * H.nz,
+                           mm, el, qn, qx);
+      unsigned long long* a = s_acc + 3 * (q - q0);
+      atomicMax(&a[0], (unsigned long long)__double_as_longlong(el[0]));
+      if (qn[0] < INFINITY) atomicMin(&a[1], (unsigned long long)__double_as_longlong(qn[0]));
+      if (qx[0] > 0.0) atomicMax(&a[2], (unsigned long long)__double_as_longlong(qx[0]));
     }
-    const uint32_t mm[1] = {mask};
-    double el[1] = {0.0}, qn[1] = {INFINITY}, qx[1] = {0.0};
-    score_chain<true, 1>(chains, nest, c, sP, sS, sH, (const double*)nullptr, sZ, zst, zrec + (size_t)l * H.nz, mm,
-                         el, qn, qx);
-    atomicMax(&acc[3 * it], (unsigned long long)__double_as_longlong(el[0]));
-    if (qn[0] < INFINITY) atomicMin(&acc[3 * it + 1], (unsigned long long)__double_as_longlong(qn[0]));
-    if (qx[0] > 0.0) atomicMax(&acc[3 * it + 2], (unsigned long long)__double_as_longlong(qx[0]));
+    __syncthreads();
+    for (int i = threadIdx.x; i <= q1 - q0; i += blockDim.x) {
+      const int q = q0 + i;
+      atomicMax(&acc[3 * q], s_acc[3 * i]);
+      if (s_acc[3 * i + 1] != (unsigned long long)__double_as_longlong(INFINITY))
+        atomicMin(&acc[3 * q + 1], s_acc[3 * i + 1]);
+      if (s_acc[3 * i + 2] != 0ull) atomicMax(&acc[3 * q + 2], s_acc[3 * i + 2]);
+    }
+    __syncthreads();
   }
 }
 
@@ -508,11 +498,13 @@ __global__ __launch_bounds__(256) void k_fac_combine(const SegHdr* __restrict__ 
                                                      size_t lstride, const int* __restrict__ tab,
                                                      const unsigned long long* __restrict__ pat,
                                                      const unsigned long long* __restrict__ ecmax, SelParams sp,
-                                                     MaskScore* __restrict__ fin, TileRec* __restrict__ tiles) {
+                                                     MaskScore* __restrict__ fin, TileRec* __restrict__ tiles,
+                                                     const int* __restrict__ gates) {
   __shared__ int s_pm[kMaxK], s_pb[kMaxK];
   __shared__ double s_pat[3 * kPatLds];
-  const SegHdr H = load_hdr(hdrs, segs);
-  if (!H.valid) return;
+  const int g = *as_cint(segs + blockIdx.z);
+  const SegHdr H = load_hdr_g(hdrs, g);
+  if (!H.valid || (gates && gates[g] == 0)) return;
   if ((uint64_t)blockIdx.x * blockDim.x >= ((uint64_t)1 << H.k)) return;  // past this segment's masks
   tab = lane_ptr(tab, lstride);
   pat = lane_ptr(pat, lstride);

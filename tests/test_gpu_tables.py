@@ -1,0 +1,93 @@
+"""The table kernel (numeric tables and chain patterns of a segment) at the
+sizes where its forms change: items that enumerate bottom slots (chains of 6
+bits and more once a segment has over 256 patterns), pattern parts (over 4096
+patterns by the plan's bound), zone records beyond the LDS stage (tables and
+patterns in two launches).  Every mask's error and band slack against the
+oracle: both evaluate sums of at most a few dozen voltage changes of order
+0.01 in FP64, which round below 1e-14; the tolerance is the 1e-9 p.u. that the
+decisions are specified to."""
+import numpy as np
+import pytest
+
+import oracle
+from synth_feeders import make_feeder
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-9
+
+
+@pytest.fixture(scope="module")
+def okr():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible MI355X")
+    import paper_2510_19608_amd as okr
+    okr.lib()
+    return okr
+
+
+def check(okr, f, precision="fp64", per_segment=256):
+    """Decisions, and sampled masks of every segment at the state the earlier
+    decisions left, against the oracle."""
+    V, I, st, _ = oracle.powerflow(f)
+    assert st == 0
+    out = okr.reduce_feeder(f, dump=True, precision=precision, want_vhat=False)
+    state = np.ones(f["n"], np.uint8)
+    rng = np.random.default_rng(0)
+    for g, s in enumerate(out["segments"]):
+        e, slack, k = out["scores"][g]
+        masks = np.unique(np.r_[0, (1 << k) - 1, s["mask"], rng.integers(0, 1 << k, per_segment)]).astype(np.uint32)
+        want = oracle.score_masks(f, V, I, state, g, masks)
+        np.testing.assert_allclose(e[masks], want["e_loc"], rtol=0, atol=TOL, err_msg=f"segment {g}")
+        fin = np.isfinite(want["slack_loc"])
+        np.testing.assert_allclose(slack[masks][fin], want["slack_loc"][fin], rtol=0, atol=TOL)
+        from synth_feeders import dfs_preorder
+        order = [int(v) for v in dfs_preorder(f["parent"]) if f["segment"][v] == g]
+        for j, v in enumerate(order):
+            if s["mask"] >> j & 1:
+                state[v] = 0
+    return out
+
+
+@pytest.mark.parametrize("k", [5, 6, 8, 9, 12, 13])
+def test_long_chains(okr, k):
+    """Deep laterals: chains of up to k bits, from one pattern per thread to
+    several parts."""
+    print(f"tables: long chains k={k}", flush=True)
+    f = make_feeder("c1", k, n=45, n_eligible=None, seg_size=(k, k), snapshots=3, p_deep=0.93, e_bar=2e-4, kappa=0.25)
+    check(okr, f)
+
+
+def zone_feeder(n, leaves):
+    """A three-phase feeder whose node 1 carries everything else: reducing it
+    moves every other node."""
+    f = make_feeder("c1", 3, n=n, n_eligible=None, p_single=0.0, p_two=0.0, snapshots=2, kappa=1 / 64)
+    parent = np.asarray(f["parent"]).copy()
+    parent[1:3] = [0, 1]
+    parent[3:] = np.maximum(parent[3:], 2)
+    Yd = np.zeros_like(f["Y_diag"])
+    for i in range(1, n):
+        Yd[i] -= f["Y_off"][i]
+        Yd[parent[i]] -= f["Y_off"][i]
+    seg = np.full(n, -1, np.int32)
+    nchild = np.bincount(parent[1:], minlength=n)
+    seg[[1] + [int(v) for v in np.flatnonzero(nchild == 0)[:leaves]]] = 0
+    return dict(f, parent=parent, Y_diag=Yd, segment=seg, eligible=(seg >= 0).astype(np.uint8), n_segments=1,
+                v_min=0.9, v_max=1.1, e_bar=3e-4)
+
+
+@pytest.mark.parametrize("n", [20, 90, 350, 900])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_many_zone_entries(okr, n, precision):
+    """One short chain above 50 to 2,700 zone entries: in the LDS stage, partly
+    beyond it, and with tables and patterns in separate launches."""
+    print(f"tables: zone entries n={n} {precision}", flush=True)
+    f = zone_feeder(n, 5)
+    if precision == "fp64":
+        check(okr, f, per_segment=64)
+    else:
+        a = okr.reduce_feeder(f, precision=precision, want_vhat=False)
+        b = okr.reduce_feeder(f, want_vhat=False)
+        assert [s["mask"] for s in a["segments"]] == [s["mask"] for s in b["segments"]]
+        np.testing.assert_array_equal(a["err_per_snapshot"], b["err_per_snapshot"])
