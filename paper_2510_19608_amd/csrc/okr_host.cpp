@@ -351,24 +351,19 @@ double method_flops(const okr_handle* h, int g, const std::vector<uint8_t>& keep
     for (int i = 0; i < L; ++i)
       for (int t = 0; t < b; ++t)
         if (nodes[bits[t]] == path[i]) bit_of[i] = t;
-    double acc = 0.0;
-    std::vector<char> carry(L);
-    for (uint32_t m = 0; m < (1u << b); ++m) {
-      int stop = -1;  // index of the nearest kept node above (-1: the head)
-      std::fill(carry.begin(), carry.end(), 0);
-      for (int i = 0; i < L; ++i) {
-        if (bit_of[i] < 0) continue;  // reduced earlier: the current passes through
-        if (!(m >> bit_of[i] & 1u)) {
-          stop = i;
-          continue;
-        }
-        acc += 2.0 * ph(path[i]) * (i - stop);
-        for (int t = i; t > stop; --t) carry[t] = 1;
-      }
-      for (int i = 0; i < L; ++i)
-        if (carry[i]) acc += 8.0 * ph(path[i]) * ph(path[i]) + 2.0 * ph(path[i]);
+    // averages over the masks in closed form.  A node's current stops at the
+    // nearest kept segment node above: the one above it with probability 1/2,
+    // the next with 1/4, ..., the head when all are reduced, so the expected
+    // stop is half the upper neighbour's index plus half that neighbour's own
+    // expected stop.  An edge carries a moved current when the first segment
+    // node at or below it is reduced: 1/2, the path's last node being one.
+    double stop = -1.0;  // expected index of the nearest kept node above (-1: the head)
+    for (int i = 0; i < L; ++i) {
+      per += 0.5 * (8.0 * ph(path[i]) * ph(path[i]) + 2.0 * ph(path[i]));
+      if (bit_of[i] < 0) continue;  // reduced earlier: the current passes through
+      per += 0.5 * 2.0 * ph(path[i]) * (i - stop);
+      stop = 0.5 * (i + stop);
     }
-    per += acc / double(1u << b);
   }
   const double masks = double(int64_t(1) << k);
   return per * masks * S + 18.0 * 0.5 * k * masks;
