@@ -67,6 +67,13 @@ __device__ __forceinline__ int tile_record(const MaskScore& r, uint32_t m, uint3
 // once and enumerates the bottom C_D of them by nested loops whose branch is
 // the same for the whole wave: about 2.75 slot evaluations per pattern of a
 // chain of 11 bits instead of 11.
+//
+// A chain with more zone entries below it than it has patterns (and at least
+// kZoneWave of them) leaves the few threads of its patterns with hundreds of
+// entries in turn while the block waits (launches of 150 to 650 us on the
+// 8400-node feeder, whose chains carry up to 1,115 entries).  Its entries are
+// evaluated by whole waves instead: one wave per pattern walks the chain for
+// its exit value and takes an entry per lane.
 struct ChainState {
   double2 S[3];   // voltage shift
   double sm[3];   // magnitude of the current super
@@ -102,6 +109,27 @@ __device__ __forceinline__ void slot_kept(ChainState& s, int ph, int r, const Ta
 }
 
 constexpr int kTermsBlock = 256;  // threads of a chain-term block
+constexpr int kZoneWave = 16;     // zone entries from which a chain's patterns may take them by waves
+
+// Whether the zone entries of a chain are taken by a wave per pattern: as
+// many entries as patterns (at equality both forms take about 100 cycles per
+// entry of the chain: an entry in turn per thread, or 64 entries a round in
+// each of 4 waves with a 6-step fold per pattern).
+__device__ __forceinline__ bool zone_by_wave(const int* cr) {
+  const int z = cr[C_ZCNT0] + cr[C_ZCNT1] + cr[C_ZCNT2];
+  return z >= kZoneWave && (1 << __popc((uint32_t)cr[C_PMASK])) <= z;
+}
+
+// The mask whose bits at pm's positions are u's low bits, the rest 0.
+__device__ __forceinline__ uint32_t deposit_bits(uint32_t u, uint32_t pm) {
+  uint32_t mask = 0;
+  for (; pm; u >>= 1) {
+    const uint32_t low = pm & (0u - pm);
+    if (u & 1u) mask |= low;
+    pm ^= low;
+  }
+  return mask;
+}
 
 template <bool BUILD, bool PAT>
 __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
@@ -114,13 +142,16 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
     int* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char ct_lds[];
   __shared__ double s_ec;
+  __shared__ int s_zw[kMaxK + 1];  // patterns of the chains before c whose zone entries go by waves
   const int u = *as_cint(units + blockIdx.x);
   const int uz = u & 255, part = (u >> 8) & 255, parts = u >> 16;
   const int g = *as_cint(segs + uz);
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid || (gates && gates[g] == 0)) return;
   const int tid = threadIdx.x;
-  if (PAT && part > 0 && part * kTermsBlock >= H.nitem) return;  // (parts come from the plan's bound)
+  // (parts come from the plan's bound on the patterns; a part without items
+  // may still have zone patterns, which are fewer than the segment's entries)
+  if (PAT && part > 0 && part * kTermsBlock >= H.nitem && part * (kTermsBlock / 64) >= H.nz) return;
   if (BUILD && PAT && H.nz > zcap) {  // the plan's bound failed: never in a consistent plan
     if (tid == 0) atomicOr(status, kStatusBuild);
     return;
@@ -250,18 +281,25 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
   const int* chains = si + H.o_chain;
   const int* nest = si + H.o_nest;
   const int nch = H.nchains;
+  if (tid < 64) {
+    const bool zw = tid < nch && zone_by_wave(chains + tid * kChainInts);
+    const int v = zw ? 1 << __popc((uint32_t)chains[tid * kChainInts + C_PMASK]) : 0;
+    int x = v;
+    for (int o = 1; o < 32; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (tid >= o) x += y;
+    }
+    if (tid <= nch) s_zw[tid] = x - v;
+  }
   int c = 0;  // (a thread's items increase, so its chain index only moves forward)
   for (int it = part * kTermsBlock + tid; it < H.nitem; it += parts * kTermsBlock) {
     while (c + 1 < nch && chains[(c + 1) * kChainInts + C_IBASE] <= it) ++c;
     const int* cr = chains + c * kChainInts;
     const uint32_t ulow = (uint32_t)(it - cr[C_IBASE]);
-    uint32_t pm = (uint32_t)cr[C_PMASK], mask = 0;
+    const uint32_t pm = (uint32_t)cr[C_PMASK];
     const int d = cr[C_D], ub = __popc(pm) - d;  // the item's own bits; the d bits above them are enumerated
-    for (int j = 0; pm; ++j) {  // deposit bit j of ulow at the j-th lowest bit of C_PMASK
-      const uint32_t low = pm & (0u - pm);
-      if (ulow >> j & 1u) mask |= low;
-      pm ^= low;
-    }
+    const uint32_t mask = deposit_bits(ulow, pm);
+    const bool zw = zone_by_wave(cr);
     ChainState s0;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
@@ -339,7 +377,7 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
           // the zone entries anchored below the chain, shifted by its exit value
 #pragma unroll
           for (int p = 0; p < 3; ++p)
-            for (int q = cr[C_ZOFF0 + p], qe = q + cr[C_ZCNT0 + p]; q < qe; ++q) {
+            for (int q = cr[C_ZOFF0 + p], qe = zw ? q : q + cr[C_ZCNT0 + p]; q < qe; ++q) {
               TargetRec t;
               if (q < zst) t = sZ[q];
               else t = gZ[q];
@@ -356,6 +394,50 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
           if (s3.qx > 0.0) atomicMax(&pat[3 * x + 2], (unsigned long long)__double_as_longlong(s3.qx));
         }
       }
+    }
+  }
+  // zone entries by waves: one (chain, pattern) per wave, one entry per lane
+  __syncthreads();
+  const int nzw = s_zw[nch], lane = tid & 63;
+  constexpr int kWaves = kTermsBlock / 64;
+  c = 0;
+  for (int x = part * kWaves + (tid >> 6); x < nzw; x += parts * kWaves) {
+    while (s_zw[c + 1] <= x) ++c;  // (chains without a wave pattern have equal entries: skipped)
+    const int* cr = chains + c * kChainInts;
+    const int ux = x - s_zw[c];
+    const uint32_t mm[1] = {deposit_bits((uint32_t)ux, (uint32_t)cr[C_PMASK])};
+    double2 B[1][3];
+    double e1[1], q1[1], q2[1];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) B[0][p] = make_double2(0.0, 0.0);
+    for (int q = 0, no = cr[C_NEST_OFF]; q < cr[C_NEST_LEN]; ++q) {  // (the path ends with the chain itself)
+      const int oc = nest[no + q];
+      walk_chain<false, 1>(chains + oc * kChainInts, sP, sS, sH, (const double*)nullptr, oc, mm, B, e1, q1, q2);
+    }
+    double e = 0.0, qn = INFINITY, qx = 0.0;
+    const int z1 = cr[C_ZOFF1], z2 = cr[C_ZOFF2], ze = z2 + cr[C_ZCNT2];
+    for (int q = cr[C_ZOFF0] + lane; q < ze; q += 64) {
+      TargetRec t;
+      if (q < zst) t = sZ[q];
+      else t = gZ[q];
+      const double2 b = q < z1 ? B[0][0] : (q < z2 ? B[0][1] : B[0][2]);
+      const double vx = t.W.x + b.x, vy = t.W.y + b.y;
+      const double q2 = fma(vx, vx, vy * vy);
+      const double mag = sqrt_nr(q2);
+      e = fmax(e, fmax(mag - t.lo, t.hi - mag));
+      qn = fmin(qn, q2);
+      qx = fmax(qx, q2);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      e = fmax(e, __shfl_xor(e, o, 64));
+      qn = fmin(qn, __shfl_xor(qn, o, 64));
+      qx = fmax(qx, __shfl_xor(qx, o, 64));
+    }
+    if (lane == 0) {
+      unsigned long long* a = pat + 3 * (cr[C_PBASE] + ux);
+      atomicMax(&a[0], (unsigned long long)__double_as_longlong(e));
+      atomicMin(&a[1], (unsigned long long)__double_as_longlong(qn));
+      atomicMax(&a[2], (unsigned long long)__double_as_longlong(qx));
     }
   }
 }
