@@ -23,10 +23,9 @@ constexpr int kTabLds = kMaxK * kChainInts + kMaxK * kMaxK + kMaxK * kSlotInts +
 
 // Child of kept node h on the tree path down to its descendant v.
 __device__ __forceinline__ int child_toward(const Topo& T, int h, int v) {
-  const int pv = T.pos[v];
   for (int q = T.ch_off[h]; q < T.ch_off[h + 1]; ++q) {
     const int x = T.ch[q];
-    if (T.pos[x] <= pv && pv < T.pos[x] + T.size[x]) return x;
+    if (x <= v && v < x + T.size[x]) return x;
   }
   return -1;
 }
@@ -93,15 +92,15 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
       c = x;
     }
     s_top[tid] = c;
-    s_spos[tid] = T.pos[e];
+    s_spos[tid] = e;
     s_ssize[tid] = T.size[e];
     s_sph[tid] = T.phase[e];
     const int hd = parent[c];
-    s_tpos[tid] = T.pos[c];
+    s_tpos[tid] = c;
     s_tsize[tid] = T.size[c];
     s_thead[tid] = hd;
     s_thph[tid] = hd >= 0 ? T.phase[hd] : 0;
-    s_thpos[tid] = hd >= 0 ? T.pos[hd] : -1;
+    s_thpos[tid] = hd;
     s_seg[tid] = e;
   }
   __syncthreads();
@@ -369,11 +368,11 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   auto classify = [&](int q, int& node, int& key) {  // key = chain * 8 | phase bits, -1: not a target
     int r = 0;
     while (r + 1 < nr && s_rcum[r + 1] <= q) ++r;
-    const int i = T.pre[s_rs[r] + (q - s_rcum[r])];
+    const int i = s_rs[r] + (q - s_rcum[r]);
     node = i;
     key = -1;
     if (segment[i] == g || !St.kept[i]) return;
-    const int pi = T.pos[i];
+    const int pi = i;
     int best = -1;
     for (int j = 0; j < k; ++j)
       if (s_spos[j] < pi && pi < s_spos[j] + s_ssize[j] && (best < 0 || s_spos[j] > s_spos[best])) best = j;

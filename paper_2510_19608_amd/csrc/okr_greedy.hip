@@ -35,13 +35,13 @@
 
 namespace okr {
 
-__global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const double2*, const double2*,
-                           double2*, int*);
+__global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const int*, const double2*,
+                           const double2*, double2*, int*);
 __global__ void k_powerflow(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                             const double2*, const double2*, double2, double2, double2, double, int, double, double,
-                            double2*, double2*, double2*, double*, int*, int*);
+                            double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
 __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const double2*, double, double, double2*,
-                            double*, int*);
+                            double*, int*, const int*, double2*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
 
 struct GState {
@@ -1341,8 +1341,8 @@ int setup(okr_greedy* g, const GPtrs& p, const okr_yblocks* Y, const okr_loads* 
   OKRG_HIP(g, hipMemcpyAsync(p.phase, g->phase.data(), n, hipMemcpyHostToDevice, st));
   OKRG_HIP(g, hipMemsetAsync(p.status, 0, sizeof(int) * 4, st));
   hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, (const int*)p.parent,
-                     (const uint8_t*)p.phase, (const int*)p.ch_off, (const int*)p.ch, (const double2*)Y->Y_diag,
-                     (const double2*)Y->Y_off, p.z, p.status);
+                     (const uint8_t*)p.phase, (const int*)p.ch_off, (const int*)p.ch,
+                     (const int*)nullptr, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
   hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, (const int*)p.parent, (const int*)p.lvl_off,
                      (const int*)p.lvl_nodes, g->nlev, (const double2*)p.z, p.Zr);
   const size_t c3 = (size_t)S * n * 3;
@@ -1351,13 +1351,13 @@ int setup(okr_greedy* g, const GPtrs& p, const okr_yblocks* Y, const okr_loads* 
     OKRG_HIP(g, hipMemcpyAsync(p.Vhat, L->Vhat, sizeof(double2) * c3, hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_from_vhat, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
                        (const uint8_t*)p.phase, (const double2*)L->S_load, (const double2*)p.Vhat, 0.0, 1e300, p.A,
-                       p.absV, p.status);
+                       p.absV, p.status, (const int*)nullptr, (double2*)nullptr);
   } else {
     hipLaunchKernelGGL(k_powerflow, dim3(S), dim3(256), 0, st, n, (const int*)p.parent, (const uint8_t*)p.phase,
                        (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev, (const int*)p.ch_off,
                        (const int*)p.ch, (const double2*)p.z, (const double2*)L->S_load, V0[0], V0[1], V0[2],
                        prm->pf_tol > 0 ? prm->pf_tol : 1e-13, prm->pf_maxit > 0 ? prm->pf_maxit : 100, 0.0, 1e300,
-                       p.Vhat, p.Ib, p.A, p.absV, p.iters, p.status);
+                       p.Vhat, p.Ib, p.A, p.absV, p.iters, p.status, (const int*)nullptr, (double2*)nullptr);
   }
   OKRG_HIP(g, hipGetLastError());
   return OKR_OK;

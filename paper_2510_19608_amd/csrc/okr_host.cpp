@@ -19,19 +19,19 @@
 
 namespace okr {
 // kernels (okr_kernels.hip, okr_build.hip)
-__global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const double2*, const double2*,
-                           double2*, int*);
+__global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const int*, const double2*,
+                           const double2*, double2*, int*);
 __global__ void k_powerflow(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                             const double2*, const double2*, double2, double2, double2, double, int, double, double,
-                            double2*, double2*, double2*, double*, int*, int*);
+                            double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
 __global__ void k_powerflow_lds(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                                 const double2*, const double2*, double2, double2, double2, double, int, double, double,
-                                double2*, double2*, double2*, double*, int*, int*);
+                                double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
 __global__ void k_powerflow_bfs(int, const uint8_t*, const int*, const int*, int, const int*, const int*,
                                 const double2*, const double2*, double2, double2, double2, double, int, double, double,
-                                double2*, double2*, double2*, double*, int*, int*);
+                                double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
 __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const double2*, double, double, double2*,
-                            double*, int*);
+                            double*, int*, const int*, double2*);
 __global__ void k_build_struct(Topo, State, const int*, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
                                unsigned long long*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
@@ -185,7 +185,7 @@ struct Layout {
 
 // offsets (in int32) of the static topology arrays inside the topology buffer
 struct TopoOffsets {
-  int parent, phase, segment, pos, size, pre, ch_off, ch, lvl_off, lvl_nodes, bfs_cf, bfs_pp, seg_off, seg_nodes,
+  int parent, phase, segment, size, ext, ch_off, ch, lvl_off, lvl_nodes, bfs_cf, bfs_pp, seg_off, seg_nodes,
       chunks, units, seg_top, total;
 };
 
@@ -621,19 +621,36 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     tp.insert(tp.end(), v.begin(), v.end());
     return o;
   };
-  TO.parent = put(h->parent);
-  TO.segment = put(h->segment);
-  TO.pos = put(h->pos);
-  TO.size = put(h->size);
-  TO.pre = put(h->pre);
-  TO.ch_off = put(h->ch_off);
-  TO.ch = put(h->ch);
+  // (device labels are preorder positions)
+  auto labels = [&](const std::vector<int>& nodes) {
+    std::vector<int> v(nodes.size());
+    for (size_t i = 0; i < nodes.size(); ++i) v[i] = nodes[i] < 0 ? -1 : h->pos[nodes[i]];
+    return v;
+  };
+  {
+    std::vector<int> par(n), seg(n), size(n), off(n + 1, 0), ch;
+    for (int q = 0; q < n; ++q) {
+      const int v = h->pre[q];
+      par[q] = h->parent[v] < 0 ? -1 : h->pos[h->parent[v]];
+      seg[q] = h->segment[v];
+      size[q] = h->size[v];
+      for (int e = h->ch_off[v]; e < h->ch_off[v + 1]; ++e) ch.push_back(h->pos[h->ch[e]]);
+      off[q + 1] = (int)ch.size();
+    }
+    if (ch.empty()) ch.push_back(0);
+    TO.parent = put(par);
+    TO.segment = put(seg);
+    TO.size = put(size);
+    TO.ext = put(h->pre);
+    TO.ch_off = put(off);
+    TO.ch = put(ch);
+  }
   TO.lvl_off = put(h->lvl_off);
-  TO.lvl_nodes = put(h->lvl_nodes);
+  TO.lvl_nodes = put(labels(h->lvl_nodes));
   TO.bfs_cf = put(h->bfs_cf);
   TO.bfs_pp = put(h->bfs_pp);
   TO.seg_off = put(h->seg_off);
-  TO.seg_nodes = put(h->seg_nodes.empty() ? std::vector<int>{0} : h->seg_nodes);
+  TO.seg_nodes = put(h->seg_nodes.empty() ? std::vector<int>{0} : labels(h->seg_nodes));
   TO.chunks = put(h->chunk_segs.empty() ? std::vector<int>{0} : h->chunk_segs);
   {  // the work units of every chunk, then one whole-segment unit per chunk position
     std::vector<int> u = h->units;
@@ -648,13 +665,16 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
       const int v = h->pre[q];
       if (h->segment[v] < 0) continue;
       const int pv = h->parent[v];
-      top[v] = (pv >= 0 && h->segment[pv] == h->segment[v]) ? top[pv] : v;
+      top[q] = (pv >= 0 && h->segment[pv] == h->segment[v]) ? top[h->pos[pv]] : q;
     }
     TO.seg_top = put(top);
   }
   TO.phase = (int)tp.size();
   tp.resize(tp.size() + (n + 3) / 4, 0);
-  std::memcpy(tp.data() + TO.phase, h->phase.data(), n);
+  {
+    uint8_t* ph = reinterpret_cast<uint8_t*>(tp.data() + TO.phase);
+    for (int q = 0; q < n; ++q) ph[q] = h->phase[h->pre[q]];
+  }
   TO.total = (int)tp.size();
   // table capacity of one segment (layout written by k_build_struct)
   h->tab_cap = kMaxK * kChainInts + kMaxK * kMaxK + n + kMaxK * kSlotInts + kMaxPairs * kPairInts + 3 * kMaxK +
@@ -819,9 +839,8 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.T.parent = tp + TO.parent;
   p.T.phase = (const uint8_t*)(tp + TO.phase);
   p.T.segment = tp + TO.segment;
-  p.T.pos = tp + TO.pos;
   p.T.size = tp + TO.size;
-  p.T.pre = tp + TO.pre;
+  p.T.ext = tp + TO.ext;
   p.T.ch_off = tp + TO.ch_off;
   p.T.ch = tp + TO.ch;
   p.T.seg_off = tp + TO.seg_off;
@@ -979,7 +998,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   hipLaunchKernelGGL(k_init_state, dim3((ninit + 255) / 256), dim3(256), 0, st, n, p.St, p.status, kStatusInts,
                      p.tickets, ntick, h->nlanes, h->L.lane_stride);
   hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, p.T.parent, p.T.phase, p.T.ch_off,
-                     p.T.ch, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
+                     p.T.ch, p.T.ext, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
   hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev,
                      (const double2*)p.z, p.Zroot);
   const size_t c3 = (size_t)S * n * 3;
@@ -987,7 +1006,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
     hipLaunchKernelGGL(k_copy2, dim3(1024), dim3(256), 0, st, (const double2*)loads->Vhat, p.Vhat, c3);
     hipLaunchKernelGGL(k_from_vhat, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S, p.T.phase,
                        (const double2*)loads->S_load, (const double2*)p.Vhat, mg->v_min, mg->v_max, p.A, p.absV,
-                       p.status);
+                       p.status, p.T.ext, p.Vcur);
   } else {
     const double2* V0 = (const double2*)loads->V0;
     // iterates and tree in LDS where both fit, else the breadth-first form
@@ -1003,14 +1022,13 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       hipLaunchKernelGGL(pf_lds ? k_powerflow_lds : k_powerflow, dim3(S), dim3(256), pf_lds, st, n, p.T.parent,
                          p.T.phase, p.lvl_off, p.lvl_nodes, h->nlev, p.T.ch_off, p.T.ch, (const double2*)p.z,
                          (const double2*)loads->S_load, V0[0], V0[1], V0[2], tol, maxit, mg->v_min, mg->v_max,
-                         p.Vhat, p.J, p.A, p.absV, p.iters, p.status);
+                         p.Vcur, p.J, p.A, p.absV, p.iters, p.status, p.T.ext, p.Vhat);
     else
       hipLaunchKernelGGL(k_powerflow_bfs, dim3(S), dim3(512), pf_bfs, st, n, p.T.phase, p.lvl_off, p.lvl_nodes,
                          h->nlev, p.bfs_cf, p.bfs_pp, (const double2*)p.z, (const double2*)loads->S_load, V0[0],
-                         V0[1], V0[2], tol, maxit, mg->v_min, mg->v_max, p.Vhat, p.J, p.A, p.absV, p.iters,
-                         p.status);
+                         V0[1], V0[2], tol, maxit, mg->v_min, mg->v_max, p.Vcur, p.J, p.A, p.absV, p.iters,
+                         p.status, p.T.ext, p.Vhat);
   }
-  hipLaunchKernelGGL(k_copy2, dim3(1024), dim3(256), 0, st, (const double2*)p.Vhat, p.Vcur, c3);
   SelParams sp;
   sp.e_bar = mg->e_bar;
   sp.vmin = mg->v_min;
@@ -1490,7 +1508,7 @@ static int reduce_feeder_impl(okr_handle* h, const okr_yblocks* Y, const okr_top
   }
   int nk = 0;
   for (int i = 0; i < n; ++i) {
-    out->super[i] = sup[i];
+    out->super[h->pre[i]] = h->pre[sup[i]];  // (labels to the caller's ids)
     out->kept_parent[i] = kp[i];
     nk += (sup[i] == i);
   }

@@ -97,15 +97,18 @@ __device__ __forceinline__ SegHdr load_hdr(const SegHdr* hdrs, const int* segs) 
   return load_hdr_g(hdrs, *as_cint(segs + blockIdx.z));
 }
 
-// Static topology on the device.
+// Static topology on the device.  A node's label on the device is its DFS
+// preorder position: a subtree (a segment's affected region) is a contiguous
+// run of labels, so a region's per-snapshot records are contiguous memory, and
+// no table maps between the two.  The caller's arrays are in the caller's node
+// ids: ext[label] is a label's id.
 struct Topo {
   int n;
   const int* parent;
   const uint8_t* phase;
   const int* segment;
-  const int* pos;       // DFS preorder position
   const int* size;      // subtree size
-  const int* pre;       // preorder -> node
+  const int* ext;       // label -> the caller's node id
   const int* ch_off;    // children CSR
   const int* ch;
   const int* seg_off;   // segment -> first index in seg_nodes

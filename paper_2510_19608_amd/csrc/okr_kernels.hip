@@ -2,9 +2,12 @@
 //
 // Data layout in HBM (complex values as double2 = (re, im)):
 //   z[n][9]            branch impedance of node i's upstream edge (restricted)
-//   Vhat, Vcur, A      [S][n][3]: scenario voltages, current candidate-state
-//                      voltages of kept nodes, aggregated load current of kept
-//                      nodes (consumed current, = -I^ moved by the assignment)
+//   Vhat               [S][n][3]: scenario voltages by the caller's node ids
+//   Vcur, A            [S][n][3] by label (DFS preorder position): current
+//                      candidate-state voltages of kept nodes, aggregated load
+//                      current of kept nodes (consumed current, = -I^ moved by
+//                      the assignment); every other per-node array goes by
+//                      label too
 //   absV[S][n][3]      |Vhat|
 //   per segment        P[S][npairs][3], slot/zone TargetRec[S][..][3], headV
 //   scores             MaskScore[snapshot group][2^k]
@@ -68,23 +71,26 @@ __device__ __forceinline__ double blk_maxabs(const double2* A) {
 
 // ---------------------------------------------------------- validation + z --
 // One thread per node: branch impedance z_i = (-Y_{i,parent})^+ and checks of
-// the admittance input (symmetry, zero absent-phase entries, no shunts).
+// the admittance input (symmetry, zero absent-phase entries, no shunts).  ext
+// (or null: the same) maps the labels of the tree arrays and z to the input's
+// node ids.
 // status bits: 1 singular, 2 absent-phase entry, 4 asymmetric, 8 shunt.
 __global__ void k_branch_z(int n, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
-                           const int* __restrict__ ch_off, const int* __restrict__ ch,
+                           const int* __restrict__ ch_off, const int* __restrict__ ch, const int* __restrict__ ext,
                            const double2* __restrict__ Ydiag, const double2* __restrict__ Yoff,
                            double2* __restrict__ z, int* __restrict__ status) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const unsigned ph = phase[i];
   int bad = 0;
-  const double2* Yd = Ydiag + (size_t)i * 9;
+  const int x = ext ? ext[i] : i;
+  const double2* Yd = Ydiag + (size_t)x * 9;
   double dscale = blk_maxabs(Yd);
   // Laplacian row: Y_ii + Y_{i,p} + sum_c Y_{i,c} = 0, with Y_{i,c} = Y_{c,i}^T
   double2 acc[9];
   for (int q = 0; q < 9; ++q) acc[q] = Yd[q];
   if (i > 0) {
-    const double2* Yo = Yoff + (size_t)i * 9;
+    const double2* Yo = Yoff + (size_t)x * 9;
     for (int q = 0; q < 9; ++q) acc[q] = cadd(acc[q], Yo[q]);
     const double oscale = blk_maxabs(Yo);
     for (int r = 0; r < 3; ++r)
@@ -101,7 +107,7 @@ __global__ void k_branch_z(int n, const int* __restrict__ parent, const uint8_t*
     for (int q = 0; q < 9; ++q) z[q] = make_double2(0.0, 0.0);
   }
   for (int e = ch_off[i]; e < ch_off[i + 1]; ++e) {
-    const double2* Yc = Yoff + (size_t)ch[e] * 9;
+    const double2* Yc = Yoff + (size_t)(ext ? ext[ch[e]] : ch[e]) * 9;
     for (int r = 0; r < 3; ++r)
       for (int c = 0; c < 3; ++c) acc[r * 3 + c] = cadd(acc[r * 3 + c], Yc[c * 3 + r]);
   }
@@ -118,6 +124,9 @@ __global__ void k_branch_z(int n, const int* __restrict__ parent, const uint8_t*
 // Scenario library (Section III): constant-PQ wye loads, backward/forward
 // sweep on the radial tree, one block per snapshot, level-synchronous.
 // status bit 16: not converged; bit 32: base network outside the band.
+// The tree arrays, V, J, A and absV go by label, Sload by the caller's node
+// ids (ext[label], or null: the same); Vext, where given, takes the voltages
+// by the caller's ids.
 // Forward-sweep update of node i: V(i) = V(parent) - z(i) J(i) on its
 // present phases, and the largest change into dmax (NaN-propagating).
 __device__ __forceinline__ void forward_node(int i, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
@@ -147,6 +156,7 @@ __device__ __forceinline__ void powerflow_body(
     const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
     double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
     double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
+    const int* __restrict__ ext, double2* __restrict__ Vext,
     double2* sbuf, double* shd) {
   constexpr bool LDS = MODE == kPfAll;
   const int l = blockIdx.x;
@@ -200,10 +210,12 @@ __device__ __forceinline__ void powerflow_body(
     // load currents conj(S/V) of every node in one pass (off the level
     // steps' latency chain), then the backward sweep adds each level's
     // children into their parents, deepest level first
-    for (int i = tid; i < n; i += bd)
+    for (int i = tid; i < n; i += bd) {
+      const int x = ext ? ext[i] : i;
       for (int p = 0; p < 3; ++p)
-        Jl[i * 3 + p] = (i > 0 && (phase[i] >> p & 1u)) ? cconj(cdiv(Sl[i * 3 + p], Vl[i * 3 + p]))
+        Jl[i * 3 + p] = (i > 0 && (phase[i] >> p & 1u)) ? cconj(cdiv(Sl[x * 3 + p], Vl[i * 3 + p]))
                                                         : make_double2(0.0, 0.0);
+    }
     __syncthreads();
     for (int lev = nlev - 2; lev >= 0; --lev) {
       for (int q = lvl_off[lev] + tid; q < lvl_off[lev + 1]; q += bd) {
@@ -265,16 +277,19 @@ __device__ __forceinline__ void powerflow_body(
     if (dmax <= tol) { conv = true; break; }
   }
   double vlo = 1e300, vhi = -1e300;
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int x = ext ? ext[i] : i;
     for (int p = 0; p < 3; ++p) {
       const bool pr = (phase[i] >> p & 1u);
       const double2 v = Vl[i * 3 + p];
       if (LDS) V[base + i * 3 + p] = v;
-      A[base + i * 3 + p] = (i > 0 && pr) ? cconj(cdiv(Sl[i * 3 + p], v)) : make_double2(0.0, 0.0);
+      if (Vext) Vext[base + x * 3 + p] = v;
+      A[base + i * 3 + p] = (i > 0 && pr) ? cconj(cdiv(Sl[x * 3 + p], v)) : make_double2(0.0, 0.0);
       const double m = pr ? sqrt(cabs2(v)) : 0.0;
       absV[base + i * 3 + p] = m;
       if (pr) { vlo = fmin(vlo, m); vhi = fmax(vhi, m); }
     }
+  }
   vlo = block_reduce(vlo, [](double a, double b) { return fmin(a, b); }, shd);
   vhi = block_reduce(vhi, [](double a, double b) { return fmax(a, b); }, shd);
   if (threadIdx.x == 0) {
@@ -291,10 +306,11 @@ __global__ __launch_bounds__(256) void k_powerflow(
     const int* __restrict__ ch_off, const int* __restrict__ ch, const double2* __restrict__ z,
     const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
     double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
-    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status) {
+    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
+    const int* __restrict__ ext, double2* __restrict__ Vext) {
   __shared__ double shd[16];
   powerflow_body<kPfGlobal>(n, parent, phase, lvl_off, lvl_nodes, nlev, ch_off, ch, z, Sload, v0a, v0b, v0c, tol, maxit,
-                            vmin, vmax, V, J, A, absV, iters, status, nullptr, shd);
+                            vmin, vmax, V, J, A, absV, iters, status, ext, Vext, nullptr, shd);
 }
 
 // The same with the voltage and current iterates in dynamic LDS (2 x n x 3
@@ -306,11 +322,12 @@ __global__ __launch_bounds__(256) void k_powerflow_lds(
     const int* __restrict__ ch_off, const int* __restrict__ ch, const double2* __restrict__ z,
     const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
     double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
-    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status) {
+    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
+    const int* __restrict__ ext, double2* __restrict__ Vext) {
   extern __shared__ double2 pf_lds[];
   __shared__ double shd[16];
   powerflow_body<kPfAll>(n, parent, phase, lvl_off, lvl_nodes, nlev, ch_off, ch, z, Sload, v0a, v0b, v0c, tol, maxit,
-                         vmin, vmax, V, J, A, absV, iters, status, pf_lds, shd);
+                         vmin, vmax, V, J, A, absV, iters, status, ext, Vext, pf_lds, shd);
 }
 
 // The same for feeders whose iterates do not fit in LDS (n < 65536): every
@@ -319,7 +336,7 @@ __global__ __launch_bounds__(256) void k_powerflow_lds(
 // cf[q] .. cf[q+1]-1 in child-list order, pp[q] the parent's position), so
 // each level step reads and writes contiguous records and a node's children
 // are one contiguous run.  The queue tables (16-bit) sit in dynamic LDS; the
-// snapshot's loads and voltages in queue order use the Vhat and A slices as
+// snapshot's loads and voltages in queue order use the V and A slices as
 // scratch until the end, the branch currents the J slice.  Each node's
 // arithmetic, and the order of every sum, is that of the node-order form.
 __global__ __launch_bounds__(512) void k_powerflow_bfs(
@@ -327,7 +344,8 @@ __global__ __launch_bounds__(512) void k_powerflow_bfs(
     int nlev, const int* __restrict__ gcf, const int* __restrict__ gpp, const double2* __restrict__ z,
     const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
     double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
-    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status) {
+    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
+    const int* __restrict__ ext, double2* __restrict__ Vext) {
   extern __shared__ double2 pf_lds[];
   __shared__ double shd[16];
   const int l = blockIdx.x, tid = threadIdx.x, bd = blockDim.x;
@@ -352,11 +370,11 @@ __global__ __launch_bounds__(512) void k_powerflow_bfs(
   __syncthreads();
   const double2 v0[3] = {v0a, v0b, v0c};
   for (int q = tid; q < n; q += bd) {
-    const int i = node[q];
+    const int x = ext[node[q]];
     const unsigned m = ph[q];
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
-      Sb[q * 3 + p] = Sl[i * 3 + p];
+      Sb[q * 3 + p] = Sl[x * 3 + p];
       Vb[q * 3 + p] = (m >> p & 1u) ? v0[p] : make_double2(0.0, 0.0);
     }
   }
@@ -428,7 +446,7 @@ __global__ __launch_bounds__(512) void k_powerflow_bfs(
     if (!(dmax <= 1e3)) break;
     if (dmax <= tol) { conv = true; break; }
   }
-  // voltages back to node order (over the loads, no longer read), then the
+  // voltages back to label order (over the loads, no longer read), then the
   // load currents and magnitudes at the final voltages
   for (int q = tid; q < n; q += bd) {
     const int i = node[q];
@@ -437,15 +455,18 @@ __global__ __launch_bounds__(512) void k_powerflow_bfs(
   }
   __syncthreads();
   double vlo = 1e300, vhi = -1e300;
-  for (int i = tid; i < n; i += bd)
+  for (int i = tid; i < n; i += bd) {
+    const int x = ext[i];
     for (int p = 0; p < 3; ++p) {
       const bool pr = (phase[i] >> p & 1u);
       const double2 v = V[base + i * 3 + p];
-      A[base + i * 3 + p] = (i > 0 && pr) ? cconj(cdiv(Sl[i * 3 + p], v)) : make_double2(0.0, 0.0);
+      Vext[base + x * 3 + p] = v;
+      A[base + i * 3 + p] = (i > 0 && pr) ? cconj(cdiv(Sl[x * 3 + p], v)) : make_double2(0.0, 0.0);
       const double m = pr ? sqrt(cabs2(v)) : 0.0;
       absV[base + i * 3 + p] = m;
       if (pr) { vlo = fmin(vlo, m); vhi = fmax(vhi, m); }
     }
+  }
   vlo = block_reduce(vlo, [](double a, double b) { return fmin(a, b); }, shd);
   vhi = block_reduce(vhi, [](double a, double b) { return fmax(a, b); }, shd);
   if (tid == 0) {
@@ -475,16 +496,21 @@ __global__ __launch_bounds__(1024) void k_zroot(int n, const int* __restrict__ p
   }
 }
 
-// Given V^ (caller supplied): load currents and magnitudes, band check.
+// Given V^ (caller supplied): load currents and magnitudes, band check; with
+// ext (label -> the caller's node id) the voltages by label too.
 __global__ void k_from_vhat(int n, int S, const uint8_t* __restrict__ phase, const double2* __restrict__ Sload,
                             const double2* __restrict__ V, double vmin, double vmax, double2* __restrict__ A,
-                            double* __restrict__ absV, int* __restrict__ status) {
+                            double* __restrict__ absV, int* __restrict__ status, const int* __restrict__ ext,
+                            double2* __restrict__ Vlab) {
   const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= (size_t)S * n * 3) return;
   const int p = q % 3, i = (q / 3) % n;
+  const size_t x = ext ? q + ((long)ext[i] - i) * 3 : q;
   const bool pr = (phase[i] >> p & 1u);
-  A[q] = (i > 0 && pr) ? cconj(cdiv(Sload[q], V[q])) : make_double2(0.0, 0.0);
-  const double m = pr ? sqrt(cabs2(V[q])) : 0.0;
+  const double2 v = V[x];
+  if (Vlab) Vlab[q] = v;
+  A[q] = (i > 0 && pr) ? cconj(cdiv(Sload[x], v)) : make_double2(0.0, 0.0);
+  const double m = pr ? sqrt(cabs2(v)) : 0.0;
   absV[q] = m;
   if (pr && (m < vmin || m > vmax)) atomicOr(status, 32);
 }
@@ -722,7 +748,7 @@ __global__ __launch_bounds__(64) void k_apply(const SegHdr* __restrict__ hdrs, c
   for (int q = threadIdx.x; q < H.nomega; q += blockDim.x) {
     int r = 0;
     while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
-    const int i = T.pre[rg[3 * r] + (q - rg[3 * r + 2])];
+    const int i = rg[3 * r] + (q - rg[3 * r + 2]);
     // up through reduced nodes; a reduced node's recorded super (before or
     // after this update) is an ancestor with only reduced nodes in between
     int v = i;
@@ -780,11 +806,12 @@ __global__ void k_kron_yeq(Topo T, State St, const double2* __restrict__ z, doub
                            double2* __restrict__ Yk_off, int* __restrict__ kp_out, int* __restrict__ status) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= T.n) return;
-  double2* yo = Yk_off + (size_t)x * 9;
+  const int xe = T.ext[x];  // (the outputs go by the caller's node ids)
+  double2* yo = Yk_off + (size_t)xe * 9;
   double2* ye = yeq + (size_t)x * 9;
   for (int q = 0; q < 9; ++q) { yo[q] = make_double2(0.0, 0.0); ye[q] = yo[q]; }
   const int kp = (x > 0 && St.kept[x]) ? St.sup[T.parent[x]] : -1;
-  kp_out[x] = kp;
+  kp_out[xe] = kp < 0 ? -1 : T.ext[kp];
   if (kp < 0) return;
   const unsigned ph = T.phase[x];
   double2 Z[9];
@@ -817,7 +844,7 @@ __global__ void k_kron_diag(Topo T, State St, const double2* __restrict__ yeq, d
         for (int q = 0; q < 9; ++q) D[q] = cadd(D[q], yeq[(size_t)v * 9 + q]);
     }
   }
-  for (int q = 0; q < 9; ++q) Yk_diag[(size_t)x * 9 + q] = D[q];
+  for (int q = 0; q < 9; ++q) Yk_diag[(size_t)T.ext[x] * 9 + q] = D[q];
 }
 
 }  // namespace okr

@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
     for (int q = tid; q < H.nomega; q += kTermsBlock) {
       int r = 0;
       while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
-      const int i = T.pre[rg[3 * r] + (q - rg[3 * r + 2])];
+      const int i = rg[3 * r] + (q - rg[3 * r + 2]);
       const int sp = St.sup[i];
       const unsigned ph = T.phase[i];
       if (T.segment[sp] == g) {

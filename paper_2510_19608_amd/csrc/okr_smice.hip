@@ -30,7 +30,7 @@ namespace okr {
 __device__ __forceinline__ int sm_omega_node(const Topo& T, const int* rg, int nr, int q) {
   int r = 0;
   while (r + 1 < nr && rg[3 * (r + 1) + 2] <= q) ++r;
-  return T.pre[rg[3 * r] + (q - rg[3 * r + 2])];
+  return rg[3 * r] + (q - rg[3 * r + 2]);
 }
 
 // Zone entry of the lowest present phase of node i, or -1 if i is not a
