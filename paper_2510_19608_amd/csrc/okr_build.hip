@@ -47,9 +47,8 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   __shared__ int s_pmask[kMaxK];                                        // chain c: mask bits of its nesting path
   __shared__ int s_okey[kMaxK];  // chain c: (preorder position << 5) | j of the deepest segment node above its head
   // exclusive prefix sums over the chains (entry nch: the totals) of: nesting
-  // depth, pairs, new Omega_g range, its nodes, chain patterns, pattern items
-  __shared__ int s_xs[6][kMaxK + 1];
-  __shared__ int s_dn[kMaxK];                 // chain c: bottom slots enumerated by one pattern item
+  // depth, pairs, new Omega_g range, its nodes, chain patterns
+  __shared__ int s_xs[5][kMaxK + 1];
   __shared__ int s_keycnt[kMaxK * 3], s_keyoff[kMaxK * 3], s_keycur[kMaxK * 3];
   __shared__ SegHdr s_h;
   __shared__ int s_err, s_nch;
@@ -205,9 +204,9 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   __syncthreads();
   // the chains' table offsets: prefix sums in one wave (lane = chain)
   if (tid < 64) {
-    int v[6] = {0, 0, 0, 0, 0, 0}, n = 0, npats = 0;
+    int v[5] = {0, 0, 0, 0, 0};
     if (tid < nch) {
-      n = s_cslot0[tid + 1] - s_cslot0[tid];
+      const int n = s_cslot0[tid + 1] - s_cslot0[tid];
       v[0] = s_depth[tid];
       v[1] = n * (n + 1) / 2;
       v[2] = s_rkeep[tid];
@@ -215,24 +214,13 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
       v[4] = 1 << __popc(s_pmask[tid]);
     }
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      if (i == 5 && tid < nch) {
-        // pattern items (the patterns' number is known by now): where one
-        // block's threads cannot take a pattern each, an item of a chain of 6
-        // bits or more enumerates its bottom 3 slots, so that the walk above
-        // them is done once for 8 patterns
-        const int bits = __popc(s_pmask[tid]);
-        const int d = (npats > 256 && bits >= 6) ? min(3, n) : 0;
-        s_dn[tid] = d;
-        v[5] = 1 << (bits - d);
-      }
+    for (int i = 0; i < 5; ++i) {
       int x = v[i];
       for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(x, o, 64);
         if (tid >= o) x += y;
       }
       if (tid <= nch) s_xs[i][tid] = x - v[i];
-      if (i == 4) npats = __shfl(x, 63, 64);
     }
   }
   __syncthreads();
@@ -259,7 +247,6 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     H.nslots = k;
     H.npairs = npairs;
     H.npat = npat;
-    H.nitem = s_xs[5][nch];
     // the structural part must fit the segment's table (and the shared image,
     // which holds the largest possible one)
     if (o_zent > tab_cap || o_zent > kTabLds) s_err = 1;
@@ -312,8 +299,6 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     cr[C_PHW2] = phw[2];
     cr[C_PMASK] = s_pmask[c];
     cr[C_PBASE] = pbase;
-    cr[C_D] = s_dn[c];
-    cr[C_IBASE] = s_xs[5][c];
     for (int p = 0; p < 3; ++p) {
       cr[C_ZOFF0 + p] = 0;  // zone ranges filled after the zone pass
       cr[C_ZCNT0 + p] = 0;
@@ -407,6 +392,30 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
       s_h.nz = acc + cnt;
       s_h.total_ints = H.o_zent + 3 * (acc + cnt);
       if (s_h.total_ints > tab_cap) s_err = 1;
+    }
+  }
+  // Pattern items of the table kernel: where one block's threads cannot take a
+  // pattern each, an item of a chain of 6 bits or more enumerates its bottom
+  // slots, up to 3 (the walk above them is done once for 8 patterns), fewer
+  // with zone entries below the chain (at most 8 entry terms per item).
+  if (tid < 64) {
+    int items = 0, d = 0;
+    if (tid < nch) {
+      const int bits = __popc(s_pmask[tid]), n = s_cslot0[tid + 1] - s_cslot0[tid];
+      const int z = s_keycnt[tid * 3] + s_keycnt[tid * 3 + 1] + s_keycnt[tid * 3 + 2];
+      if (npat > 256 && bits >= 6) d = min(n, z <= 1 ? 3 : (z <= 2 ? 2 : (z <= 4 ? 1 : 0)));
+      items = 1 << (bits - d);
+    }
+    int x = items;
+    for (int o = 1; o < 32; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (tid >= o) x += y;
+    }
+    if (tid < nch) {
+      int* cr = tab + H.o_chain + tid * kChainInts;
+      cr[C_D] = d;
+      cr[C_IBASE] = x - items;
+      if (tid == nch - 1) s_h.nitem = x;
     }
   }
   // Lane bits of the scoring kernel: a wave's 64 lanes vary 6 mask bits, and

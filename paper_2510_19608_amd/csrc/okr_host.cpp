@@ -35,10 +35,10 @@ __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const doub
 __global__ void k_build_struct(Topo, State, const int*, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
                                unsigned long long*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
-template <bool BUILD, bool PAT>
+template <bool BUILD, bool PAT, int NS, bool DEEP>
 __global__ void k_seg_terms(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, const double2*,
                             const double2*, const double2*, const double*, double2*, TargetRec*, double2*, TargetRec*,
-                            double*, int, int, unsigned long long*, unsigned long long*, const int*, int*);
+                            double*, TermsCaps, unsigned long long*, unsigned long long*, const int*, int*);
 __global__ void k_terms_init(const int*, int, size_t, unsigned long long*);
 __global__ void k_chain_terms(const SegHdr*, const int*, size_t, const int*, const double2*, const TargetRec*,
                               const double2*, const TargetRec*, const double*, const uint32_t*, const int*, int, int,
@@ -228,8 +228,9 @@ struct okr_handle {
   int nlanes = 1;
   std::vector<int> chunk_off, chunk_segs, chunk_k;
   // table-kernel work units of chunk c: units[unit_off[c] .. unit_off[c + 1])
-  // (unit_pack); chunk_nz = the most zone entries a segment of it can have
-  std::vector<int> units, unit_off, chunk_nz;
+  // (unit_pack); chunk_caps = the plan's bounds on its segments' tables
+  std::vector<int> units, unit_off;
+  std::vector<TermsCaps> chunk_caps;
 };
 
 namespace {
@@ -244,9 +245,14 @@ size_t terms_lds_bytes(int k, int zcap) {
          (size_t)k * 3 * (sizeof(TargetRec) + sizeof(double2)) + (size_t)zcap * sizeof(TargetRec);
 }
 // The tables and the patterns of a chunk come from one launch while its zone
-// records fit in LDS beside the rest (62 KB: two blocks on a compute unit);
-// beyond, one launch builds the tables and another evaluates the patterns.
+// records fit in LDS beside the rest (62 KB per snapshot); beyond, one launch
+// builds the tables and another evaluates the patterns, each with its first
+// kTermsZone zone entries in LDS.  Blocks of several snapshots stay within
+// 76 KB, two of them on a compute unit.
 constexpr size_t kTermsLdsMax = 62 * 1024;
+constexpr size_t kTermsLdsMulti = 76 * 1024;
+constexpr size_t kTermsPairs2 = 256;  // (unit, snapshot) pairs from which a block takes two
+constexpr int kTermsPats = 1024;  // patterns folded in LDS over a block's snapshots (24 KB)
 }  // namespace
 
 #define OKR_FAIL(h, code, ...)            \
@@ -577,16 +583,19 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     // of 2^(segment nodes on the node's root path) patterns; one unit per 4096
     // of that bound, at most 16 (each unit forms the snapshot's tables again).
     // Zone entries are node-phases of the segment's region outside it.
-    std::vector<int> parts(nseg, 1), nzb(nseg, 0);
+    std::vector<int> parts(nseg, 1);
+    std::vector<TermsCaps> caps(nseg);
     for (int g = 0; g < nseg; ++g) {
       const int* nodes = h->seg_nodes.data() + h->seg_off[g];
       const int k = ksz(g);
       double pats = 0.0;
+      int pairs = 0;  // (a node pairs with its chain's head and the slots above it)
       std::vector<int> open;  // the segment nodes above the current one (preorder)
       for (int j = 0; j < k; ++j) {
         while (!open.empty() && h->pos[nodes[j]] >= h->pos[open.back()] + h->size[open.back()]) open.pop_back();
         open.push_back(nodes[j]);
         pats += std::ldexp(1.0, (int)open.size());
+        pairs += (int)open.size();
       }
       pats = std::min(pats, std::ldexp(1.0, k + 1));
       parts[g] = (int)std::min(16.0, std::max(1.0, std::ceil(pats / 4096.0)));
@@ -596,20 +605,21 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
           const int v = h->pre[q];
           if (h->segment[v] != g) nz += __builtin_popcount(h->phase[v]);
         }
-      nzb[g] = (int)std::min<long>(nz, INT32_MAX);
+      caps[g] = {terms_icap(k), pairs, k, (int)std::min<long>(nz, 1 << 20), (int)std::min<double>(pats, kTermsPats)};
     }
     h->units.clear();
     h->unit_off.assign(1, 0);
-    h->chunk_nz.clear();
+    h->chunk_caps.clear();
     for (size_t c = 0; c < h->chunk_k.size(); ++c) {
-      int nz = 0;
+      TermsCaps m{};
       for (int i = h->chunk_off[c]; i < h->chunk_off[c + 1]; ++i) {
         const int g = h->chunk_segs[i];
-        nz = std::max(nz, nzb[g]);
+        m = {std::max(m.ints, caps[g].ints), std::max(m.pairs, caps[g].pairs), std::max(m.slots, caps[g].slots),
+             std::max(m.zones, caps[g].zones), std::max(m.pats, caps[g].pats)};
         for (int q = 0; q < parts[g]; ++q) h->units.push_back(unit_pack(i - h->chunk_off[c], q, parts[g]));
       }
       h->unit_off.push_back((int)h->units.size());
-      h->chunk_nz.push_back(nz);
+      h->chunk_caps.push_back(m);
     }
   }
   // packed static topology
@@ -944,22 +954,37 @@ void list_score(const okr_handle* h, const Ptrs& w, const int* segp, int nz, int
 // One launch of the table kernel over chunk c: the segments' numeric tables
 // (build) and their chain patterns (pats).
 void launch_terms(const okr_handle* h, const Ptrs& q, int c, bool build, bool pats, const int* gates, hipStream_t st) {
-  const int kc = h->chunk_k[c], c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
+  const int c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0, S = h->S;
   // building alone takes one unit per segment: the pattern parts' first units
   // (part 0 of each segment) are not contiguous, so such a launch passes the
   // plain list of positions
   const int u0 = pats ? h->unit_off[c] : 0, nu = pats ? h->unit_off[c + 1] - u0 : nz;
   const int* units = pats ? q.units + u0 : q.units + h->units.size();
-  const int zcap = build && pats ? h->chunk_nz[c] : kTermsZone;
-  const size_t lds = terms_lds_bytes(kc, zcap);
-#define OKR_SEG_TERMS(B_, P_)                                                                                          \
-  hipLaunchKernelGGL((k_seg_terms<B_, P_>), dim3(nu, h->S), dim3(256), lds, st, (const SegHdr*)q.hdrs, q.chunks + c0,  \
-                     h->L.lane_stride, units, (const int*)q.tab, q.T, q.St, (const double2*)q.Zroot,                   \
-                     (const double2*)q.Vcur, (const double2*)q.A, (const double*)q.absV, q.P, q.srec, q.headV, q.zrec, \
-                     q.econst, terms_icap(kc), zcap, q.pat, q.ecmax, gates, q.status)
-  if (build && pats) OKR_SEG_TERMS(true, true);
-  else if (build) OKR_SEG_TERMS(true, false);
-  else OKR_SEG_TERMS(false, true);
+  TermsCaps caps = h->chunk_caps[c];
+  // Two snapshots per block once the launch has a block for every compute unit
+  // without: half of the patterns' atomics fold in LDS (8400-node launches 74
+  // -> 60 us; four per block, in lockstep on a compute unit, took 70).  The
+  // snapshot is the grid's fast index, so that the blocks of a heavy segment
+  // spread over the XCDs (60 -> 55 us; one segment's blocks otherwise all land
+  // on one XCD where a chunk has 8 units).
+  const bool deep = nu > nz;  // a segment of several parts
+  int ns = 1;
+  if (build && pats && !deep) {
+    ns = (size_t)S * nu >= kTermsPairs2 ? 2 : 1;
+    while (ns > 1 && terms_lds(caps, ns) > kTermsLdsMulti) ns /= 2;
+  }
+  if (!(build && pats)) caps.zones = std::min(caps.zones, kTermsZone);
+  if (ns == 1) caps.pats = 0;
+#define OKR_SEG_TERMS(B_, P_, N_, D_)                                                                                  \
+  hipLaunchKernelGGL((k_seg_terms<B_, P_, N_, D_>), dim3((S + N_ - 1) / N_, nu), dim3(256 * N_), terms_lds(caps, N_), st,  \
+                     (const SegHdr*)q.hdrs, q.chunks + c0, h->L.lane_stride, units, (const int*)q.tab, q.T, q.St,      \
+                     (const double2*)q.Zroot, (const double2*)q.Vcur, (const double2*)q.A, (const double*)q.absV, q.P, \
+                     q.srec, q.headV, q.zrec, q.econst, caps, q.pat, q.ecmax, gates, q.status)
+  if (build && pats && deep) OKR_SEG_TERMS(true, true, 1, true);
+  else if (build && pats && ns == 2) OKR_SEG_TERMS(true, true, 2, false);
+  else if (build && pats) OKR_SEG_TERMS(true, true, 1, false);
+  else if (build) OKR_SEG_TERMS(true, false, 1, false);
+  else OKR_SEG_TERMS(false, true, 1, true);
 #undef OKR_SEG_TERMS
 }
 
@@ -976,7 +1001,9 @@ void launch_terms(const okr_handle* h, const Ptrs& q, int c, bool build, bool pa
 void pattern_score(const okr_handle* h, const Ptrs& q, int c, bool build, const SelParams& sp, const int* gates,
                    hipStream_t st) {
   const int kc = h->chunk_k[c], c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
-  const bool fused = build && terms_lds_bytes(kc, h->chunk_nz[c]) <= kTermsLdsMax;
+  TermsCaps one = h->chunk_caps[c];
+  one.pats = 0;
+  const bool fused = build && terms_lds(one, 1) <= kTermsLdsMax;
   if (build && !fused) launch_terms(h, q, c, true, false, nullptr, st);
   launch_terms(h, q, c, fused, true, gates, st);
   hipLaunchKernelGGL(k_fac_combine, dim3(((1u << kc) + 255) / 256, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs,
@@ -1327,6 +1354,8 @@ static int reduce_feeder_impl(okr_handle* h, const okr_yblocks* Y, const okr_top
       OKR_HIP(h, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_powerflow_bfs),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPfLdsMax));
   }
+  OKR_HIP(h, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_seg_terms<true, true, 2, false>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTermsLdsMulti));
   const auto t0 = clk::now();
   {
     const size_t tb = sizeof(int) * h->TO.total;

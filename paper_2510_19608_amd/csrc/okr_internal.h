@@ -78,6 +78,18 @@ __device__ __forceinline__ T* lane_ptr_z(T* p, size_t lstride, int z) {
 // count of its segment's pattern items, one int32 per unit.
 __host__ __device__ __forceinline__ int unit_pack(int z, int part, int parts) { return z | part << 8 | parts << 16; }
 
+// LDS capacities of the table kernel for a chunk (the plan's bounds on its
+// segments): table ints, pairs, slots, zone entries, patterns folded in LDS.
+struct TermsCaps {
+  int ints, pairs, slots, zones, pats;
+};
+__host__ __device__ __forceinline__ size_t terms_snap_lds(const TermsCaps& c) {  // of one snapshot's tables
+  return (size_t)c.pairs * 3 * 16 + (size_t)c.slots * 3 * (sizeof(double) * 4 + 16) + (size_t)c.zones * sizeof(double) * 4;
+}
+__host__ __device__ __forceinline__ size_t terms_lds(const TermsCaps& c, int ns) {
+  return (size_t)(c.ints + 3) / 4 * 16 + (size_t)(c.pats + 1) / 2 * 48 + ns * terms_snap_lds(c);
+}
+
 // Read-only int tables (segment structure) in the constant address space:
 // kernels never write them while reading, so wave-uniform reads compile to
 // scalar loads through the scalar cache instead of per-lane vector loads.

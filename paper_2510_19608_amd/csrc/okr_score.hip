@@ -3,6 +3,7 @@
 // a mask list.  Built with NaNs excluded (no input or intermediate here is
 // NaN), which lets max/min compile to single instructions.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -52,21 +53,25 @@ __device__ __forceinline__ int tile_record(const MaskScore& r, uint32_t m, uint3
 
 // ---- a segment's numeric tables and its chain patterns, per snapshot ----
 //
-// A block serves one snapshot (blockIdx.y) of one unit (a segment of the
-// chunk, or a part of its pattern items).  With BUILD it forms the snapshot's
-// tables in LDS from the search state -- P = Z(super -> reduced) A_reduced
-// with Z(s -> r) = Zroot(r) - Zroot(s), the records' voltages, every
-// cluster's smallest and largest |V^| over its members, the constant error of
-// clusters outside Omega_g -- and writes them out (part 0) for the kernels
-// that read them later (state update, SMICE, short lists, the FP32 screen);
-// without, it stages the tables an earlier launch wrote.  With PAT it then
-// folds every pattern's terms into the segment's pattern table.
+// A block serves NS snapshots (blockIdx.x; 256 threads and tables of its own
+// each) of one unit (a segment of the chunk, or a part of its pattern items).
+// With BUILD it forms the snapshots' tables in LDS from the search state -- P =
+// Z(super -> reduced) A_reduced with Z(s -> r) = Zroot(r) - Zroot(s), the
+// records' voltages, every cluster's smallest and largest |V^| over its
+// members, the constant error of clusters outside Omega_g -- and writes them
+// out (part 0) for the kernels that read them later (state update, SMICE, short
+// lists, the FP32 screen); without, it stages the tables an earlier launch
+// wrote.  With PAT it then folds every pattern's terms into the segment's
+// pattern table, in LDS over its NS snapshots first where the table fits there:
+// the atomics to memory are performed beyond the XCDs' caches and bound the
+// launch (31 of 78 us on the 8400-node feeder with one snapshot per block).
 //
 // Building where the patterns are evaluated saves two launches and the
 // tables' round trip through memory.  An item walks its chain's upper slots
 // once and enumerates the bottom C_D of them by nested loops whose branch is
 // the same for the whole wave: about 2.75 slot evaluations per pattern of a
-// chain of 11 bits instead of 11.
+// chain of 11 bits instead of 11.  (Chains with zone entries enumerate fewer
+// slots: a thread would go through the entries once per pattern of its item.)
 //
 // A chain with more zone entries below it than it has patterns (and at least
 // kZoneWave of them) leaves the few threads of its patterns with hundreds of
@@ -81,43 +86,107 @@ struct ChainState {
   double e, qn, qx;
 };
 
-// Slot r of the chain reduced: the moved current's rise, the slot's cluster
-// against the current super.
+// One slot for the present phases `ph`: reduced (the moved current's rise pr,
+// the slot's cluster against the current super) or kept (it becomes the super
+// of the slots below).  No branch on the phase: the three phases' loads and
+// square roots overlap (a branch each made a slot wait for them in turn), and
+// an absent phase contributes nothing -- its magnitude is taken of 1 and its
+// terms are discarded; its shift is never read again, since phases only
+// shrink down a chain.  SKIP branches instead: segments with thousands of
+// patterns keep every lane of a wave on one chain and are bound by the
+// arithmetic (79 against 88 ms on a 300-node feeder of 20-node chains).
+template <bool SKIP>
 __device__ __forceinline__ void slot_reduced(ChainState& s, int ph, const double2* pr, const TargetRec* tr) {
 #pragma unroll
-  for (int p = 0; p < 3; ++p)
-    if (ph >> p & 1) {
-      s.S[p].x += pr[p].x;
-      s.S[p].y += pr[p].y;
-      s.e = fmax(s.e, fmax(s.sm[p] - tr[p].lo, tr[p].hi - s.sm[p]));
-    }
+  for (int p = 0; p < 3; ++p) {
+    if (SKIP && !(ph >> p & 1)) continue;
+    const double2 pv = pr[p];
+    s.S[p].x += pv.x;
+    s.S[p].y += pv.y;
+    const double d = fmax(s.sm[p] - tr[p].lo, tr[p].hi - s.sm[p]);
+    s.e = fmax(s.e, (ph >> p & 1) ? d : 0.0);
+  }
 }
-// Slot r kept: it becomes the super of the slots below.
+template <bool SKIP>
 __device__ __forceinline__ void slot_kept(ChainState& s, int ph, int r, const TargetRec* tr) {
 #pragma unroll
-  for (int p = 0; p < 3; ++p)
-    if (ph >> p & 1) {
-      const TargetRec t = tr[p];
-      const double vx = t.W.x + s.S[p].x, vy = t.W.y + s.S[p].y;
-      const double q = fma(vx, vx, vy * vy);
-      s.sm[p] = sqrt_nr(q);
-      s.qn = fmin(s.qn, q);
-      s.qx = fmax(s.qx, q);
-      s.e = fmax(s.e, fmax(s.sm[p] - t.lo, t.hi - s.sm[p]));
-    }
+  for (int p = 0; p < 3; ++p) {
+    if (SKIP && !(ph >> p & 1)) continue;
+    const bool on = ph >> p & 1;
+    const TargetRec t = tr[p];
+    const double vx = t.W.x + s.S[p].x, vy = t.W.y + s.S[p].y;
+    const double q = on ? fma(vx, vx, vy * vy) : 1.0;
+    s.sm[p] = sqrt_nr(q);
+    s.qn = fmin(s.qn, on ? q : INFINITY);
+    s.qx = fmax(s.qx, on ? q : 0.0);
+    const double d = fmax(s.sm[p] - t.lo, t.hi - s.sm[p]);
+    s.e = fmax(s.e, on ? d : 0.0);
+  }
   s.sidx = r + 1;
+}
+// The same with lanes that differ in the slot's bit: both sides by selects.
+template <bool SKIP>
+__device__ __forceinline__ void slot_either(ChainState& s, int ph, int r, bool red, const double2* pr,
+                                            const TargetRec* tr) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    if (SKIP && !(ph >> p & 1)) continue;
+    const bool on = ph >> p & 1;
+    const TargetRec t = tr[p];
+    const double2 pv = pr[p];
+    s.S[p].x += red ? pv.x : 0.0;
+    s.S[p].y += red ? pv.y : 0.0;
+    const double vx = t.W.x + s.S[p].x, vy = t.W.y + s.S[p].y;
+    const double q = on ? fma(vx, vx, vy * vy) : 1.0;
+    const double m = sqrt_nr(q);
+    s.sm[p] = red ? s.sm[p] : m;
+    s.qn = fmin(s.qn, on && !red ? q : INFINITY);
+    s.qx = fmax(s.qx, on && !red ? q : 0.0);
+    const double d = fmax(s.sm[p] - t.lo, t.hi - s.sm[p]);
+    s.e = fmax(s.e, on ? d : 0.0);
+  }
+  s.sidx = red ? s.sidx : r + 1;
+}
+// One zone entry of the chain, shifted by its exit value b.
+__device__ __forceinline__ void zone_term(ChainState& s, const TargetRec& t, double2 b) {
+  const double vx = t.W.x + b.x, vy = t.W.y + b.y;
+  const double q = fma(vx, vx, vy * vy);
+  const double mag = sqrt_nr(q);
+  s.e = fmax(s.e, fmax(mag - t.lo, t.hi - mag));
+  s.qn = fmin(s.qn, q);
+  s.qx = fmax(s.qx, q);
+}
+// Voltage shift of one slot alone.
+__device__ __forceinline__ void slot_shift(double2 (&S)[3], int& sidx, int r, bool red, const double2* pr) {
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    const double2 pv = pr[p];
+    S[p].x += red ? pv.x : 0.0;
+    S[p].y += red ? pv.y : 0.0;
+  }
+  sidx = red ? sidx : r + 1;
+}
+
+// Voltage shift through a whole chain (its rows of the pair table at P).  A
+// slot's row is zero on phases absent from the chain's paths; a row's value on
+// a phase absent from its slot only reaches phases that no lower slot has.
+__device__ __forceinline__ void chain_shift(const int* cr, const double2* P, uint32_t m, double2 (&S)[3]) {
+  const int ns = cr[C_NSLOT], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
+  int sidx = 0;
+  for (int r = 0; r < ns; ++r)
+    slot_shift(S, sidx, r, (m >> (bit0 + r)) & 1u, P + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3);
 }
 
 constexpr int kTermsBlock = 256;  // threads of a chain-term block
-constexpr int kZoneWave = 16;     // zone entries from which a chain's patterns may take them by waves
+constexpr int kZoneWave = 32;     // zone entries from which a chain's patterns may take them by waves
 
-// Whether the zone entries of a chain are taken by a wave per pattern: as
-// many entries as patterns (at equality both forms take about 100 cycles per
-// entry of the chain: an entry in turn per thread, or 64 entries a round in
-// each of 4 waves with a 6-step fold per pattern).
+// Whether the zone entries of a chain are taken by a wave per pattern: where
+// it has 8 times as many entries as patterns (a wave takes about 2000 cycles
+// per pattern -- the walk, the entries, a 6-step fold -- and a block has 4; a
+// thread going through the entries of its pattern about 70 per entry).
 __device__ __forceinline__ bool zone_by_wave(const int* cr) {
   const int z = cr[C_ZCNT0] + cr[C_ZCNT1] + cr[C_ZCNT2];
-  return z >= kZoneWave && (1 << __popc((uint32_t)cr[C_PMASK])) <= z;
+  return z >= kZoneWave && (8 << __popc((uint32_t)cr[C_PMASK])) <= z;
 }
 
 // The mask whose bits at pm's positions are u's low bits, the rest 0.
@@ -131,29 +200,33 @@ __device__ __forceinline__ uint32_t deposit_bits(uint32_t u, uint32_t pm) {
   return mask;
 }
 
-template <bool BUILD, bool PAT>
-__global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
+template <bool BUILD, bool PAT, int NS, bool DEEP>
+__global__ __launch_bounds__(kTermsBlock * NS) void k_seg_terms(
     const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ units,
     const int* __restrict__ tab, Topo T, State St, const double2* __restrict__ Zroot,
     const double2* __restrict__ Vcur, const double2* __restrict__ A, const double* __restrict__ absV,
     double2* __restrict__ P, TargetRec* __restrict__ srec, double2* __restrict__ headV,
-    TargetRec* __restrict__ zrec, double* __restrict__ econst, int icap, int zcap,
+    TargetRec* __restrict__ zrec, double* __restrict__ econst, TermsCaps caps,
     unsigned long long* __restrict__ pat, unsigned long long* __restrict__ ecmax, const int* __restrict__ gates,
     int* __restrict__ status) {
   extern __shared__ __align__(16) unsigned char ct_lds[];
-  __shared__ double s_ec;
+  __shared__ double s_ecs[NS];
   __shared__ int s_zw[kMaxK + 1];  // patterns of the chains before c whose zone entries go by waves
-  const int u = *as_cint(units + blockIdx.x);
+  const int u = *as_cint(units + blockIdx.y);
   const int uz = u & 255, part = (u >> 8) & 255, parts = u >> 16;
   const int g = *as_cint(segs + uz);
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid || (gates && gates[g] == 0)) return;
-  const int tid = threadIdx.x;
+  const int sub = NS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / kTermsBlock) : 0;
+  const int tid = threadIdx.x - sub * kTermsBlock;  // within the snapshot's threads
   // (parts come from the plan's bound on the patterns; a part without items
   // may still have zone patterns, which are fewer than the segment's entries)
-  if (PAT && part > 0 && part * kTermsBlock >= H.nitem && part * (kTermsBlock / 64) >= H.nz) return;
-  if (BUILD && PAT && H.nz > zcap) {  // the plan's bound failed: never in a consistent plan
-    if (tid == 0) atomicOr(status, kStatusBuild);
+  if (PAT && part > 0 && part * kTermsBlock >= (DEEP ? H.nitem : H.npat) && part * (kTermsBlock / 64) >= H.nz) return;
+  // the plan's bounds hold the tables (zone entries beyond their LDS take
+  // memory; with BUILD and PAT together they all fit)
+  if (H.npairs > caps.pairs || H.nslots > caps.slots || H.o_slot > caps.ints ||
+      (BUILD && PAT && H.nz > caps.zones)) {
+    if (threadIdx.x == 0) atomicOr(status, kStatusBuild);
     return;
   }
   tab = lane_ptr_z(tab, lstride, uz);
@@ -162,19 +235,29 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
   headV = lane_ptr_z(headV, lstride, uz);
   zrec = lane_ptr_z(zrec, lstride, uz);
   econst = lane_ptr_z(econst, lstride, uz);
-  const int l = blockIdx.y, n = T.n;
+  const int l = blockIdx.x * NS + sub, n = T.n;
+  const bool on = l < H.S;  // (the last block's surplus threads only pass the barriers)
   const int nint = H.o_slot;  // chain records and nesting paths
-  const int zst = min(H.nz, zcap);
+  const int zst = min(H.nz, caps.zones);
+  const bool fold_lds = NS > 1 && H.npat <= caps.pats;  // patterns folded in LDS over the block's snapshots
   int* si = (int*)ct_lds;
-  double2* sP = (double2*)(ct_lds + (size_t)((icap * 4 + 15) / 16) * 16);
-  TargetRec* sS = (TargetRec*)(sP + (size_t)H.npairs * 3);
-  double2* sH = (double2*)(sS + (size_t)H.nslots * 3);
-  TargetRec* sZ = (TargetRec*)(sH + (size_t)H.nchains * 3);
+  unsigned long long* sA = (unsigned long long*)(ct_lds + (size_t)(caps.ints + 3) / 4 * 16);
+  double2* sP = (double2*)((unsigned char*)(sA + (size_t)(caps.pats + 1) / 2 * 6) + (size_t)sub * terms_snap_lds(caps));
+  TargetRec* sS = (TargetRec*)(sP + (size_t)caps.pairs * 3);
+  double2* sH = (double2*)(sS + (size_t)caps.slots * 3);
+  TargetRec* sZ = (TargetRec*)(sH + (size_t)caps.slots * 3);
+  double& s_ec = s_ecs[sub];
   double2* gP = P + (size_t)l * H.npairs * 3;
   TargetRec* gS = srec + (size_t)l * H.nslots * 3;
   double2* gH = headV + (size_t)l * H.nchains * 3;
   TargetRec* gZ = zrec + (size_t)l * H.nz;
-  for (int i = tid; i < nint; i += kTermsBlock) si[i] = tab[i];
+  for (int i = threadIdx.x; i < nint; i += kTermsBlock * NS) si[i] = tab[i];
+  if (fold_lds)
+    for (int x = threadIdx.x; x < H.npat; x += kTermsBlock * NS) {
+      sA[3 * x] = 0ull;
+      sA[3 * x + 1] = (unsigned long long)__double_as_longlong(INFINITY);
+      sA[3 * x + 2] = 0ull;
+    }
   const double2* Vl = Vcur + (size_t)l * n * 3;
   if (BUILD) {
     const double2* Al = A + (size_t)l * n * 3;
@@ -182,7 +265,7 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
     if (tid == 0) s_ec = 0.0;
     // one index space over pairs, slot-phases, chains and zone entries
     const int nP = H.npairs, nS = H.nslots * 3, nC = H.nchains * 3;
-    for (int x = tid; x < nP + nS + nC + H.nz; x += kTermsBlock) {
+    for (int x = on ? tid : INT_MAX; x < nP + nS + nC + H.nz; x += kTermsBlock) {
       if (x < nP) {
         const int* pr = tab + H.o_pair + x * kPairInts;
         const int rn = pr[PR_RNODE], sn = pr[PR_SUPER];
@@ -224,7 +307,7 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
       atomicMin((unsigned long long*)&r->lo, (unsigned long long)__double_as_longlong(v));
       atomicMax((unsigned long long*)&r->hi, (unsigned long long)__double_as_longlong(v));
     };
-    for (int q = tid; q < H.nomega; q += kTermsBlock) {
+    for (int q = on ? tid : INT_MAX; q < H.nomega; q += kTermsBlock) {
       int r = 0;
       while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
       const int i = rg[3 * r] + (q - rg[3 * r + 2]);
@@ -255,7 +338,7 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
       }
     }
     __syncthreads();
-    if (part == 0) {
+    if (part == 0 && on) {
       uint4 *dP = (uint4*)gP, *dS = (uint4*)gS, *dH = (uint4*)gH, *dZ = (uint4*)gZ;
       for (int i = tid; i < H.npairs * 3; i += kTermsBlock) dP[i] = ((const uint4*)sP)[i];
       for (int i = tid; i < H.nslots * 6; i += kTermsBlock) dS[i] = ((const uint4*)sS)[i];
@@ -265,23 +348,37 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
     }
   } else {
     const int cP = H.npairs * 3, cS = H.nslots * 6, cH = H.nchains * 3, cZ = zst * 2;
-    for (int i = tid; i < cP + cS + cH + cZ; i += kTermsBlock) {
+    for (int i = on ? tid : INT_MAX; i < cP + cS + cH + cZ; i += kTermsBlock) {
       if (i < cP) ((uint4*)sP)[i] = ((const uint4*)gP)[i];
       else if (i < cP + cS) ((uint4*)sS)[i - cP] = ((const uint4*)gS)[i - cP];
       else if (i < cP + cS + cH) ((uint4*)sH)[i - cP - cS] = ((const uint4*)gH)[i - cP - cS];
       else ((uint4*)sZ)[i - cP - cS - cH] = ((const uint4*)gZ)[i - cP - cS - cH];
     }
-    if (tid == 0) s_ec = econst[l];
+    if (tid == 0 && on) s_ec = econst[l];
     __syncthreads();
   }
   if (!PAT) return;
   pat = lane_ptr_z(pat, lstride, uz);
-  if (part == 0 && tid == 0)
+  if (part == 0 && tid == 0 && on)
     atomicMax(lane_ptr_z(ecmax, lstride, uz), (unsigned long long)__double_as_longlong(s_ec));
   const int* chains = si + H.o_chain;
   const int* nest = si + H.o_nest;
   const int nch = H.nchains;
-  if (tid < 64) {
+  auto emit = [&](int x, double e, double qn, double qx) {
+    const unsigned long long ve = (unsigned long long)__double_as_longlong(e),
+                             vn = (unsigned long long)__double_as_longlong(qn),
+                             vx = (unsigned long long)__double_as_longlong(qx);
+    if (fold_lds) {
+      atomicMax(&sA[3 * x], ve);
+      atomicMin(&sA[3 * x + 1], vn);
+      atomicMax(&sA[3 * x + 2], vx);
+    } else {
+      atomicMax(&pat[3 * (size_t)x], ve);
+      if (qn < INFINITY) atomicMin(&pat[3 * (size_t)x + 1], vn);
+      if (qx > 0.0) atomicMax(&pat[3 * (size_t)x + 2], vx);
+    }
+  };
+  if (threadIdx.x < 64) {
     const bool zw = tid < nch && zone_by_wave(chains + tid * kChainInts);
     const int v = zw ? 1 << __popc((uint32_t)chains[tid * kChainInts + C_PMASK]) : 0;
     int x = v;
@@ -291,13 +388,15 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
     }
     if (tid <= nch) s_zw[tid] = x - v;
   }
+  constexpr int kBase = DEEP ? (int)C_IBASE : (int)C_PBASE;
+  const int nitem = DEEP ? H.nitem : H.npat;
   int c = 0;  // (a thread's items increase, so its chain index only moves forward)
-  for (int it = part * kTermsBlock + tid; it < H.nitem; it += parts * kTermsBlock) {
-    while (c + 1 < nch && chains[(c + 1) * kChainInts + C_IBASE] <= it) ++c;
+  for (int it = on ? part * kTermsBlock + tid : INT_MAX; it < nitem; it += parts * kTermsBlock) {
+    while (c + 1 < nch && chains[(c + 1) * kChainInts + kBase] <= it) ++c;
     const int* cr = chains + c * kChainInts;
-    const uint32_t ulow = (uint32_t)(it - cr[C_IBASE]);
+    const uint32_t ulow = (uint32_t)(it - cr[kBase]);
     const uint32_t pm = (uint32_t)cr[C_PMASK];
-    const int d = cr[C_D], ub = __popc(pm) - d;  // the item's own bits; the d bits above them are enumerated
+    const int d = DEEP ? cr[C_D] : 0, ub = __popc(pm) - d;  // the item's own bits; the d bits above them are enumerated
     const uint32_t mask = deposit_bits(ulow, pm);
     const bool zw = zone_by_wave(cr);
     ChainState s0;
@@ -311,145 +410,122 @@ __global__ __launch_bounds__(kTermsBlock) void k_seg_terms(
     s0.qn = INFINITY;
     s0.qx = 0.0;
     const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
-    {  // the nesting path down to the chain's head: voltage shifts only
-      double2 B[1][3];
-      double e1[1], q1[1], q2[1];
-      const uint32_t mm[1] = {mask};
-#pragma unroll
-      for (int p = 0; p < 3; ++p) B[0][p] = make_double2(0.0, 0.0);
-      for (int q = 0; q + 1 < nl; ++q) {
-        const int oc = nest[no + q];
-        walk_chain<false, 1>(chains + oc * kChainInts, sP, sS, sH, (const double*)nullptr, oc, mm, B, e1, q1, q2);
-      }
-#pragma unroll
-      for (int p = 0; p < 3; ++p) s0.S[p] = B[0][p];
-    }
-    {  // the head's magnitude (0 on absent phases), moved by the outer chains when it lies below one
+    for (int q = 0; q + 1 < nl; ++q)  // the nesting path down to the chain's head: voltage shifts only
+      chain_shift(chains + nest[no + q] * kChainInts, sP, mask, s0.S);
+    {  // the head's magnitude (1 on absent phases, never read), moved by the outer chains when it lies below one
       const int hph = cr[C_PHASE];
 #pragma unroll
       for (int p = 0; p < 3; ++p)
-        if (hph >> p & 1) s0.sm[p] = vmag(nl > 1 ? cadd(sH[c * 3 + p], s0.S[p]) : sH[c * 3 + p]);
+      {
+        const double2 h = nl > 1 ? cadd(sH[c * 3 + p], s0.S[p]) : sH[c * 3 + p];
+        s0.sm[p] = sqrt_nr((hph >> p & 1) ? mag2(h) : 1.0);
+      }
     }
     const int ns = cr[C_NSLOT], slot0 = cr[C_SLOT0], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
     const int phw0 = cr[C_PHW0], phw1 = cr[C_PHW1], phw2 = cr[C_PHW2];
     auto phase_of = [&](int r) { return ((r < 8 ? phw0 : (r < 16 ? phw1 : phw2)) >> (3 * (r & 7))) & 7; };
     auto pair_row = [&](int r, int sidx) { return sP + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3; };
-    for (int r = 0; r < ns - d; ++r) {  // the item's own slots: lanes differ, both sides by selects
-      const int ph = phase_of(r);
-      const TargetRec* tr = sS + (slot0 + r) * 3;
-      const bool red = (mask >> (bit0 + r)) & 1u;
-      const double rf = red ? 1.0 : 0.0;
-      const double2* pp = pair_row(r, s0.sidx);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        if (!(ph >> p & 1)) continue;
-        const TargetRec t = tr[p];
-        s0.S[p].x = fma(rf, pp[p].x, s0.S[p].x);
-        s0.S[p].y = fma(rf, pp[p].y, s0.S[p].y);
-        const double vx = t.W.x + s0.S[p].x, vy = t.W.y + s0.S[p].y;
-        const double q = fma(vx, vx, vy * vy);
-        if (!red) s0.sm[p] = sqrt_nr(q);
-        s0.qn = fmin(s0.qn, red ? INFINITY : q);
-        s0.qx = fmax(s0.qx, red ? 0.0 : q);
-        s0.e = fmax(s0.e, fmax(s0.sm[p] - t.lo, t.hi - s0.sm[p]));
-      }
-      s0.sidx = red ? s0.sidx : r + 1;
-    }
-    auto step = [&](ChainState& s, int r, int red) {
-      const int ph = phase_of(r);
-      const TargetRec* tr = sS + (slot0 + r) * 3;
-      if (red) slot_reduced(s, ph, pair_row(r, s.sidx), tr);
-      else slot_kept(s, ph, r, tr);
-    };
+    for (int r = 0; r < ns - d; ++r)  // the item's own slots
+      slot_either<DEEP>(s0, phase_of(r), r, (mask >> (bit0 + r)) & 1u, pair_row(r, s0.sidx), sS + (slot0 + r) * 3);
     const int pb = cr[C_PBASE] + (int)ulow;
+    auto zones = [&](ChainState& s, int p, double2 b) {  // the entries anchored below, shifted by the chain's exit value
+      int q = cr[C_ZOFF0 + p];
+      const int qe = zw ? q : q + cr[C_ZCNT0 + p];
+#pragma unroll 2
+      for (const int ql = min(qe, zst); q < ql; ++q) zone_term(s, sZ[q], b);
+      if (!BUILD)  // (entries past the LDS stage, which holds them all when this launch built them)
+        for (; q < qe; ++q) zone_term(s, gZ[q], b);
+    };
+    auto finish = [&](ChainState& s, int x) {
+      zones(s, 0, s.S[0]);
+      zones(s, 1, s.S[1]);
+      zones(s, 2, s.S[2]);
+      emit(x, s.e, s.qn, s.qx);
+    };
+    if (!DEEP) {
+      finish(s0, pb);
+    } else {
+      auto step = [&](ChainState& s, int r, int red) {
+        const int ph = phase_of(r);
+        const TargetRec* tr = sS + (slot0 + r) * 3;
+        if (red) slot_reduced<true>(s, ph, pair_row(r, s.sidx), tr);
+        else slot_kept<true>(s, ph, r, tr);
+      };
 #pragma unroll 1
-    for (int b0 = 0; b0 < (d > 2 ? 2 : 1); ++b0) {
-      ChainState s1 = s0;
-      if (d > 2) step(s1, ns - 3, b0);
+      for (int b0 = 0; b0 < (d > 2 ? 2 : 1); ++b0) {
+        ChainState s1 = s0;
+        if (d > 2) step(s1, ns - 3, b0);
 #pragma unroll 1
-      for (int b1 = 0; b1 < (d > 1 ? 2 : 1); ++b1) {
-        ChainState s2 = s1;
-        if (d > 1) step(s2, ns - 2, b1);
+        for (int b1 = 0; b1 < (d > 1 ? 2 : 1); ++b1) {
+          ChainState s2 = s1;
+          if (d > 1) step(s2, ns - 2, b1);
 #pragma unroll 1
-        for (int b2 = 0; b2 < (d > 0 ? 2 : 1); ++b2) {
-          ChainState s3 = s2;
-          if (d > 0) step(s3, ns - 1, b2);
-          // the zone entries anchored below the chain, shifted by its exit value
-#pragma unroll
-          for (int p = 0; p < 3; ++p)
-            for (int q = cr[C_ZOFF0 + p], qe = zw ? q : q + cr[C_ZCNT0 + p]; q < qe; ++q) {
-              TargetRec t;
-              if (q < zst) t = sZ[q];
-              else t = gZ[q];
-              const double vx = t.W.x + s3.S[p].x, vy = t.W.y + s3.S[p].y;
-              const double q2 = fma(vx, vx, vy * vy);
-              const double mag = sqrt_nr(q2);
-              s3.e = fmax(s3.e, fmax(mag - t.lo, t.hi - mag));
-              s3.qn = fmin(s3.qn, q2);
-              s3.qx = fmax(s3.qx, q2);
-            }
-          const int x = pb + (((b0 | b1 << 1 | b2 << 2) >> (3 - d)) << ub);
-          atomicMax(&pat[3 * x], (unsigned long long)__double_as_longlong(s3.e));
-          if (s3.qn < INFINITY) atomicMin(&pat[3 * x + 1], (unsigned long long)__double_as_longlong(s3.qn));
-          if (s3.qx > 0.0) atomicMax(&pat[3 * x + 2], (unsigned long long)__double_as_longlong(s3.qx));
+          for (int b2 = 0; b2 < (d > 0 ? 2 : 1); ++b2) {
+            ChainState s3 = s2;
+            if (d > 0) step(s3, ns - 1, b2);
+            finish(s3, pb + (((b0 | b1 << 1 | b2 << 2) >> (3 - d)) << ub));
+          }
         }
       }
     }
   }
   // zone entries by waves: one (chain, pattern) per wave, one entry per lane
   __syncthreads();
-  const int nzw = s_zw[nch], lane = tid & 63;
+  const int nzw = on ? s_zw[nch] : 0, lane = tid & 63;
   constexpr int kWaves = kTermsBlock / 64;
   c = 0;
   for (int x = part * kWaves + (tid >> 6); x < nzw; x += parts * kWaves) {
     while (s_zw[c + 1] <= x) ++c;  // (chains without a wave pattern have equal entries: skipped)
     const int* cr = chains + c * kChainInts;
     const int ux = x - s_zw[c];
-    const uint32_t mm[1] = {deposit_bits((uint32_t)ux, (uint32_t)cr[C_PMASK])};
-    double2 B[1][3];
-    double e1[1], q1[1], q2[1];
+    const uint32_t mm = deposit_bits((uint32_t)ux, (uint32_t)cr[C_PMASK]);
+    double2 B[3];
 #pragma unroll
-    for (int p = 0; p < 3; ++p) B[0][p] = make_double2(0.0, 0.0);
-    for (int q = 0, no = cr[C_NEST_OFF]; q < cr[C_NEST_LEN]; ++q) {  // (the path ends with the chain itself)
-      const int oc = nest[no + q];
-      walk_chain<false, 1>(chains + oc * kChainInts, sP, sS, sH, (const double*)nullptr, oc, mm, B, e1, q1, q2);
-    }
-    double e = 0.0, qn = INFINITY, qx = 0.0;
-    const int z1 = cr[C_ZOFF1], z2 = cr[C_ZOFF2], ze = z2 + cr[C_ZCNT2];
-    for (int q = cr[C_ZOFF0] + lane; q < ze; q += 64) {
-      TargetRec t;
-      if (q < zst) t = sZ[q];
-      else t = gZ[q];
-      const double2 b = q < z1 ? B[0][0] : (q < z2 ? B[0][1] : B[0][2]);
-      const double vx = t.W.x + b.x, vy = t.W.y + b.y;
-      const double q2 = fma(vx, vx, vy * vy);
-      const double mag = sqrt_nr(q2);
-      e = fmax(e, fmax(mag - t.lo, t.hi - mag));
-      qn = fmin(qn, q2);
-      qx = fmax(qx, q2);
-    }
+    for (int p = 0; p < 3; ++p) B[p] = make_double2(0.0, 0.0);
+    for (int q = 0, no = cr[C_NEST_OFF]; q < cr[C_NEST_LEN]; ++q)  // (the path ends with the chain itself)
+      chain_shift(chains + nest[no + q] * kChainInts, sP, mm, B);
+    ChainState t;
+    t.e = 0.0;
+    t.qn = INFINITY;
+    t.qx = 0.0;
+    auto zones = [&](int p, double2 b) {
+      int q = cr[C_ZOFF0 + p] + lane;
+      const int qe = cr[C_ZOFF0 + p] + cr[C_ZCNT0 + p];
+      for (const int ql = min(qe, zst); q < ql; q += 64) zone_term(t, sZ[q], b);
+      if (!BUILD)
+        for (; q < qe; q += 64) zone_term(t, gZ[q], b);
+    };
+    zones(0, B[0]);
+    zones(1, B[1]);
+    zones(2, B[2]);
+    double e = t.e, qn = t.qn, qx = t.qx;
     for (int o = 32; o > 0; o >>= 1) {
       e = fmax(e, __shfl_xor(e, o, 64));
       qn = fmin(qn, __shfl_xor(qn, o, 64));
       qx = fmax(qx, __shfl_xor(qx, o, 64));
     }
-    if (lane == 0) {
-      unsigned long long* a = pat + 3 * (cr[C_PBASE] + ux);
-      atomicMax(&a[0], (unsigned long long)__double_as_longlong(e));
-      atomicMin(&a[1], (unsigned long long)__double_as_longlong(qn));
-      atomicMax(&a[2], (unsigned long long)__double_as_longlong(qx));
-    }
+    if (lane == 0) emit(cr[C_PBASE] + ux, e, qn, qx);
+  }
+  if (!fold_lds) return;
+  __syncthreads();
+  for (int x = threadIdx.x; x < H.npat; x += kTermsBlock * NS) {
+    if (sA[3 * x] != 0ull) atomicMax(&pat[3 * (size_t)x], sA[3 * x]);
+    if (sA[3 * x + 1] != (unsigned long long)__double_as_longlong(INFINITY))
+      atomicMin(&pat[3 * (size_t)x + 1], sA[3 * x + 1]);
+    if (sA[3 * x + 2] != 0ull) atomicMax(&pat[3 * (size_t)x + 2], sA[3 * x + 2]);
   }
 }
 
-#define OKR_SEG_TERMS_INST(B_, P_)                                                                                    \
-  template __global__ void k_seg_terms<B_, P_>(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, \
-                                               const double2*, const double2*, const double2*, const double*, double2*, \
-                                               TargetRec*, double2*, TargetRec*, double*, int, int,                    \
-                                               unsigned long long*, unsigned long long*, const int*, int*);
-OKR_SEG_TERMS_INST(true, true)
-OKR_SEG_TERMS_INST(true, false)
-OKR_SEG_TERMS_INST(false, true)
+#define OKR_SEG_TERMS_INST(B_, P_, N_, D_)                                                                            \
+  template __global__ void k_seg_terms<B_, P_, N_, D_>(                                                               \
+      const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, const double2*, const double2*,         \
+      const double2*, const double*, double2*, TargetRec*, double2*, TargetRec*, double*, TermsCaps,                  \
+      unsigned long long*, unsigned long long*, const int*, int*);
+OKR_SEG_TERMS_INST(true, true, 1, false)
+OKR_SEG_TERMS_INST(true, true, 2, false)
+OKR_SEG_TERMS_INST(true, true, 1, true)
+OKR_SEG_TERMS_INST(true, false, 1, false)
+OKR_SEG_TERMS_INST(false, true, 1, true)
 #undef OKR_SEG_TERMS_INST
 
 // ---- terms of a short mask list ----
