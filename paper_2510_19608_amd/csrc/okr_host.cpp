@@ -50,7 +50,7 @@ __global__ void k_surr_rank(const SegHdr*, int, const int*, const float*, const 
 __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, const unsigned long long*,
                               const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*);
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
-                         DevDecision*, const int*);
+                         DevDecision*, const int*, uint32_t*, int*);
 __global__ void k_apply(const SegHdr*, const int*, size_t, const int*, Topo, State, const DevDecision*,
                         const double2*, const TargetRec*, const TargetRec*, double2*, double2*);
 __global__ void k_init_state(int, State, int*, int, int*, int, int, size_t);
@@ -104,10 +104,10 @@ __global__ void k_smice_prep(const SegHdr*, const int*, size_t, const int*, Topo
 __global__ void k_smice_hconst(const SegHdr*, const int*, size_t, Topo, State, const double2*, const double*,
                                const int*, double*, int);
 __global__ void k_smice_score(const SegHdr*, const int*, size_t, const int*, const double2*, const TargetRec*,
-                              const double2*, const TargetRec*, const int*, const double*, const MaskScore*,
-                              const TileRec*, const DevDecision*, SelParams, double*, double*);
-__global__ void k_smice_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, const double*,
-                               const double*, double, DevDecision*);
+                              const double2*, const TargetRec*, const int*, const double*, const uint32_t*,
+                              const int*, double*);
+__global__ void k_smice_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, const uint32_t*,
+                               const int*, const double*, double, DevDecision*);
 }  // namespace okr
 
 using namespace okr;
@@ -134,7 +134,7 @@ size_t pf_bfs_lds_bytes(int n, int nlev) {
   const size_t b = sizeof(int) * ((size_t)nlev + 1) + sizeof(uint16_t) * ((size_t)3 * n + 1) + (size_t)n;
   return (n < 65536 && b <= kPfLdsMax) ? b : 0;
 }
-constexpr int kSmiceThreadsHost = 128;  // masks per block of the SMICE scoring
+constexpr int kSmiceThreadsHost = 128;  // threads per block of the SMICE scoring (4 masks a round)
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -177,8 +177,8 @@ struct Layout {
   // surrogate: feature tables (always), ranking buffers (when planned with top_k)
   size_t spz, szs, sss, skeys, slist, sscore, scount, sgates, sW1b, sW2b, sW2tb, slevel,
       sstage;
-  // SMICE key (when planned with it): prep table, fixed head maxima, per-mask SMICE, mask 0's
-  size_t stab, hK, smv, smv0;
+  // SMICE key (when planned with it): prep table, fixed head maxima, listed masks, their number and SMICE
+  size_t stab, hK, smv, smlist, smcount;
   size_t lane0, lane_stride;  // per-lane scratch block (tab .. scount)
   size_t total;
 };
@@ -763,7 +763,8 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     L.stab = take(sizeof(int) * on * ((size_t)SM_ZREC + (size_t)kZrecInts * n));
     L.hK = take(sizeof(double) * on * (size_t)kMaxK * S);
     L.smv = take(sizeof(double) * on * ((size_t)1 << h->kmax));
-    L.smv0 = take(sizeof(double) * on);
+    L.smlist = take(sizeof(uint32_t) * on * ((size_t)1 << h->kmax));
+    L.smcount = take(sizeof(int) * on);
   }
   L.lane_stride = off - L.lane0;
   off = L.lane0 + L.lane_stride * (size_t)h->nlanes;
@@ -830,7 +831,9 @@ struct Ptrs {
   MaskScore* sscore;
   int *scount, *sgates, *sstage;
   int* stab;
-  double *hK, *smv, *smv0;
+  double *hK, *smv;
+  uint32_t* smlist;
+  int* smcount;
 };
 
 // Device pointers, with the scratch block of chunk position `lane`.
@@ -923,7 +926,8 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.stab = (int*)at(L.stab);
   p.hK = (double*)at(L.hK);
   p.smv = (double*)at(L.smv);
-  p.smv0 = (double*)at(L.smv0);
+  p.smlist = (uint32_t*)at(L.smlist);
+  p.smcount = (int*)at(L.smcount);
   return p;
 }
 
@@ -1069,6 +1073,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   if (surr)
     hipLaunchKernelGGL(k_refresh_weights, dim3((kSurrH * kSurrH + 255) / 256), dim3(256), 0, st, mg->surrogate,
                        p.sW1b, p.sW2b, (__bf16*)nullptr);
+  const bool smice = mg->secondary == OKR_SECONDARY_SMICE && !surr;
   const int members_blocks = std::min(2048, std::max(1, (int)(((size_t)n * S + 255) / 256)));
   // per-mask feature rows of segment g start at foff[g] (segments in id order)
   std::vector<size_t> foff(h->nseg + 1, 0);
@@ -1153,23 +1158,25 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       pattern_score(h, q, c, !tables_first, sp, gates, st);
       if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
       hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                         (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates);
-      if (mg->secondary == OKR_SECONDARY_SMICE && !surr) {
+                         (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates,
+                         smice ? q.smlist : (uint32_t*)nullptr, smice ? q.smcount : (int*)nullptr);
+      if (smice) {
         // SMICE of the feasible masks of the chosen level, and the decision under it
         hipLaunchKernelGGL(k_smice_prep, dim3(1, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                            (const int*)q.tab, q.T, q.St, q.stab, q.hK, S);
         hipLaunchKernelGGL(k_smice_hconst, dim3(members_blocks, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs,
                            lstride, q.T, q.St, (const double2*)q.Vcur, (const double*)q.absV, (const int*)q.stab,
                            q.hK, S);
-        hipLaunchKernelGGL(k_smice_score, dim3((nmask + kSmiceThreadsHost - 1) / kSmiceThreadsHost, 1, nz),
-                           dim3(kSmiceThreadsHost), 0, st, (const SegHdr*)q.hdrs, segs, lstride, (const int*)q.tab,
-                           (const double2*)q.P, (const TargetRec*)q.srec, (const double2*)q.headV,
-                           (const TargetRec*)q.zrec, (const int*)q.stab, (const double*)q.hK,
-                           (const MaskScore*)q.fin, (const TileRec*)q.tiles, (const DevDecision*)q.decs, sp, q.smv,
-                           q.smv0);
+        // (as many blocks as fill the chip, or take every mask of the largest level at 4 per block)
+        const int sb = std::max(1, std::min((int)(nmask / 4), 2048 / nz));
+        hipLaunchKernelGGL(k_smice_score, dim3(sb, 1, nz), dim3(kSmiceThreadsHost), 0, st, (const SegHdr*)q.hdrs, segs,
+                           lstride, (const int*)q.tab, (const double2*)q.P, (const TargetRec*)q.srec,
+                           (const double2*)q.headV, (const TargetRec*)q.zrec, (const int*)q.stab, (const double*)q.hK,
+                           (const uint32_t*)q.smlist, (const int*)q.smcount, q.smv);
         hipLaunchKernelGGL(k_smice_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                           (const MaskScore*)q.fin, (const TileRec*)q.tiles, (const double*)q.smv,
-                           (const double*)q.smv0, mg->smice_tol > 0.0 ? mg->smice_tol : kSmiceTol, q.decs);
+                           (const MaskScore*)q.fin, (const TileRec*)q.tiles, (const uint32_t*)q.smlist,
+                           (const int*)q.smcount, (const double*)q.smv,
+                           mg->smice_tol > 0.0 ? mg->smice_tol : kSmiceTol, q.decs);
       }
       for (int z = 0; z < nz; ++z) {
         const int g = h->chunk_segs[c0 + z];
@@ -1230,7 +1237,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
         const int* redo = q.sgates;
         pattern_score(h, q, c, false, sp, redo, st);
         hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                           (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, redo);
+                             (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, redo,
+                           (uint32_t*)nullptr, (int*)nullptr);
       }
       if (dump)
         for (int z = 0; z < nz; ++z) {

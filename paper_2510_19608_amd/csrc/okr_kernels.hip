@@ -522,22 +522,28 @@ __global__ void k_from_vhat(int n, int S, const uint8_t* __restrict__ phase, con
 // mask within amb of the tie threshold) are rescanned mask by mask.
 // Ambiguous when a mask at the chosen level or above lies within amb of the
 // e_bar / band boundary, or a feasible mask at the chosen level lies within
-// amb of e_min + tie_tol.
+// amb of e_min + tie_tol.  With slist (SMICE as the key) it also lists mask 0
+// and then every feasible mask of the chosen level, in any order (the listed
+// masks are a few hundred of 65,536 on the 1000-node workload; scoring them
+// from a dense list keeps every lane busy).
 __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
                                                  size_t lstride, const MaskScore* __restrict__ fin,
                                                  const TileRec* __restrict__ tiles, SelParams sp,
                                                  const int* __restrict__ status, DevDecision* __restrict__ decs,
-                                                 const int* __restrict__ gates) {
+                                                 const int* __restrict__ gates, uint32_t* __restrict__ slist,
+                                                 int* __restrict__ scount) {
   // one slot per wave for each reduction (each its own array, so no
   // reduction's slots are written while another's are still being read)
   __shared__ int s_best[16], s_amb[16], s_amb2[16];
   __shared__ double s_emin[16], s_run[16];
   __shared__ unsigned s_pick[16];
-  __shared__ int ncand;
+  __shared__ int ncand, nlist;
   __shared__ int cand[1024];
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
   if (gates && gates[g] == 0) return;  // decided without the full enumeration
+  slist = lane_ptr(slist, lstride);
+  scount = lane_ptr(scount, lstride);
   fin = lane_ptr(fin, lstride);
   tiles = lane_ptr(tiles, lstride);
   DevDecision* dec = decs + g;
@@ -550,6 +556,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
       d.key_gap = INFINITY;
       d.smice_rise = 0.0;
       *dec = d;
+      if (slist) *scount = 0;
     }
     return;
   }
@@ -659,6 +666,27 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
     }
     *dec = d;
   }
+  if (!slist) return;
+  if (tid == 0) {
+    nlist = best >= 0 ? 1 : 0;
+    slist[0] = 0;
+  }
+  for (int base = 0; base < ntiles && best > 0; base += bd) {  // (at level 0 the list is mask 0)
+    if (tid == 0) ncand = 0;
+    __syncthreads();
+    const int t = base + tid;
+    if (t < ntiles && (one ? r0 : tiles[t]).best == best) cand[atomicAdd(&ncand, 1)] = t;
+    __syncthreads();
+    const int nc = ncand;
+    for (int q = tid; q < nc * 64; q += bd) {
+      if ((q & 63) >> lb) continue;
+      const uint32_t mm = tile_mask(L, (uint32_t)cand[q >> 6], (uint32_t)(q & 63), k);
+      if (__popc(mm) == best && feasible(fin[mm], sp.e_bar)) slist[atomicAdd(&nlist, 1)] = mm;
+    }
+    __syncthreads();
+  }
+  __syncthreads();
+  if (tid == 0) *scount = nlist;
 }
 
 // Self-test hook: sqrt_nr on an array (host compares with the libm result).

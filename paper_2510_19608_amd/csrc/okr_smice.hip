@@ -15,7 +15,8 @@
 //   k_smice_prep   (1 block)  distinct heads, zone targets grouped by their
 //                             anchor chain in Omega_g order, head maxima zeroed
 //   k_smice_hconst (grid)     fixed error of each outside head's cluster
-//   k_smice_score  (grid)     SMICE of every candidate mask (and of mask 0)
+//   (k_argmin)                lists mask 0 and the candidate masks
+//   k_smice_score  (grid)     SMICE of every listed mask
 //   k_smice_argmin (1 block)  the smallest SMICE, tie rule, margin, flags
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -209,29 +210,26 @@ __device__ __forceinline__ void sm_shift_chain(const cint* cr, const double2* Pl
 __device__ __forceinline__ double sm_group(double mag, double lo, double hi) { return fmax(mag - lo, hi - mag); }
 
 // SMICE over the clusters a mask can touch, summed over the snapshots, for
-// every feasible mask of the chosen level (others: +inf) and for mask 0.
-// One mask per thread; per-thread head maxima in LDS.
-constexpr int kSmiceThreads = 128;
+// every listed mask (mask 0 first, then the feasible masks of the chosen
+// level).  kSmiceLanes lanes per mask, each taking every kSmiceLanes-th
+// snapshot, their sums folded in a fixed order; per-lane head maxima in LDS.
+// The walk of one (mask, snapshot) is a serial chain of table reads of about
+// 1.2 us per chain, so one lane per mask over the 24 snapshots of the
+// 1000-node workload took 320-420 us per launch.
+constexpr int kSmiceThreads = 128, kSmiceLanes = 32;
 __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
     const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ tab,
     const double2* __restrict__ P, const TargetRec* __restrict__ srec, const double2* __restrict__ headV,
     const TargetRec* __restrict__ zrec, const int* __restrict__ stab, const double* __restrict__ hK,
-    const MaskScore* __restrict__ fin, const TileRec* __restrict__ tiles, const DevDecision* __restrict__ decs,
-    SelParams sp, double* __restrict__ smv, double* __restrict__ smv0) {
+    const uint32_t* __restrict__ slist, const int* __restrict__ scount, double* __restrict__ smv) {
   __shared__ double s_acc[kMaxK][kSmiceThreads];
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid) return;
-  const DevDecision d = decs[g];
-  if (!d.found) return;
-  const uint32_t nmask = 1u << H.k;
-  // thread i: lane i % 64 of scoring tile i / 64 (tile_mask), so that the
-  // tile record of its mask is at hand
-  const uint32_t L = (uint32_t)H.lanebits;
-  const uint32_t ti = blockIdx.x * kSmiceThreads + threadIdx.x;
-  const uint32_t tile = ti / kScoreBlock, q = ti % kScoreBlock;
-  if ((tile << __popc(L)) >= nmask || (q >> __popc(L)) != 0) return;
-  const uint32_t m = tile_mask(L, tile, q, H.k);
+  slist = lane_ptr(slist, lstride);
+  scount = lane_ptr(scount, lstride);
+  constexpr int kMasks = kSmiceThreads / kSmiceLanes;  // masks per block and round
+  const int count = *as_cint(scount);
   tab = lane_ptr(tab, lstride);
   P = lane_ptr(P, lstride);
   srec = lane_ptr(srec, lstride);
@@ -239,25 +237,16 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
   zrec = lane_ptr(zrec, lstride);
   stab = lane_ptr(stab, lstride);
   hK = lane_ptr(hK, lstride);
-  fin = lane_ptr(fin, lstride);
-  tiles = lane_ptr(tiles, lstride);
   smv = lane_ptr(smv, lstride);
-  smv0 = lane_ptr(smv0, lstride);
-  // (a tile stores the scores of its best feasible level only: a tile whose
-  // best is below the chosen level has no feasible mask at it)
-  const bool cand = __popc(m) == d.popcount && tiles[tile].best == d.popcount &&
-                    feasible(fin[m], sp.e_bar);
-  if (!cand && m != 0) {
-    smv[m] = INFINITY;
-    return;
-  }
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, sl = tid % kSmiceLanes;
   const int S = H.S, nh = stab[SM_NH];
   const cint* chains = as_cint(tab + H.o_chain);
   const cint* nest = as_cint(tab + H.o_nest);
   const int* zr0 = stab + SM_ZREC;
+  for (int i = blockIdx.x * kMasks + tid / kSmiceLanes; i < count; i += gridDim.x * kMasks) {
+  const uint32_t m = slist[i];
   double total = 0.0;
-  for (int l = 0; l < S; ++l) {
+  for (int l = sl; l < S; l += kSmiceLanes) {
     const double2* Pl = P + (size_t)l * H.npairs * 3;
     const TargetRec* Tl = srec + (size_t)l * H.nslots * 3;
     const double2* Hl = headV + (size_t)l * H.nchains * 3;
@@ -337,8 +326,9 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
     for (int x = 0; x < nh; ++x) tot += s_acc[x][tid];
     total += tot;
   }
-  if (m == 0) *smv0 = total;
-  smv[m] = cand ? total : INFINITY;
+  for (int o = kSmiceLanes / 2; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
+  if (sl == 0) smv[i] = total;
+  }
 }
 
 // The decision under SMICE: the smallest SMICE among the candidates, the
@@ -348,8 +338,9 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
 __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
                                                        size_t lstride, const MaskScore* __restrict__ fin,
                                                        const TileRec* __restrict__ tiles,
-                                                       const double* __restrict__ smv,
-                                                       const double* __restrict__ smv0, double tol,
+                                                       const uint32_t* __restrict__ slist,
+                                                       const int* __restrict__ scount,
+                                                       const double* __restrict__ smv, double tol,
                                                        DevDecision* __restrict__ decs) {
   __shared__ double shd[16];
   __shared__ int shi[16];
@@ -361,35 +352,42 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
   if (!d.found) return;
   fin = lane_ptr(fin, lstride);
   tiles = lane_ptr(tiles, lstride);
+  slist = lane_ptr(slist, lstride);
+  scount = lane_ptr(scount, lstride);
   smv = lane_ptr(smv, lstride);
-  smv0 = lane_ptr(smv0, lstride);
-  const uint32_t nm = 1u << H.k;
-  const int ntiles = (int)(nm >> __popc((uint32_t)H.lanebits));
+  const int ntiles = (int)((1u << H.k) >> __popc((uint32_t)H.lanebits));
+  // (the list's first entry is mask 0, a candidate at level 0 only)
+  const int count = *scount, first = d.popcount == 0 ? 0 : 1;
   double smin = INFINITY;
-  for (uint32_t m = threadIdx.x; m < nm; m += blockDim.x) smin = fmin(smin, smv[m]);
+  for (int i = first + threadIdx.x; i < count; i += blockDim.x) smin = fmin(smin, smv[i]);
   smin = block_reduce(smin, [](double a, double b) { return fmin(a, b); }, shd);
   const double thr = smin + tol, atol = tol / 100.0;
   unsigned pick = 0xffffffffu;
+  int at = -1;  // list position of this thread's pick
   double runner = INFINITY;
   int amb = 0;
-  for (uint32_t m = threadIdx.x; m < nm; m += blockDim.x) {
-    const double v = smv[m];
-    if (!(v < INFINITY)) continue;
+  for (int i = first + threadIdx.x; i < count; i += blockDim.x) {
+    const double v = smv[i];
     if (fabs(v - thr) <= atol) amb = 1;
-    if (v <= thr) pick = min(pick, m);
-    else runner = fmin(runner, v);
+    if (v > thr) {
+      runner = fmin(runner, v);
+    } else if (slist[i] < pick) {
+      pick = slist[i];
+      at = i;
+    }
   }
+  const unsigned mine = pick;
   for (int t = threadIdx.x; t < ntiles; t += blockDim.x)
     if (tiles[t].near >= d.popcount) amb = 1;
   pick = block_reduce(pick, [](unsigned a, unsigned b) { return min(a, b); }, shu);
   amb = block_reduce(amb, [](int a, int b) { return a | b; }, shi);
   runner = block_reduce(runner, [](double a, double b) { return fmin(a, b); }, shd);
-  if (threadIdx.x == 0 && pick != 0xffffffffu) {
+  if (at >= 0 && mine == pick) {  // one thread: the list holds a mask once
     d.mask = pick;
     d.e_loc = fin[pick].e;
     d.ambiguous = amb;
     d.key_gap = runner - smin;
-    d.smice_rise = smv[pick] - *smv0;
+    d.smice_rise = smv[at] - smv[0];
     decs[g] = d;
   }
 }

@@ -91,3 +91,20 @@ def test_many_zone_entries(okr, n, precision):
         b = okr.reduce_feeder(f, want_vhat=False)
         assert [s["mask"] for s in a["segments"]] == [s["mask"] for s in b["segments"]]
         np.testing.assert_array_equal(a["err_per_snapshot"], b["err_per_snapshot"])
+
+
+@pytest.mark.parametrize("snapshots", [2, 31, 32, 33, 70])
+def test_smice_snapshot_lanes(okr, snapshots):
+    """SMICE sums taken by 32 lanes per mask: fewer snapshots than lanes, as
+    many, one more, several rounds.  Sums of up to a few hundred errors of order
+    1e-3: the tolerance is the tests' 1e-11 for SMICE sums (rounding 1e-16 each)."""
+    print(f"tables: smice snapshots={snapshots}", flush=True)
+    f = make_feeder("c1", 2, n=24, n_eligible=None, seg_size=(4, 6), snapshots=snapshots, scale=(0.3, 1.0), e_bar=2e-4)
+    V, I, st, _ = oracle.powerflow(f)
+    keep, dec, _ = oracle.search(f, V, I, secondary="smice")
+    assert st == 0 and not any(d["ambiguous"] for d in dec)
+    out = okr.reduce_feeder(f, secondary="smice")
+    for s, d in zip(out["segments"], dec):
+        assert s["mask"] == d["mask"]
+        assert abs(s["smice_rise"] - d["smice_rise"]) < 1e-11
+    np.testing.assert_array_equal(out["kept"], keep)
