@@ -34,7 +34,8 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
                                                       int S, SegHdr* __restrict__ hdrs, int* __restrict__ tab,
                                                       int tab_cap, int* __restrict__ status,
                                                       unsigned long long* __restrict__ pat,
-                                                      unsigned long long* __restrict__ ecmax) {
+                                                      unsigned long long* __restrict__ ecmax,
+                                                      int2* __restrict__ pat32) {
   __shared__ int s_top[kMaxK], s_slotnode[kMaxK], s_slotbit[kMaxK], s_slotchain[kMaxK];
   __shared__ int s_cslot0[kMaxK + 1], s_head[kMaxK], s_outer[kMaxK], s_jslot[kMaxK];
   __shared__ int s_spos[kMaxK], s_ssize[kMaxK], s_sph[kMaxK];           // segment node j
@@ -52,8 +53,6 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   __shared__ int s_keycnt[kMaxK * 3], s_keyoff[kMaxK * 3], s_keycur[kMaxK * 3];
   __shared__ SegHdr s_h;
   __shared__ int s_err, s_nch;
-  __shared__ int s_cw[kMaxK];                 // chain c: its per-lane scoring work
-  __shared__ uint32_t s_clos[kMaxK];          // chain c: chains whose terms depend on c's bits
   __shared__ int s_zi[kOmegaLds], s_zk[kOmegaLds];  // zone pass: node and key of Omega index q
   __shared__ int s_tab[kTabLds];                     // structural tables before they are written out
   const int g = segs[blockIdx.z];
@@ -334,6 +333,10 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     pat[3 * q + 1] = (unsigned long long)__double_as_longlong(INFINITY);
     pat[3 * q + 2] = 0ull;
   }
+  if (pat32) {  // the FP32 screen's (error, ordered bits of the slack)
+    pat32 = lane_ptr(pat32, lstride);
+    for (int q = tid; q < npat; q += blockDim.x) pat32[q] = make_int2(0, __float_as_int(INFINITY));
+  }
   if (tid == 0) *lane_ptr(ecmax, lstride) = 0ull;
   // the structural tables, built in shared memory, written out by all threads
   for (int q = tid; q < o_zent; q += blockDim.x) tab[q] = s_tab[q];
@@ -417,58 +420,6 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
       cr[C_IBASE] = x - items;
       if (tid == nch - 1) s_h.nitem = x;
     }
-  }
-  // Lane bits of the scoring kernel: a wave's 64 lanes vary 6 mask bits, and
-  // a chain none of whose bits (its own and its nesting path's) is among them
-  // is evaluated once per wave instead of per lane.  Chosen greedily: take
-  // the bits of the chain that adds the least per-lane work per bit gained
-  // (work of a chain: 2 per slot-phase, 1 per zone record, 1 per slot walked
-  // on its nesting path), until 6 bits are taken.
-  if (!s_err && tid < nch) {
-    const int c = tid;
-    int wk = 0;
-    for (int q = s_cslot0[c]; q < s_cslot0[c + 1]; ++q) wk += 2 * __popc(s_sph[s_slotbit[q]]);
-    for (int p = 0; p < 3; ++p) wk += s_keycnt[c * 3 + p];
-    for (int x = s_outer[c]; x >= 0; x = s_outer[x]) wk += s_cslot0[x + 1] - s_cslot0[x];
-    s_cw[c] = wk;
-    const int n = s_cslot0[c + 1] - s_cslot0[c];
-    const uint32_t own = ((1u << n) - 1u) << s_slotbit[s_cslot0[c]];
-    uint32_t cl = 0;
-    for (int d = 0; d < nch; ++d)
-      if ((uint32_t)s_pmask[d] & own) cl |= 1u << d;
-    s_clos[c] = cl;
-  }
-  __syncthreads();
-  // the greedy choice itself in one wave (candidates in lanes, wave-wide
-  // minimum; the chosen bits and the chains they touch kept in registers)
-  if (tid < 64) {
-    uint32_t lane_bits = 0, touched = 0;
-    for (int need = s_err ? 0 : min(6, k); need > 0;) {
-      long long key = LLONG_MAX;
-      if (tid < nch) {
-        const int c = tid;
-        const int n = s_cslot0[c + 1] - s_cslot0[c];
-        const uint32_t own = ((1u << n) - 1u) << s_slotbit[s_cslot0[c]];
-        const int nb = min(__popc(own & ~lane_bits), need);
-        if (nb > 0) {
-          int add = 0;
-          for (uint32_t x = s_clos[c] & ~touched; x; x &= x - 1) add += s_cw[__builtin_ctz(x)];
-          // added work per bit, in 1/720 units (exact for 1..6 bits), then the chain
-          key = ((long long)(add * (720 / nb)) << 8) | c;
-        }
-      }
-      for (int o = 32; o > 0; o >>= 1) {
-        const long long other = __shfl_xor(key, o, 64);
-        key = other < key ? other : key;
-      }
-      const int best = (int)(key & 255);
-      const int n = s_cslot0[best + 1] - s_cslot0[best];
-      uint32_t free_bits = (((1u << n) - 1u) << s_slotbit[s_cslot0[best]]) & ~lane_bits;
-      for (int b = 0; b < need && free_bits; ++b, free_bits &= free_bits - 1) lane_bits |= free_bits & (0u - free_bits);
-      touched |= s_clos[best];
-      need = min(6, k) - __popc(lane_bits);
-    }
-    if (tid == 0) s_h.lanebits = (int)lane_bits;
   }
   __syncthreads();
   if (!s_err)

@@ -147,6 +147,21 @@ __device__ __forceinline__ void walk_chain(const int* __restrict__ cr, const dou
     for (int p = 0; p < 3; ++p) B[i][p] = S[i][p];
 }
 
+// The mask's bits at pm's positions, gathered (run by run).
+__device__ __forceinline__ uint32_t gather_bits(uint32_t m, uint32_t pm) {
+  uint32_t u = 0;
+  int j = 0;
+  while (pm) {
+    const int b = __builtin_ctz(pm);
+    const int run = __builtin_ctz(~(pm >> b));
+    const uint32_t ones = (1u << run) - 1u;
+    u |= ((m >> b) & ones) << j;
+    j += run;
+    pm &= ~(ones << b);
+  }
+  return u;
+}
+
 // Band slack of a mask from the extreme squared magnitudes of its kept
 // node-phases: min(|V| - vmin, vmax - |V|) over them (+inf if there are none).
 __device__ __forceinline__ double band_slack(double qmin, double qmax, double vmin, double vmax) {
@@ -160,60 +175,6 @@ __device__ __forceinline__ bool near_boundary(const MaskScore& r, double e_bar, 
   const bool rin = r.e <= e_bar - amb && r.slack >= amb;
   const bool rout = r.e > e_bar + amb || r.slack < -amb;
   return !rin && !rout;
-}
-
-// Per-snapshot LDS stage of the scoring kernels, in 16-byte chunks: pair
-// table, slot records (2 chunks each), chain heads, then the first kZoneLds
-// zone records (2 chunks each; later ones are read from global memory).
-constexpr int kZoneLds = 256;
-
-struct Stage {
-  int cP, cT, cH, cZ, total;
-};
-
-__device__ __forceinline__ Stage stage_sizes(const SegHdr& H) {
-  Stage z;
-  z.cP = H.npairs * 3;
-  z.cT = H.nslots * 6;
-  z.cH = H.nchains * 3;
-  z.cZ = min(H.nz, kZoneLds) * 2;
-  z.total = z.cP + z.cT + z.cH + z.cZ;
-  return z;
-}
-
-__device__ __forceinline__ uint4 stage_src(const Stage& z, int i, const uint4* __restrict__ P_l,
-                                           const uint4* __restrict__ S_l, const uint4* __restrict__ H_l,
-                                           const uint4* __restrict__ Z_l) {
-  if (i < z.cP) return P_l[i];
-  i -= z.cP;
-  if (i < z.cT) return S_l[i];
-  i -= z.cT;
-  if (i < z.cH) return H_l[i];
-  return Z_l[i - z.cH];
-}
-
-// Store chunk i; with Hm (FP64 heads) also the head magnitude (absent phases 0).
-__device__ __forceinline__ void stage_put(const Stage& z, int i, const uint4& v, uint4* Pd, uint4* Sd, uint4* Hd,
-                                          double* Hm, uint4* Zd) {
-  if (i < z.cP) {
-    Pd[i] = v;
-    return;
-  }
-  i -= z.cP;
-  if (i < z.cT) {
-    Sd[i] = v;
-    return;
-  }
-  i -= z.cT;
-  if (i < z.cH) {
-    Hd[i] = v;
-    if (Hm) {
-      const double2 hv = make_double2(__hiloint2double((int)v.y, (int)v.x), __hiloint2double((int)v.w, (int)v.z));
-      Hm[i] = (hv.x != 0.0 || hv.y != 0.0) ? hmag(hv) : 0.0;
-    }
-    return;
-  }
-  Zd[i - z.cH] = v;
 }
 
 // Terms of chain c for M masks and one snapshot folded into el, kept squared

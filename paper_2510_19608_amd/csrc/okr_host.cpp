@@ -33,7 +33,7 @@ __global__ void k_powerflow_bfs(int, const uint8_t*, const int*, const int*, int
 __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const double2*, double, double, double2*,
                             double*, int*, const int*, double2*);
 __global__ void k_build_struct(Topo, State, const int*, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
-                               unsigned long long*);
+                               unsigned long long*, int2*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
 template <bool BUILD, bool PAT, int NS, bool DEEP>
 __global__ void k_seg_terms(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, const double2*,
@@ -48,32 +48,24 @@ __global__ void k_surr_rank(const SegHdr*, int, const int*, const float*, const 
                             const uint32_t*, int, const __bf16*, const __bf16*, const float*, float, uint32_t*,
                             const int*, int);
 __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, const unsigned long long*,
-                              const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*);
+                              const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*, int, int);
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
                          DevDecision*, const int*, uint32_t*, int*);
 __global__ void k_apply(const SegHdr*, const int*, size_t, const int*, Topo, State, const DevDecision*,
                         const double2*, const TargetRec*, const TargetRec*, double2*, double2*);
-__global__ void k_init_state(int, State, int*, int, int*, int, int, size_t);
+__global__ void k_init_state(int, State, int*, int);
 __global__ void k_copy2(const double2*, double2*, size_t);
 __global__ void k_final_err(int, const uint8_t*, const int*, const double2*, const double*, double*);
 __global__ void k_kron_yeq(Topo, State, const double2*, double2*, double2*, int*, int*);
 __global__ void k_kron_diag(Topo, State, const double2*, double2*);
 __global__ void k_sqrt_selftest(const double*, double*, int);
-__global__ void k_build_mixed(const SegHdr*, const int*, size_t, const int*, int, const double2*, const double2*,
-                              const TargetRec*, const double2*, const TargetRec*, double, double, Pair32*, Rec32*,
-                              Head32*, Rec32*);
-template <int M>
-__global__ void k_score_fp32(const SegHdr*, const int*, size_t, const int*, const Pair32*, const Rec32*, const Head32*,
-                             const Rec32*, const double*, int, int, SelParams, MaskScore32*, MaskScore32*, TileRec32*,
-                             int*);
-__global__ void k_mixed_select_a(const SegHdr*, const int*, size_t, const MaskScore32*, const TileRec32*, SelParams,
-                                 const int*, MixedState*, uint32_t*, int*);
-__global__ void k_mixed_select_b(const SegHdr*, const int*, size_t, const MaskScore32*, const TileRec32*, SelParams,
-                                 const int*, MixedState*, const uint32_t*, const int*, const MaskScore*, uint32_t*,
-                                 int*);
-__global__ void k_mixed_final(const SegHdr*, const int*, size_t, SelParams, const int*, MixedState*,
-                              const MaskScore32*, const uint32_t*, const int*, const MaskScore*, const uint32_t*,
-                              const int*, const MaskScore*, DevDecision*, int*);
+__global__ void k_pat32(const SegHdr*, const int*, size_t, const int*, const int*, const double2*, const TargetRec*,
+                        const double2*, const TargetRec*, double, double, TermsCaps, int2*, int*);
+__global__ void k_combine32(const SegHdr*, const int*, size_t, const int*, const int2*, const unsigned long long*,
+                            SelParams, MaskScore32*, TileRec32*, int);
+__global__ void k_mixed_decide(const SegHdr*, const int*, size_t, const int*, const unsigned long long*,
+                               const unsigned long long*, const MaskScore32*, const TileRec32*, SelParams, const int*,
+                               MixedState*, uint32_t*, MaskScore*, uint32_t*, MaskScore*, DevDecision*, int*);
 __global__ void k_surr_tables(const SegHdr*, int, const int*, int, const double2*, const double2*, const double2*,
                               const TargetRec*, float*, float*, SurrSlot*);
 __global__ void k_surr_features(const SegHdr*, int, const int*, const float*, const float*, const SurrSlot*,
@@ -114,7 +106,6 @@ using namespace okr;
 
 namespace {
 
-constexpr int kMaxSnapGroups = 32;
 constexpr int kMaxLanes = 8;      // segments per chunk (each needs a scratch block)
 constexpr int kDefaultLanes = 8;
 constexpr int kStatusInts = 16;
@@ -138,39 +129,14 @@ constexpr int kSmiceThreadsHost = 128;  // threads per block of the SMICE scorin
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Snapshot groups of the FP32 screen for
-// segments of k nodes, each group a contiguous run of snapshots: a
-// group of about 8 snapshots for segments of up to 9 nodes, 16 up to 12, 32
-// up to 16 and 64 above, scaled by (S / 96)^0.37 for S above 96 (a fit on
-// MI355X on the 1000-, 6000- and 8400-node
-// workloads: 24, 96 and 288 snapshots, segments of 8 to 20 nodes).
-int screen32_groups(int k, int S, int* spg) {
-  const double base = k <= 9 ? 8.0 : (k <= 12 ? 16.0 : (k <= 16 ? 32.0 : 64.0));
-  const double want = base * (S > 96 ? std::pow(S / 96.0, 0.37) : 1.0);
-  int SG = (int)std::ceil(S / want - 1e-9);
-  SG = std::max(1, std::min(std::min(SG, S), kMaxSnapGroups));
-  *spg = (S + SG - 1) / SG;
-  return (S + *spg - 1) / *spg;
-}
-
-// Launch shape of the FP32 screen: masks per lane by segment size, snapshot
-// groups by the rule above (on MI355X 10% faster than a
-// block-count target on the 8400-node workload, within 2% on the 6000-node
-// one).  The workspace planner sizes the screen's partial scores from this
-// same function.
-int screen32_shape(int k, int S, int* spg, int* mpl) {
-  *mpl = k >= 12 ? 4 : (k >= 10 ? 2 : 1);
-  return screen32_groups(k, S, spg);
-}
-
 struct Layout {
   size_t topo, z, Zroot, Vhat, Vcur, A, J, absV, kept, sup, slot_of, zent_of, status, iters, hdrs, decs, tab, P, srec,
-      headV, zrec, econst, fin, tiles, tickets, kp, yeq, Ykd, Yko, err;
+      headV, zrec, econst, fin, tiles, kp, yeq, Ykd, Yko, err;
   // factored FP64 scoring: chain-pattern table, largest constant error;
   // accumulators of the short-list scoring
   size_t pat, ecmax, lacc;
   // mixed precision
-  size_t P32, S32, H32, Z32, part32, fin32, tiles32, listA, listB, scoreA, scoreB, counts, mstate;
+  size_t pat32, fin32, tiles32, listA, listB, scoreA, scoreB, mstate;
   // results the host reads after a search, contiguous (one transfer):
   // status .. err, from res0, res_bytes long
   size_t res0, res_bytes;
@@ -721,30 +687,19 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     const size_t nm = (size_t)1 << h->kmax, nt = (nm + 63) / 64;
     L.fin = take(sizeof(MaskScore) * nm);
     L.tiles = take(sizeof(TileRec) * nt);
-    L.tickets = take(sizeof(int) * nt);
     L.pat = take(sizeof(PatScore) * 2 * nm);
     L.ecmax = take(sizeof(double));
     L.lacc = take(sizeof(unsigned long long) * 3 * nm);
   }
   {
-    size_t most = 1;
-    for (int k = 1; k <= h->kmax; ++k) {
-      int spg, mpl;
-      most = std::max(most, (size_t)screen32_shape(k, S, &spg, &mpl) << k);
-    }
     const size_t nm = (size_t)1 << h->kmax, nt = (nm + 63) / 64;
-    L.P32 = take(sizeof(Pair32) * 3 * (size_t)S * kMaxPairs);
-    L.S32 = take(sizeof(Rec32) * 3 * (size_t)S * kMaxK);
-    L.H32 = take(sizeof(Head32) * 3 * (size_t)S * kMaxK);
-    L.Z32 = take(sizeof(Rec32) * (size_t)S * 3 * n);
-    L.part32 = take(sizeof(MaskScore32) * most);
+    L.pat32 = take(sizeof(int2) * 2 * nm);
     L.fin32 = take(sizeof(MaskScore32) * nm);
     L.tiles32 = take(sizeof(TileRec32) * nt);
     L.listA = take(sizeof(uint32_t) * nm);
     L.listB = take(sizeof(uint32_t) * nm);
     L.scoreA = take(sizeof(MaskScore) * nm);
     L.scoreB = take(sizeof(MaskScore) * nm);
-    L.counts = take(sizeof(int) * 4);
   }
   h->topk = (mg->top_k > 0) ? mg->top_k : 0;
   {
@@ -808,21 +763,18 @@ struct Ptrs {
   const int *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks, *units;
   double2 *z, *Zroot, *Vhat, *Vcur, *A, *J, *P, *headV, *yeq, *Ykd, *Yko;
   double *absV, *econst, *err;
-  int *status, *iters, *tab, *tickets, *kp;
+  int *status, *iters, *tab, *kp;
   SegHdr* hdrs;
   DevDecision* decs;
   TargetRec *srec, *zrec;
   MaskScore* fin;
   TileRec* tiles;
   unsigned long long *pat, *ecmax, *lacc;
-  Pair32* P32;
-  Rec32 *S32, *Z32;
-  Head32* H32;
-  MaskScore32 *part32, *fin32;
+  int2* pat32;
+  MaskScore32* fin32;
   TileRec32* tiles32;
   uint32_t *listA, *listB;
   MaskScore *scoreA, *scoreB;
-  int* counts;
   MixedState* mstate;
   float *spz, *szs;
   SurrSlot* sss;
@@ -891,24 +843,18 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.pat = (unsigned long long*)at(L.pat);
   p.ecmax = (unsigned long long*)at(L.ecmax);
   p.lacc = (unsigned long long*)at(L.lacc);
-  p.tickets = (int*)at(L.tickets);
   p.kp = (int*)at(L.kp);
   p.yeq = (double2*)at(L.yeq);
   p.Ykd = (double2*)at(L.Ykd);
   p.Yko = (double2*)at(L.Yko);
   p.err = (double*)at(L.err);
-  p.P32 = (Pair32*)at(L.P32);
-  p.S32 = (Rec32*)at(L.S32);
-  p.H32 = (Head32*)at(L.H32);
-  p.Z32 = (Rec32*)at(L.Z32);
-  p.part32 = (MaskScore32*)at(L.part32);
+  p.pat32 = (int2*)at(L.pat32);
   p.fin32 = (MaskScore32*)at(L.fin32);
   p.tiles32 = (TileRec32*)at(L.tiles32);
   p.listA = (uint32_t*)at(L.listA);
   p.listB = (uint32_t*)at(L.listB);
   p.scoreA = (MaskScore*)at(L.scoreA);
   p.scoreB = (MaskScore*)at(L.scoreB);
-  p.counts = (int*)at(L.counts);
   p.mstate = (MixedState*)at(L.mstate);
   p.spz = (float*)at(L.spz);
   p.szs = (float*)at(L.szs);
@@ -992,27 +938,42 @@ void launch_terms(const okr_handle* h, const Ptrs& q, int c, bool build, bool pa
 #undef OKR_SEG_TERMS
 }
 
-// Every mask's FP64 score for the segments of chunk c: each chain's terms for
-// every assignment of the mask bits they depend on (at most 2^(k+1) patterns
-// in all), then one table entry per chain for every mask, its score and the
-// tile records.  Exact, since max and min are: the scores are those of
-// walking every chain for every mask, which took 1.8x (1000 nodes, 24
-// snapshots) to 19x (8400 nodes, 288) as long per search and was no faster on
-// single chains of 16 to 20 nodes, where the patterns are as many as the masks
-// (163 against 85 ms, 610 against 445 ms).  With build, the segments' tables
-// are formed too.  With gates, only segments whose entry is nonzero are
-// scored.
-void pattern_score(const okr_handle* h, const Ptrs& q, int c, bool build, const SelParams& sp, const int* gates,
-                   hipStream_t st) {
-  const int kc = h->chunk_k[c], c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
+// The segments' numeric tables and chain patterns: one launch where the tables
+// fit in LDS, else one each.
+void pattern_tables(const okr_handle* h, const Ptrs& q, int c, hipStream_t st) {
   TermsCaps one = h->chunk_caps[c];
   one.pats = 0;
-  const bool fused = build && terms_lds(one, 1) <= kTermsLdsMax;
-  if (build && !fused) launch_terms(h, q, c, true, false, nullptr, st);
-  launch_terms(h, q, c, fused, true, gates, st);
-  hipLaunchKernelGGL(k_fac_combine, dim3(((1u << kc) + 255) / 256, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs,
-                     q.chunks + c0, h->L.lane_stride, (const int*)q.tab, (const unsigned long long*)q.pat,
-                     (const unsigned long long*)q.ecmax, sp, q.fin, q.tiles, gates);
+  const bool fused = terms_lds(one, 1) <= kTermsLdsMax;
+  if (!fused) launch_terms(h, q, c, true, false, nullptr, st);
+  launch_terms(h, q, c, fused, true, nullptr, st);
+}
+
+// Blocks per segment of the combine kernels and tiles per wave: few tiles where
+// the launch is small and waits for its slowest wave, more where it has waves
+// to spare (1000-node chunks 6.5, 7.3 and 9.5 us with 2, 4 and 8; 8400-node
+// chunks 15.9, 14.1 and 16.0).
+int combine_blocks(int kc, int nz, int* per) {
+  const uint32_t tiles = ((1u << kc) + 63) / 64;
+  *per = (size_t)tiles * nz <= 8192 ? 2 : ((size_t)tiles * nz <= 65536 ? 4 : 8);
+  return (int)((tiles + 4 * *per - 1) / (4 * *per));
+}
+
+// Every mask's FP64 score for the segments of chunk c from their chain
+// patterns (each chain's terms for every assignment of the mask bits they
+// depend on, at most 2^(k+1) in all): one entry per chain.  Exact, since max
+// and min are: the scores are those of walking every chain for every mask,
+// which took 1.8x (1000 nodes, 24 snapshots) to 19x (8400 nodes, 288) as long
+// per search and was no faster on single chains of 16 to 20 nodes, where the
+// patterns are as many as the masks.  With gates, only segments whose entry is
+// nonzero are scored; all_scores stores every mask's score.
+void pattern_combine(const okr_handle* h, const Ptrs& q, int c, const SelParams& sp, const int* gates, bool all_scores,
+                     hipStream_t st) {
+  const int kc = h->chunk_k[c], c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
+  int per;
+  const int cb = combine_blocks(kc, nz, &per);
+  hipLaunchKernelGGL(k_fac_combine, dim3(cb, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, q.chunks + c0,
+                     h->L.lane_stride, (const int*)q.tab, (const unsigned long long*)q.pat,
+                     (const unsigned long long*)q.ecmax, sp, q.fin, q.tiles, gates, all_scores ? 1 : 0, per);
 }
 
 void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loads* loads,
@@ -1024,10 +985,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   std::vector<Ptrs> lp(h->nlanes);
   for (int l = 0; l < h->nlanes; ++l) lp[l] = pointers(h, ws, l);
   const bool vhat_given = (mg->flags & OKR_FLAG_VHAT_GIVEN) != 0;
-  const int ntick = (int)((((size_t)1 << h->kmax) + 63) / 64);
-  const int ninit = std::max(n, std::max(kStatusInts, ntick));
-  hipLaunchKernelGGL(k_init_state, dim3((ninit + 255) / 256), dim3(256), 0, st, n, p.St, p.status, kStatusInts,
-                     p.tickets, ntick, h->nlanes, h->L.lane_stride);
+  const int ninit = std::max(n, kStatusInts);
+  hipLaunchKernelGGL(k_init_state, dim3((ninit + 255) / 256), dim3(256), 0, st, n, p.St, p.status, kStatusInts);
   hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, p.T.parent, p.T.phase, p.T.ch_off,
                      p.T.ch, p.T.ext, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
   hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev,
@@ -1086,9 +1045,9 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
     const int kc = h->chunk_k[c];
     const Ptrs& q = lp[0];  // scratch of chunk position 0; position z is z * lstride further
     hipLaunchKernelGGL(k_build_struct, dim3(1, 1, nz), dim3(256), 0, st, q.T, q.St, segs, lstride, S, q.hdrs, q.tab,
-                       h->tab_cap, q.status, q.pat, q.ecmax);
+                       h->tab_cap, q.status, q.pat, q.ecmax, mixed ? q.pat32 : (int2*)nullptr);
     // the tables come with the scoring, or first where something reads them before
-    const bool tables_first = mixed || surr || feat_out;
+    const bool tables_first = surr || feat_out;
     if (tables_first) launch_terms(h, q, c, true, false, nullptr, st);
     const uint32_t nmask = 1u << kc;
     const int* gates = surr ? q.sgates : nullptr;
@@ -1155,7 +1114,9 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
     if (!mixed) {
       // timing: the scoring launches between two recorded events
       if (ev) (void)hipEventRecord((*ev)[2 * c], st);
-      pattern_score(h, q, c, !tables_first, sp, gates, st);
+      if (tables_first) launch_terms(h, q, c, false, true, gates, st);
+      else pattern_tables(h, q, c, st);
+      pattern_combine(h, q, c, sp, gates, dump || feat_out, st);
       if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
       hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates,
@@ -1197,49 +1158,33 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
         }
       }
     } else {
-      // mixed precision, one launch per step over the chunk: FP32 tables and
-      // screen, shortlist A and its FP64 scores, shortlist B and its FP64
-      // scores, the decision; then the FP64 scoring and arg-min of the
+      // mixed precision, one launch per step over the chunk: FP64 tables and
+      // patterns, FP32 patterns and screen, the shortlists with their FP64
+      // scores and the decision; then the FP64 combine and arg-min of the
       // segments whose FP32 deviation exceeded the bound (gated on device)
-      int spg32, mpl32;
-      const int SG32 = screen32_shape(kc, S, &spg32, &mpl32);
-      hipLaunchKernelGGL(k_build_mixed, dim3(256, 4, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                         (const int*)q.tab, n, (const double2*)q.Vcur, (const double2*)q.P, (const TargetRec*)q.srec,
-                         (const double2*)q.headV, (const TargetRec*)q.zrec, mg->v_min, mg->v_max, q.P32, q.S32, q.H32,
-                         q.Z32);
+      pattern_tables(h, q, c, st);
       if (ev) (void)hipEventRecord((*ev)[2 * c], st);
-      const int mblocks32 = (int)((nmask + kScoreThreads * mpl32 - 1) / (kScoreThreads * mpl32));
-#define OKR_SCORE32(M_)                                                                                          \
-  hipLaunchKernelGGL(k_score_fp32<M_>, dim3(mblocks32, SG32, nz), dim3(kScoreThreads), 0, st, (const SegHdr*)q.hdrs, \
-                     segs, lstride, (const int*)q.tab, (const Pair32*)q.P32, (const Rec32*)q.S32,                  \
-                     (const Head32*)q.H32, (const Rec32*)q.Z32, (const double*)q.econst, spg32, SG32, sp, q.part32,  \
-                     q.fin32, q.tiles32, q.tickets)
-      if (mpl32 == 4) OKR_SCORE32(4);
-      else if (mpl32 == 2) OKR_SCORE32(2);
-      else OKR_SCORE32(1);
-#undef OKR_SCORE32
+      TermsCaps caps = h->chunk_caps[c];
+      caps.ints += kc * kSlotInts + caps.pairs * kPairInts;
+      caps.zones = std::min(caps.zones, kTermsZone);
+      hipLaunchKernelGGL(k_pat32, dim3(S, h->unit_off[c + 1] - h->unit_off[c]), dim3(256), pat32_lds(caps), st,
+                         (const SegHdr*)q.hdrs, segs, lstride, q.units + h->unit_off[c], (const int*)q.tab,
+                         (const double2*)q.P, (const TargetRec*)q.srec, (const double2*)q.headV,
+                         (const TargetRec*)q.zrec, mg->v_min, mg->v_max, caps, q.pat32, q.status);
+      int per;
+      const int cb = combine_blocks(kc, nz, &per);
+      hipLaunchKernelGGL(k_combine32, dim3(cb, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
+                         (const int*)q.tab, (const int2*)q.pat32, (const unsigned long long*)q.ecmax, sp, q.fin32,
+                         q.tiles32, per);
       if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
-      int* cA = q.counts;
-      int* cB = q.counts + 1;
-      hipLaunchKernelGGL(k_mixed_select_a, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
+      hipLaunchKernelGGL(k_mixed_decide, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
+                         (const int*)q.tab, (const unsigned long long*)q.pat, (const unsigned long long*)q.ecmax,
                          (const MaskScore32*)q.fin32, (const TileRec32*)q.tiles32, sp, (const int*)q.status, q.mstate,
-                         q.listA, cA);
-      list_score(h, q, segs, nz, kc, q.listA, cA, (int)nmask, q.scoreA, sp, st);
-      hipLaunchKernelGGL(k_mixed_select_b, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                         (const MaskScore32*)q.fin32, (const TileRec32*)q.tiles32, sp, (const int*)q.status, q.mstate,
-                         (const uint32_t*)q.listA, (const int*)cA, (const MaskScore*)q.scoreA, q.listB, cB);
-      list_score(h, q, segs, nz, kc, q.listB, cB, (int)nmask, q.scoreB, sp, st);
-      hipLaunchKernelGGL(k_mixed_final, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride, sp,
-                         (const int*)q.status, q.mstate, (const MaskScore32*)q.fin32, (const uint32_t*)q.listA,
-                         (const int*)cA, (const MaskScore*)q.scoreA, (const uint32_t*)q.listB, (const int*)cB,
-                         (const MaskScore*)q.scoreB, q.decs, q.sgates);
-      {
-        const int* redo = q.sgates;
-        pattern_score(h, q, c, false, sp, redo, st);
-        hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                             (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, redo,
-                           (uint32_t*)nullptr, (int*)nullptr);
-      }
+                         q.listA, q.scoreA, q.listB, q.scoreB, q.decs, q.sgates);
+      pattern_combine(h, q, c, sp, q.sgates, false, st);
+      hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
+                         (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs,
+                         (const int*)q.sgates, (uint32_t*)nullptr, (int*)nullptr);
       if (dump)
         for (int z = 0; z < nz; ++z) {
           const int g = h->chunk_segs[c0 + z];

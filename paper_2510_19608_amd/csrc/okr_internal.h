@@ -9,7 +9,6 @@ namespace okr {
 constexpr int kMaxK = 24;                    // eligible nodes per segment
 constexpr int kMaxPairs = kMaxK * (kMaxK + 1) / 2;  // (super slot, reduced slot) pairs
 constexpr int kScoreBlock = 64;              // masks per tile record (one wave)
-constexpr int kScoreThreads = 256;           // scoring block: 4 waves, one mask per lane
 
 // status bit set when a structural invariant of a segment's tables fails (the
 // segment is then skipped by the scoring path and the call reports an error)
@@ -37,27 +36,11 @@ struct SegHdr {
   int total_ints;
   int npat;       // chain patterns: sum over chains of 2^popcount(C_PMASK)
   int nitem;      // work items of the pattern table: sum over chains of 2^(popcount(C_PMASK) - C_D)
-  int lanebits;   // the mask bits that vary across a scoring wave's 64 lanes
-                  // (6 of them, all k when k < 6); a tile is the 64 masks
-                  // sharing every other bit (tile_mask)
 };
 
-// Mask of scoring tile t, lane q: q's bits at the positions of the segment's
-// lane bits L, t's bits at the other positions of the k mask bits.
-// (lane_part: q's bits at L's positions; tile_part: t's bits at the others)
-__host__ __device__ __forceinline__ uint32_t lane_part(uint32_t L, uint32_t q) {
-  uint32_t m = 0;
-  for (uint32_t l = L; l; l &= l - 1, q >>= 1) m |= (q & 1u) << __builtin_ctz(l);
-  return m;
-}
-__host__ __device__ __forceinline__ uint32_t tile_part(uint32_t L, uint32_t t, int k) {
-  uint32_t m = 0;
-  for (uint32_t o = ((k >= 32 ? 0u : (1u << k)) - 1u) & ~L; o; o &= o - 1, t >>= 1) m |= (t & 1u) << __builtin_ctz(o);
-  return m;
-}
-__host__ __device__ __forceinline__ uint32_t tile_mask(uint32_t L, uint32_t t, uint32_t q, int k) {
-  return tile_part(L, t, k) | lane_part(L, q);
-}
+// A scoring tile is 64 consecutive masks (all 2^k of them where k < 6): lane q
+// of tile t holds mask (t << tile_bits(k)) | q.
+__host__ __device__ __forceinline__ int tile_bits(int k) { return k < 6 ? k : 6; }
 
 // A search step launched over a chunk of mutually independent segments:
 // blockIdx.z picks the segment (segs[blockIdx.z]) and its scratch block; each
@@ -88,6 +71,11 @@ __host__ __device__ __forceinline__ size_t terms_snap_lds(const TermsCaps& c) { 
 }
 __host__ __device__ __forceinline__ size_t terms_lds(const TermsCaps& c, int ns) {
   return (size_t)(c.ints + 3) / 4 * 16 + (size_t)(c.pats + 1) / 2 * 48 + ns * terms_snap_lds(c);
+}
+
+// (of the FP32 pattern kernel: one snapshot's FP32 tables)
+__host__ __device__ __forceinline__ size_t pat32_lds(const TermsCaps& c) {
+  return (size_t)(c.ints + 3) / 4 * 16 + (size_t)c.pairs * 3 * 16 + (size_t)c.slots * 3 * (32 + 16) + (size_t)c.zones * 32;
 }
 
 // Read-only int tables (segment structure) in the constant address space:

@@ -563,8 +563,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   const int tid = threadIdx.x, bd = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = bd >> 6;
   const int k = H.k;
   const uint32_t nm = 1u << k;
-  const uint32_t L = (uint32_t)H.lanebits;  // tile t, lane q holds tile_mask(L, t, q, k)
-  const int lb = __popc(L);
+  const int lb = tile_bits(k);
   const int ntiles = (int)(nm >> lb);
   // up to one tile per thread (segments of up to 16 nodes): its record is
   // read once and kept in registers
@@ -627,7 +626,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
     const int nc = ncand;
     for (int q = tid; q < nc * 64; q += bd) {
       if ((q & 63) >> lb) continue;
-      const uint32_t mm = tile_mask(L, (uint32_t)cand[q >> 6], (uint32_t)(q & 63), k);
+      const uint32_t mm = (uint32_t)cand[q >> 6] << lb | (uint32_t)(q & 63);
       if (__popc(mm) != best) continue;  // (only these masks' scores are stored)
       const MaskScore r = fin[mm];
       if (!feasible(r, sp.e_bar)) continue;
@@ -680,7 +679,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
     const int nc = ncand;
     for (int q = tid; q < nc * 64; q += bd) {
       if ((q & 63) >> lb) continue;
-      const uint32_t mm = tile_mask(L, (uint32_t)cand[q >> 6], (uint32_t)(q & 63), k);
+      const uint32_t mm = (uint32_t)cand[q >> 6] << lb | (uint32_t)(q & 63);
       if (__popc(mm) == best && feasible(fin[mm], sp.e_bar)) slist[atomicAdd(&nlist, 1)] = mm;
     }
     __syncthreads();
@@ -790,8 +789,7 @@ __global__ __launch_bounds__(64) void k_apply(const SegHdr* __restrict__ hdrs, c
 
 // Reset of the search state at the start of a call (no memset nodes, so the
 // sequence can be captured in a graph).
-__global__ void k_init_state(int n, State St, int* __restrict__ status, int nstatus, int* __restrict__ tickets,
-                             int ntickets, int nlanes, size_t lstride) {
+__global__ void k_init_state(int n, State St, int* __restrict__ status, int nstatus) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     St.kept[i] = 1;
@@ -800,8 +798,6 @@ __global__ void k_init_state(int n, State St, int* __restrict__ status, int nsta
     St.zent_of[3 * i] = St.zent_of[3 * i + 1] = St.zent_of[3 * i + 2] = -1;
   }
   if (i < nstatus) status[i] = 0;
-  if (i < ntickets)  // every chunk position's ticket counters (position z: z * lstride bytes further)
-    for (int z = 0; z < nlanes; ++z) ((int*)((char*)tickets + (size_t)z * lstride))[i] = 0;
 }
 
 __global__ void k_copy2(const double2* __restrict__ a, double2* __restrict__ b, size_t count) {

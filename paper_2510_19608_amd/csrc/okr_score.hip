@@ -13,32 +13,6 @@
 namespace okr {
 
 // ---------------------------------------------------------------- scoring --
-// Tile record of one wave's 64 masks (lane q holds mask
-// tile_mask(lanebits, tile, q, k), final score r): highest feasible level,
-// smallest error at that level, highest level of a mask near the e_bar /
-// band boundary.
-__device__ __forceinline__ int tile_record(const MaskScore& r, uint32_t m, uint32_t tile, bool valid,
-                                           const SelParams& sp, TileRec* __restrict__ tiles) {
-  const int pc = __popc(m);
-  const bool feas = valid && feasible(r, sp.e_bar);
-  int best = feas ? pc : -1;
-  int nearl = (valid && near_boundary(r, sp.e_bar, sp.amb)) ? pc : -1;
-  for (int o = 32; o > 0; o >>= 1) {
-    best = max(best, __shfl_xor(best, o, 64));
-    nearl = max(nearl, __shfl_xor(nearl, o, 64));
-  }
-  double em = (feas && pc == best) ? r.e : INFINITY;
-  for (int o = 32; o > 0; o >>= 1) em = fmin(em, __shfl_xor(em, o, 64));
-  if ((threadIdx.x & 63) == 0) {
-    TileRec t;
-    t.best = best;
-    t.near = nearl;
-    t.emin = em;
-    tiles[tile] = t;
-  }
-  return best;
-}
-
 // ------------------------------------------------- chain-term kernels --
 // Exact FP64 terms of chains for given mask bits, folded into per-item
 // accumulators by 64-bit atomics on the IEEE bit patterns.  Items are either
@@ -646,78 +620,124 @@ __global__ void k_list_finish(const int* __restrict__ count, const unsigned long
   }
 }
 
-// Every mask's score from the pattern table (one thread per mask): the
-// largest constant error and each chain's entry for the mask's bits, then
-// the band slack; per-mask scores and 64-mask tile records as the per-mask
-// scoring kernel writes them.
-constexpr int kPatLds = 1024;  // pattern-table entries staged in LDS
+// Every mask's score from the pattern table: the largest constant error and
+// each chain's entry for the mask's bits, then the per-mask scores and 64-mask
+// tile records that the arg-min reads.
+//
+// A wave takes per tiles (2, 4 or 8).  Against a tile's 6 lane bits a chain is
+// inside (its entry is the lane's for every tile: folded once per wave),
+// outside (the same for the tile's 64 masks: tile t's fold is formed in lane t
+// and read from there) or across (an entry per mask); so a mask costs about one
+// entry instead of one per chain (11 on the 1000-node workload).  Entries are
+// (error, band slack): the slack of an entry's extreme squared magnitudes is
+// formed once when it is staged, which is exact, the square root being
+// monotone.  Levels come from ballots, and a score is stored only where it is
+// read: every mask when all are wanted (dumps, surrogate targets), else mask 0
+// and the tile's masks at its best feasible level (on segments of 20 nodes the
+// stores of all, 16 MB each, took most of the launch).
+constexpr int kPatLds = 2048;      // pattern-table entries staged in LDS (32 KB)
 
 __global__ __launch_bounds__(256) void k_fac_combine(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
                                                      size_t lstride, const int* __restrict__ tab,
                                                      const unsigned long long* __restrict__ pat,
                                                      const unsigned long long* __restrict__ ecmax, SelParams sp,
                                                      MaskScore* __restrict__ fin, TileRec* __restrict__ tiles,
-                                                     const int* __restrict__ gates) {
+                                                     const int* __restrict__ gates, int full_fin, int per) {
   __shared__ int s_pm[kMaxK], s_pb[kMaxK];
-  __shared__ double s_pat[3 * kPatLds];
+  __shared__ double2 s_pat[kPatLds];
   const int g = *as_cint(segs + blockIdx.z);
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid || (gates && gates[g] == 0)) return;
-  if ((uint64_t)blockIdx.x * blockDim.x >= ((uint64_t)1 << H.k)) return;  // past this segment's masks
+  const int lb = tile_bits(H.k);
+  const uint32_t ntiles = 1u << (H.k - lb);
+  if (blockIdx.x * (4 * per) >= ntiles) return;  // past this segment's masks
   tab = lane_ptr(tab, lstride);
   pat = lane_ptr(pat, lstride);
   ecmax = lane_ptr(ecmax, lstride);
   fin = lane_ptr(fin, lstride);
   tiles = lane_ptr(tiles, lstride);
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int nch = H.nchains;
   if (tid < nch) {
     s_pm[tid] = tab[H.o_chain + tid * kChainInts + C_PMASK];
     s_pb[tid] = tab[H.o_chain + tid * kChainInts + C_PBASE];
   }
-  const int np = min(H.npat, kPatLds);
-  for (int i = tid; i < 3 * np; i += blockDim.x) s_pat[i] = __longlong_as_double((long long)pat[i]);
+  auto entry = [&](int i) {  // (error, band slack) of pattern i
+    return make_double2(__longlong_as_double((long long)pat[3 * (size_t)i]),
+                        band_slack(__longlong_as_double((long long)pat[3 * (size_t)i + 1]),
+                                   __longlong_as_double((long long)pat[3 * (size_t)i + 2]), sp.vmin, sp.vmax));
+  };
+  for (int i = tid; i < min(H.npat, kPatLds); i += 256) s_pat[i] = entry(i);
+  const double ec = __longlong_as_double((long long)*ecmax);
   __syncthreads();
-  const uint32_t nmask = 1u << H.k;
-  const uint32_t L = (uint32_t)H.lanebits;
-  const uint32_t tile = (blockIdx.x * blockDim.x + tid) / kScoreBlock;
-  const uint32_t m = tile_mask(L, tile, (uint32_t)(tid & (kScoreBlock - 1)), H.k);
-  const bool tile_ok = (tile << __popc(L)) < nmask;
-  const bool valid = tile_ok && ((uint32_t)(tid & (kScoreBlock - 1)) >> __popc(L)) == 0;
-  double e = __longlong_as_double((long long)*ecmax), qn = INFINITY, qx = 0.0;
+  auto look = [&](int i) { return i < kPatLds ? s_pat[i] : entry(i); };
+  const uint32_t t0 = (blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6)) * per;
+  if (t0 >= ntiles) return;
+  const uint32_t lmask = (1u << lb) - 1u;
+  double el = ec, sl = INFINITY;    // chains inside the lane bits, this lane's
+  double eu = 0.0, su = INFINITY;   // chains outside, of tile t0 + lane
+  uint32_t across = 0;              // chains across
+  const uint32_t mt = (t0 + (uint32_t)(lane & (per - 1))) << lb;
   for (int c = 0; c < nch; ++c) {
-    uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane(s_pm[c]);
+    const uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane(s_pm[c]);
     const int pb = __builtin_amdgcn_readfirstlane(s_pb[c]);
-    uint32_t u = 0;
-    int j = 0;
-    while (pm) {  // gather the mask's bits at C_PMASK's positions, run by run
-      const int b = __builtin_ctz(pm);
-      const int run = __builtin_ctz(~(pm >> b));
-      const uint32_t ones = (1u << run) - 1u;
-      u |= ((m >> b) & ones) << j;
-      j += run;
-      pm &= ~(ones << b);
-    }
-    const int idx = pb + (int)u;
-    double pe, pn, px;
-    if (idx < kPatLds) {
-      pe = s_pat[3 * idx];
-      pn = s_pat[3 * idx + 1];
-      px = s_pat[3 * idx + 2];
+    if ((pm & lmask) == 0) {
+      const double2 v = look(pb + (int)gather_bits(mt, pm));
+      eu = fmax(eu, v.x);
+      su = fmin(su, v.y);
+    } else if ((pm & ~lmask) == 0) {
+      const double2 v = look(pb + (int)gather_bits((uint32_t)lane & lmask, pm));
+      el = fmax(el, v.x);
+      sl = fmin(sl, v.y);
     } else {
-      pe = __longlong_as_double((long long)pat[3 * idx]);
-      pn = __longlong_as_double((long long)pat[3 * idx + 1]);
-      px = __longlong_as_double((long long)pat[3 * idx + 2]);
+      across |= 1u << c;
     }
-    e = fmax(e, pe);
-    qn = fmin(qn, pn);
-    qx = fmax(qx, px);
   }
-  MaskScore r;
-  r.e = e;
-  r.slack = band_slack(qn, qx, sp.vmin, sp.vmax);
-  if (valid) fin[m] = r;
-  if (tile_ok) tile_record(r, m, tile, valid, sp, tiles);
+  // lanes by popcount: level[j] of the lane bits
+  const int pcl = __popc((uint32_t)lane);
+  const bool valid = (uint32_t)lane <= lmask;
+  const int nt = (int)min((uint32_t)per, ntiles - t0);
+  for (int i = 0; i < nt; ++i) {
+    const uint32_t tile = t0 + i, m = tile << lb | ((uint32_t)lane & lmask);
+    MaskScore r;
+    r.e = fmax(el, __shfl(eu, i, 64));
+    r.slack = fmin(sl, __shfl(su, i, 64));
+    for (uint32_t x = across; x; x &= x - 1) {
+      const int c = __builtin_ctz(x);
+      const uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane(s_pm[c]);
+      const double2 v = look(__builtin_amdgcn_readfirstlane(s_pb[c]) + (int)gather_bits(m, pm));
+      r.e = fmax(r.e, v.x);
+      r.slack = fmin(r.slack, v.y);
+    }
+    const bool feas = valid && feasible(r, sp.e_bar), near = valid && near_boundary(r, sp.e_bar, sp.amb);
+    const int pct = __popc(tile);
+    TileRec t;
+    t.best = t.near = -1;
+    t.emin = INFINITY;
+    const unsigned long long fb = __ballot(feas), nb = __ballot(near);
+    if (nb)
+      for (int j = lb; j >= 0; --j)
+        if (nb & __ballot(pcl == j)) {
+          t.near = pct + j;
+          break;
+        }
+    if (fb) {
+      int j = lb;
+      unsigned long long at = 0;
+      for (; j >= 0; --j)
+        if ((at = fb & __ballot(pcl == j)) != 0) break;
+      t.best = pct + j;
+      double em = (at >> lane & 1ull) ? r.e : INFINITY;
+      if (at & (at - 1)) {
+        for (int o = 32; o > 0; o >>= 1) em = fmin(em, __shfl_xor(em, o, 64));
+      } else {
+        em = __shfl(em, __builtin_ctzll(at), 64);
+      }
+      t.emin = em;
+    }
+    if (lane == 0) tiles[tile] = t;
+    if (valid && (full_fin || m == 0 || pct + pcl == t.best)) fin[m] = r;
+  }
 }
 
 // d = |W + S| - |W| in difference form (w = |W| given):
@@ -731,289 +751,266 @@ __device__ __forceinline__ float diff32(float2 W, float w, float2 S) {
   return num * __builtin_amdgcn_rcpf(m + w);
 }
 
-// FP32 chain walk for M masks per lane (as walk_chain): d is the difference
-// |W + S| - |W| of a slot's voltage; a non-nested head is unaffected (d = 0).
-template <bool ERR, int M>
-__device__ __forceinline__ void walk32(const int* __restrict__ cr, const Pair32* Ps, const Rec32* Ss,
-                                       const Head32* Hs, int c, const uint32_t (&m)[M], float2 (&B)[M][3],
-                                       float (&el)[M], float (&slack)[M]) {
-  float2 S[M][3];
-  float dd[M][3];  // d of the current super on each phase
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      S[i][p] = B[i][p];
-      dd[i][p] = 0.f;
-    }
-  if (ERR && cr[C_OUTER] >= 0) {
-    const int hph = cr[C_PHASE];
-    const Head32* hv = Hs + c * 3;
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      if (hph >> p & 1) {
-        const Head32 h = hv[p];
-#pragma unroll
-        for (int i = 0; i < M; ++i) dd[i][p] = diff32(h.W, h.w, B[i][p]);
-      }
-  }
-  const int ns = cr[C_NSLOT], s0 = cr[C_SLOT0], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
-  const int phw0 = cr[C_PHW0], phw1 = cr[C_PHW1], phw2 = cr[C_PHW2];
-  int sidx[M];
-#pragma unroll
-  for (int i = 0; i < M; ++i) sidx[i] = 0;
-  for (int r = 0; r < ns; ++r) {
-    const int w = r < 8 ? phw0 : (r < 16 ? phw1 : phw2);
-    const int ph = (w >> (3 * (r & 7))) & 7;
-    const int prow = pair0 + ((r * (r + 1)) >> 1);
-    const Rec32* tr = Ss + (s0 + r) * 3;
-    bool red[M];
-    float rf[M];
-    const Pair32* pp[M];
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      red[i] = (m[i] >> (bit0 + r)) & 1u;
-      rf[i] = red[i] ? 1.f : 0.f;
-      pp[i] = Ps + (prow + sidx[i]) * 3;
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      if (!(ph >> p & 1)) continue;
-      Rec32 t;
-      if (ERR) t = tr[p];
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const Pair32 q = pp[i][p];
-        S[i][p].x = fmaf(rf[i], q.P.x, S[i][p].x);
-        S[i][p].y = fmaf(rf[i], q.P.y, S[i][p].y);
-        if (ERR) {
-          const float d = diff32(t.W, t.w, S[i][p]);
-          const float ek = fmaxf(t.a + d, t.b - d);
-          const float er = fmaxf(q.a + dd[i][p], q.b - dd[i][p]);
-          el[i] = fmaxf(el[i], red[i] ? er : ek);
-          slack[i] = red[i] ? slack[i] : fminf(slack[i], fminf(t.bmin + d, t.bmax - d));
-          dd[i][p] = red[i] ? dd[i][p] : d;
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < M; ++i) sidx[i] = red[i] ? sidx[i] : r + 1;
-  }
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) B[i][p] = S[i][p];
+// ---- FP32 screen ----
+// The chain patterns again, in FP32 difference form: k_pat32 evaluates every
+// pattern's terms per snapshot and folds them into (error, band slack) pairs,
+// k_combine32 gives every mask its pair and the tiles their levels.  The terms
+// are those of walking each chain for each mask in FP32, so the screen's
+// scores are too; walking them took 34 of the 45 ms of the 6000-node search.
+
+// Floats as ints that order alike (the slack can be negative).
+__device__ __forceinline__ int float_key(float x) {
+  const int i = __float_as_int(x);
+  return i < 0 ? i ^ 0x7fffffff : i;
+}
+__device__ __forceinline__ float key_float(int k) { return __int_as_float(k < 0 ? k ^ 0x7fffffff : k); }
+
+__device__ __forceinline__ Rec32 rec32(const TargetRec& r, double vmin, double vmax, bool on) {
+  const double w = sqrt(cabs2(r.W));
+  Rec32 o;
+  o.W = make_float2((float)r.W.x, (float)r.W.y);
+  o.w = (float)w;
+  o.a = on ? (float)(w - r.lo) : -INFINITY;
+  o.b = on ? (float)(r.hi - w) : -INFINITY;
+  o.bmin = on ? (float)(w - vmin) : INFINITY;
+  o.bmax = on ? (float)(vmax - w) : INFINITY;
+  o.pad = 0.f;
+  return o;
 }
 
-// FP32 screen of every mask (M masks per lane, layout as in k_score_fp64):
-// tile records of sure / possible / uncertain feasibility.
-template <int M>
-__global__ __launch_bounds__(kScoreThreads) void k_score_fp32(
-    const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ tab,
-    const Pair32* __restrict__ P32, const Rec32* __restrict__ S32, const Head32* __restrict__ H32,
-    const Rec32* __restrict__ Z32, const double* __restrict__ econst, int snaps_per_group, int SG, SelParams sp,
-    MaskScore32* __restrict__ part, MaskScore32* __restrict__ fin, TileRec32* __restrict__ tiles,
-    int* __restrict__ tickets) {
-  __shared__ Pair32 Ps[kMaxPairs * 3];
-  __shared__ Rec32 Ts[kMaxK * 3];
-  __shared__ Head32 Hv[kMaxK * 3];
-  __shared__ Rec32 Zs[kZoneLds];
-  __shared__ double s_ec;
-  __shared__ int ticket;
+// A block serves one snapshot (blockIdx.x) of one unit (blockIdx.y, as in
+// k_seg_terms): the snapshot's FP32 tables are formed in LDS from the FP64
+// ones (rounded once), then every pattern is a thread's.  Zone entries past
+// the LDS stage are formed from memory.
+__global__ __launch_bounds__(kTermsBlock) void k_pat32(
+    const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ units,
+    const int* __restrict__ tab, const double2* __restrict__ P, const TargetRec* __restrict__ srec,
+    const double2* __restrict__ headV, const TargetRec* __restrict__ zrec, double vmin, double vmax, TermsCaps caps,
+    int2* __restrict__ pat32, int* __restrict__ status) {
+  extern __shared__ __align__(16) unsigned char ct_lds[];
+  const int u = *as_cint(units + blockIdx.y);
+  const int uz = u & 255, part = (u >> 8) & 255, parts = u >> 16;
+  const int g = *as_cint(segs + uz);
+  const SegHdr H = load_hdr_g(hdrs, g);
+  if (!H.valid) return;
+  const int tid = threadIdx.x, l = blockIdx.x;
+  if (part > 0 && part * kTermsBlock >= H.npat) return;
+  if (H.npairs > caps.pairs || H.nslots > caps.slots || H.o_range > caps.ints) {  // never in a consistent plan
+    if (tid == 0) atomicOr(status, kStatusBuild);
+    return;
+  }
+  tab = lane_ptr_z(tab, lstride, uz);
+  const double2* gP = lane_ptr_z(P, lstride, uz) + (size_t)l * H.npairs * 3;
+  const TargetRec* gS = lane_ptr_z(srec, lstride, uz) + (size_t)l * H.nslots * 3;
+  const double2* gH = lane_ptr_z(headV, lstride, uz) + (size_t)l * H.nchains * 3;
+  const TargetRec* gZ = lane_ptr_z(zrec, lstride, uz) + (size_t)l * H.nz;
+  pat32 = lane_ptr_z(pat32, lstride, uz);
+  const int zst = min(H.nz, caps.zones);
+  int* si = (int*)ct_lds;
+  Pair32* sP = (Pair32*)(ct_lds + (size_t)(caps.ints + 3) / 4 * 16);
+  Rec32* sS = (Rec32*)(sP + (size_t)caps.pairs * 3);
+  Head32* sH = (Head32*)(sS + (size_t)caps.slots * 3);
+  Rec32* sZ = (Rec32*)(sH + (size_t)caps.slots * 3);
+  for (int i = tid; i < H.o_range; i += kTermsBlock) si[i] = tab[i];  // chains, nesting paths, slots, pairs
+  __syncthreads();
+  const int nP = H.npairs * 3, nS = H.nslots * 3, nC = H.nchains * 3;
+  for (int x = tid; x < nP + nS + nC + zst; x += kTermsBlock) {
+    if (x < nP) {
+      const int q = x / 3, p = x - q * 3;
+      const int rs = si[H.o_pair + q * kPairInts + PR_RSLOT];
+      const int* sr = si + H.o_slot + rs * kSlotInts;
+      const int c = sr[SL_CHAIN], sx = q - sr[SL_PAIRBASE];  // the super: the chain's head, or its slot sx - 1
+      const double2 pv = gP[x];
+      const TargetRec r = gS[rs * 3 + p];
+      const double2 w = sx == 0 ? gH[c * 3 + p] : gS[(si[c * kChainInts + C_SLOT0] + sx - 1) * 3 + p].W;
+      const double ws = sqrt(cabs2(w));
+      const bool on = sr[SL_PHASE] >> p & 1;
+      Pair32 o;
+      o.P = make_float2((float)pv.x, (float)pv.y);
+      o.a = on ? (float)(ws - r.lo) : -INFINITY;
+      o.b = on ? (float)(r.hi - ws) : -INFINITY;
+      sP[x] = o;
+    } else if (x < nP + nS) {
+      const int y = x - nP, s = y / 3, p = y - s * 3;
+      sS[y] = rec32(gS[y], vmin, vmax, si[H.o_slot + s * kSlotInts + SL_PHASE] >> p & 1);
+    } else if (x < nP + nS + nC) {
+      const double2 v = gH[x - nP - nS];
+      Head32 o;
+      o.W = make_float2((float)v.x, (float)v.y);
+      o.w = (float)sqrt(cabs2(v));
+      o.pad = 0.f;
+      sH[x - nP - nS] = o;
+    } else {
+      sZ[x - nP - nS - nC] = rec32(gZ[x - nP - nS - nC], vmin, vmax, true);
+    }
+  }
+  __syncthreads();
+  const int* chains = si + H.o_chain;
+  const int* nest = si + H.o_nest;
+  const int nch = H.nchains;
+  int c = 0;  // (a thread's items increase, so its chain index only moves forward)
+  for (int it = part * kTermsBlock + tid; it < H.npat; it += parts * kTermsBlock) {
+    while (c + 1 < nch && chains[(c + 1) * kChainInts + C_PBASE] <= it) ++c;
+    const int* cr = chains + c * kChainInts;
+    const uint32_t m = deposit_bits((uint32_t)(it - cr[C_PBASE]), (uint32_t)cr[C_PMASK]);
+    float2 S[3];
+    float dd[3];  // d of the current super on each phase
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      S[p] = make_float2(0.f, 0.f);
+      dd[p] = 0.f;
+    }
+    float e = 0.f, slack = INFINITY;
+    const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
+    for (int q = 0; q < nl; ++q) {  // the nesting path down to the head, then the chain itself
+      const bool own = q + 1 == nl;
+      const int* xr = chains + nest[no + q] * kChainInts;
+      if (own && nl > 1) {  // the head is moved by the outer chains
+        const int hph = cr[C_PHASE];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          const Head32 h = sH[c * 3 + p];
+          const float d = diff32(h.W, h.w, S[p]);
+          dd[p] = (hph >> p & 1) ? d : 0.f;
+        }
+      }
+      const int ns = xr[C_NSLOT], s0 = xr[C_SLOT0], pair0 = xr[C_PAIR0], bit0 = xr[C_BIT0];
+      const int phw0 = xr[C_PHW0], phw1 = xr[C_PHW1], phw2 = xr[C_PHW2];
+      int sidx = 0;
+      for (int r = 0; r < ns; ++r) {
+        const int ph = ((r < 8 ? phw0 : (r < 16 ? phw1 : phw2)) >> (3 * (r & 7))) & 7;
+        const bool red = (m >> (bit0 + r)) & 1u;
+        const Pair32* pr = sP + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3;
+        const Rec32* tr = sS + (s0 + r) * 3;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          const bool on = ph >> p & 1;
+          const Pair32 q32 = pr[p];
+          S[p].x += red && on ? q32.P.x : 0.f;
+          S[p].y += red && on ? q32.P.y : 0.f;
+          if (own) {
+            const Rec32 t = tr[p];
+            const float d = diff32(t.W, t.w, S[p]);
+            const float ek = fmaxf(t.a + d, t.b - d), er = fmaxf(q32.a + dd[p], q32.b - dd[p]);
+            const float sk = fminf(t.bmin + d, t.bmax - d);
+            e = fmaxf(e, on ? (red ? er : ek) : 0.f);
+            slack = fminf(slack, on && !red ? sk : INFINITY);
+            dd[p] = on && !red ? d : dd[p];
+          }
+        }
+        sidx = red ? sidx : r + 1;
+      }
+    }
+    auto zones = [&](int p, float2 b) {
+      int q = cr[C_ZOFF0 + p];
+      const int qe = q + cr[C_ZCNT0 + p];
+      auto term = [&](const Rec32& t) {
+        const float d = diff32(t.W, t.w, b);
+        e = fmaxf(e, fmaxf(t.a + d, t.b - d));
+        slack = fminf(slack, fminf(t.bmin + d, t.bmax - d));
+      };
+#pragma unroll 4
+      for (const int ql = min(qe, zst); q < ql; ++q) term(sZ[q]);
+      for (; q < qe; ++q) term(rec32(gZ[q], vmin, vmax, true));
+    };
+    zones(0, S[0]);
+    zones(1, S[1]);
+    zones(2, S[2]);
+    atomicMax(&pat32[it].x, __float_as_int(e));  // (e >= 0: its bits order like it)
+    atomicMin(&pat32[it].y, float_key(slack));
+  }
+}
+
+// Every mask's FP32 score from the FP32 pattern table (chains inside, outside
+// and across a tile's lane bits as in k_fac_combine), and the tiles' levels of
+// surely feasible, possibly feasible and uncertain masks.
+__global__ __launch_bounds__(256) void k_combine32(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
+                                                   size_t lstride, const int* __restrict__ tab,
+                                                   const int2* __restrict__ pat32,
+                                                   const unsigned long long* __restrict__ ecmax, SelParams sp,
+                                                   MaskScore32* __restrict__ fin, TileRec32* __restrict__ tiles,
+                                                   int per) {
+  __shared__ int s_pm[kMaxK], s_pb[kMaxK];
+  __shared__ float2 s_pat[kPatLds];
   const SegHdr H = load_hdr(hdrs, segs);
   if (!H.valid) return;
-  // blocks past this segment's masks (a chunk's launch covers its largest segment)
-  if ((uint64_t)blockIdx.x * (kScoreThreads * M) >= ((uint64_t)1 << H.k)) return;
+  const int lb = tile_bits(H.k);
+  const uint32_t ntiles = 1u << (H.k - lb);
+  if (blockIdx.x * (4 * per) >= ntiles) return;  // past this segment's masks
   tab = lane_ptr(tab, lstride);
-  P32 = lane_ptr(P32, lstride);
-  S32 = lane_ptr(S32, lstride);
-  H32 = lane_ptr(H32, lstride);
-  Z32 = lane_ptr(Z32, lstride);
-  econst = lane_ptr(econst, lstride);
-  part = lane_ptr(part, lstride);
+  pat32 = lane_ptr(pat32, lstride);
+  ecmax = lane_ptr(ecmax, lstride);
   fin = lane_ptr(fin, lstride);
   tiles = lane_ptr(tiles, lstride);
-  tickets = lane_ptr(tickets, lstride);
-  const int tid = threadIdx.x;
-  // lane set i of the block: tile x[i] / 64 (tile_mask over the segment's lane bits)
-  const uint32_t L = (uint32_t)H.lanebits;
-  uint32_t x[M], m[M];
-#pragma unroll
-  for (int i = 0; i < M; ++i) {
-    x[i] = blockIdx.x * (kScoreThreads * M) + i * kScoreThreads + tid;
-    m[i] = tile_mask(L, x[i] / kScoreBlock, x[i] % kScoreBlock, H.k);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int nch = H.nchains;
+  if (tid < nch) {
+    s_pm[tid] = tab[H.o_chain + tid * kChainInts + C_PMASK];
+    s_pb[tid] = tab[H.o_chain + tid * kChainInts + C_PBASE];
   }
-  const int sg = blockIdx.y;
-  const int l0 = sg * snaps_per_group;
-  const int l1 = min(H.S, l0 + snaps_per_group);
-  const int* chains = tab + H.o_chain;
-  const int* nest = tab + H.o_nest;
-  const Stage z = stage_sizes(H);
-  float e[M], slack[M];
-#pragma unroll
-  for (int i = 0; i < M; ++i) {
-    e[i] = 0.f;
-    slack[i] = INFINITY;
-  }
-  for (int l = l0; l < l1; ++l) {
-    {
-      const uint4* P_l = (const uint4*)(P32 + (size_t)l * H.npairs * 3);
-      const uint4* S_l = (const uint4*)(S32 + (size_t)l * H.nslots * 3);
-      const uint4* H_l = (const uint4*)(H32 + (size_t)l * H.nchains * 3);
-      const uint4* Z_l = (const uint4*)(Z32 + (size_t)l * H.nz);
-      for (int i = tid; i < z.total; i += kScoreThreads)
-        stage_put(z, i, stage_src(z, i, P_l, S_l, H_l, Z_l), (uint4*)Ps, (uint4*)Ts, (uint4*)Hv, (double*)nullptr,
-                  (uint4*)Zs);
-      if (tid == 0) s_ec = econst[l];
-      __syncthreads();
-    }
-    const Rec32* Zl = Z32 + (size_t)l * H.nz;
-    float el[M];
-    const float ec = (float)s_ec;
-#pragma unroll
-    for (int i = 0; i < M; ++i) el[i] = ec;
-    for (int c = 0; c < H.nchains; ++c) {
-      const int* cr = chains + c * kChainInts;
-      if (!(cr[C_PMASK] & L)) continue;  // the same for the wave's lanes: below
-      float2 B[M][3];
-#pragma unroll
-      for (int i = 0; i < M; ++i)
-#pragma unroll
-        for (int p = 0; p < 3; ++p) B[i][p] = make_float2(0.f, 0.f);
-      const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
-      for (int q = 0; q + 1 < nl; ++q) {
-        const int oc = nest[no + q];
-        walk32<false, M>(chains + oc * kChainInts, Ps, Ts, Hv, oc, m, B, el, slack);
-      }
-      walk32<true, M>(cr, Ps, Ts, Hv, c, m, B, el, slack);
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-        for (int q = cr[C_ZOFF0 + p], qe = q + cr[C_ZCNT0 + p]; q < qe; ++q) {
-          Rec32 t;
-          if (q < kZoneLds) t = Zs[q];
-          else t = Zl[q];
-#pragma unroll
-          for (int i = 0; i < M; ++i) {
-            const float d = diff32(t.W, t.w, B[i][p]);
-            el[i] = fmaxf(el[i], fmaxf(t.a + d, t.b - d));
-            slack[i] = fminf(slack[i], fminf(t.bmin + d, t.bmax - d));
-          }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < M; ++i) e[i] = fmaxf(e[i], el[i]);
-    __syncthreads();
-  }
-  // Chains none of whose bits is among the lane bits (the 6 that vary across
-  // a wave's lanes) have the same terms for the wave's 64 masks of each of
-  // its M mask sets:
-  // evaluated once per wave and mask set, one snapshot per lane, from the
-  // tables in global memory, folded across the lanes.
-  {
-    const int lane = tid & 63;
-    for (int c = 0; c < H.nchains; ++c) {
-      const int* cr = chains + c * kChainInts;
-      if (cr[C_PMASK] & L) continue;
-      const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const uint32_t mi[1] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)m[i])};
-        float ue = 0.f, us = INFINITY;
-        for (int l = l0 + lane; l < l1; l += 64) {
-          const Pair32* P_l = P32 + (size_t)l * H.npairs * 3;
-          const Rec32* S_l = S32 + (size_t)l * H.nslots * 3;
-          const Head32* H_l = H32 + (size_t)l * H.nchains * 3;
-          const Rec32* Z_l = Z32 + (size_t)l * H.nz;
-          float2 B[1][3];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) B[0][p] = make_float2(0.f, 0.f);
-          float el1[1] = {0.f}, sl1[1] = {INFINITY};
-          for (int q = 0; q + 1 < nl; ++q) {
-            const int oc = nest[no + q];
-            walk32<false, 1>(chains + oc * kChainInts, P_l, S_l, H_l, oc, mi, B, el1, sl1);
-          }
-          walk32<true, 1>(cr, P_l, S_l, H_l, c, mi, B, el1, sl1);
-#pragma unroll
-          for (int p = 0; p < 3; ++p)
-            for (int q = cr[C_ZOFF0 + p], qe = q + cr[C_ZCNT0 + p]; q < qe; ++q) {
-              const Rec32 t = Z_l[q];
-              const float d = diff32(t.W, t.w, B[0][p]);
-              el1[0] = fmaxf(el1[0], fmaxf(t.a + d, t.b - d));
-              sl1[0] = fminf(sl1[0], fminf(t.bmin + d, t.bmax - d));
-            }
-          ue = fmaxf(ue, el1[0]);
-          us = fminf(us, sl1[0]);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-          ue = fmaxf(ue, __shfl_xor(ue, o, 64));
-          us = fminf(us, __shfl_xor(us, o, 64));
-        }
-        e[i] = fmaxf(e[i], ue);
-        slack[i] = fminf(slack[i], us);
-      }
-    }
-  }
-  const uint32_t nmask = 1u << H.k;
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-    if (x[i] < nmask) {
-      MaskScore32 r;
-      r.e = e[i];
-      r.slack = slack[i];
-      part[(size_t)sg * nmask + m[i]] = r;
-    }
-  // every wave's partial scores are written and visible before the block
-  // takes its ticket (the last block to take one reads them all)
-  __threadfence();
+  auto entry = [&](int i) {
+    const int2 v = pat32[i];
+    return make_float2(__int_as_float(v.x), key_float(v.y));
+  };
+  for (int i = tid; i < min(H.npat, kPatLds); i += 256) s_pat[i] = entry(i);
+  const float ec = (float)__longlong_as_double((long long)*ecmax);
   __syncthreads();
-  if (tid == 0) ticket = atomicAdd(&tickets[blockIdx.x], 1);
-  __syncthreads();
-  if (ticket != SG - 1) return;
-  __threadfence();
+  auto look = [&](int i) { return i < kPatLds ? s_pat[i] : entry(i); };
+  const uint32_t t0 = (blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6)) * per;
+  if (t0 >= ntiles) return;
+  const uint32_t lmask = (1u << lb) - 1u;
+  float el = ec, sl = INFINITY;    // chains inside the lane bits, this lane's
+  float eu = 0.f, su = INFINITY;   // chains outside, of tile t0 + lane
+  uint32_t across = 0;             // chains across
+  const uint32_t mt = (t0 + (uint32_t)(lane & (per - 1))) << lb;
+  for (int c = 0; c < nch; ++c) {
+    const uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane(s_pm[c]);
+    const int pb = __builtin_amdgcn_readfirstlane(s_pb[c]);
+    if ((pm & lmask) == 0) {
+      const float2 v = look(pb + (int)gather_bits(mt, pm));
+      eu = fmaxf(eu, v.x);
+      su = fminf(su, v.y);
+    } else if ((pm & ~lmask) == 0) {
+      const float2 v = look(pb + (int)gather_bits((uint32_t)lane & lmask, pm));
+      el = fmaxf(el, v.x);
+      sl = fminf(sl, v.y);
+    } else {
+      across |= 1u << c;
+    }
+  }
+  const int pcl = __popc((uint32_t)lane);
+  const bool valid = (uint32_t)lane <= lmask;
   const double dlt = sp.delta + sp.amb;
-#pragma unroll
-  for (int i = 0; i < M; ++i) {
-    const bool valid = x[i] < nmask;
+  const int nt = (int)min((uint32_t)per, ntiles - t0);
+  for (int i = 0; i < nt; ++i) {
+    const uint32_t tile = t0 + i, m = tile << lb | ((uint32_t)lane & lmask);
     MaskScore32 r;
-    r.e = 0.f;
-    r.slack = INFINITY;
-    if (valid) {
-      for (int q = 0; q < SG; ++q) {
-        const volatile MaskScore32* x = part + (size_t)q * nmask + m[i];
-        r.e = fmaxf(r.e, x->e);
-        r.slack = fminf(r.slack, x->slack);
-      }
-      fin[m[i]] = r;
+    r.e = fmaxf(el, __shfl(eu, i, 64));
+    r.slack = fminf(sl, __shfl(su, i, 64));
+    for (uint32_t x = across; x; x &= x - 1) {
+      const int c = __builtin_ctz(x);
+      const uint32_t pm = (uint32_t)__builtin_amdgcn_readfirstlane(s_pm[c]);
+      const float2 v = look(__builtin_amdgcn_readfirstlane(s_pb[c]) + (int)gather_bits(m, pm));
+      r.e = fmaxf(r.e, v.x);
+      r.slack = fminf(r.slack, v.y);
     }
+    if (valid) fin[m] = r;
     const bool sure = valid && (double)r.e <= sp.e_bar - dlt && (double)r.slack >= dlt;
     const bool poss = valid && (double)r.e <= sp.e_bar + dlt && (double)r.slack >= -dlt;
-    const int pc = __popc(m[i]);
-    int a = sure ? pc : -1, b = poss ? pc : -1, c = (poss && !sure) ? pc : -1;
-    for (int o = 32; o > 0; o >>= 1) {
-      a = max(a, __shfl_xor(a, o, 64));
-      b = max(b, __shfl_xor(b, o, 64));
-      c = max(c, __shfl_xor(c, o, 64));
-    }
-    const uint32_t tile = x[i] / kScoreBlock;
-    if ((tid & 63) == 0 && tile * kScoreBlock < nmask) {
-      TileRec32 t;
-      t.sure = a;
-      t.poss = b;
-      t.unc = c;
-      t.pad = 0;
-      tiles[tile] = t;
-    }
+    const unsigned long long bs = __ballot(sure), bp = __ballot(poss), bu = bp & ~bs;
+    TileRec32 t;
+    t.sure = t.poss = t.unc = -1;
+    t.pad = 0;
+    const int pct = __popc(tile);
+    if (bp)
+      for (int j = lb; j >= 0; --j) {
+        const unsigned long long at = __ballot(pcl == j);
+        if (t.sure < 0 && (bs & at)) t.sure = pct + j;
+        if (t.poss < 0 && (bp & at)) t.poss = pct + j;
+        if (t.unc < 0 && (bu & at)) t.unc = pct + j;
+      }
+    if (lane == 0) tiles[tile] = t;
   }
-  if (tid == 0) tickets[blockIdx.x] = 0;
 }
-
-#define OKR_SCORE32_INST(M_)                                                                                   \
-  template __global__ void k_score_fp32<M_>(const SegHdr*, const int*, size_t, const int*, const Pair32*, const Rec32*,       \
-                                            const Head32*, const Rec32*, const double*, int, int, SelParams,  \
-                                            MaskScore32*, MaskScore32*, TileRec32*, int*);
-OKR_SCORE32_INST(1)
-OKR_SCORE32_INST(2)
-OKR_SCORE32_INST(4)
-#undef OKR_SCORE32_INST
 
 }  // namespace okr

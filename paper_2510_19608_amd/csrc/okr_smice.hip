@@ -355,7 +355,7 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
   slist = lane_ptr(slist, lstride);
   scount = lane_ptr(scount, lstride);
   smv = lane_ptr(smv, lstride);
-  const int ntiles = (int)((1u << H.k) >> __popc((uint32_t)H.lanebits));
+  const int ntiles = (int)((1u << H.k) >> tile_bits(H.k));
   // (the list's first entry is mask 0, a candidate at level 0 only)
   const int count = *scount, first = d.popcount == 0 ? 0 : 1;
   double smin = INFINITY;
