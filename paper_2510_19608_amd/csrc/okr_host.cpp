@@ -79,9 +79,8 @@ __global__ void k_gemm_nt(const __bf16*, int, const __bf16*, int, int, float*, i
 __global__ void k_rowdot_finish(const float*, int, int, const float*, float*, const int*, int);
 __global__ void k_batch_cast(const float*, int, __bf16*, __bf16*);
 __global__ void k_loss_dy(const float*, const float*, int, float*, float*);
-__global__ void k_dz2(const float*, const float*, const float*, int, __bf16*, __bf16*);
-__global__ void k_dz1(const float*, const float*, int, __bf16*);
-__global__ void k_colsums_part(const float*, const float*, const float*, const float*, const float*, int, float*);
+__global__ void k_dz2(const float*, const float*, const float*, int, __bf16*, __bf16*, float*);
+__global__ void k_dz1(const float*, const float*, int, __bf16*, float*);
 __global__ void k_colsums_final(const float*, int, float*, float*, float*, float*);
 __global__ void k_copy_cols(const float*, int, float*, int, int);
 __global__ void k_sum_splits(const float*, int, int, float*);
@@ -1545,7 +1544,7 @@ struct SurrWork {
 };
 
 constexpr int kMaxEpochs = 4096;
-constexpr int kColChunkHost = 256;  // rows per partial column sum (k_colsums_part)
+constexpr int kColTileHost = 64;    // rows per partial column sum (k_dz2, k_dz1); batches are multiples of it
 constexpr int kSplitK = 256;        // batch rows per K slice of the weight-gradient GEMMs
 
 // K slices of the weight-gradient GEMMs for a batch of B rows (B % 64 == 0).
@@ -1582,16 +1581,16 @@ SurrWork surr_layout(int B, void* base) {
   w.m = (float*)take(f4 * kSurrParams);
   w.v = (float*)take(f4 * kSurrParams);
   w.loss = (float*)take(f4 * kMaxEpochs);
-  w.colpart = (float*)take(f4 * (3 * kSurrH + 1) * ((B + kColChunkHost - 1) / kColChunkHost));
+  w.colpart = (float*)take(f4 * (3 * kSurrH + 1) * (B / kColTileHost));
   w.gpart = (float*)take(f4 * kSurrH * kSurrH * surr_splits(B));
   w.bytes = off;
   return w;
 }
 
-// Forward of one batch (B rows of FP32 features at X) into w.y; with `train`
+// Forward of one batch (B rows of FP32 features at X) into y; with `train`
 // the pre-activations and the transposed activations are kept for backward.
-void surr_forward(const SurrWork& w, const float* prm, const float* X, int B, bool train, hipStream_t st) {
-  hipLaunchKernelGGL(k_batch_cast, dim3((B * 64 + 255) / 256), dim3(256), 0, st, X, B, w.Xb, w.Xt);
+void surr_forward(const SurrWork& w, const float* prm, const float* X, int B, bool train, float* y, hipStream_t st) {
+  hipLaunchKernelGGL(k_batch_cast, dim3(B / 64), dim3(256), 0, st, X, B, w.Xb, train ? w.Xt : (__bf16*)nullptr);
   hipLaunchKernelGGL(k_gemm_nt<1>, dim3(kSurrH / 64, B / 64), dim3(256), 0, st, (const __bf16*)w.Xb, kSurrF,
                      (const __bf16*)w.W1b, kSurrF, kSurrF, (float*)nullptr, kSurrH, prm + kOffB1,
                      train ? w.Z1 : (float*)nullptr, w.H1b, train ? w.H1t : (__bf16*)nullptr, B, (const float*)nullptr,
@@ -1601,14 +1600,16 @@ void surr_forward(const SurrWork& w, const float* prm, const float* X, int B, bo
                      train ? w.Z2 : (float*)nullptr, (__bf16*)nullptr, (__bf16*)nullptr, B, prm + kOffW3, w.part,
                      (const int*)nullptr, 0);
   hipLaunchKernelGGL(k_rowdot_finish, dim3((B + 255) / 256), dim3(256), 0, st, (const float*)w.part, kSurrH / 32, B,
-                     prm + kOffB3, w.y, (const int*)nullptr, 0);
+                     prm + kOffB3, y, (const int*)nullptr, 0);
 }
 
-// Loss gradient of one batch into w.grads; the batch loss is added to *loss.
-void surr_backward(const SurrWork& w, const float* prm, const float* t, int B, float* loss, hipStream_t st) {
+// Loss gradient of one batch into grads; the batch loss is added to *loss.
+void surr_backward(const SurrWork& w, const float* prm, const float* t, int B, float* grads, float* loss,
+                   hipStream_t st) {
   hipLaunchKernelGGL(k_loss_dy, dim3((B + 255) / 256), dim3(256), 0, st, (const float*)w.y, t, B, w.dy, loss);
-  hipLaunchKernelGGL(k_dz2, dim3((B * kSurrH + 255) / 256), dim3(256), 0, st, (const float*)w.Z2, (const float*)w.dy,
-                     prm + kOffW3, B, w.dZ2b, w.dZ2t);
+  const dim3 tiles(kSurrH / 64, B / kColTileHost);
+  hipLaunchKernelGGL(k_dz2, tiles, dim3(256), 0, st, (const float*)w.Z2, (const float*)w.dy, prm + kOffW3, B, w.dZ2b,
+                     w.dZ2t, w.colpart);
   // dW2 = dZ2^T H1, K = B split into slices of kSplitK rows
   const int splits = surr_splits(B);
   hipLaunchKernelGGL(k_gemm_nt<0>, dim3(kSurrH / 64, kSurrH / 64, splits), dim3(256), 0, st, (const __bf16*)w.dZ2t,
@@ -1616,14 +1617,13 @@ void surr_backward(const SurrWork& w, const float* prm, const float* t, int B, f
                      (__bf16*)nullptr, (__bf16*)nullptr, kSurrH, (const float*)nullptr, (float*)nullptr,
                      (const int*)nullptr, 0);
   hipLaunchKernelGGL(k_sum_splits, dim3(kSurrH * kSurrH / 256), dim3(256), 0, st, (const float*)w.gpart, splits,
-                     kSurrH * kSurrH, w.grads + kOffW2);
+                     kSurrH * kSurrH, grads + kOffW2);
   // dH1 = dZ2 W2
   hipLaunchKernelGGL(k_gemm_nt<0>, dim3(kSurrH / 64, B / 64), dim3(256), 0, st, (const __bf16*)w.dZ2b, kSurrH,
                      (const __bf16*)w.W2tb, kSurrH, kSurrH, w.dH1, kSurrH, (const float*)nullptr, (float*)nullptr,
                      (__bf16*)nullptr, (__bf16*)nullptr, B, (const float*)nullptr, (float*)nullptr,
                      (const int*)nullptr, 0);
-  hipLaunchKernelGGL(k_dz1, dim3((B * kSurrH + 255) / 256), dim3(256), 0, st, (const float*)w.dH1, (const float*)w.Z1,
-                     B, w.dZ1t);
+  hipLaunchKernelGGL(k_dz1, tiles, dim3(256), 0, st, (const float*)w.dH1, (const float*)w.Z1, B, w.dZ1t, w.colpart);
   // dW1 = dZ1^T X (X^T padded to 64 rows), split like dW2
   hipLaunchKernelGGL(k_gemm_nt<0>, dim3(1, kSurrH / 64, splits), dim3(256), 0, st, (const __bf16*)w.dZ1t, B,
                      (const __bf16*)w.Xt, B, B, w.gpart, 64, (const float*)nullptr, (float*)nullptr,
@@ -1632,12 +1632,9 @@ void surr_backward(const SurrWork& w, const float* prm, const float* t, int B, f
   hipLaunchKernelGGL(k_sum_splits, dim3(kSurrH * 64 / 256), dim3(256), 0, st, (const float*)w.gpart, splits,
                      kSurrH * 64, w.gW1full);
   hipLaunchKernelGGL(k_copy_cols, dim3((kSurrH * kSurrF + 255) / 256), dim3(256), 0, st, (const float*)w.gW1full, 64,
-                     w.grads + kOffW1, kSurrH, kSurrF);
-  const int nchunk = (B + kColChunkHost - 1) / kColChunkHost;
-  hipLaunchKernelGGL(k_colsums_part, dim3(nchunk), dim3(kSurrH + 1), 0, st, (const float*)w.Z1, (const float*)w.dH1,
-                     (const float*)w.Z2, (const float*)w.dy, prm + kOffW3, B, w.colpart);
+                     grads + kOffW1, kSurrH, kSurrF);
   hipLaunchKernelGGL(k_colsums_final, dim3((3 * kSurrH + 1 + 255) / 256), dim3(256), 0, st, (const float*)w.colpart,
-                     nchunk, w.grads + kOffB1, w.grads + kOffB2, w.grads + kOffW3, w.grads + kOffB3);
+                     B / kColTileHost, grads + kOffB1, grads + kOffB2, grads + kOffW3, grads + kOffB3);
 }
 
 void surr_refresh(const SurrWork& w, const float* prm, hipStream_t st) {
@@ -1661,10 +1658,8 @@ extern "C" int okr_surrogate_grad(const float* params, const float* X, const flo
   hipStream_t st = static_cast<hipStream_t>(stream);
   surr_refresh(w, params, st);
   hipLaunchKernelGGL(k_zero_f32, dim3(1), dim3(64), 0, st, w.loss, 1);
-  surr_forward(w, params, X, B, true, st);
-  surr_backward(w, params, t, B, w.loss, st);
-  if (hipMemcpyAsync(grads, w.grads, sizeof(float) * kSurrParams, hipMemcpyDeviceToDevice, st) != hipSuccess)
-    return OKR_E_HIP;
+  surr_forward(w, params, X, B, true, w.y, st);
+  surr_backward(w, params, t, B, grads, w.loss, st);
   float l = 0.f;
   if (hipMemcpyAsync(&l, w.loss, sizeof(float), hipMemcpyDeviceToHost, st) != hipSuccess) return OKR_E_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return OKR_E_HIP;
@@ -1697,8 +1692,8 @@ extern "C" int okr_train_surrogate(const float* X, const float* t, int64_t n, in
     for (int64_t q = 0; q < nb; ++q) {
       const int64_t off = order[q] * batch;
       surr_refresh(w, params, st);
-      surr_forward(w, params, X + off * kSurrF, batch, true, st);
-      surr_backward(w, params, t + off, batch, w.loss + e, st);
+      surr_forward(w, params, X + off * kSurrF, batch, true, w.y, st);
+      surr_backward(w, params, t + off, batch, w.grads, w.loss + e, st);
       ++step;
       const float c1 = 1.f - std::pow(0.9f, (float)step), c2 = 1.f - std::pow(0.999f, (float)step);
       hipLaunchKernelGGL(k_adam, dim3((kSurrParams + 255) / 256), dim3(256), 0, st, params, (const float*)w.grads,
@@ -1721,8 +1716,7 @@ extern "C" int okr_surrogate_forward(const float* params, const float* X, int64_
   if (work_bytes < w.bytes) return OKR_E_WORKSPACE;
   hipStream_t st = static_cast<hipStream_t>(stream);
   surr_refresh(w, params, st);
-  surr_forward(w, params, X, (int)n, false, st);
-  if (hipMemcpyAsync(y, w.y, sizeof(float) * n, hipMemcpyDeviceToDevice, st) != hipSuccess) return OKR_E_HIP;
+  surr_forward(w, params, X, (int)n, false, y, st);
   if (hipStreamSynchronize(st) != hipSuccess) return OKR_E_HIP;
   return hipGetLastError() == hipSuccess ? OKR_OK : OKR_E_HIP;
 }

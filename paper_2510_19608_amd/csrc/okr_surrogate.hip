@@ -318,15 +318,27 @@ __global__ void k_rowdot_finish(const float* __restrict__ part, int nblk, int M,
 }
 
 // ------------------------------------------------------------- training --
-// Batch rows (FP32 [B][F]) to BF16 [B][F] and the transposed [64][B] (rows
-// F..63 zero) for the weight gradient of layer 1.
-__global__ void k_batch_cast(const float* __restrict__ X, int B, __bf16* __restrict__ Xb, __bf16* __restrict__ Xt) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * 64) return;
-  const int b = i / 64, j = i % 64;
-  const float v = j < kSurrF ? X[(size_t)b * kSurrF + j] : 0.f;
-  if (j < kSurrF) Xb[(size_t)b * kSurrF + j] = (__bf16)v;
-  Xt[(size_t)j * B + b] = (__bf16)v;
+// Batch rows (FP32 [B][F]) to BF16 [B][F] and, for training (Xt not null), the
+// transposed [64][B] (rows F..63 zero) for the weight gradient of layer 1.  A
+// block takes 64 rows and transposes them in LDS, so that both are written in
+// whole lines (one 2-byte element per row and line before: 17 us for 65,536
+// rows, most of it the transposed copy that a forward pass never reads).
+__global__ __launch_bounds__(256) void k_batch_cast(const float* __restrict__ X, int B, __bf16* __restrict__ Xb,
+                                                    __bf16* __restrict__ Xt) {
+  __shared__ __bf16 s_x[64][kSurrF + 2];
+  const int b0 = blockIdx.x * 64;
+  for (int i = threadIdx.x; i < 64 * kSurrF; i += 256) {
+    const int b = i / kSurrF, j = i % kSurrF;
+    const __bf16 v = (__bf16)X[(size_t)b0 * kSurrF + i];
+    Xb[(size_t)b0 * kSurrF + i] = v;
+    s_x[b][j] = v;
+  }
+  if (!Xt) return;
+  __syncthreads();
+  for (int i = threadIdx.x; i < 64 * 64; i += 256) {
+    const int j = i / 64, b = i % 64;
+    Xt[(size_t)j * B + b0 + b] = j < kSurrF ? s_x[b][j] : (__bf16)0.f;
+  }
 }
 
 __global__ void k_loss_dy(const float* __restrict__ y, const float* __restrict__ t, int B, float* __restrict__ dy,
@@ -342,61 +354,81 @@ __global__ void k_loss_dy(const float* __restrict__ y, const float* __restrict__
   if ((threadIdx.x & 63) == 0) atomicAdd(loss, l);
 }
 
-// dZ2 = dy w3^T * gelu'(Z2) as BF16 [B][256] and transposed [256][B]
-__global__ void k_dz2(const float* __restrict__ Z2, const float* __restrict__ dy, const float* __restrict__ w3, int B,
-                      __bf16* __restrict__ dZ2b, __bf16* __restrict__ dZ2t) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * kSurrH) return;
-  const int b = i / kSurrH, o = i % kSurrH;
-  const float v = dy[b] * w3[o] * gelu_grad_f(Z2[i]);
-  dZ2b[i] = (__bf16)v;
-  dZ2t[(size_t)o * B + b] = (__bf16)v;
-}
-
-// dZ1 = dH1 * gelu'(Z1), transposed BF16 [256][B]
-__global__ void k_dz1(const float* __restrict__ dH1, const float* __restrict__ Z1, int B, __bf16* __restrict__ dZ1t) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * kSurrH) return;
-  const int b = i / kSurrH, o = i % kSurrH;
-  dZ1t[(size_t)o * B + b] = (__bf16)(dH1[i] * gelu_grad_f(Z1[i]));
-}
-
-// Column reductions over the batch, in two passes with a fixed order (no
-// atomics): partial sums over row chunks of kColChunk, then their sum.
-//   gb2[o] = sum_b dy[b] w3[o] gelu'(Z2[b][o]);  gw3[o] = sum_b gelu(Z2[b][o]) dy[b]
-//   gb1[o] = sum_b dH1[b][o] gelu'(Z1[b][o]);    gb3 = sum_b dy[b]
-constexpr int kColChunk = 256;
+// Backward pass through a layer's activation, 64 rows x 64 columns per block:
+// the layer's dZ (as BF16 [B][256] and transposed [256][B], transposed in LDS)
+// and the column sums over the block's rows that the bias and output gradients
+// are made of, in a fixed order (16 rows per thread, 4 threads per column, then
+// the row tiles in k_colsums_final).  The column sums were a kernel of their own
+// that read both layers again with one thread per column and 256 rows (206 us
+// for 4,096 rows, 16 blocks); taken here they cost nothing measurable.
 constexpr int kColVals = 3 * kSurrH + 1;  // gb2, gw3, gb1 per column, then gb3
+constexpr int kColTile = 64;              // rows per partial sum
 
-__global__ void k_colsums_part(const float* __restrict__ Z1, const float* __restrict__ dH1,
-                               const float* __restrict__ Z2, const float* __restrict__ dy,
-                               const float* __restrict__ w3, int B, float* __restrict__ part) {
-  const int o = threadIdx.x;  // blockDim = kSurrH + 1
-  const int b0 = blockIdx.x * kColChunk, b1 = min(B, b0 + kColChunk);
-  float* out = part + (size_t)blockIdx.x * kColVals;
-  if (o < kSurrH) {
-    float a = 0.f, c = 0.f, d = 0.f;
-    for (int b = b0; b < b1; ++b) {
-      const float z2 = Z2[(size_t)b * kSurrH + o];
-      a += dy[b] * w3[o] * gelu_grad_f(z2);
-      c += gelu_f(z2) * dy[b];
-      d += dH1[(size_t)b * kSurrH + o] * gelu_grad_f(Z1[(size_t)b * kSurrH + o]);
-    }
-    out[o] = a;
-    out[kSurrH + o] = c;
-    out[2 * kSurrH + o] = d;
-  } else if (o == kSurrH) {
-    float t = 0.f;
-    for (int b = b0; b < b1; ++b) t += dy[b];
-    out[3 * kSurrH] = t;
+// dZ2 = dy w3^T * gelu'(Z2);  gb2[o] = sum_b dZ2[b][o], gw3[o] = sum_b gelu(Z2[b][o]) dy[b], gb3 = sum_b dy[b]
+__global__ __launch_bounds__(256) void k_dz2(const float* __restrict__ Z2, const float* __restrict__ dy,
+                                             const float* __restrict__ w3, int B, __bf16* __restrict__ dZ2b,
+                                             __bf16* __restrict__ dZ2t, float* __restrict__ part) {
+  __shared__ __bf16 s_t[64][66];
+  __shared__ float s_a[4][64], s_c[4][64];
+  const int c = threadIdx.x & 63, r = threadIdx.x >> 6;
+  const int o = blockIdx.x * 64 + c, b0 = blockIdx.y * kColTile;
+  const float w = w3[o];
+  float a = 0.f, q = 0.f;
+  for (int i = 0; i < 16; ++i) {
+    const int b = b0 + r * 16 + i;
+    const float z = Z2[(size_t)b * kSurrH + o], d = dy[b];
+    const float v = d * w * gelu_grad_f(z);
+    dZ2b[(size_t)b * kSurrH + o] = (__bf16)v;
+    s_t[c][r * 16 + i] = (__bf16)v;
+    a += v;
+    q += gelu_f(z) * d;
   }
+  s_a[r][c] = a;
+  s_c[r][c] = q;
+  __syncthreads();
+  float* out = part + (size_t)blockIdx.y * kColVals;
+  if (r == 0) {
+    out[o] = ((s_a[0][c] + s_a[1][c]) + s_a[2][c]) + s_a[3][c];
+    out[kSurrH + o] = ((s_c[0][c] + s_c[1][c]) + s_c[2][c]) + s_c[3][c];
+  }
+  if (blockIdx.x == 0 && r == 1) {
+    float t = dy[b0 + c];
+    for (int x = 32; x > 0; x >>= 1) t += __shfl_xor(t, x, 64);
+    if (c == 0) out[3 * kSurrH] = t;
+  }
+  for (int i = threadIdx.x; i < 64 * 64; i += 256)
+    dZ2t[(size_t)(blockIdx.x * 64 + i / 64) * B + b0 + i % 64] = s_t[i / 64][i % 64];
 }
 
+// dZ1 = dH1 * gelu'(Z1), transposed;  gb1[o] = sum_b dZ1[b][o]
+__global__ __launch_bounds__(256) void k_dz1(const float* __restrict__ dH1, const float* __restrict__ Z1, int B,
+                                             __bf16* __restrict__ dZ1t, float* __restrict__ part) {
+  __shared__ __bf16 s_t[64][66];
+  __shared__ float s_a[4][64];
+  const int c = threadIdx.x & 63, r = threadIdx.x >> 6;
+  const int o = blockIdx.x * 64 + c, b0 = blockIdx.y * kColTile;
+  float a = 0.f;
+  for (int i = 0; i < 16; ++i) {
+    const size_t x = (size_t)(b0 + r * 16 + i) * kSurrH + o;
+    const float v = dH1[x] * gelu_grad_f(Z1[x]);
+    s_t[c][r * 16 + i] = (__bf16)v;
+    a += v;
+  }
+  s_a[r][c] = a;
+  __syncthreads();
+  if (r == 0)
+    part[(size_t)blockIdx.y * kColVals + 2 * kSurrH + o] = ((s_a[0][c] + s_a[1][c]) + s_a[2][c]) + s_a[3][c];
+  for (int i = threadIdx.x; i < 64 * 64; i += 256)
+    dZ1t[(size_t)(blockIdx.x * 64 + i / 64) * B + b0 + i % 64] = s_t[i / 64][i % 64];
+}
+
+// The column sums from the row tiles' partial sums, in order.
 __global__ void k_colsums_final(const float* __restrict__ part, int nchunk, float* __restrict__ gb1,
                                 float* __restrict__ gb2, float* __restrict__ gw3, float* __restrict__ gb3) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= kColVals) return;
   float t = 0.f;
+#pragma unroll 8
   for (int c = 0; c < nchunk; ++c) t += part[(size_t)c * kColVals + q];
   if (q < kSurrH) gb2[q] = t;
   else if (q < 2 * kSurrH) gw3[q - kSurrH] = t;
