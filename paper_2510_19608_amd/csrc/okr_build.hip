@@ -1,7 +1,8 @@
 // Device-side construction of one segment's tables from the cumulative kept
-// state (no host round trip between segments).
+// state (no host round trip between segments), and the numeric state update of
+// the segments decided before it.
 //
-//   k_build_struct  (1 block)  chains, slots, pairs, nesting, Omega ranges,
+//   build_struct    (1 block)  chains, slots, pairs, nesting, Omega ranges,
 //                              zone entries grouped by (chain, phase)
 //
 // The numeric tables that follow from them (per snapshot) are built by
@@ -30,7 +31,7 @@ __device__ __forceinline__ int child_toward(const Topo& T, int h, int v) {
   return -1;
 }
 
-__global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const int* __restrict__ segs, size_t lstride,
+__device__ __forceinline__ void build_struct(Topo T, State St, const int* __restrict__ segs, int z, size_t lstride,
                                                       int S, SegHdr* __restrict__ hdrs, int* __restrict__ tab,
                                                       int tab_cap, int* __restrict__ status,
                                                       unsigned long long* __restrict__ pat,
@@ -55,8 +56,8 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   __shared__ int s_err, s_nch;
   __shared__ int s_zi[kOmegaLds], s_zk[kOmegaLds];  // zone pass: node and key of Omega index q
   __shared__ int s_tab[kTabLds];                     // structural tables before they are written out
-  const int g = segs[blockIdx.z];
-  tab = lane_ptr(tab, lstride);
+  const int g = segs[z];
+  tab = lane_ptr_z(tab, lstride, z);
   const int* parent = T.parent;
   const int* segment = T.segment;
   const int tid = threadIdx.x;
@@ -327,17 +328,17 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
   // largest kept squared magnitude of each pattern; the largest constant
   // error): cleared here, where their number is first known, which saves the
   // scoring a launch of its own (4.3 us per chunk)
-  pat = lane_ptr(pat, lstride);
+  pat = lane_ptr_z(pat, lstride, z);
   for (int q = tid; q < npat; q += blockDim.x) {
     pat[3 * q] = 0ull;
     pat[3 * q + 1] = (unsigned long long)__double_as_longlong(INFINITY);
     pat[3 * q + 2] = 0ull;
   }
   if (pat32) {  // the FP32 screen's (error, ordered bits of the slack)
-    pat32 = lane_ptr(pat32, lstride);
+    pat32 = lane_ptr_z(pat32, lstride, z);
     for (int q = tid; q < npat; q += blockDim.x) pat32[q] = make_int2(0, __float_as_int(INFINITY));
   }
-  if (tid == 0) *lane_ptr(ecmax, lstride) = 0ull;
+  if (tid == 0) *lane_ptr_z(ecmax, lstride, z) = 0ull;
   // the structural tables, built in shared memory, written out by all threads
   for (int q = tid; q < o_zent; q += blockDim.x) tab[q] = s_tab[q];
   // Omega_g ranges for the zone pass (shared copy)
@@ -452,6 +453,95 @@ __global__ __launch_bounds__(256) void k_build_struct(Topo T, State St, const in
     }
     hdrs[g] = H;
   }
+}
+
+// The numeric part of applying a segment's decided mask (Algorithm 1 state
+// update), one wave per snapshot: aggregated currents move to the new
+// super-nodes, kept slots and zone targets take their candidate voltages (same
+// arithmetic as the scoring).  Bs: the wave's chains' exit values.
+__device__ __forceinline__ void apply_values(const SegHdr& H, const int* tab, int n, int l, bool on, uint32_t m,
+                                             const double2* P, const TargetRec* srec, const TargetRec* zrec,
+                                             double2* Vcur, double2* A, double2* Bs) {
+  const int lane = threadIdx.x & 63;
+  if (on && lane < 3) {  // phases are independent: one thread each
+    const int p = lane;
+    const cint* chains = as_cint(tab + H.o_chain);
+    const cint* slots = as_cint(tab + H.o_slot);
+    const double2* Pl = P + (size_t)l * H.npairs * 3;
+    const TargetRec* srec_l = srec + (size_t)l * H.nslots * 3;
+    for (int c = 0; c < H.nchains; ++c) {
+      const cint* cr = chains + c * kChainInts;
+      const int outer = cr[C_OUTER];
+      double2 S = outer >= 0 ? Bs[outer * 3 + p] : make_double2(0.0, 0.0);
+      int sidx = 0;
+      // the current super-node's aggregated current, kept in a register
+      // while reduced slots add theirs (the same additions, in order)
+      size_t a = ((size_t)l * n + cr[C_HEAD]) * 3 + p;
+      double2 acc = A[a];
+      const int ns = cr[C_NSLOT], s0 = cr[C_SLOT0];
+      for (int r = 0; r < ns; ++r) {
+        const cint* sr = slots + (s0 + r) * kSlotInts;
+        const int node = sr[SL_NODE];
+        if ((m >> sr[SL_BIT]) & 1u) {
+          const double2 pv = Pl[(sr[SL_PAIRBASE] + sidx) * 3 + p];
+          S = make_double2(S.x + pv.x, S.y + pv.y);
+          const size_t b = ((size_t)l * n + node) * 3 + p;
+          const double2 ab = A[b];
+          acc = make_double2(acc.x + ab.x, acc.y + ab.y);
+          A[b] = make_double2(0.0, 0.0);
+        } else {
+          if (sr[SL_PHASE] >> p & 1) {
+            const double2 w = srec_l[(s0 + r) * 3 + p].W;
+            Vcur[((size_t)l * n + node) * 3 + p] = make_double2(w.x + S.x, w.y + S.y);
+          }
+          sidx = r + 1;
+          A[a] = acc;
+          a = ((size_t)l * n + node) * 3 + p;
+          acc = A[a];
+        }
+      }
+      A[a] = acc;
+      Bs[c * 3 + p] = S;
+    }
+  }
+  __syncthreads();
+  if (!on) return;
+  for (int q = lane; q < H.nz; q += 64) {
+    const int* ze = tab + H.o_zent + q * 3;
+    const int node = ze[0], p = ze[1], c = ze[2];
+    const double2 w = zrec[(size_t)l * H.nz + q].W, b = Bs[c * 3 + p];
+    Vcur[((size_t)l * n + node) * 3 + p] = make_double2(w.x + b.x, w.y + b.y);
+  }
+}
+
+// One step between two chunks' scorings: blocks [0, nz) build the structural
+// tables of the next chunk's segments, the others move the voltages and
+// currents of the previous chunk's decided segments (4 snapshots per block).
+// The two share nothing: the kept set and super-nodes are final when the
+// previous decision is, the build reads and writes no voltage or current, and
+// the chunks' tables alternate between two buffers.  As launches of their own
+// the build (13.7 us) and the update (11.6) ran one after the other.
+__global__ __launch_bounds__(256) void k_step(Topo T, State St, const int* __restrict__ segs, int nz, size_t lstride,
+                                              int S, SegHdr* __restrict__ hdrs, int* __restrict__ tab, int tab_cap,
+                                              int* __restrict__ status, unsigned long long* __restrict__ pat,
+                                              unsigned long long* __restrict__ ecmax, int2* __restrict__ pat32,
+                                              const int* __restrict__ psegs, const int* __restrict__ ptab,
+                                              const DevDecision* __restrict__ decs, const double2* __restrict__ P,
+                                              const TargetRec* __restrict__ srec, const TargetRec* __restrict__ zrec,
+                                              double2* __restrict__ Vcur, double2* __restrict__ A) {
+  if ((int)blockIdx.x < nz) {
+    build_struct(T, St, segs, blockIdx.x, lstride, S, hdrs, tab, tab_cap, status, pat, ecmax, pat32);
+    return;
+  }
+  __shared__ double2 s_B[4][kMaxK * 3];
+  const int per = (S + 3) / 4, x = (int)blockIdx.x - nz, z = x / per;
+  const int l = (x - z * per) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = *as_cint(psegs + z);
+  const SegHdr H = load_hdr_g(hdrs, g);
+  if (!H.valid) return;
+  apply_values(H, lane_ptr_z(ptab, lstride, z), T.n, l, l < S, *as_cint((const int*)&decs[g].mask),
+               lane_ptr_z(P, lstride, z), lane_ptr_z(srec, lstride, z), lane_ptr_z(zrec, lstride, z), Vcur, A,
+               s_B[threadIdx.x >> 6]);
 }
 
 }  // namespace okr

@@ -218,6 +218,41 @@ __device__ __forceinline__ void score_chain(const int* __restrict__ chains, cons
     }
 }
 
+// ---------------------------------------------------------- state update --
+// The structural part of applying mask m to segment H (one block, called by
+// every thread): kept flags and super-nodes over Omega_g, and the node -> slot
+// and zone-entry maps cleared for the next segment.  Run by the kernel that
+// settles the decision, so that the next chunk's table build can start while
+// the voltages and currents of this one are still being moved.
+__device__ __forceinline__ void update_state(const SegHdr& H, const int* tab, const Topo& T, const State& St,
+                                             uint32_t m) {
+  const int* slots = tab + H.o_slot;
+  if ((int)threadIdx.x < H.nslots) {
+    const int* sr = slots + threadIdx.x * kSlotInts;
+    if ((m >> sr[SL_BIT]) & 1u) St.kept[sr[SL_NODE]] = 0;
+    St.slot_of[sr[SL_NODE]] = -1;
+  }
+  for (int q = threadIdx.x; q < H.nz; q += blockDim.x) {
+    const int* ze = tab + H.o_zent + q * 3;
+    St.zent_of[ze[0] * 3 + ze[1]] = -1;
+  }
+  __syncthreads();
+  const int* rg = tab + H.o_range;
+  for (int q = threadIdx.x; q < H.nomega; q += blockDim.x) {
+    int r = 0;
+    while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
+    const int i = rg[3 * r] + (q - rg[3 * r + 2]);
+    // up through reduced nodes; a reduced node's recorded super (before or
+    // after this update) is an ancestor with only reduced nodes in between
+    int v = i;
+    while (!St.kept[v]) {
+      const int s = St.sup[v];
+      v = (s >= 0 && s != v) ? s : T.parent[v];
+    }
+    St.sup[i] = v;
+  }
+}
+
 // ------------------------------------------------------------ block reduce --
 template <typename T, typename Op>
 __device__ T block_reduce(T v, Op op, T* sh) {

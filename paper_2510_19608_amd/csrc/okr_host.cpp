@@ -32,8 +32,9 @@ __global__ void k_powerflow_bfs(int, const uint8_t*, const int*, const int*, int
                                 double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
 __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const double2*, double, double, double2*,
                             double*, int*, const int*, double2*);
-__global__ void k_build_struct(Topo, State, const int*, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
-                               unsigned long long*, int2*);
+__global__ void k_step(Topo, State, const int*, int, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
+                       unsigned long long*, int2*, const int*, const int*, const DevDecision*, const double2*,
+                       const TargetRec*, const TargetRec*, double2*, double2*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
 template <bool BUILD, bool PAT, int NS, bool DEEP>
 __global__ void k_seg_terms(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, const double2*,
@@ -50,9 +51,7 @@ __global__ void k_surr_rank(const SegHdr*, int, const int*, const float*, const 
 __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, const unsigned long long*,
                               const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*, int, int);
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
-                         DevDecision*, const int*, uint32_t*, int*);
-__global__ void k_apply(const SegHdr*, const int*, size_t, const int*, Topo, State, const DevDecision*,
-                        const double2*, const TargetRec*, const TargetRec*, double2*, double2*);
+                         DevDecision*, const int*, uint32_t*, int*, const int*, Topo, State);
 __global__ void k_init_state(int, State, int*, int);
 __global__ void k_copy2(const double2*, double2*, size_t);
 __global__ void k_final_err(int, const uint8_t*, const int*, const double2*, const double*, double*);
@@ -98,7 +97,7 @@ __global__ void k_smice_score(const SegHdr*, const int*, size_t, const int*, con
                               const double2*, const TargetRec*, const int*, const double*, const uint32_t*,
                               const int*, double*);
 __global__ void k_smice_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, const uint32_t*,
-                               const int*, const double*, double, DevDecision*);
+                               const int*, const double*, double, DevDecision*, const int*, Topo, State);
 }  // namespace okr
 
 using namespace okr;
@@ -129,7 +128,7 @@ constexpr int kSmiceThreadsHost = 128;  // threads per block of the SMICE scorin
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout {
-  size_t topo, z, Zroot, Vhat, Vcur, A, J, absV, kept, sup, slot_of, zent_of, status, iters, hdrs, decs, tab, P, srec,
+  size_t topo, z, Zroot, Vhat, Vcur, A, J, absV, kept, sup, slot_of, zent_of, status, iters, hdrs, decs, tab, tab2, P, srec,
       headV, zrec, econst, fin, tiles, kp, yeq, Ykd, Yko, err;
   // factored FP64 scoring: chain-pattern table, largest constant error;
   // accumulators of the short-list scoring
@@ -651,7 +650,7 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     for (int q = 0; q < n; ++q) ph[q] = h->phase[h->pre[q]];
   }
   TO.total = (int)tp.size();
-  // table capacity of one segment (layout written by k_build_struct)
+  // table capacity of one segment (layout written by build_struct)
   h->tab_cap = kMaxK * kChainInts + kMaxK * kMaxK + n + kMaxK * kSlotInts + kMaxPairs * kPairInts + 3 * kMaxK +
                9 * n + 64;
   // workspace layout
@@ -677,6 +676,7 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
   // per-segment scratch (one block per chunk position z, at + z * lane_stride)
   L.lane0 = off;
   L.tab = take(sizeof(int) * h->tab_cap);
+  L.tab2 = take(sizeof(int) * h->tab_cap);  // chunks alternate between the two
   L.P = take(sizeof(double2) * 3 * (size_t)S * kMaxPairs);
   L.srec = take(sizeof(TargetRec) * 3 * (size_t)S * kMaxK);
   L.headV = take(sizeof(double2) * 3 * (size_t)S * kMaxK);
@@ -762,7 +762,7 @@ struct Ptrs {
   const int *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks, *units;
   double2 *z, *Zroot, *Vhat, *Vcur, *A, *J, *P, *headV, *yeq, *Ykd, *Yko;
   double *absV, *econst, *err;
-  int *status, *iters, *tab, *kp;
+  int *status, *iters, *tab, *tab2, *kp;
   SegHdr* hdrs;
   DevDecision* decs;
   TargetRec *srec, *zrec;
@@ -832,6 +832,7 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.hdrs = (SegHdr*)at(L.hdrs);
   p.decs = (DevDecision*)at(L.decs);
   p.tab = (int*)at(L.tab);
+  p.tab2 = (int*)at(L.tab2);
   p.P = (double2*)at(L.P);
   p.srec = (TargetRec*)at(L.srec);
   p.headV = (double2*)at(L.headV);
@@ -1042,9 +1043,13 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
     const int c0 = h->chunk_off[c], nz = h->chunk_off[c + 1] - c0;
     const int* segs = p.chunks + c0;  // device copy of this chunk's segment ids
     const int kc = h->chunk_k[c];
+    for (Ptrs& w : lp) std::swap(w.tab, w.tab2);
     const Ptrs& q = lp[0];  // scratch of chunk position 0; position z is z * lstride further
-    hipLaunchKernelGGL(k_build_struct, dim3(1, 1, nz), dim3(256), 0, st, q.T, q.St, segs, lstride, S, q.hdrs, q.tab,
-                       h->tab_cap, q.status, q.pat, q.ecmax, mixed ? q.pat32 : (int2*)nullptr);
+    const int pz = c > 0 ? c0 - h->chunk_off[c - 1] : 0;  // the previous chunk's segments
+    hipLaunchKernelGGL(k_step, dim3(nz + pz * ((S + 3) / 4)), dim3(256), 0, st, q.T, q.St, segs, nz, lstride, S, q.hdrs,
+                       q.tab, h->tab_cap, q.status, q.pat, q.ecmax, mixed ? q.pat32 : (int2*)nullptr, segs - pz,
+                       (const int*)q.tab2, (const DevDecision*)q.decs, (const double2*)q.P, (const TargetRec*)q.srec,
+                       (const TargetRec*)q.zrec, q.Vcur, q.A);
     // the tables come with the scoring, or first where something reads them before
     const bool tables_first = surr || feat_out;
     if (tables_first) launch_terms(h, q, c, true, false, nullptr, st);
@@ -1119,7 +1124,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
       hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates,
-                         smice ? q.smlist : (uint32_t*)nullptr, smice ? q.smcount : (int*)nullptr);
+                         smice ? q.smlist : (uint32_t*)nullptr, smice ? q.smcount : (int*)nullptr,
+                         smice ? (const int*)nullptr : (const int*)q.tab, q.T, q.St);
       if (smice) {
         // SMICE of the feasible masks of the chosen level, and the decision under it
         hipLaunchKernelGGL(k_smice_prep, dim3(1, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
@@ -1136,7 +1142,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
         hipLaunchKernelGGL(k_smice_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                            (const MaskScore*)q.fin, (const TileRec*)q.tiles, (const uint32_t*)q.smlist,
                            (const int*)q.smcount, (const double*)q.smv,
-                           mg->smice_tol > 0.0 ? mg->smice_tol : kSmiceTol, q.decs);
+                           mg->smice_tol > 0.0 ? mg->smice_tol : kSmiceTol, q.decs, (const int*)q.tab, q.T, q.St);
       }
       for (int z = 0; z < nz; ++z) {
         const int g = h->chunk_segs[c0 + z];
@@ -1183,7 +1189,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       pattern_combine(h, q, c, sp, q.sgates, false, st);
       hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs,
-                         (const int*)q.sgates, (uint32_t*)nullptr, (int*)nullptr);
+                         (const int*)q.sgates, (uint32_t*)nullptr, (int*)nullptr, (const int*)q.tab, q.T, q.St);
       if (dump)
         for (int z = 0; z < nz; ++z) {
           const int g = h->chunk_segs[c0 + z];
@@ -1192,9 +1198,14 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
           (void)hipMemcpyAsync((*dump32)[g].data(), lp[z].fin32, sizeof(MaskScore32) * nm, hipMemcpyDeviceToHost, st);
         }
     }
-    hipLaunchKernelGGL(k_apply, dim3(S, 1, nz), dim3(64), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                       (const int*)q.tab, q.T, q.St, (const DevDecision*)q.decs, (const double2*)q.P,
-                       (const TargetRec*)q.srec, (const TargetRec*)q.zrec, q.Vcur, q.A);
+  }
+  if (nchunk > 0) {  // the last chunk's voltages and currents
+    const Ptrs& q = lp[0];
+    const int c0 = h->chunk_off[nchunk - 1], pz = h->chunk_off[nchunk] - c0;
+    hipLaunchKernelGGL(k_step, dim3(pz * ((S + 3) / 4)), dim3(256), 0, st, q.T, q.St, (const int*)nullptr, 0, lstride, S,
+                       q.hdrs, q.tab2, h->tab_cap, q.status, q.pat, q.ecmax, (int2*)nullptr, p.chunks + c0,
+                       (const int*)q.tab, (const DevDecision*)q.decs, (const double2*)q.P, (const TargetRec*)q.srec,
+                       (const TargetRec*)q.zrec, q.Vcur, q.A);
   }
   hipLaunchKernelGGL(k_kron_yeq, dim3((n + 127) / 128), dim3(128), 0, st, p.T, p.St, (const double2*)p.z, p.yeq,
                      p.Yko, p.kp, p.status);

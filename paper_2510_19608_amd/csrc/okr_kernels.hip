@@ -522,7 +522,8 @@ __global__ void k_from_vhat(int n, int S, const uint8_t* __restrict__ phase, con
 // mask within amb of the tie threshold) are rescanned mask by mask.
 // Ambiguous when a mask at the chosen level or above lies within amb of the
 // e_bar / band boundary, or a feasible mask at the chosen level lies within
-// amb of e_min + tie_tol.  With slist (SMICE as the key) it also lists mask 0
+// amb of e_min + tie_tol.  With tab the decision is final and the state's
+// structure is updated.  With slist (SMICE as the key) it also lists mask 0
 // and then every feasible mask of the chosen level, in any order (the listed
 // masks are a few hundred of 65,536 on the 1000-node workload; scoring them
 // from a dense list keeps every lane busy).
@@ -531,7 +532,8 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
                                                  const TileRec* __restrict__ tiles, SelParams sp,
                                                  const int* __restrict__ status, DevDecision* __restrict__ decs,
                                                  const int* __restrict__ gates, uint32_t* __restrict__ slist,
-                                                 int* __restrict__ scount) {
+                                                 int* __restrict__ scount, const int* __restrict__ tab, Topo T,
+                                                 State St) {
   // one slot per wave for each reduction (each its own array, so no
   // reduction's slots are written while another's are still being read)
   __shared__ int s_best[16], s_amb[16], s_amb2[16];
@@ -541,7 +543,11 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   __shared__ int cand[1024];
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
-  if (gates && gates[g] == 0) return;  // decided without the full enumeration
+  tab = lane_ptr(tab, lstride);
+  if (gates && gates[g] == 0) {  // decided without the full enumeration
+    if (tab && H.valid) update_state(H, tab, T, St, decs[g].mask);
+    return;
+  }
   slist = lane_ptr(slist, lstride);
   scount = lane_ptr(scount, lstride);
   fin = lane_ptr(fin, lstride);
@@ -550,6 +556,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   // nothing is reduced when the full network violates the band, the load
   // flow failed, or the segment's tables are inconsistent
   if (!H.valid || (*status & (16 | 32))) {
+    if (tab && H.valid) update_state(H, tab, T, St, 0u);
     if (threadIdx.x == 0) {
       DevDecision d;
       d.mask = 0; d.popcount = 0; d.e_loc = 0.0; d.e_min = 0.0; d.ambiguous = 0; d.found = 0;
@@ -664,6 +671,11 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
       d.smice_rise = 0.0;
     }
     *dec = d;
+    s_pick[0] = d.mask;
+  }
+  if (tab) {  // this decision is final
+    __syncthreads();
+    update_state(H, tab, T, St, s_pick[0]);
   }
   if (!slist) return;
   if (tid == 0) {
@@ -692,99 +704,6 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
 __global__ void k_sqrt_selftest(const double* __restrict__ x, double* __restrict__ y, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = sqrt_nr(x[i]);
-}
-
-// ------------------------------------------------------------ state update --
-// Apply the chosen mask to the cumulative state (Algorithm 1 state update):
-// aggregated currents move to the new super-nodes, kept slots and zone
-// targets take their candidate voltages (same arithmetic as the scoring).
-// Block 0 then updates the kept flags and super-nodes over Omega_g and clears
-// the node -> slot / zone-entry maps for the next segment.
-__global__ __launch_bounds__(64) void k_apply(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
-                                              size_t lstride, const int* __restrict__ tab,
-                                              Topo T, State St, const DevDecision* __restrict__ decs,
-                                              const double2* __restrict__ P, const TargetRec* __restrict__ srec,
-                                              const TargetRec* __restrict__ zrec, double2* __restrict__ Vcur,
-                                              double2* __restrict__ A) {
-  __shared__ double2 Bs[kMaxK * 3];
-  const int g = segs[blockIdx.z];
-  const SegHdr H = load_hdr_g(hdrs, g);
-  if (!H.valid) return;
-  tab = lane_ptr(tab, lstride);
-  P = lane_ptr(P, lstride);
-  srec = lane_ptr(srec, lstride);
-  zrec = lane_ptr(zrec, lstride);
-  const int n = T.n;
-  const int l = blockIdx.x;
-  const uint32_t m = *as_cint((const int*)&decs[g].mask);
-  const cint* chains = as_cint(tab + H.o_chain);
-  const cint* slots = as_cint(tab + H.o_slot);
-  if (threadIdx.x < 3) {  // phases are independent: one thread each
-    const int p = threadIdx.x;
-    const double2* Pl = P + (size_t)l * H.npairs * 3;
-    const TargetRec* srec_l = srec + (size_t)l * H.nslots * 3;
-    for (int c = 0; c < H.nchains; ++c) {
-      const cint* cr = chains + c * kChainInts;
-      const int outer = cr[C_OUTER];
-      double2 S = outer >= 0 ? Bs[outer * 3 + p] : make_double2(0.0, 0.0);
-      int sidx = 0;
-      // the current super-node's aggregated current, kept in a register
-      // while reduced slots add theirs (the same additions, in order)
-      size_t a = ((size_t)l * n + cr[C_HEAD]) * 3 + p;
-      double2 acc = A[a];
-      const int ns = cr[C_NSLOT], s0 = cr[C_SLOT0];
-      for (int r = 0; r < ns; ++r) {
-        const cint* sr = slots + (s0 + r) * kSlotInts;
-        const int node = sr[SL_NODE];
-        if ((m >> sr[SL_BIT]) & 1u) {
-          S = cadd(S, Pl[(sr[SL_PAIRBASE] + sidx) * 3 + p]);
-          const size_t b = ((size_t)l * n + node) * 3 + p;
-          acc = cadd(acc, A[b]);
-          A[b] = make_double2(0.0, 0.0);
-        } else {
-          if (sr[SL_PHASE] >> p & 1) Vcur[((size_t)l * n + node) * 3 + p] = cadd(srec_l[(s0 + r) * 3 + p].W, S);
-          sidx = r + 1;
-          A[a] = acc;
-          a = ((size_t)l * n + node) * 3 + p;
-          acc = A[a];
-        }
-      }
-      A[a] = acc;
-      Bs[c * 3 + p] = S;
-    }
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < H.nz; q += blockDim.x) {
-    const int* ze = tab + H.o_zent + q * 3;
-    const int node = ze[0], p = ze[1], c = ze[2];
-    Vcur[((size_t)l * n + node) * 3 + p] = cadd(zrec[(size_t)l * H.nz + q].W, Bs[c * 3 + p]);
-  }
-  if (blockIdx.x != 0) return;
-  __syncthreads();
-  if (threadIdx.x < H.nslots) {
-    const cint* sr = slots + threadIdx.x * kSlotInts;
-    if ((m >> sr[SL_BIT]) & 1u) St.kept[sr[SL_NODE]] = 0;
-    St.slot_of[sr[SL_NODE]] = -1;
-  }
-  for (int q = threadIdx.x; q < H.nz; q += blockDim.x) {
-    const int* ze = tab + H.o_zent + q * 3;
-    St.zent_of[ze[0] * 3 + ze[1]] = -1;
-  }
-  __syncthreads();
-  const int* rg = tab + H.o_range;
-  for (int q = threadIdx.x; q < H.nomega; q += blockDim.x) {
-    int r = 0;
-    while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
-    const int i = rg[3 * r] + (q - rg[3 * r + 2]);
-    // up through reduced nodes; a reduced node's recorded super (before or
-    // after this update) is an ancestor with only reduced nodes in between
-    int v = i;
-    while (!St.kept[v]) {
-      const int s = St.sup[v];
-      v = (s >= 0 && s != v) ? s : T.parent[v];
-    }
-    St.sup[i] = v;
-  }
 }
 
 // Reset of the search state at the start of a call (no memset nodes, so the

@@ -505,7 +505,7 @@ OKR_SEG_TERMS_INST(false, true, 1, true)
 // ---- terms of a short mask list ----
 
 // Clears the list's accumulators (the pattern table's are cleared by
-// k_build_struct).
+// the table build).
 __global__ void k_terms_init(const int* __restrict__ count, int cap, size_t lstride,
                              unsigned long long* __restrict__ acc) {
   count = lane_ptr(count, lstride);

@@ -341,7 +341,8 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
                                                        const uint32_t* __restrict__ slist,
                                                        const int* __restrict__ scount,
                                                        const double* __restrict__ smv, double tol,
-                                                       DevDecision* __restrict__ decs) {
+                                                       DevDecision* __restrict__ decs, const int* __restrict__ tab,
+                                                       Topo T, State St) {
   __shared__ double shd[16];
   __shared__ int shi[16];
   __shared__ unsigned shu[16];
@@ -349,7 +350,11 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid) return;
   DevDecision d = decs[g];
-  if (!d.found) return;
+  tab = lane_ptr(tab, lstride);
+  if (!d.found) {
+    update_state(H, tab, T, St, d.mask);
+    return;
+  }
   fin = lane_ptr(fin, lstride);
   tiles = lane_ptr(tiles, lstride);
   slist = lane_ptr(slist, lstride);
@@ -390,6 +395,7 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
     d.smice_rise = smv[at] - smv[0];
     decs[g] = d;
   }
+  update_state(H, tab, T, St, pick != 0xffffffffu ? pick : d.mask);
 }
 
 }  // namespace okr
