@@ -277,10 +277,10 @@ def greedy_section(seed, reps=3, cpu=True):
     shape: sub-feeders of 100-1000 nodes with the highest- and lowest-loaded
     of 168 hourly scenarios; the 168-hour robustness check of the 1000-node
     reduction; and the oracle's scoring of one iteration as the CPU baseline.
-    Roofline of the candidate-scoring kernel: 9 flops per present node-phase
-    and scenario per candidate (voltage magnitude, error, maxima; the
-    voltage-change products of moved nodes are not counted, so this is a lower
-    bound) against the FP64 vector peak."""
+    Rate of the candidate-scoring kernel: one addition and one maximum per
+    cluster left, scenario and candidate (what summing every cluster's error
+    cannot do without; the rescored clusters' arithmetic is not counted)
+    against the FP64 vector peak; the launches are bound by latency."""
     import numpy as np
     from paper_2510_19608_amd import Greedy
     from synth_feeders import extreme_scenarios, hourly_feeder
@@ -299,17 +299,16 @@ def greedy_section(seed, reps=3, cpu=True):
         G.close()
         ms = statistics.median(x["t_search_ms"] for x in runs)
         sms = r["t_score_ms"]
-        node_phases = int(sum(bin(int(v)).count("1") for v in f["phase"]))
-        flops = r["n_scored"] * 9.0 * node_phases * f["snapshots"]
+        flops = 2.0 * f["snapshots"] * sum(s["n_cand"] * (n - t) for t, s in enumerate(r["steps"]))
         achieved = flops / (sms * 1e-3) / 1e12 if sms > 0 else None
         out["sizes"][str(n)] = dict(
             moves=r["n_steps"], kept=r["n_kept"], reduction_pct=100.0 * (1 - r["n_kept"] / n), max_err=r["max_err"],
             search_ms=ms, per_iteration_us=1e3 * ms / max(r["n_steps"], 1), candidates_scored=r["n_scored"],
             candidates_per_s=r["n_scored"] / (ms * 1e-3),
             score_kernel_avg_us=1e3 * sms / max(r["n_score_launches"], 1),
-            roofline={"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
+            roofline={"bound": "latency", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                       "frac": achieved / FP64_VECTOR_PEAK_TFLOPS if achieved else None, "traffic": None,
-                      "kernel": "okr::k_greedy_score" if r["incremental"] else "okr::k_greedy_score_full"})
+                      "kernel": "okr::k_greedy_score"})
         if n == 1000:
             sup1000, fh1000 = r["super"], fh
     E = Greedy(fh1000)

@@ -9,13 +9,21 @@
 // r to super-node s therefore changes node y's voltage by
 //     dV_y = (Zroot(lca(y, r)) - Zroot(lca(y, s))) J,
 // which is nonzero exactly on the subtrees of w = lca(r, s)'s children
-// towards r and towards s.  Lowest common ancestors are O(1) lookups in a
-// sparse table over the Euler tour (built once per topology).  Every
-// iteration keeps each cluster's MICE, their total, block maxima over DFS
-// positions and the member lists; one block scores one candidate by
-// re-scoring only the clusters whose super-node lies in those two subtrees
-// and the merged cluster, and one block picks the move, applies it to the
-// voltages with the scoring's expression and rebuilds the cluster state.
+// towards r and towards s.
+// Nodes are labelled by their position in a depth-first order, so a subtree is
+// an interval of labels and the lowest common ancestor of u < v is the
+// smallest parent over (u, v]: one lookup in a sparse table.
+// A cluster enters only through the smallest and largest |V^| of its members
+// per phase and scenario: its largest member error against magnitude m is
+// max(hi - m, m - lo), the same number as the maximum over the members
+// (rounding is monotone and |a - b| symmetric), so no kernel walks members and
+// merging two clusters takes their extremes.  The super-nodes are kept as a
+// dense list in label order, with every label's rank in it: an interval of
+// labels is an interval of the list, and the work of a move shrinks with the
+// clusters that are left.
+// Every move is two launches: k_greedy_score scores all candidates (both
+// directions of the edge above one cluster together), k_greedy_apply settles
+// the move in every block alike and writes the next list, voltages and errors.
 // A search starts from the exact fixed-current solve (a level-synchronous
 // sweep), which also serves the evaluation of a given assignment.
 
@@ -47,7 +55,8 @@ __global__ void k_zroot(int, const int*, const int*, const int*, int, const doub
 struct GState {
   int iter;  // moves applied
   int done;  // no feasible candidate left
-  int s, r;  // the move chosen by the last pick
+  int s;     // the last move's super-node and the labels whose voltages it changed
+  int a0, a1, b0, b1;
 };
 
 struct GStep {  // layout of okr_greedy_step
@@ -58,202 +67,95 @@ struct GStep {  // layout of okr_greedy_step
 constexpr int kGreedyThreads = 256;
 constexpr int kGreedyPickThreads = 1024;
 constexpr int kGreedyMaxS = 64;      // scenarios of a search (moved currents staged in LDS)
-constexpr int kGreedyMaxN = 12288;   // nodes of a search (member counts in LDS)
-constexpr int kSmallCluster = 8;    // clusters up to this size are scored by one lane
-constexpr int kGreedyFullSN = 6144;  // S x n up to which every candidate scores every node
+constexpr int kGreedyMaxN = 12288;   // nodes of an incremental search
+constexpr int kGreedyFullSN = 6144;  // S x n up to which every candidate sums every cluster
 
-// O(1) lowest common ancestors: the Euler tour of the DFS (E = 2n - 1
-// entries), every node's first index in it, and a sparse table of the
-// shallowest node over power-of-two ranges of the tour (level k at st[k * E]).
+// Lowest common ancestors of labels (depth-first positions): the smallest
+// (parent, last position) over power-of-two runs of labels, level k at
+// st[k * n].  Every label in (u, v] lies below lca(u, v), and the child of it
+// that leads to v is the last of them whose parent it is.
 struct LcaTab {
-  const int* first;
-  const int* st;
-  const int* depth;
-  int E;
-  __device__ __forceinline__ int lca(int u, int v) const {
-    int a = first[u], b = first[v];
-    if (a > b) {
-      const int t = a;
-      a = b;
-      b = t;
-    }
-    const int k = 31 - __clz(b - a + 1);
-    const int x = st[(size_t)k * E + a], y = st[(size_t)k * E + b - (1 << k) + 1];
-    return depth[x] <= depth[y] ? x : y;
+  const unsigned long long* st;
+  int n;
+  __device__ __forceinline__ unsigned long long key(int lo, int hi) const {  // over (lo, hi], lo < hi
+    const int k = 31 - __clz(hi - lo);
+    const unsigned long long x = st[(size_t)k * n + lo + 1], y = st[(size_t)k * n + hi - (1 << k) + 1];
+    return x < y ? x : y;
   }
+  static __device__ __forceinline__ int parent_of(unsigned long long k) { return (int)(k >> 32); }
+  static __device__ __forceinline__ int child_of(unsigned long long k) { return (int)(0xffffffffu - (unsigned)k); }
+  __device__ __forceinline__ int lca(int u, int v) const { return u == v ? u : parent_of(key(min(u, v), max(u, v))); }
 };
 
-// The child of w whose subtree holds t (t strictly below w): children are
-// stored in increasing DFS position.
-__device__ __forceinline__ int child_toward(const int* ch_off, const int* ch, const int* pos, int w, int t) {
-  int lo = ch_off[w], hi = ch_off[w + 1] - 1;
-  const int q = pos[t];
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (pos[ch[mid]] <= q) lo = mid;
-    else hi = mid - 1;
-  }
-  return ch[lo];
+// A cluster of the list: its super-node, its topmost node, the super-node of
+// the cluster above it, and the phases of the two super-nodes (u's in bits
+// 0-2, b's in bits 8-10).
+struct GClus {
+  int u, top, b, ph;
+};
+
+// The candidate pair of the edge above a cluster: super-nodes a (below) and b
+// (above), w = lca(a, b), and the label intervals of the subtrees of w's
+// children towards a and towards b (the latter empty when b is w).
+struct GEdge {
+  int a, b, w, ja, jb;  // ja, jb: ranks of a and b
+  int a0, a1, b0, b1;
+  int ea, eb;  // ends of a's and b's own subtrees
+};
+
+// Rescored clusters of a candidate pair: their old errors, their new errors
+// and the largest one per direction (0: the cluster below moves up, 1: the one
+// above moves down).
+struct GPart {
+  double olds, n0, n1, e0, e1;
+};
+
+// Scoring results of one block of candidates.
+struct GBlk {
+  double mn, snd;          // smallest SMICE, and the smallest of the others
+  unsigned long long key;  // mn's candidate: id << 32 | 2 * rank + direction
+  unsigned long long cnt;  // candidates, feasible ones << 20, ones with an error within amb of e_bar << 40
+};
+
+// State of the search.  Arrays with two copies are written for the next
+// iteration while the current one is read (iteration parity).
+struct GreedyState {
+  GState* gs[2];
+  GClus* cl[2];       // [n] the list of clusters, by label of the super-node
+  int2* rank[2];      // [n] super-nodes below a label, and below the end of its subtree
+  double* mice[2];    // [S][n] every cluster's largest error, by rank
+  double* arr[2];     // [n] its maximum over scenarios
+  double* bmax[2];    // maxima of arr over runs of 64 ranks
+  double* bsum[2];    // sums of mice over runs of 64 ranks and all scenarios
+  double* ext;        // [S][n][6] by label: smallest and largest |V^| of the cluster's members, 3 phases each
+  GEdge* edge;        // [n] by rank
+  GPart* part;        // [n] by label of the cluster below the edge
+  double *sm, *em;    // [2n] SMICE and largest error, by rank and direction
+  GBlk* blk;          // [n]
+  int* sup;           // [n]
+  double2 *V, *I;     // [S][n][3] voltages (current at super-nodes) and aggregated currents
+};
+
+// Largest error of a cluster against magnitude m on one phase: the members'
+// largest |a - m| (the extremes are +inf and -inf where no member has the
+// phase, which never wins).
+__device__ __forceinline__ double ext_err(double e, double lo, double hi, double m) {
+  return fmax(e, fmax(hi - m, m - lo));
 }
 
-// Voltage change at node y of moving load current J (one scenario, 3 phases)
-// from r to s: (Zroot(lca(y, r)) - Zroot(lca(y, s))) J; `moved` is false when
-// both lca are the same node (no change).
+// Impedance change of an affected super-node: Zroot(a) - Zroot(b).
 struct MoveDelta {
   double2 dZ[9];
-  bool moved;
-  __device__ __forceinline__ void at(const LcaTab& T, const double2* Zr, int y, int r, int s) {
-    between(Zr, T.lca(y, r), T.lca(y, s));
-  }
-  // a = lca(y, r), b = lca(y, s), when already known
   __device__ __forceinline__ void between(const double2* Zr, int a, int b) {
-    moved = a != b;
-    if (moved) {
-      const double2* Za = Zr + (size_t)a * 9;
-      const double2* Zb = Zr + (size_t)b * 9;
+    const double2* Za = Zr + (size_t)a * 9;
+    const double2* Zb = Zr + (size_t)b * 9;
 #pragma unroll
-      for (int q = 0; q < 9; ++q) dZ[q] = csub(Za[q], Zb[q]);
-    }
+    for (int q = 0; q < 9; ++q) dZ[q] = csub(Za[q], Zb[q]);
   }
   __device__ __forceinline__ double2 dv(int p, const double2* J) const {
     return cadd(cadd(cmul(dZ[p * 3], J[0]), cmul(dZ[p * 3 + 1], J[1])), cmul(dZ[p * 3 + 2], J[2]));
   }
 };
-
-// Per-iteration cluster state (device): MICE of every cluster per scenario
-// (0 for nodes that are not super-nodes), their sum, the largest MICE over
-// scenarios by DFS position and its maxima over blocks of 64 positions, and
-// every cluster's members (CSR, any order: only maxima are taken over them).
-// The member counts are built in LDS: a search takes at most kGreedyMaxN
-// nodes.
-struct Clusters {
-  double* mice;   // [S][n]
-  double* arr;    // [n], by DFS position
-  double* bmax;   // [ceil(n / 64)]
-  int* moff;      // [n + 1]
-  int* mem;       // [n]
-  double* tot;    // [1]
-};
-
-// Largest error over scenarios' phases of member x against magnitudes mag
-// (3 per scenario): e_l = max_p ||V^_x| - mag_p|.
-__device__ __forceinline__ double member_err(const double* absV, int n, int x, int l, unsigned ph,
-                                             const double* mag) {
-  const size_t xb = ((size_t)l * n + x) * 3;
-  double e = 0.0;
-#pragma unroll
-  for (int p = 0; p < 3; ++p)
-    if (ph >> p & 1u) e = fmax(e, fabs(absV[xb + p] - mag[p]));
-  return e;
-}
-
-// Builds the cluster state of the current assignment and voltages (one
-// block; called with every thread).  Member counts and fill pointers live in
-// LDS (lcnt, n ints); every cluster's MICE is a wave-wide maximum over its
-// members (one wave per super-node, 64 members at a time), so large clusters
-// cost neither serial walks nor same-address atomics.
-__device__ void cluster_prep(int n, int S, const uint8_t* phase, const int* pre, const int* sup, const double2* V,
-                             const double* absV, const Clusters& C, int* lcnt, int* shi, double* shd) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int y = threadIdx.x; y < n; y += blockDim.x) lcnt[y] = 0;
-  __syncthreads();
-  for (int x = threadIdx.x; x < n; x += blockDim.x) atomicAdd(&lcnt[sup[x]], 1);
-  __syncthreads();
-  // member offsets: each thread scans a contiguous chunk, the chunk sums are
-  // scanned across the block
-  const int chunk = (n + blockDim.x - 1) / blockDim.x, c0 = threadIdx.x * chunk, c1 = min(n, c0 + chunk);
-  int loc = 0;
-  for (int y = c0; y < c1; ++y) loc += lcnt[y];
-  const int base = block_exclusive_scan(loc, shi);
-  for (int y = c0, acc = base; y < c1; ++y) {
-    const int c = lcnt[y];
-    C.moff[y] = acc;
-    lcnt[y] = acc;  // fill pointer
-    acc += c;
-  }
-  if (threadIdx.x == blockDim.x - 1) C.moff[n] = base + loc;
-  __syncthreads();
-  for (int x = threadIdx.x; x < n; x += blockDim.x) C.mem[atomicAdd(&lcnt[sup[x]], 1)] = x;
-  __syncthreads();
-  // MICE of every cluster (0 for nodes that are not super-nodes): a lane
-  // takes a cluster of at most kSmallCluster members, a wave the larger ones
-  for (int y0 = wv * 64; y0 < n; y0 += nw * 64) {
-    const int y = y0 + lane;
-    const bool is = y < n && sup[y] == y;
-    const int m0 = is ? C.moff[y] : 0, m1 = is ? C.moff[y + 1] : 0;
-    const bool big = is && m1 - m0 > kSmallCluster;
-    if (y < n && !big)
-      for (int l = 0; l < S; l += 2) {  // two scenarios per pass over the members
-        const int l1 = l + 1 < S ? l + 1 : l;
-        double mx0 = 0.0, mx1 = 0.0;
-        if (is) {
-          double mag0[3], mag1[3];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) {
-            mag0[p] = sqrt(cabs2(V[((size_t)l * n + y) * 3 + p]));
-            mag1[p] = sqrt(cabs2(V[((size_t)l1 * n + y) * 3 + p]));
-          }
-          for (int k = m0; k < m1; ++k) {
-            const int m = C.mem[k];
-            const unsigned ph = phase[m];
-            mx0 = fmax(mx0, member_err(absV, n, m, l, ph, mag0));
-            mx1 = fmax(mx1, member_err(absV, n, m, l1, ph, mag1));
-          }
-        }
-        C.mice[(size_t)l * n + y] = mx0;
-        if (l1 != l) C.mice[(size_t)l1 * n + y] = mx1;
-      }
-    unsigned long long mask = __ballot(big);
-    while (mask) {
-      const int bit = __ffsll((long long)mask) - 1;
-      mask &= mask - 1;
-      const int u = y0 + bit, k0 = __shfl(m0, bit, 64), k1 = __shfl(m1, bit, 64);
-      for (int l = 0; l < S; l += 2) {  // two scenarios per pass over the members
-        const int l1 = l + 1 < S ? l + 1 : l;
-        double mag0[3], mag1[3];
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          mag0[p] = sqrt(cabs2(V[((size_t)l * n + u) * 3 + p]));
-          mag1[p] = sqrt(cabs2(V[((size_t)l1 * n + u) * 3 + p]));
-        }
-        double mx0 = 0.0, mx1 = 0.0;
-        for (int k = k0 + lane; k < k1; k += 64) {
-          const int m = C.mem[k];
-          const unsigned ph = phase[m];
-          mx0 = fmax(mx0, member_err(absV, n, m, l, ph, mag0));
-          mx1 = fmax(mx1, member_err(absV, n, m, l1, ph, mag1));
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-          mx0 = fmax(mx0, __shfl_xor(mx0, o, 64));
-          mx1 = fmax(mx1, __shfl_xor(mx1, o, 64));
-        }
-        if (lane == 0) {
-          C.mice[(size_t)l * n + u] = mx0;
-          if (l1 != l) C.mice[(size_t)l1 * n + u] = mx1;
-        }
-      }
-    }
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < n; q += blockDim.x) {
-    double m = 0.0;
-    for (int l = 0; l < S; ++l) m = fmax(m, C.mice[(size_t)l * n + pre[q]]);
-    C.arr[q] = m;
-  }
-  double t = 0.0;
-  for (int q = threadIdx.x; q < S * n; q += blockDim.x) t += C.mice[q];
-  t = block_reduce(t, [](double a, double b) { return a + b; }, shd);
-  __syncthreads();
-  // block maxima: a wave per block of 64 positions, a position per lane
-  for (int k = wv; k < (n + 63) / 64; k += nw) {
-    const int q = k * 64 + lane;
-    double m = q < n ? C.arr[q] : 0.0;
-    for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if (lane == 0) C.bmax[k] = m;
-  }
-  if (threadIdx.x == 0) *C.tot = t;
-  __syncthreads();
-}
 
 // Fixed-current solve of one scenario on the radial network: branch currents
 // by subtree sums of the load currents I (deepest level first), then
@@ -305,11 +207,7 @@ __global__ void k_greedy_init(int n, int S, const double2* __restrict__ A, doubl
   const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < (size_t)S * n * 3) Iagg[t] = A[t];
   if (t < (size_t)n) sup[t] = (int)t;
-  if (t == 0) {
-    gs->iter = 0;
-    gs->done = 0;
-    gs->s = gs->r = -1;
-  }
+  if (t == 0) *gs = GState{0, 0, 0, 0, n, 0, 0};  // (every candidate is still to be scored)
 }
 
 // Fixed-current solve of every scenario (one block each) from Iagg.
@@ -323,612 +221,521 @@ __global__ __launch_bounds__(kGreedyThreads) void k_greedy_sweep(
   sweep_block(n, parent, phase, lvl_off, lvl_nodes, nlev, ch_off, ch, z, v0, Iagg + base, Ib + base, V + base);
 }
 
-// Cluster state of the search's starting point (one block).
-__global__ __launch_bounds__(kGreedyPickThreads) void k_greedy_prep(int n, int S, const uint8_t* __restrict__ phase,
-                                                                    const int* __restrict__ pre,
-                                                                    const int* __restrict__ sup,
-                                                                    const double2* __restrict__ V,
-                                                                    const double* __restrict__ absV, Clusters C) {
-  extern __shared__ __align__(16) unsigned char g_lds[];
-  __shared__ int shi[kGreedyPickThreads];
-  __shared__ double shd[kGreedyPickThreads / 64];
-  cluster_prep(n, S, phase, pre, sup, V, absV, C, (int*)g_lds, shi, shd);
+// Maxima and sums over a wave's run of 64 ranks (summed in a fixed tree).
+__device__ __forceinline__ void run_totals(double mx, double sum, double* bmax, double* bsum) {
+  for (int o = 32; o > 0; o >>= 1) {
+    mx = fmax(mx, __shfl_xor(mx, o, 64));
+    sum += __shfl_xor(sum, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    *bmax = mx;
+    *bsum = sum;
+  }
 }
 
-// Score of one candidate per block (grid: 2n blocks, id = blockIdx.x):
-// SMICE (+inf when infeasible) and the largest error (-1 when the id is not a
-// candidate in this state).  Only the clusters the move can change are
-// scored again: with w = lca(r, s), voltages change exactly on the subtrees
-// of w's children towards r and towards s (DFS intervals I_r, I_s), so the
-// clusters whose super-node lies there (which, other than r's and s's, lie
-// wholly inside them) and the merged cluster s + r; every other cluster keeps
-// its MICE.  SMICE = (total - old MICE of the changed clusters) + their new
-// MICE; the largest error is the maximum of the new MICE and of the other
-// clusters' (block maxima over DFS positions outside the intervals and w).
-__global__ __launch_bounds__(kGreedyThreads) void k_greedy_score(
-    int n, int S, const int* __restrict__ parent, const uint8_t* __restrict__ phase, const int* __restrict__ pos,
-    const int* __restrict__ size, const int* __restrict__ pre, const int* __restrict__ ch_off,
-    const int* __restrict__ ch, const int* __restrict__ sup, LcaTab T, const double2* __restrict__ Zr,
-    const double2* __restrict__ Iagg, const double2* __restrict__ Vcur, const double* __restrict__ absV,
-    double e_bar, const GState* __restrict__ gs, Clusters C, double* __restrict__ sm, double* __restrict__ em) {
-  __shared__ double2 J[kGreedyMaxS * 3];
-  __shared__ double magS[kGreedyMaxS * 3];
-  __shared__ unsigned long long newS[kGreedyMaxS];
-  __shared__ double red[kGreedyThreads / 64];
-  if (gs->done) return;
-  const int cand = blockIdx.x, x = cand >> 1, dir = cand & 1, tid = threadIdx.x;
-  int r = -1, s = -1;
-  if (x > 0) {
-    const int a = sup[x], b = sup[parent[x]];
-    if (a != b) {
-      r = dir ? b : a;
-      s = dir ? a : b;
-      if (r == 0 || (phase[r] & ~phase[s])) r = -1;
-    }
-  }
-  if (r < 0) {  // not a candidate (uniform over the block)
-    if (tid == 0) {
-      sm[cand] = INFINITY;
-      em[cand] = -1.0;
-    }
-    return;
-  }
-  const int w = T.lca(r, s);
-  int a1 = 0, b1 = 0, a2 = 0, b2 = 0;  // I_r = [a1, b1), I_s = [a2, b2)
-  if (r != w) {
-    const int c = child_toward(ch_off, ch, pos, w, r);
-    a1 = pos[c];
-    b1 = a1 + size[c];
-  }
-  if (s != w) {
-    const int c = child_toward(ch_off, ch, pos, w, s);
-    a2 = pos[c];
-    b2 = a2 + size[c];
-  }
-  const int qw = pos[w];
-  MoveDelta msd;
-  msd.between(Zr, w, s);  // lca(s, r) = w, lca(s, s) = s
-  for (int q = tid; q < S * 3; q += kGreedyThreads) {
-    J[q] = Iagg[((size_t)(q / 3) * n + r) * 3 + q % 3];
-  }
-  for (int l = tid; l < S; l += kGreedyThreads) newS[l] = 0ull;
-  __syncthreads();
-  for (int l = tid; l < S; l += kGreedyThreads) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {  // unrolled: msd.dZ stays in registers
-      double2 v = Vcur[((size_t)l * n + s) * 3 + p];
-      if (msd.moved) v = cadd(v, msd.dv(p, J + l * 3));
-      magS[l * 3 + p] = sqrt(cabs2(v));
-    }
-  }
-  __syncthreads();
-  double olds = 0.0, news = 0.0, emx = 0.0;
-  // clusters whose super-node lies in I_r or I_s (other than r and s), the
-  // two intervals walked as one range: each wave takes 64 positions at a
-  // time; a lane scores the cluster of its position when it has at most
-  // kSmallCluster members, and the wave scores the larger ones together (64
-  // members at a time)
-  {
-    const int lane = tid & 63, wv = tid >> 6, L1 = b1 - a1, L = L1 + (b2 - a2);
-    for (int c0 = wv * 64; c0 < L; c0 += kGreedyThreads) {
-      const int qi = c0 + lane;  // index into I_r then I_s
-      int u = -1, m0 = 0, m1 = 0;
-      bool is = false;
-      if (qi < L) {
-        u = pre[qi < L1 ? a1 + qi : a2 + (qi - L1)];
-        is = sup[u] == u && u != r && u != s;
-        if (is) {
-          m0 = C.moff[u];
-          m1 = C.moff[u + 1];
-        }
-      }
-      const bool big = is && m1 - m0 > kSmallCluster;
-      // in I_r, lca(u, s) = w; in I_s, lca(u, r) = w: one lca to look up
-      const bool inR = qi < L1;
-      if (is && !big) {
-        MoveDelta md;
-        const int a = T.lca(u, inR ? r : s);
-        md.between(Zr, inR ? a : w, inR ? w : a);
-        for (int l = 0; l < S; l += 2) {  // two scenarios per pass over the members
-          const int l1 = l + 1 < S ? l + 1 : l;
-          double mag0[3], mag1[3];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) {
-            double2 v0 = Vcur[((size_t)l * n + u) * 3 + p], v1 = Vcur[((size_t)l1 * n + u) * 3 + p];
-            if (md.moved) {
-              v0 = cadd(v0, md.dv(p, J + l * 3));
-              v1 = cadd(v1, md.dv(p, J + l1 * 3));
-            }
-            mag0[p] = sqrt(cabs2(v0));
-            mag1[p] = sqrt(cabs2(v1));
-          }
-          double mx0 = 0.0, mx1 = 0.0;
-          for (int k = m0; k < m1; ++k) {
-            const int m = C.mem[k];
-            const unsigned ph = phase[m];
-            mx0 = fmax(mx0, member_err(absV, n, m, l, ph, mag0));
-            mx1 = fmax(mx1, member_err(absV, n, m, l1, ph, mag1));
-          }
-          olds += C.mice[(size_t)l * n + u];
-          news += mx0;
-          emx = fmax(emx, mx0);
-          if (l1 != l) {
-            olds += C.mice[(size_t)l1 * n + u];
-            news += mx1;
-            emx = fmax(emx, mx1);
-          }
-        }
-      }
-      unsigned long long mask = __ballot(big);
-      while (mask) {
-        const int bit = __ffsll((long long)mask) - 1;
-        mask &= mask - 1;
-        const int uu = __shfl(u, bit, 64), k0 = __shfl(m0, bit, 64), k1 = __shfl(m1, bit, 64);
-        const bool uinR = __shfl(qi, bit, 64) < L1;
-        MoveDelta md;
-        const int a = T.lca(uu, uinR ? r : s);
-        md.between(Zr, uinR ? a : w, uinR ? w : a);
-        for (int l = 0; l < S; l += 2) {  // two scenarios per pass over the members
-          const int l1 = l + 1 < S ? l + 1 : l;
-          double mag0[3], mag1[3];
-#pragma unroll
-          for (int p = 0; p < 3; ++p) {
-            double2 v0 = Vcur[((size_t)l * n + uu) * 3 + p], v1 = Vcur[((size_t)l1 * n + uu) * 3 + p];
-            if (md.moved) {
-              v0 = cadd(v0, md.dv(p, J + l * 3));
-              v1 = cadd(v1, md.dv(p, J + l1 * 3));
-            }
-            mag0[p] = sqrt(cabs2(v0));
-            mag1[p] = sqrt(cabs2(v1));
-          }
-          double mx0 = 0.0, mx1 = 0.0;
-          for (int k = k0 + lane; k < k1; k += 64) {
-            const int m = C.mem[k];
-            const unsigned ph = phase[m];
-            mx0 = fmax(mx0, member_err(absV, n, m, l, ph, mag0));
-            mx1 = fmax(mx1, member_err(absV, n, m, l1, ph, mag1));
-          }
-          for (int o = 32; o > 0; o >>= 1) {
-            mx0 = fmax(mx0, __shfl_xor(mx0, o, 64));
-            mx1 = fmax(mx1, __shfl_xor(mx1, o, 64));
-          }
-          if (lane == 0) {
-            olds += C.mice[(size_t)l * n + uu];
-            news += mx0;
-            emx = fmax(emx, mx0);
-            if (l1 != l) {
-              olds += C.mice[(size_t)l1 * n + uu];
-              news += mx1;
-              emx = fmax(emx, mx1);
-            }
-          }
-        }
-      }
-    }
-  }
-  // the merged cluster: r's members, and s's own when s's voltage moves
-  for (int pass = 0; pass < 2; ++pass) {
-    const int y = pass ? s : r;
-    if (pass && !msd.moved) break;
-    for (int k = C.moff[y] + tid; k < C.moff[y + 1]; k += kGreedyThreads) {
-      const int m = C.mem[k];
-      const unsigned ph = phase[m];
-      for (int l = 0; l < S; ++l)
-        atomicMax(&newS[l], (unsigned long long)__double_as_longlong(member_err(absV, n, m, l, ph, magS + l * 3)));
-    }
-  }
-  // every other cluster keeps its MICE: largest over positions outside
-  // I_r, I_s and w's
-  double umax = 0.0;
-  const int nb = (n + 63) / 64;
-  for (int k = tid; k < nb; k += kGreedyThreads) {
-    const int lo = k * 64, hi = min(n, lo + 64);
-    const bool touch = (lo <= qw && qw < hi) || (lo < b1 && a1 < hi) || (lo < b2 && a2 < hi);
-    if (!touch) umax = fmax(umax, C.bmax[k]);
-  }
-  // a touched block holds an end of I_r or I_s or w's position, or lies
-  // wholly inside I_r or I_s (nothing to add): the five blocks that hold
-  // those positions are read by one wave each, a position per lane (a block
-  // named twice gives the same maximum)
-  for (int j = tid >> 6; j < 5; j += kGreedyThreads / 64) {
-    const int k = j == 0   ? qw >> 6
-                  : j == 1 ? (a1 < b1 ? a1 >> 6 : -1)
-                  : j == 2 ? (a1 < b1 ? (b1 - 1) >> 6 : -1)
-                  : j == 3 ? (a2 < b2 ? a2 >> 6 : -1)
-                           : (a2 < b2 ? (b2 - 1) >> 6 : -1);
-    const int q = k * 64 + (tid & 63);
-    if (k >= 0 && q < n && q != qw && !(a1 <= q && q < b1) && !(a2 <= q && q < b2)) umax = fmax(umax, C.arr[q]);
-  }
-  __syncthreads();
-  olds = block_reduce(olds, [](double a, double b) { return a + b; }, red);
-  news = block_reduce(news, [](double a, double b) { return a + b; }, red);
-  emx = block_reduce(fmax(emx, umax), [](double a, double b) { return fmax(a, b); }, red);
-  if (tid == 0) {
+// The search's starting point: every node a cluster (one thread per node).
+__global__ __launch_bounds__(kGreedyThreads) void k_greedy_prep(int n, int S, const int* __restrict__ parent,
+                                                                const int* __restrict__ end,
+                                                                const uint8_t* __restrict__ phase,
+                                                                const double* __restrict__ absV, GreedyState G) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < n) G.rank[0][t] = make_int2(t, end[t]);
+  double mx = 0.0, sum = 0.0;
+  if (t < n) {
+    const int b = t > 0 ? parent[t] : 0;
+    const unsigned ph = phase[t];
+    G.cl[0][t] = GClus{t, t, b, (int)(ph | (unsigned)phase[b] << 8)};
     for (int l = 0; l < S; ++l) {
-      double v = __longlong_as_double((long long)newS[l]);
-      if (!msd.moved) v = fmax(v, C.mice[(size_t)l * n + s]);
-      olds += C.mice[(size_t)l * n + s] + C.mice[(size_t)l * n + r];
-      news += v;
-      emx = fmax(emx, v);
-    }
-    em[cand] = emx;
-    sm[cand] = emx <= e_bar ? (*C.tot - olds) + news : INFINITY;
-  }
-}
-
-// The iteration's move (one block of 1024): the smallest SMICE among
-// feasible candidates, ties within tie_tol to the lowest id; the step is
-// recorded, r's current joins s's, r's cluster is reassigned, every node's
-// voltage takes the move's change (the expression the scoring evaluated),
-// and the cluster state is rebuilt.  With no feasible candidate the search
-// is marked done.
-__global__ __launch_bounds__(kGreedyPickThreads) void k_greedy_pick_apply(
-    int n, int S, const int* __restrict__ parent, const uint8_t* __restrict__ phase, const int* __restrict__ pre,
-    const int* __restrict__ pos, const int* __restrict__ size, const int* __restrict__ ch_off,
-    const int* __restrict__ ch, LcaTab T, const double2* __restrict__ Zr, const double* __restrict__ absV, const double* __restrict__ sm,
-    const double* __restrict__ em, double e_bar, double tie, double amb, GState* __restrict__ gs,
-    GStep* __restrict__ steps, int* __restrict__ sup, double2* __restrict__ Iagg, double2* __restrict__ V,
-    Clusters C) {
-  extern __shared__ __align__(16) unsigned char g_lds[];
-  __shared__ double shd[kGreedyPickThreads / 64];
-  __shared__ int shi[kGreedyPickThreads];
-  __shared__ double2 J[kGreedyMaxS * 3];
-  if (gs->done) return;
-  const int tid = threadIdx.x, ncand = 2 * n;
-  double mn = INFINITY;
-  int nact = 0, nfeas = 0;
-  for (int c = tid; c < ncand; c += kGreedyPickThreads) {
-    mn = fmin(mn, sm[c]);
-    nact += em[c] >= 0.0;
-    nfeas += sm[c] < INFINITY;
-  }
-  mn = block_reduce(mn, [](double a, double b) { return fmin(a, b); }, shd);
-  nact = block_reduce(nact, [](int a, int b) { return a + b; }, shi);
-  nfeas = block_reduce(nfeas, [](int a, int b) { return a + b; }, shi);
-  if (!(mn < INFINITY)) {
-    if (tid == 0) gs->done = 1;
-    return;
-  }
-  const double thr = mn + tie;
-  int win = 0x7fffffff, fl = 0;
-  for (int c = tid; c < ncand; c += kGreedyPickThreads) {
-    const double v = sm[c];
-    if (v <= thr) win = min(win, c);
-    if (v < INFINITY && fabs(v - thr) <= amb) fl = 1;
-    if (em[c] >= 0.0 && fabs(em[c] - e_bar) <= amb) fl = 1;
-  }
-  win = block_reduce(win, [](int a, int b) { return min(a, b); }, shi);
-  fl = block_reduce(fl, [](int a, int b) { return max(a, b); }, shi);
-  const int wx = win >> 1, wa = sup[wx], wb = sup[parent[wx]];
-  const int r = (win & 1) ? wb : wa, s = (win & 1) ? wa : wb;
-  for (int q = tid; q < S * 3; q += kGreedyPickThreads) J[q] = Iagg[((size_t)(q / 3) * n + r) * 3 + q % 3];
-  __syncthreads();  // sup and Iagg read by every thread before they change
-  if (tid == 0) {
-    GStep st;
-    st.cand = win;
-    st.s = s;
-    st.r = r;
-    st.ambiguous = fl;
-    st.n_cand = nact;
-    st.n_feasible = nfeas;
-    st.smice = sm[win];
-    st.emax = em[win];
-    steps[gs->iter] = st;
-    gs->s = s;
-    gs->r = r;
-    gs->iter += 1;
-  }
-  for (int q = tid; q < S * 3; q += kGreedyPickThreads) {
-    const size_t lr = ((size_t)(q / 3) * n + r) * 3 + q % 3, ls = ((size_t)(q / 3) * n + s) * 3 + q % 3;
-    Iagg[ls] = cadd(Iagg[ls], J[q]);
-    Iagg[lr] = make_double2(0.0, 0.0);
-  }
-  for (int u = tid; u < n; u += kGreedyPickThreads)
-    if (sup[u] == r) sup[u] = s;
-  // only the subtrees of w = lca(r, s)'s children towards r and s (DFS
-  // intervals I_r, I_s) change; in I_r, lca(x, s) = w, in I_s lca(x, r) = w
-  const int w = T.lca(r, s);
-  int a1 = 0, b1 = 0, a2 = 0, b2 = 0;
-  if (r != w) {
-    const int c = child_toward(ch_off, ch, pos, w, r);
-    a1 = pos[c];
-    b1 = a1 + size[c];
-  }
-  if (s != w) {
-    const int c = child_toward(ch_off, ch, pos, w, s);
-    a2 = pos[c];
-    b2 = a2 + size[c];
-  }
-  for (int xn = tid; xn < n; xn += kGreedyPickThreads) {
-    const int q = pos[xn];
-    const bool inR = a1 <= q && q < b1;
-    if (!inR && !(a2 <= q && q < b2)) continue;
-    MoveDelta md;
-    const int a = T.lca(xn, inR ? r : s);
-    md.between(Zr, inR ? a : w, inR ? w : a);
-    for (int l = 0; l < S; ++l) {
-      const size_t vb = ((size_t)l * n + xn) * 3;
-#pragma unroll
-      for (int p = 0; p < 3; ++p) V[vb + p] = cadd(V[vb + p], md.dv(p, J + l * 3));
-    }
-  }
-  __syncthreads();
-  cluster_prep(n, S, phase, pre, sup, V, absV, C, (int*)g_lds, shi, shd);
-}
-
-// ---- full-scoring form --------------------------------------------------
-
-// Every node's largest error per scenario against its super-node's voltage
-// in the current state (e0[l][x]); the full-form scoring reads it for nodes
-// whose super-node's voltage a move leaves unchanged.
-__device__ __forceinline__ void node_errors(int n, int S, const uint8_t* phase, const int* sup, const double2* V,
-                                            const double* absV, double* e0, int t0, int dt) {
-  for (int t = t0; t < n * S; t += dt) {
-    const int x = t % n, l = t / n;
-    const unsigned ph = phase[x];
-    const size_t vb = ((size_t)l * n + sup[x]) * 3, xb = ((size_t)l * n + x) * 3;
-    double ex = 0.0;
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      if (ph >> p & 1u) ex = fmax(ex, fabs(absV[xb + p] - sqrt(cabs2(V[vb + p]))));
-    e0[t] = ex;
-  }
-}
-
-__global__ __launch_bounds__(kGreedyThreads) void k_greedy_e0(int n, int S, const uint8_t* __restrict__ phase,
-                                                               const int* __restrict__ sup,
-                                                               const double2* __restrict__ V,
-                                                               const double* __restrict__ absV,
-                                                               double* __restrict__ e0) {
-  node_errors(n, S, phase, sup, V, absV, e0, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
-}
-
-struct PathRec {
-  int node, lo, hi;  // an ancestor and the DFS position range of its subtree
-};
-
-// Depth of lca(y, t) where path[d] is t's ancestor at depth d (d <= dmax) and
-// q is y's DFS position: the deepest d whose subtree range holds q.
-__device__ __forceinline__ int lca_depth(const PathRec* path, int dmax, int q) {
-  int lo = 0, hi = dmax;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (path[mid].lo <= q && q < path[mid].hi) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
-
-// Root paths of r and s in LDS: pr[d] / ps[d] = the ancestor at depth d and
-// its DFS position range (every depth up to the node's own has one).
-__device__ __forceinline__ void load_paths(int n, const int* pos, const int* size, const int* depth, int r, int s,
-                                           PathRec* pr, PathRec* ps) {
-  const int qr = pos[r], qs = pos[s];
-  for (int u = threadIdx.x; u < n; u += blockDim.x) {
-    const int lo = pos[u], hi = lo + size[u];
-    if (lo <= qr && qr < hi) pr[depth[u]] = PathRec{u, lo, hi};
-    if (lo <= qs && qs < hi) ps[depth[u]] = PathRec{u, lo, hi};
-  }
-}
-
-// DFS intervals of the subtrees of w = lca(r, s)'s children towards r and
-// towards s (empty when r or s is w itself), from the staged root paths:
-// only nodes in them can change voltage when r's current moves to s.
-struct MoveIntervals {
-  int a1, b1, a2, b2;
-  __device__ __forceinline__ void from(const PathRec* pr, int dr, const PathRec* ps, int ds, int qs) {
-    const int dw = lca_depth(pr, min(dr, ds), qs);
-    a1 = b1 = a2 = b2 = 0;
-    if (dr > dw) {
-      a1 = pr[dw + 1].lo;
-      b1 = pr[dw + 1].hi;
-    }
-    if (ds > dw) {
-      a2 = ps[dw + 1].lo;
-      b2 = ps[dw + 1].hi;
-    }
-  }
-  __device__ __forceinline__ bool holds(int q) const { return (a1 <= q && q < b1) || (a2 <= q && q < b2); }
-};
-
-// MoveDelta with the lowest common ancestors found in the root paths of r
-// and s staged in LDS (binary search by DFS position; the full-scoring form).
-struct PathDelta {
-  double2 dZ[9];
-  bool moved;
-  __device__ __forceinline__ void at(const PathRec* pr, int dr, const PathRec* ps, int ds, const double2* Zr, int qy,
-                                     int dy) {
-    const int da = lca_depth(pr, min(dy, dr), qy), db = lca_depth(ps, min(dy, ds), qy);
-    moved = da != db;
-    if (moved) {
-      const double2* Za = Zr + (size_t)pr[da].node * 9;
-      const double2* Zb = Zr + (size_t)ps[db].node * 9;
-#pragma unroll
-      for (int q = 0; q < 9; ++q) dZ[q] = csub(Za[q], Zb[q]);
-    }
-  }
-  __device__ __forceinline__ double2 dv(int p, const double2* J) const {
-    return cadd(cadd(cmul(dZ[p * 3], J[0]), cmul(dZ[p * 3 + 1], J[1])), cmul(dZ[p * 3 + 2], J[2]));
-  }
-};
-
-// Full-scoring form (every node of every candidate; for S * n up to
-// kGreedyFullSN): one candidate per block (grid: 2n blocks, id =
-// blockIdx.x), SMICE (+inf when infeasible) and the largest error (-1 when
-// the id is not a candidate).  Dynamic LDS: S * n cluster maxima (uint64 bit
-// patterns), then the root paths of r and s.
-__global__ __launch_bounds__(kGreedyThreads) void k_greedy_score_full(
-    int n, int S, const int* __restrict__ parent, const uint8_t* __restrict__ phase, const int* __restrict__ pos,
-    const int* __restrict__ size, const int* __restrict__ depth, const int* __restrict__ sup,
-    const double2* __restrict__ Zr, const double2* __restrict__ Iagg, const double2* __restrict__ Vcur,
-    const double* __restrict__ absV, const double* __restrict__ e0, double e_bar, const GState* __restrict__ gs,
-    double* __restrict__ sm, double* __restrict__ em) {
-  extern __shared__ __align__(16) unsigned char g_lds[];
-  __shared__ double2 J[kGreedyMaxS * 3];
-  __shared__ double red[kGreedyThreads / 64];
-  if (gs->done) return;
-  const int cand = blockIdx.x, x = cand >> 1, dir = cand & 1, tid = threadIdx.x;
-  int r = -1, s = -1;
-  if (x > 0) {
-    const int a = sup[x], b = sup[parent[x]];
-    if (a != b) {
-      r = dir ? b : a;
-      s = dir ? a : b;
-      if (r == 0 || (phase[r] & ~phase[s])) r = -1;
-    }
-  }
-  if (r < 0) {  // not a candidate (uniform over the block)
-    if (tid == 0) {
-      sm[cand] = INFINITY;
-      em[cand] = -1.0;
-    }
-    return;
-  }
-  unsigned long long* mice = (unsigned long long*)g_lds;
-  PathRec* pr = (PathRec*)(mice + (size_t)S * n);
-  const int dr = depth[r], ds = depth[s];
-  PathRec* ps = pr + dr + 1;
-  for (int q = tid; q < S * n; q += kGreedyThreads) mice[q] = 0ull;
-  load_paths(n, pos, size, depth, r, s, pr, ps);
-  for (int q = tid; q < S * 3; q += kGreedyThreads) J[q] = Iagg[((size_t)(q / 3) * n + r) * 3 + q % 3];
-  __syncthreads();
-  MoveIntervals mi;
-  mi.from(pr, dr, ps, ds, pos[s]);
-  double emax = 0.0;
-  for (int xn = tid; xn < n; xn += kGreedyThreads) {
-    const int y0 = sup[xn], y = y0 == r ? s : y0;
-    const int qy = pos[y];
-    if (y0 != r && !mi.holds(qy)) {  // same super-node, same voltage: the stored errors
-      for (int l = 0; l < S; ++l) {
-        const double ex = e0[(size_t)l * n + xn];
-        atomicMax(&mice[(size_t)l * n + y], (unsigned long long)__double_as_longlong(ex));
-        emax = fmax(emax, ex);
-      }
-      continue;
-    }
-    PathDelta md;
-    if (mi.holds(qy)) md.at(pr, dr, ps, ds, Zr, qy, depth[y]);
-    else md.moved = false;
-    const unsigned ph = phase[xn];
-    for (int l = 0; l < S; ++l) {
-      const size_t vb = ((size_t)l * n + y) * 3, xb = ((size_t)l * n + xn) * 3;
-      double ex = 0.0;
+      const size_t at = (size_t)l * n + t;
+      double e = 0.0;
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
-        if (!(ph >> p & 1u)) continue;
-        double2 v = Vcur[vb + p];
-        if (md.moved) v = cadd(v, md.dv(p, J + l * 3));
-        ex = fmax(ex, fabs(absV[xb + p] - sqrt(cabs2(v))));
+        const bool on = ph >> p & 1u;
+        const double a = absV[at * 3 + p], lo = on ? a : INFINITY, hi = on ? a : -INFINITY;
+        G.ext[at * 6 + p] = lo;
+        G.ext[at * 6 + 3 + p] = hi;
+        e = ext_err(e, lo, hi, sqrt(cabs2(G.V[at * 3 + p])));
       }
-      atomicMax(&mice[(size_t)l * n + y], (unsigned long long)__double_as_longlong(ex));
-      emax = fmax(emax, ex);
+      G.mice[0][at] = e;
+      mx = fmax(mx, e);
+      sum += e;
+    }
+    G.arr[0][t] = mx;
+  }
+  if (t - (int)(threadIdx.x & 63) < n) run_totals(mx, sum, G.bmax[0] + (t >> 6), G.bsum[0] + (t >> 6));
+}
+
+// Scores of every candidate: SMICE (+inf when infeasible) and the largest error
+// (-1 when the direction is not a candidate), by rank of the cluster below the
+// edge and direction.  With w = lca(a, b), voltages change exactly on the
+// subtrees of w's children towards a and b, so only the clusters whose
+// super-node lies there and the merged cluster (a's or b's) have a new error;
+// their sums stay as they are until a move reaches those subtrees, a or b, and
+// only then are they formed again.  In a's (b's) own subtree the voltage change
+// is the same everywhere and stands in LDS for up to kGreedyDv scenarios.
+// FULL: a block of 4 waves per edge adds every other cluster's present error.
+// Otherwise SMICE = (total - old errors of the changed clusters) + their new
+// ones, and the largest error takes the unchanged clusters from the maxima of
+// runs of 64 ranks and from the positions of the runs that hold an end of an
+// interval, a or b; a block of 8 waves takes 8 edges, one per wave, and waves
+// share those with more than kGreedyWaveL clusters to score again.  Edges near
+// the root have the long intervals and neighbouring ranks: a block's 8 edges
+// lie a grid's width apart, which also leaves one edge per block when few are
+// left.
+// Bound by latency: eight dependent loads, the rounds over the longest interval
+// and instruction fetch, so the rescoring stands in the code once.  Per launch,
+// 2 scenarios: 5591 nodes 168 us as one block per candidate that walked nodes
+// and members; 33 with cluster extremes, the list and both directions of an
+// edge together; 20 (28 at the first moves, 12 at the last) with the sums that
+// stand and the common voltage changes.  1000 nodes, FULL: 22, 11, 9.5.
+// 4 edges per block 22 us, 16 24; one wave alone up to 32, 128 or 256 clusters
+// within 4%.
+constexpr int kGreedyEdges = 8;   // edges per block (incremental form)
+constexpr int kGreedyWaveL = 64;  // clusters that one wave scores alone
+constexpr int kGreedyDv = 8;       // scenarios whose common voltage changes are kept in LDS
+
+template <bool FULL>
+__global__ __launch_bounds__(FULL ? kGreedyThreads : kGreedyEdges * 64) void k_greedy_score(
+    int n, int S, int cur, LcaTab T, const int* __restrict__ end, const int* __restrict__ label_id,
+    const double2* __restrict__ Zr, double e_bar, double amb, GreedyState G) {
+  constexpr int NW = FULL ? kGreedyThreads / 64 : kGreedyEdges, NE = FULL ? 1 : kGreedyEdges;
+  __shared__ GEdge s_edge[NE];
+  __shared__ int4 s_rank[NE];
+  __shared__ int s_todo[NE];
+  __shared__ GPart s_part[NE][NW];
+  __shared__ double2 s_dv[NE][2][kGreedyDv][2][3];  // side, scenario, direction, phase
+  __shared__ double s_out[NW], s_um[NW];
+  __shared__ double s_v[2 * NE];
+  __shared__ unsigned long long s_key[2 * NE], s_cnt[2 * NE];
+  const GClus* __restrict__ cl = G.cl[cur];
+  const double* __restrict__ mice = G.mice[cur];
+  const double* __restrict__ ext = G.ext;
+  const double2* __restrict__ V = G.V;
+  const double2* __restrict__ I = G.I;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int me = FULL ? 0 : wv, j = 1 + me * (int)gridDim.x + (int)blockIdx.x;
+  const GState st = *G.gs[cur];
+  const GClus c = cl[j < n ? j : 0];
+  const int m = n - st.iter;
+  if (st.done || (int)blockIdx.x >= m - 1) return;
+  GEdge E{};
+  int4 R = make_int4(0, 0, 0, 0);  // the intervals' ranks
+  bool d0 = false, d1 = false;
+  unsigned id = 0;
+  int todo = 0;  // 1: this wave scores the edge alone, 2: every wave, 3: its sums stand
+  if (j < m) {
+    const unsigned pa = c.ph & 7u, pb = (unsigned)c.ph >> 8;
+    d0 = !(pa & ~pb);
+    d1 = c.b != 0 && !(pb & ~pa);
+  }
+  const bool on = d0 || d1;
+  if (on) {
+    const int2* __restrict__ rank = G.rank[cur];
+    id = 2u * (unsigned)label_id[c.top];
+    E.a = c.u;
+    E.b = c.b;
+    E.ja = j;
+    E.jb = rank[E.b].x;
+    E.ea = end[E.a];
+    E.eb = end[E.b];
+    const int near = min(E.a, E.b);
+    const unsigned long long k = T.key(near, max(E.a, E.b));
+    E.w = LcaTab::parent_of(k);
+    const int far = LcaTab::child_of(k);
+    // a lies strictly below w; b may be w
+    const int other = near != E.w ? LcaTab::child_of(T.key(E.w, near)) : -1;
+    E.a0 = E.a > E.b ? far : other;
+    E.b0 = E.a > E.b ? other : far;
+    const int2 ra = rank[E.a0];
+    E.a1 = end[E.a0];
+    R.x = ra.x;
+    R.y = ra.y;
+    if (E.b0 >= 0) {
+      const int2 rb = rank[E.b0];
+      E.b1 = end[E.b0];
+      R.z = rb.x;
+      R.w = rb.y;
+    } else {
+      E.b0 = 0;
+    }
+    const bool hit = (E.a0 < st.a1 && st.a0 < E.a1) || (E.a0 < st.b1 && st.b0 < E.a1) ||
+                     (E.b0 < st.a1 && st.a0 < E.b1) || (E.b0 < st.b1 && st.b0 < E.b1);
+    todo = !hit && E.a != st.s && E.b != st.s ? 3 : FULL || (R.y - R.x) + (R.w - R.z) > kGreedyWaveL ? 2 : 1;
+    if (todo != 3 && S <= kGreedyDv)
+      for (int q = FULL ? tid : lane; q < 12 * S; q += FULL ? kGreedyThreads : 64) {
+        const int p = q % 3, d = q / 3 & 1, l = (q / 6) % S, b = q / (6 * S);
+        const double2* Za = Zr + (size_t)(b ? E.w : E.a) * 9 + p * 3;
+        const double2* Zb = Zr + (size_t)(b ? E.b : E.w) * 9 + p * 3;
+        const double2* J = I + ((size_t)l * n + (d ? E.b : E.a)) * 3;
+        s_dv[me][b][l][d][p] = cadd(cadd(cmul(csub(Za[0], Zb[0]), J[0]), cmul(csub(Za[1], Zb[1]), J[1])),
+                                    cmul(csub(Za[2], Zb[2]), J[2]));
+      }
+  }
+  // the unchanged clusters: FULL their sum, else the total to take the changed
+  // ones' old errors from, and their largest error
+  double um = 0.0, out = 0.0;
+  if (on && FULL) {
+    int l = tid / m, q = tid - l * m;
+    const int dl = kGreedyThreads / m, dq = kGreedyThreads - dl * m;
+    while (l < S) {
+      if (!(R.x <= q && q < R.y) && !(R.z <= q && q < R.w) && q != E.jb) {
+        const double e = mice[(size_t)l * n + q];
+        out += e;
+        um = fmax(um, e);
+      }
+      l += dl;
+      q += dq;
+      if (q >= m) {
+        q -= m;
+        ++l;
+      }
+    }
+  } else if (on) {
+    const int nruns = (m + 63) >> 6;
+    for (int k = lane; k < nruns; k += 64) {
+      const int lo = k * 64, hi = lo + 64;
+      const bool touch = (lo <= E.ja && E.ja < hi) || (lo <= E.jb && E.jb < hi) || (lo < R.y && R.x < hi) ||
+                         (lo < R.w && R.z < hi);
+      if (!touch) um = fmax(um, G.bmax[cur][k]);
+      out += G.bsum[cur][k];
+    }
+    // a touched run holds a, b or an end of an interval, or lies wholly inside
+    // one (a run named twice gives the same maximum)
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const int at = k == 0 ? E.ja : k == 1 ? E.jb : k == 2 ? R.x : k == 3 ? R.y - 1 : k == 4 ? R.z : R.w - 1;
+      const int q = (at & ~63) + lane;
+      if (at >= 0 && q < m && q != E.ja && q != E.jb && !(R.x <= q && q < R.y) && !(R.z <= q && q < R.w))
+        um = fmax(um, G.arr[cur][q]);
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    out += __shfl_xor(out, o, 64);
+    um = fmax(um, __shfl_xor(um, o, 64));
+  }
+  if (lane == 0) {
+    if (FULL) {
+      s_out[wv] = out;
+      s_um[wv] = um;
+    }
+    if (!FULL || wv == 0) {
+      s_edge[me] = E;
+      s_rank[me] = R;
+      s_todo[me] = todo;
     }
   }
   __syncthreads();
-  // SMICE: every thread sums its strided share in order, then a fixed tree
-  double acc = 0.0;
-  for (int q = tid; q < S * n; q += kGreedyThreads) acc += __longlong_as_double((long long)mice[q]);
-  for (int o = 32; o > 0; o >>= 1) {
-    acc += __shfl_xor(acc, o, 64);
-    emax = fmax(emax, __shfl_xor(emax, o, 64));
+  // round -1: the wave's own edge; round h: edge h by every wave
+  for (int h = FULL ? 0 : -1; h < NE; ++h) {
+    const int x = h < 0 ? me : h;
+    if (__builtin_amdgcn_readfirstlane(s_todo[x]) != (h < 0 ? 1 : 2)) continue;
+    const GEdge F = s_edge[x];
+    const int4 r = s_rank[x];
+    const int stride = h < 0 ? 64 : NW * 64, first = h < 0 ? lane : tid;
+    // clusters of the two intervals, and b's when it is w; an item per cluster and scenario
+    const int L1 = r.y - r.x, L2 = r.w - r.z, L = L1 + max(L2, 1);
+    GPart P{0.0, 0.0, 0.0, 0.0, 0.0};
+    int l = first / L, q = first - l * L;
+    const int dl = stride / L, dq = stride - dl * L;
+    while (l < S) {
+      const bool inA = q < L1;
+      const int k = inA ? r.x + q : L2 > 0 ? r.z + (q - L1) : F.jb;
+      const int u = cl[k].u;
+      const size_t at = (size_t)l * n + u;
+      const bool isA = k == F.ja, isB = k == F.jb;
+      const size_t mt = (size_t)l * n + (isA ? F.b : isB ? F.a : u);  // the cluster merged with u's
+      double2 v[3], v0[3], v1[3];
+      double lo[3], hi[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        v[p] = V[at * 3 + p];
+        lo[p] = fmin(ext[at * 6 + p], ext[mt * 6 + p]);
+        hi[p] = fmax(ext[at * 6 + 3 + p], ext[mt * 6 + 3 + p]);
+      }
+      P.olds += mice[(size_t)l * n + k];
+      if (S <= kGreedyDv && (inA ? F.a <= u && u < F.ea : F.b <= u && u < F.eb)) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          v0[p] = s_dv[x][!inA][l][0][p];
+          v1[p] = s_dv[x][!inA][l][1][p];
+        }
+      } else {
+        // towards a, lca(u, b) = w; towards b, lca(u, a) = w
+        const int y = T.lca(u, inA ? F.a : F.b);
+        MoveDelta md;
+        md.between(Zr, inA ? y : F.w, inA ? F.w : y);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          v0[p] = md.dv(p, I + ((size_t)l * n + F.a) * 3);
+          v1[p] = md.dv(p, I + ((size_t)l * n + F.b) * 3);
+        }
+      }
+      double x0 = 0.0, x1 = 0.0;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        x0 = ext_err(x0, lo[p], hi[p], sqrt(cabs2(cadd(v[p], v0[p]))));
+        x1 = ext_err(x1, lo[p], hi[p], sqrt(cabs2(csub(v[p], v1[p]))));
+      }
+      // a's cluster is gone when it moves up, b's when it moves down
+      if (isA) x0 = 0.0;
+      if (isB) x1 = 0.0;
+      P.n0 += x0;
+      P.n1 += x1;
+      P.e0 = fmax(P.e0, x0);
+      P.e1 = fmax(P.e1, x1);
+      l += dl;
+      q += dq;
+      if (q >= L) {
+        q -= L;
+        ++l;
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      P.olds += __shfl_xor(P.olds, o, 64);
+      P.n0 += __shfl_xor(P.n0, o, 64);
+      P.n1 += __shfl_xor(P.n1, o, 64);
+      P.e0 = fmax(P.e0, __shfl_xor(P.e0, o, 64));
+      P.e1 = fmax(P.e1, __shfl_xor(P.e1, o, 64));
+    }
+    if (lane == 0) s_part[x][h < 0 ? 0 : wv] = P;
   }
-  if ((tid & 63) == 0) red[tid >> 6] = acc;
   __syncthreads();
-  const double tot = (red[0] + red[1]) + (red[2] + red[3]);
+  if (wv < NE && lane == 0) {
+    double v0 = INFINITY, v1 = INFINITY;
+    unsigned near = 0;
+    if (on) {
+      GPart P = todo == 3 ? G.part[E.a] : s_part[me][0];
+      if (todo == 2)  // the waves' parts, in order
+        for (int k = 1; k < NW; ++k) {
+          const GPart Q = s_part[me][k];
+          P.olds += Q.olds;
+          P.n0 += Q.n0;
+          P.n1 += Q.n1;
+          P.e0 = fmax(P.e0, Q.e0);
+          P.e1 = fmax(P.e1, Q.e1);
+        }
+      if (todo != 3) G.part[E.a] = P;
+      if (FULL) {
+        for (int k = 1; k < NW; ++k) {
+          out += s_out[k];
+          um = fmax(um, s_um[k]);
+        }
+      } else {
+        out -= P.olds;
+      }
+      P.e0 = fmax(P.e0, um);
+      P.e1 = fmax(P.e1, um);
+      if (d0 && P.e0 <= e_bar) v0 = out + P.n0;
+      if (d1 && P.e1 <= e_bar) v1 = out + P.n1;
+      near = (d0 && fabs(P.e0 - e_bar) <= amb) + (d1 && fabs(P.e1 - e_bar) <= amb);
+      G.em[2 * j] = d0 ? P.e0 : -1.0;
+      G.em[2 * j + 1] = d1 ? P.e1 : -1.0;
+      G.edge[j] = E;
+    }
+    if (j < m) {
+      G.sm[2 * j] = v0;
+      G.sm[2 * j + 1] = v1;
+    }
+    s_v[2 * me] = v0;
+    s_v[2 * me + 1] = v1;
+    s_key[2 * me] = (unsigned long long)id << 32 | (unsigned)(2 * j);
+    s_key[2 * me + 1] = (unsigned long long)(id + 1) << 32 | (unsigned)(2 * j + 1);
+    s_cnt[2 * me] = (unsigned)d0 + (unsigned)d1;
+    s_cnt[2 * me + 1] = (unsigned long long)((v0 < INFINITY) + (v1 < INFINITY)) << 20 | (unsigned long long)near << 40;
+  }
   __syncthreads();
-  if ((tid & 63) == 0) red[tid >> 6] = emax;
-  __syncthreads();
-  if (tid == 0) {
-    const double e = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-    em[cand] = e;
-    sm[cand] = e <= e_bar ? tot : INFINITY;
+  if (wv == 0) {
+    const int k = min(lane, 2 * NE - 1);
+    double mn = s_v[k], snd = INFINITY;
+    unsigned long long key = s_key[k], cnt = lane < 2 * NE ? s_cnt[k] : 0ull;
+    for (int o = NE; o > 0; o >>= 1) {
+      const double om = __shfl_xor(mn, o, 64), os = __shfl_xor(snd, o, 64);
+      const unsigned long long ok = __shfl_xor(key, o, 64);
+      snd = fmin(fmin(snd, os), fmax(mn, om));
+      if (om < mn || (om == mn && ok < key)) key = ok;
+      mn = fmin(mn, om);
+      cnt += __shfl_xor(cnt, o, 64);
+    }
+    if (lane == 0) G.blk[blockIdx.x] = GBlk{mn, snd, key, cnt};
   }
 }
 
-// The move of the full-scoring form (one block of 1024): as
-// k_greedy_pick_apply without the cluster state.  Dynamic LDS: the two root
-// paths.
-__global__ __launch_bounds__(kGreedyPickThreads) void k_greedy_pick_apply_full(
-    int n, int S, const int* __restrict__ parent, const int* __restrict__ pos, const int* __restrict__ size,
-    const int* __restrict__ depth, const double2* __restrict__ Zr, const double* __restrict__ sm,
-    const double* __restrict__ em, double e_bar, double tie, double amb, GState* __restrict__ gs,
-    GStep* __restrict__ steps, int* __restrict__ sup, double2* __restrict__ Iagg, double2* __restrict__ V,
-    const uint8_t* __restrict__ phase, const double* __restrict__ absV, double* __restrict__ e0) {
-  extern __shared__ __align__(16) unsigned char g_lds[];
-  __shared__ double shd[kGreedyPickThreads / 64];
-  __shared__ int shi[kGreedyPickThreads / 64];
+// The iteration's move: the smallest SMICE among feasible candidates, ties
+// within tie_tol to the lowest id.  Every block settles it alike from the
+// scoring blocks' records (a record's candidates are opened only when its
+// second value reaches the tie threshold); then one thread per remaining
+// cluster writes the next list, moves its super-node's voltage when the move
+// reaches it (the expression the scoring evaluated) and its error.  What other
+// blocks still read is never written: the list, ranks and errors have two
+// copies, r's current is left as it is (r is no super-node any more).  With no
+// feasible candidate the search is marked done.
+// Bound by latency; what does not depend on the move is loaded before it is
+// settled.  5591 nodes 8.9 us, 1000 nodes 8.6 (79 and 14.9 as one block that
+// walked every node and rebuilt every cluster's members).
+__global__ __launch_bounds__(kGreedyPickThreads) void k_greedy_apply(
+    int n, int S, int cur, int edges, LcaTab T, const int* __restrict__ end, const int* __restrict__ label_id,
+    const double2* __restrict__ Zr, double tie, double amb, GStep* __restrict__ steps, GreedyState G) {
+  constexpr int NW = kGreedyPickThreads / 64;
+  __shared__ double s_mn[NW];
+  __shared__ unsigned long long s_cnt[NW], s_win[NW];
   __shared__ double2 J[kGreedyMaxS * 3];
-  if (gs->done) return;
-  const int tid = threadIdx.x, ncand = 2 * n;
-  double mn = INFINITY;
-  int nact = 0, nfeas = 0;
-  for (int c = tid; c < ncand; c += kGreedyPickThreads) {
-    mn = fmin(mn, sm[c]);
-    nact += em[c] >= 0.0;
-    nfeas += sm[c] < INFINITY;
+  const int nxt = 1 - cur, tid = threadIdx.x, lane = tid & 63, t = blockIdx.x * kGreedyPickThreads + tid;
+  const int grid = (n - 2) / edges + 1;  // scoring blocks
+  const GState st = *G.gs[cur];
+  const int tc = min(t, n - 1), t1 = min(t + 1, n - 1);
+  const int2 rk = G.rank[cur][tc];
+  const int te = end[tc], sup = G.sup[tc];
+  const GClus c0 = G.cl[cur][tc], c1 = G.cl[cur][t1];
+  if (st.done) {
+    if (t == 0) *G.gs[nxt] = GState{st.iter, 1, 0, 0, 0, 0, 0};
+    return;
   }
-  mn = block_reduce(mn, [](double a, double b) { return fmin(a, b); }, shd);
-  nact = block_reduce(nact, [](int a, int b) { return a + b; }, shi);
-  nfeas = block_reduce(nfeas, [](int a, int b) { return a + b; }, shi);
+  const int m = n - st.iter, nb = min(grid, m - 1);
+  double mn = INFINITY;
+  unsigned long long cnt = 0;
+  GBlk B{INFINITY, INFINITY, 0, 0};
+  for (int b = tid; b < nb; b += kGreedyPickThreads) {
+    B = G.blk[b];
+    mn = fmin(mn, B.mn);
+    cnt += B.cnt;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    mn = fmin(mn, __shfl_xor(mn, o, 64));
+    cnt += __shfl_xor(cnt, o, 64);
+  }
+  if (lane == 0) {
+    s_mn[tid >> 6] = mn;
+    s_cnt[tid >> 6] = cnt;
+  }
+  __syncthreads();
+  mn = s_mn[lane & (NW - 1)];
+  cnt = s_cnt[lane & (NW - 1)];
+  for (int o = NW / 2; o > 0; o >>= 1) {
+    mn = fmin(mn, __shfl_xor(mn, o, 64));
+    cnt += __shfl_xor(cnt, o, 64);
+  }
   if (!(mn < INFINITY)) {
-    if (tid == 0) gs->done = 1;
+    if (t == 0) *G.gs[nxt] = GState{st.iter, 1, 0, 0, 0, 0, 0};
     return;
   }
   const double thr = mn + tie;
-  int win = 0x7fffffff, fl = 0;
-  for (int c = tid; c < ncand; c += kGreedyPickThreads) {
-    const double v = sm[c];
-    if (v <= thr) win = min(win, c);
-    if (v < INFINITY && fabs(v - thr) <= amb) fl = 1;
-    if (em[c] >= 0.0 && fabs(em[c] - e_bar) <= amb) fl = 1;
+  unsigned long long win = ~0ull;  // smallest key
+  bool near = false;
+  for (int b = tid; b < nb; b += kGreedyPickThreads) {
+    if (nb > kGreedyPickThreads) B = G.blk[b];
+    if (!(B.mn <= thr + 2.0 * amb)) continue;
+    near |= fabs(B.mn - thr) <= amb;
+    if (B.mn <= thr && B.key < win) win = B.key;
+    if (!(B.snd <= thr + 2.0 * amb)) continue;
+    for (int k = 0; k < edges; ++k) {
+      const int j = 1 + k * grid + b;
+      if (j >= m) break;
+      for (int d = 0; d < 2; ++d) {
+        const double v = G.sm[2 * j + d];
+        if (!(v < INFINITY)) continue;
+        near |= fabs(v - thr) <= amb;
+        if (v <= thr) {
+          const unsigned id = 2u * (unsigned)label_id[G.cl[cur][j].top] + d;
+          const unsigned long long key = (unsigned long long)id << 32 | (unsigned)(2 * j + d);
+          win = key < win ? key : win;
+        }
+      }
+    }
   }
-  win = block_reduce(win, [](int a, int b) { return min(a, b); }, shi);
-  fl = block_reduce(fl, [](int a, int b) { return max(a, b); }, shi);
-  const int wx = win >> 1, wa = sup[wx], wb = sup[parent[wx]];
-  const int r = (win & 1) ? wb : wa, s = (win & 1) ? wa : wb;
-  PathRec* pr = (PathRec*)g_lds;
-  const int dr = depth[r], ds = depth[s];
-  PathRec* ps = pr + dr + 1;
-  load_paths(n, pos, size, depth, r, s, pr, ps);
-  for (int q = tid; q < S * 3; q += kGreedyPickThreads) J[q] = Iagg[((size_t)(q / 3) * n + r) * 3 + q % 3];
-  __syncthreads();  // sup and Iagg read by every thread before they change
-  if (tid == 0) {
-    GStep st;
-    st.cand = win;
-    st.s = s;
-    st.r = r;
-    st.ambiguous = fl;
-    st.n_cand = nact;
-    st.n_feasible = nfeas;
-    st.smice = sm[win];
-    st.emax = em[win];
-    steps[gs->iter] = st;
-    gs->s = s;
-    gs->r = r;
-    gs->iter += 1;
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long x = __shfl_xor(win, o, 64);
+    win = x < win ? x : win;
   }
-  for (int q = tid; q < S * 3; q += kGreedyPickThreads) {
-    const size_t lr = ((size_t)(q / 3) * n + r) * 3 + q % 3, ls = ((size_t)(q / 3) * n + s) * 3 + q % 3;
-    Iagg[ls] = cadd(Iagg[ls], J[q]);
-    Iagg[lr] = make_double2(0.0, 0.0);
+  if (lane == 0) s_win[tid >> 6] = win;
+  const int fl = __syncthreads_or(near) || (cnt >> 40) ? 1 : 0;
+  win = s_win[lane & (NW - 1)];
+  for (int o = NW / 2; o > 0; o >>= 1) {
+    const unsigned long long x = __shfl_xor(win, o, 64);
+    win = x < win ? x : win;
   }
-  for (int u = tid; u < n; u += kGreedyPickThreads)
-    if (sup[u] == r) sup[u] = s;
-  MoveIntervals mi;
-  mi.from(pr, dr, ps, ds, pos[s]);
-  for (int t = tid; t < n * S; t += kGreedyPickThreads) {
-    const int xn = t % n, l = t / n;
-    const int qx = pos[xn];
-    if (!mi.holds(qx)) continue;
-    PathDelta md;
-    md.at(pr, dr, ps, ds, Zr, qx, depth[xn]);
-    if (!md.moved) continue;
-    const size_t vb = ((size_t)l * n + xn) * 3;
-#pragma unroll
-    for (int p = 0; p < 3; ++p) V[vb + p] = cadd(V[vb + p], md.dv(p, J + l * 3));
-  }
+  const int wc = __builtin_amdgcn_readfirstlane((int)(unsigned)win), wj = wc >> 1, dir = wc & 1;
+  const GEdge E = G.edge[wj];
+  const int r = dir ? E.b : E.a, s = dir ? E.a : E.b, jr = dir ? E.jb : E.ja;
+  for (int q = tid; q < S * 3; q += kGreedyPickThreads) J[q] = G.I[((size_t)(q / 3) * n + r) * 3 + q % 3];
+  const GClus cr = G.cl[cur][jr], cs = G.cl[cur][dir ? E.ja : E.jb];
   __syncthreads();
-  node_errors(n, S, phase, sup, V, absV, e0, tid, kGreedyPickThreads);
+  if (blockIdx.x == 0) {
+    if (tid == 0) {
+      GStep sp;
+      sp.cand = (int)(win >> 32);
+      sp.s = label_id[s];
+      sp.r = label_id[r];
+      sp.ambiguous = fl;
+      sp.n_cand = (int)(cnt & 0xfffffu);
+      sp.n_feasible = (int)(cnt >> 20 & 0xfffffu);
+      sp.smice = G.sm[wc];
+      sp.emax = G.em[wc];
+      steps[st.iter] = sp;
+      *G.gs[nxt] = GState{st.iter + 1, 0, s, E.a0, E.a1, E.b0, E.b1};
+    }
+    for (int q = tid; q < S * 3; q += kGreedyPickThreads) {
+      const size_t ls = ((size_t)(q / 3) * n + s) * 3 + q % 3;
+      G.I[ls] = cadd(G.I[ls], J[q]);
+    }
+  }
+  if (t < n) {
+    G.rank[nxt][t] = make_int2(rk.x - (t > r), rk.y - (te > r));
+    if (sup == r) G.sup[t] = s;
+  }
+  if (t - lane >= m - 1) return;
+  double mx = 0.0, sum = 0.0;
+  if (t < m - 1) {
+    const int jo = t + (t >= jr);
+    GClus c = t >= jr ? c1 : c0;
+    const bool inA = E.a0 <= c.u && c.u < E.a1, in = inA || (E.b0 <= c.u && c.u < E.b1);
+    if (in || c.u == s) {
+      const int x = T.lca(c.u, inA ? E.a : E.b);
+      const bool up = inA != (dir != 0);  // r's side
+      MoveDelta md;
+      md.between(Zr, up ? x : E.w, up ? E.w : x);
+      for (int l = 0; l < S; ++l) {
+        const size_t at = (size_t)l * n + c.u, ar = (size_t)l * n + (c.u == s ? r : c.u);
+        double e = 0.0;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          double2 v = G.V[at * 3 + p];
+          if (in) {
+            v = cadd(v, md.dv(p, J + l * 3));
+            G.V[at * 3 + p] = v;
+          }
+          const double lo = fmin(G.ext[at * 6 + p], G.ext[ar * 6 + p]);
+          const double hi = fmax(G.ext[at * 6 + 3 + p], G.ext[ar * 6 + 3 + p]);
+          if (c.u == s) {
+            G.ext[at * 6 + p] = lo;
+            G.ext[at * 6 + 3 + p] = hi;
+          }
+          e = ext_err(e, lo, hi, sqrt(cabs2(v)));
+        }
+        G.mice[nxt][(size_t)l * n + t] = e;
+        mx = fmax(mx, e);
+        sum += e;
+      }
+    } else {
+      for (int l = 0; l < S; ++l) {
+        const double e = G.mice[cur][(size_t)l * n + jo];
+        G.mice[nxt][(size_t)l * n + t] = e;
+        mx = fmax(mx, e);
+        sum += e;
+      }
+    }
+    if (c.b == r && c.u != s) {
+      c.b = s;
+      c.ph = (c.ph & 7) | (cs.ph & 7) << 8;
+    }
+    if (c.u == s && dir) {  // s takes r's place under the cluster above r's
+      c.top = cr.top;
+      c.b = cr.b;
+      c.ph = (c.ph & 7) | (cr.ph & ~7);
+    }
+    G.cl[nxt][t] = c;
+    G.arr[nxt][t] = mx;
+  }
+  run_totals(mx, sum, G.bmax[nxt] + (t >> 6), G.bsum[nxt] + (t >> 6));
 }
 
 // ---- radialization (Section V) --------------------------------------------
@@ -1004,8 +811,8 @@ __global__ __launch_bounds__(kGreedyPickThreads) void k_radialize(
 // every kept pair's lowest common ancestor is kept, i.e. when the network is
 // radial with the same voltages.
 __global__ __launch_bounds__(kGreedyThreads) void k_radial_check(
-    int n, int S, const uint8_t* __restrict__ phase, LcaTab T, const double2* __restrict__ Zr,
-    const int* __restrict__ sup, const uint8_t* __restrict__ kept_rad, const int* __restrict__ kp, int use_rad,
+    int n, int S, const uint8_t* __restrict__ phase, const int* __restrict__ pos, LcaTab T,
+    const double2* __restrict__ Zr, const int* __restrict__ sup, const uint8_t* __restrict__ kept_rad, const int* __restrict__ kp, int use_rad,
     const double2* __restrict__ Iagg, const double2* __restrict__ V, double2 v0a, double2 v0b, double2 v0c,
     unsigned long long* __restrict__ dv) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1016,7 +823,8 @@ __global__ __launch_bounds__(kGreedyThreads) void k_radial_check(
     if (kx) {
       const double2 v0[3] = {v0a, v0b, v0c};
       double2 acc[3] = {v0[0], v0[1], v0[2]};
-      for (int j = 1; j < n; ++j) {
+      for (int k = 1; k < n; ++k) {  // in the caller's node order
+        const int j = pos[k];
         if (sup[j] != j) continue;  // only super-nodes carry current
         int a = T.lca(x, j);
         const bool ka = use_rad ? kept_rad[a] != 0 : sup[a] == a;
@@ -1077,20 +885,21 @@ struct okr_greedy {
   std::string err;
   bool planned = false;
   int n = 0, S = 0, nlev = 0;
-  std::vector<int> parent, pos, size, depth, lvl_off, lvl_nodes, ch_off, ch;
-  std::vector<uint8_t> phase;
+  std::vector<int> parent, pos, pre;  // by the caller's id: parent, label; by label: the caller's id
+  std::vector<uint8_t> phase, lphase;  // by the caller's id, by label
   // workspace layout (byte offsets)
-  size_t o_topo = 0, o_phase = 0, o_z = 0, o_Zr = 0, o_Vhat = 0, o_A = 0, o_absV = 0, o_I = 0, o_V = 0, o_Ib = 0,
-         o_sup = 0, o_sm = 0, o_em = 0, o_steps = 0, o_gs = 0, o_status = 0, o_iters = 0, o_err = 0, total = 0;
-  // packed int arrays: parent, pos, size, depth, lvl_off, lvl_nodes, ch_off, ch
-  size_t t_parent = 0, t_pos = 0, t_size = 0, t_depth = 0, t_lvl_off = 0, t_lvl_nodes = 0, t_ch_off = 0, t_ch = 0,
-         t_pre = 0, t_first = 0, t_st = 0;
-  int euler_len = 0;
-  // cluster state of the search
-  size_t o_mice = 0, o_arr = 0, o_bmax = 0, o_moff = 0, o_mem = 0, o_tot = 0;
+  size_t o_topo = 0, o_phase = 0, o_z = 0, o_Zr = 0, o_A = 0, o_absV = 0, o_Vhat = 0, o_I = 0, o_V = 0, o_Ib = 0,
+         o_sup = 0, o_sm = 0, o_em = 0, o_steps = 0, o_status = 0, o_iters = 0, o_err = 0, o_csr = 0, total = 0;
+  // packed int arrays over labels: parent, end of the subtree, level offsets,
+  // level nodes, children; the caller's id and its inverse; then (64-bit) the
+  // lca table, which only a search and the radialization read
+  size_t t_parent = 0, t_end = 0, t_lvl_off = 0, t_lvl_nodes = 0, t_ch_off = 0, t_ch = 0, t_pre = 0, t_pos = 0,
+         t_lca = 0;
+  // state of the search (two copies of what each iteration rewrites)
+  size_t o_gs[2] = {}, o_cl[2] = {}, o_rank[2] = {}, o_mice[2] = {}, o_arr[2] = {}, o_bmax[2] = {}, o_bsum[2] = {};
+  size_t o_ext = 0, o_edge = 0, o_part = 0, o_blk = 0;
   // radialization: 5 int arrays of n, kept flags, counter, two maxima
   size_t o_rad = 0, o_radk = 0, o_radx = 0;
-  size_t o_e0 = 0;  // every node's error per scenario in the current state
   std::vector<int> topo_host;
 };
 
@@ -1138,15 +947,16 @@ extern "C" int okr_greedy_plan(okr_greedy* g, int32_t n, const int32_t* parent, 
   for (int i = 1; i < n; ++i)
     if (g->parent[i] < 0 || g->parent[i] >= n || g->parent[i] == i)
       OKRG_FAIL(g, OKR_E_NOT_TREE, "parent[%d] = %d out of range", i, g->parent[i]);
-  g->ch_off.assign(n + 1, 0);
-  for (int i = 1; i < n; ++i) g->ch_off[g->parent[i] + 1]++;
-  for (int i = 0; i < n; ++i) g->ch_off[i + 1] += g->ch_off[i];
-  g->ch.assign(std::max(n - 1, 1), 0);
+  std::vector<int> coff(n + 1, 0), cch(std::max(n - 1, 1), 0);  // children by the caller's id
+  for (int i = 1; i < n; ++i) coff[g->parent[i] + 1]++;
+  for (int i = 0; i < n; ++i) coff[i + 1] += coff[i];
   {
-    std::vector<int> fill(n, 0);
-    for (int i = 1; i < n; ++i) g->ch[g->ch_off[g->parent[i]] + fill[g->parent[i]]++] = i;
+    std::vector<int> fill(coff.begin(), coff.begin() + n);
+    for (int i = 1; i < n; ++i) cch[fill[g->parent[i]]++] = i;
   }
-  std::vector<int> pre;
+  // labels: positions in a depth-first order, children in increasing id
+  std::vector<int>& pre = g->pre;
+  pre.clear();
   pre.reserve(n);
   {
     std::vector<int> st{0};
@@ -1154,35 +964,39 @@ extern "C" int okr_greedy_plan(okr_greedy* g, int32_t n, const int32_t* parent, 
       const int v = st.back();
       st.pop_back();
       pre.push_back(v);
-      for (int e = g->ch_off[v + 1] - 1; e >= g->ch_off[v]; --e) st.push_back(g->ch[e]);
+      for (int e = coff[v + 1] - 1; e >= coff[v]; --e) st.push_back(cch[e]);
     }
   }
   if ((int)pre.size() != n) OKRG_FAIL(g, OKR_E_NOT_TREE, "parent[] is not a tree rooted at node 0");
   g->pos.assign(n, 0);
   for (int q = 0; q < n; ++q) g->pos[pre[q]] = q;
-  g->size.assign(n, 1);
-  for (int q = n - 1; q >= 1; --q) g->size[g->parent[pre[q]]] += g->size[pre[q]];
-  g->depth.assign(n, 0);
+  std::vector<int> par(n, -1), end(n, 0), depth(n, 0);  // by label
+  for (int q = 1; q < n; ++q) par[q] = g->pos[g->parent[pre[q]]];
+  for (int q = 0; q < n; ++q) end[q] = q + 1;
+  for (int q = n - 1; q >= 1; --q) end[par[q]] = std::max(end[par[q]], end[q]);
   int dmax = 0;
   for (int q = 1; q < n; ++q) {
-    const int v = pre[q];
-    g->depth[v] = g->depth[g->parent[v]] + 1;
-    dmax = std::max(dmax, g->depth[v]);
+    depth[q] = depth[par[q]] + 1;
+    dmax = std::max(dmax, depth[q]);
   }
   g->nlev = dmax + 1;
-  g->lvl_off.assign(g->nlev + 1, 0);
-  for (int i = 0; i < n; ++i) g->lvl_off[g->depth[i] + 1]++;
-  for (int d = 0; d < g->nlev; ++d) g->lvl_off[d + 1] += g->lvl_off[d];
-  g->lvl_nodes.assign(n, 0);
+  std::vector<int> lvl_off(g->nlev + 1, 0), lvl_nodes(n), ch_off(n + 1, 0), ch(std::max(n - 1, 1), 0);
+  for (int q = 0; q < n; ++q) lvl_off[depth[q] + 1]++;
+  for (int d = 0; d < g->nlev; ++d) lvl_off[d + 1] += lvl_off[d];
+  for (int q = 1; q < n; ++q) ch_off[par[q] + 1]++;
+  for (int q = 0; q < n; ++q) ch_off[q + 1] += ch_off[q];
   {
-    std::vector<int> fill(g->nlev, 0);
-    for (int i = 0; i < n; ++i) g->lvl_nodes[g->lvl_off[g->depth[i]] + fill[g->depth[i]]++] = i;
+    std::vector<int> fl(lvl_off.begin(), lvl_off.begin() + g->nlev), fc(ch_off.begin(), ch_off.begin() + n);
+    for (int q = 0; q < n; ++q) lvl_nodes[fl[depth[q]]++] = q;
+    for (int q = 1; q < n; ++q) ch[fc[par[q]]++] = q;
   }
   for (int i = 0; i < n; ++i) {
     if (g->phase[i] == 0 || g->phase[i] > 7) OKRG_FAIL(g, OKR_E_PHASE, "node %d has phase mask %d", i, g->phase[i]);
     if (i > 0 && (g->phase[i] & ~g->phase[g->parent[i]]))
       OKRG_FAIL(g, OKR_E_PHASE, "phases of node %d are not a subset of its parent's", i);
   }
+  g->lphase.resize(n);
+  for (int q = 0; q < n; ++q) g->lphase[q] = g->phase[pre[q]];
   // packed topology
   g->topo_host.clear();
   auto put = [&](const std::vector<int>& v) {
@@ -1190,51 +1004,29 @@ extern "C" int okr_greedy_plan(okr_greedy* g, int32_t n, const int32_t* parent, 
     g->topo_host.insert(g->topo_host.end(), v.begin(), v.end());
     return at;
   };
-  g->t_parent = put(g->parent);
-  g->t_pos = put(g->pos);
-  g->t_size = put(g->size);
-  g->t_depth = put(g->depth);
-  g->t_lvl_off = put(g->lvl_off);
-  g->t_lvl_nodes = put(g->lvl_nodes);
-  g->t_ch_off = put(g->ch_off);
-  g->t_ch = put(g->ch);
+  g->t_parent = put(par);
+  g->t_end = put(end);
+  g->t_lvl_off = put(lvl_off);
+  g->t_lvl_nodes = put(lvl_nodes);
+  g->t_ch_off = put(ch_off);
+  g->t_ch = put(ch);
   g->t_pre = put(pre);
-  // Euler tour of the DFS (children in increasing id, i.e. increasing DFS
-  // position), first occurrences, and the sparse table of shallowest nodes
+  g->t_pos = put(g->pos);
   {
-    std::vector<int> euler, first(n, -1);
-    euler.reserve(2 * (size_t)n);
-    std::vector<std::pair<int, int>> stk{{0, g->ch_off[0]}};
-    euler.push_back(0);
-    first[0] = 0;
-    while (!stk.empty()) {
-      const int v = stk.back().first, e = stk.back().second;
-      if (e < g->ch_off[v + 1]) {
-        stk.back().second = e + 1;
-        const int c = g->ch[e];
-        first[c] = (int)euler.size();
-        euler.push_back(c);
-        stk.push_back({c, g->ch_off[c]});
-      } else {
-        stk.pop_back();
-        if (!stk.empty()) euler.push_back(stk.back().first);
+    int K = 1;
+    while ((1 << K) <= n) ++K;
+    std::vector<unsigned long long> sp((size_t)K * n, ~0ull);
+    for (int q = 1; q < n; ++q) sp[q] = (unsigned long long)par[q] << 32 | (0xffffffffu - (unsigned)q);
+    for (int k = 1; k < K; ++k)
+      for (int q = 0; q < n; ++q) {
+        const unsigned long long a = sp[(size_t)(k - 1) * n + q];
+        const int j = q + (1 << (k - 1));
+        sp[(size_t)k * n + q] = j < n ? std::min(a, sp[(size_t)(k - 1) * n + j]) : a;
       }
-    }
-    const int E = (int)euler.size();
-    int L = 1;
-    while ((1 << L) <= E) ++L;
-    std::vector<int> sp((size_t)L * E);
-    for (int i = 0; i < E; ++i) sp[i] = euler[i];
-    for (int k = 1; k < L; ++k)
-      for (int i = 0; i < E; ++i) {
-        const int a = sp[(size_t)(k - 1) * E + i];
-        const int j = i + (1 << (k - 1));
-        const int b = j < E ? sp[(size_t)(k - 1) * E + j] : a;
-        sp[(size_t)k * E + i] = g->depth[a] <= g->depth[b] ? a : b;
-      }
-    g->euler_len = E;
-    g->t_first = put(first);
-    g->t_st = put(sp);
+    if (g->topo_host.size() & 1) g->topo_host.push_back(0);  // 8-byte entries
+    g->t_lca = g->topo_host.size();
+    g->topo_host.resize(g->t_lca + 2 * sp.size());
+    std::memcpy(g->topo_host.data() + g->t_lca, sp.data(), sizeof(unsigned long long) * sp.size());
   }
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -1257,20 +1049,27 @@ extern "C" int okr_greedy_plan(okr_greedy* g, int32_t n, const int32_t* parent, 
   g->o_sm = take(sizeof(double) * 2 * n);
   g->o_em = take(sizeof(double) * 2 * n);
   g->o_steps = take(sizeof(GStep) * n);
-  g->o_gs = take(sizeof(GState));
   g->o_status = take(sizeof(int) * 4);
   g->o_iters = take(sizeof(int) * S);
   g->o_err = take(sizeof(double) * S);
-  g->o_mice = take(sizeof(double) * (size_t)S * n);
-  g->o_arr = take(sizeof(double) * n);
-  g->o_bmax = take(sizeof(double) * ((n + 63) / 64));
-  g->o_moff = take(sizeof(int) * (n + 1));
-  g->o_mem = take(sizeof(int) * n);
-  g->o_tot = take(sizeof(double));
+  const size_t runs = ((size_t)n + 63) / 64;
+  for (int k = 0; k < 2; ++k) {
+    g->o_gs[k] = take(sizeof(GState));
+    g->o_cl[k] = take(sizeof(GClus) * n);
+    g->o_rank[k] = take(sizeof(int2) * n);
+    g->o_mice[k] = take(sizeof(double) * (size_t)S * n);
+    g->o_arr[k] = take(sizeof(double) * n);
+    g->o_bmax[k] = take(sizeof(double) * runs);
+    g->o_bsum[k] = take(sizeof(double) * runs);
+  }
+  g->o_ext = take(sizeof(double) * 2 * c3);
+  g->o_edge = take(sizeof(GEdge) * n);
+  g->o_part = take(sizeof(GPart) * n);
+  g->o_blk = take(sizeof(GBlk) * n);
+  g->o_csr = take(sizeof(int) * (2 * (size_t)n + 1));
   g->o_rad = take(sizeof(int) * 5 * (size_t)n);
   g->o_radk = take(n);
   g->o_radx = take(sizeof(unsigned long long) * 4);
-  g->o_e0 = take(sizeof(double) * (size_t)S * n);
   g->total = off;
   *workspace_bytes = off;
   g->planned = true;
@@ -1279,14 +1078,13 @@ extern "C" int okr_greedy_plan(okr_greedy* g, int32_t n, const int32_t* parent, 
 
 namespace {
 struct GPtrs {
-  int *topo, *parent, *pos, *size, *depth, *lvl_off, *lvl_nodes, *ch_off, *ch, *pre, *first, *sp, *sup, *status,
-      *iters;
-  Clusters C;
+  int *topo, *parent, *end, *lvl_off, *lvl_nodes, *ch_off, *ch, *pre, *pos, *sup, *status, *iters, *csr;
+  LcaTab T;
+  GreedyState G;
   uint8_t* phase;
   double2 *z, *Zr, *Vhat, *A, *I, *V, *Ib;
-  double *absV, *sm, *em, *err, *e0;
+  double *absV, *err;
   GStep* steps;
-  GState* gs;
 };
 
 GPtrs gptrs(const okr_greedy* g, void* ws) {
@@ -1294,22 +1092,16 @@ GPtrs gptrs(const okr_greedy* g, void* ws) {
   GPtrs p;
   p.topo = (int*)(b + g->o_topo);
   p.parent = p.topo + g->t_parent;
-  p.pos = p.topo + g->t_pos;
-  p.size = p.topo + g->t_size;
-  p.depth = p.topo + g->t_depth;
+  p.end = p.topo + g->t_end;
   p.lvl_off = p.topo + g->t_lvl_off;
   p.lvl_nodes = p.topo + g->t_lvl_nodes;
   p.ch_off = p.topo + g->t_ch_off;
   p.ch = p.topo + g->t_ch;
   p.pre = p.topo + g->t_pre;
-  p.first = p.topo + g->t_first;
-  p.sp = p.topo + g->t_st;
-  p.C.mice = (double*)(b + g->o_mice);
-  p.C.arr = (double*)(b + g->o_arr);
-  p.C.bmax = (double*)(b + g->o_bmax);
-  p.C.moff = (int*)(b + g->o_moff);
-  p.C.mem = (int*)(b + g->o_mem);
-  p.C.tot = (double*)(b + g->o_tot);
+  p.pos = p.topo + g->t_pos;
+  p.csr = (int*)(b + g->o_csr);
+  p.T.st = (const unsigned long long*)(p.topo + g->t_lca);
+  p.T.n = g->n;
   p.phase = (uint8_t*)(b + g->o_phase);
   p.z = (double2*)(b + g->o_z);
   p.Zr = (double2*)(b + g->o_Zr);
@@ -1320,44 +1112,60 @@ GPtrs gptrs(const okr_greedy* g, void* ws) {
   p.V = (double2*)(b + g->o_V);
   p.Ib = (double2*)(b + g->o_Ib);
   p.sup = (int*)(b + g->o_sup);
-  p.sm = (double*)(b + g->o_sm);
-  p.em = (double*)(b + g->o_em);
   p.steps = (GStep*)(b + g->o_steps);
-  p.gs = (GState*)(b + g->o_gs);
   p.status = (int*)(b + g->o_status);
   p.iters = (int*)(b + g->o_iters);
   p.err = (double*)(b + g->o_err);
-  p.e0 = (double*)(b + g->o_e0);
+  GreedyState& G = p.G;
+  for (int k = 0; k < 2; ++k) {
+    G.gs[k] = (GState*)(b + g->o_gs[k]);
+    G.cl[k] = (GClus*)(b + g->o_cl[k]);
+    G.rank[k] = (int2*)(b + g->o_rank[k]);
+    G.mice[k] = (double*)(b + g->o_mice[k]);
+    G.arr[k] = (double*)(b + g->o_arr[k]);
+    G.bmax[k] = (double*)(b + g->o_bmax[k]);
+    G.bsum[k] = (double*)(b + g->o_bsum[k]);
+  }
+  G.ext = (double*)(b + g->o_ext);
+  G.edge = (GEdge*)(b + g->o_edge);
+  G.part = (GPart*)(b + g->o_part);
+  G.sm = (double*)(b + g->o_sm);
+  G.em = (double*)(b + g->o_em);
+  G.blk = (GBlk*)(b + g->o_blk);
+  G.sup = p.sup;
+  G.V = p.V;
+  G.I = p.I;
   return p;
 }
 
 // Common set-up of a run or an evaluation: topology upload, branch
 // impedances, impedances from the root, scenario library (load flow unless
-// V^ is given); returns the status word and the largest load-flow count.
-int setup(okr_greedy* g, const GPtrs& p, const okr_yblocks* Y, const okr_loads* L, const okr_greedy_params* prm) {
+// V^ is given).  lca: the lowest-common-ancestor table too.
+int setup(okr_greedy* g, const GPtrs& p, const okr_yblocks* Y, const okr_loads* L, const okr_greedy_params* prm,
+          bool lca) {
   const hipStream_t st = g->stream;
   const int n = g->n, S = g->S;
-  OKRG_HIP(g, hipMemcpyAsync(p.topo, g->topo_host.data(), sizeof(int) * g->topo_host.size(), hipMemcpyHostToDevice, st));
-  OKRG_HIP(g, hipMemcpyAsync(p.phase, g->phase.data(), n, hipMemcpyHostToDevice, st));
+  OKRG_HIP(g, hipMemcpyAsync(p.topo, g->topo_host.data(), sizeof(int) * (lca ? g->topo_host.size() : g->t_lca),
+                             hipMemcpyHostToDevice, st));
+  OKRG_HIP(g, hipMemcpyAsync(p.phase, g->lphase.data(), n, hipMemcpyHostToDevice, st));
   OKRG_HIP(g, hipMemsetAsync(p.status, 0, sizeof(int) * 4, st));
   hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, (const int*)p.parent,
                      (const uint8_t*)p.phase, (const int*)p.ch_off, (const int*)p.ch,
-                     (const int*)nullptr, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
+                     (const int*)p.pre, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
   hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, (const int*)p.parent, (const int*)p.lvl_off,
                      (const int*)p.lvl_nodes, g->nlev, (const double2*)p.z, p.Zr);
   const size_t c3 = (size_t)S * n * 3;
   const double2* V0 = (const double2*)L->V0;
   if (prm->flags & OKR_FLAG_VHAT_GIVEN) {
-    OKRG_HIP(g, hipMemcpyAsync(p.Vhat, L->Vhat, sizeof(double2) * c3, hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_from_vhat, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
-                       (const uint8_t*)p.phase, (const double2*)L->S_load, (const double2*)p.Vhat, 0.0, 1e300, p.A,
-                       p.absV, p.status, (const int*)nullptr, (double2*)nullptr);
+                       (const uint8_t*)p.phase, (const double2*)L->S_load, (const double2*)L->Vhat, 0.0, 1e300, p.A,
+                       p.absV, p.status, (const int*)p.pre, (double2*)nullptr);
   } else {
     hipLaunchKernelGGL(k_powerflow, dim3(S), dim3(256), 0, st, n, (const int*)p.parent, (const uint8_t*)p.phase,
                        (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev, (const int*)p.ch_off,
                        (const int*)p.ch, (const double2*)p.z, (const double2*)L->S_load, V0[0], V0[1], V0[2],
                        prm->pf_tol > 0 ? prm->pf_tol : 1e-13, prm->pf_maxit > 0 ? prm->pf_maxit : 100, 0.0, 1e300,
-                       p.Vhat, p.Ib, p.A, p.absV, p.iters, p.status, (const int*)nullptr, (double2*)nullptr);
+                       p.Vhat, p.Ib, p.A, p.absV, p.iters, p.status, (const int*)p.pre, (double2*)nullptr);
   }
   OKRG_HIP(g, hipGetLastError());
   return OKR_OK;
@@ -1400,6 +1208,21 @@ int check_assignment(okr_greedy* g, const int32_t* super) {
   }
   return OKR_OK;
 }
+
+// The assignment by label, and the members of every cluster in the caller's
+// node order (CSR over labels: n + 1 offsets, then n members).
+void assignment(const okr_greedy* g, const int32_t* super, std::vector<int>& lsup, std::vector<int>& csr) {
+  const int n = g->n;
+  lsup.resize(n);
+  csr.assign(2 * (size_t)n + 1, 0);
+  for (int x = 0; x < n; ++x) {
+    lsup[g->pos[x]] = g->pos[super[x]];
+    csr[g->pos[super[x]] + 1]++;
+  }
+  for (int y = 0; y < n; ++y) csr[y + 1] += csr[y];
+  std::vector<int> fill(csr.begin(), csr.begin() + n);
+  for (int x = 0; x < n; ++x) csr[n + 1 + fill[g->pos[super[x]]]++] = g->pos[x];
+}
 }  // namespace
 
 extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loads* L, const okr_greedy_params* prm,
@@ -1410,16 +1233,13 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
   if (!out || !out->super || !out->steps || !out->err_per_snapshot) OKRG_FAIL(g, OKR_E_ARG, "null result buffer");
   const int n = g->n, S = g->S;
   if (S > kGreedyMaxS) OKRG_FAIL(g, OKR_E_UNSUPPORTED, "the search takes at most %d scenarios", kGreedyMaxS);
-  // every candidate scores every node while the cluster table fits in LDS;
-  // beyond that (or when asked) only the clusters a move can change
-  const size_t lds_full = sizeof(unsigned long long) * (size_t)S * n + sizeof(PathRec) * 2 * (size_t)g->nlev;
-  const size_t lds_paths = sizeof(PathRec) * 2 * (size_t)g->nlev;
-  // (the full-scoring kernel also holds about 3 KB of static LDS)
-  const bool incremental =
-      (prm->flags & OKR_GREEDY_INCREMENTAL) || (size_t)S * n > kGreedyFullSN || lds_full > 60 * 1024;
+  // every candidate sums every cluster while there are few (1000 nodes, 2
+  // scenarios: 9.5 us a scoring against 10.7); beyond that, or when asked, only
+  // the clusters a move can change
+  const bool incremental = (prm->flags & OKR_GREEDY_INCREMENTAL) || (size_t)S * n > kGreedyFullSN ||
+                           8 * (size_t)S * n + 24 * (size_t)g->nlev > 60 * 1024;
   if (incremental && n > kGreedyMaxN)
     OKRG_FAIL(g, OKR_E_UNSUPPORTED, "the search takes at most %d nodes", kGreedyMaxN);
-  const size_t lds_cnt = sizeof(int) * (size_t)n;
   const hipStream_t st = g->stream;
   const GPtrs p = gptrs(g, ws);
   hipEvent_t ev[3];
@@ -1431,28 +1251,18 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
     }
   } guard{ev};
   OKRG_HIP(g, hipEventRecord(ev[0], st));
-  rc = setup(g, p, Y, L, prm);
+  rc = setup(g, p, Y, L, prm, true);
   if (rc) return rc;
   const double2* V0 = (const double2*)L->V0;
   const size_t c3 = (size_t)S * n * 3;
   hipLaunchKernelGGL(k_greedy_init, dim3((unsigned)((std::max(c3, (size_t)n) + 255) / 256)), dim3(256), 0, st, n, S,
-                     (const double2*)p.A, p.I, p.sup, p.gs);
+                     (const double2*)p.A, p.I, p.sup, p.G.gs[0]);
   hipLaunchKernelGGL(k_greedy_sweep, dim3(S), dim3(kGreedyThreads), 0, st, n, (const int*)p.parent,
                      (const uint8_t*)p.phase, (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev,
                      (const int*)p.ch_off, (const int*)p.ch, (const double2*)p.z, V0[0], V0[1], V0[2],
                      (const double2*)p.I, p.Ib, p.V);
-  LcaTab T;
-  T.first = p.first;
-  T.st = p.sp;
-  T.depth = p.depth;
-  T.E = g->euler_len;
-  if (incremental)
-    hipLaunchKernelGGL(k_greedy_prep, dim3(1), dim3(kGreedyPickThreads), lds_cnt, st, n, S, (const uint8_t*)p.phase,
-                       (const int*)p.pre, (const int*)p.sup, (const double2*)p.V, (const double*)p.absV, p.C);
-  else
-    hipLaunchKernelGGL(k_greedy_e0, dim3((unsigned)(((size_t)n * S + kGreedyThreads - 1) / kGreedyThreads)),
-                       dim3(kGreedyThreads), 0, st, n, S, (const uint8_t*)p.phase, (const int*)p.sup,
-                       (const double2*)p.V, (const double*)p.absV, p.e0);
+  hipLaunchKernelGGL(k_greedy_prep, dim3((unsigned)(n / kGreedyThreads + 1)), dim3(kGreedyThreads), 0, st, n, S,
+                     (const int*)p.parent, (const int*)p.end, (const uint8_t*)p.phase, (const double*)p.absV, p.G);
   OKRG_HIP(g, hipGetLastError());
   OKRG_HIP(g, hipEventRecord(ev[1], st));
   const double e_bar = prm->e_bar, tie = prm->tie_tol > 0 ? prm->tie_tol : 1e-11;
@@ -1479,36 +1289,21 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
       const hipError_t e = hipEventRecord(tev[2 * t], st);
       if (e != hipSuccess) return e;
     }
-    if (incremental) {
-      hipLaunchKernelGGL(k_greedy_score, dim3(2 * n), dim3(kGreedyThreads), 0, st, n, S, (const int*)p.parent,
-                         (const uint8_t*)p.phase, (const int*)p.pos, (const int*)p.size, (const int*)p.pre,
-                         (const int*)p.ch_off, (const int*)p.ch, (const int*)p.sup, T, (const double2*)p.Zr,
-                         (const double2*)p.I, (const double2*)p.V, (const double*)p.absV, e_bar,
-                         (const GState*)p.gs, p.C, p.sm, p.em);
-      if (timing) {
-        const hipError_t e = hipEventRecord(tev[2 * t + 1], st);
-        if (e != hipSuccess) return e;
-      }
-      hipLaunchKernelGGL(k_greedy_pick_apply, dim3(1), dim3(kGreedyPickThreads), lds_cnt, st, n, S,
-                         (const int*)p.parent, (const uint8_t*)p.phase, (const int*)p.pre, (const int*)p.pos,
-                         (const int*)p.size, (const int*)p.ch_off, (const int*)p.ch, T, (const double2*)p.Zr,
-                         (const double*)p.absV, (const double*)p.sm, (const double*)p.em, e_bar, tie, amb, p.gs,
-                         p.steps, p.sup, p.I, p.V, p.C);
-    } else {
-      hipLaunchKernelGGL(k_greedy_score_full, dim3(2 * n), dim3(kGreedyThreads), lds_full, st, n, S,
-                         (const int*)p.parent, (const uint8_t*)p.phase, (const int*)p.pos, (const int*)p.size,
-                         (const int*)p.depth, (const int*)p.sup, (const double2*)p.Zr, (const double2*)p.I,
-                         (const double2*)p.V, (const double*)p.absV, (const double*)p.e0, e_bar,
-                         (const GState*)p.gs, p.sm, p.em);
-      if (timing) {
-        const hipError_t e = hipEventRecord(tev[2 * t + 1], st);
-        if (e != hipSuccess) return e;
-      }
-      hipLaunchKernelGGL(k_greedy_pick_apply_full, dim3(1), dim3(kGreedyPickThreads), lds_paths, st, n, S,
-                         (const int*)p.parent, (const int*)p.pos, (const int*)p.size, (const int*)p.depth,
-                         (const double2*)p.Zr, (const double*)p.sm, (const double*)p.em, e_bar, tie, amb, p.gs,
-                         p.steps, p.sup, p.I, p.V, (const uint8_t*)p.phase, (const double*)p.absV, p.e0);
+    const int cur = t & 1;  // batches start with copy 0
+    const int edges = incremental ? kGreedyEdges : 1;
+    if (incremental)
+      hipLaunchKernelGGL(k_greedy_score<false>, dim3((unsigned)((n - 2) / kGreedyEdges + 1)), dim3(kGreedyEdges * 64),
+                         0, st, n, S, cur, p.T, (const int*)p.end, (const int*)p.pre, (const double2*)p.Zr, e_bar, amb, p.G);
+    else
+      hipLaunchKernelGGL(k_greedy_score<true>, dim3((unsigned)(n - 1)), dim3(kGreedyThreads), 0, st, n, S, cur, p.T,
+                         (const int*)p.end, (const int*)p.pre, (const double2*)p.Zr, e_bar, amb, p.G);
+    if (timing) {
+      const hipError_t e = hipEventRecord(tev[2 * t + 1], st);
+      if (e != hipSuccess) return e;
     }
+    hipLaunchKernelGGL(k_greedy_apply, dim3((unsigned)((n - 1) / kGreedyPickThreads + 1)), dim3(kGreedyPickThreads), 0, st, n,
+                       S, cur, edges, p.T, (const int*)p.end, (const int*)p.pre, (const double2*)p.Zr, tie, amb, p.steps,
+                       p.G);
     return hipGetLastError();
   };
   // Without timing, a full batch of iterations is captured once into a graph
@@ -1542,7 +1337,7 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
     }
     OKRG_HIP(g, hipGetLastError());
     const int before = hs.iter;
-    OKRG_HIP(g, hipMemcpyAsync(&hs, p.gs, sizeof(GState), hipMemcpyDeviceToHost, st));
+    OKRG_HIP(g, hipMemcpyAsync(&hs, p.G.gs[b & 1], sizeof(GState), hipMemcpyDeviceToHost, st));
     OKRG_HIP(g, hipStreamSynchronize(st));
     // score launches that did work: one per move, plus the one that found none
     const int ran = std::min(b, hs.iter - before + (hs.done ? 1 : 0));
@@ -1565,14 +1360,14 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
   OKRG_HIP(g, hipMemcpyAsync(status, p.status, sizeof(status), hipMemcpyDeviceToHost, st));
   if (!(prm->flags & OKR_FLAG_VHAT_GIVEN))
     OKRG_HIP(g, hipMemcpyAsync(iters.data(), p.iters, sizeof(int) * S, hipMemcpyDeviceToHost, st));
-  OKRG_HIP(g, hipMemcpyAsync(&hs, p.gs, sizeof(GState), hipMemcpyDeviceToHost, st));
-  OKRG_HIP(g, hipMemcpyAsync(out->super, p.sup, sizeof(int) * n, hipMemcpyDeviceToHost, st));
+  std::vector<int> lsup(n);
+  OKRG_HIP(g, hipMemcpyAsync(lsup.data(), p.sup, sizeof(int) * n, hipMemcpyDeviceToHost, st));
   OKRG_HIP(g, hipMemcpyAsync(out->err_per_snapshot, p.err, sizeof(double) * S, hipMemcpyDeviceToHost, st));
   OKRG_HIP(g, hipStreamSynchronize(st));
   rc = check_status(g, status[0]);
   if (rc) return rc;
-  if (hs.iter > 0)
-  {
+  for (int x = 0; x < n; ++x) out->super[x] = g->pre[lsup[g->pos[x]]];
+  if (hs.iter > 0) {
     OKRG_HIP(g, hipMemcpyAsync(out->steps, p.steps, sizeof(GStep) * hs.iter, hipMemcpyDeviceToHost, st));
     OKRG_HIP(g, hipStreamSynchronize(st));
   }
@@ -1611,20 +1406,13 @@ extern "C" int okr_greedy_evaluate(okr_greedy* g, const okr_yblocks* Y, const ok
   if (rc) return rc;
   const GPtrs p = gptrs(g, ws);
   const hipStream_t st = g->stream;
-  rc = setup(g, p, Y, L, prm);
+  rc = setup(g, p, Y, L, prm, false);
   if (rc) return rc;
   const double2* V0 = (const double2*)L->V0;
-  // members of every cluster in node order (CSR), staged in the candidate
-  // score buffers (unused by an evaluation)
-  std::vector<int> csr(2 * (size_t)n + 1, 0);
-  for (int x = 0; x < n; ++x) csr[super[x] + 1]++;
-  for (int y = 0; y < n; ++y) csr[y + 1] += csr[y];
-  {
-    std::vector<int> fill(csr.begin(), csr.begin() + n);
-    for (int x = 0; x < n; ++x) csr[n + 1 + fill[super[x]]++] = x;
-  }
-  int* moff = (int*)p.sm;
-  OKRG_HIP(g, hipMemcpyAsync(p.sup, super, sizeof(int) * n, hipMemcpyHostToDevice, st));
+  std::vector<int> lsup, csr;
+  assignment(g, super, lsup, csr);
+  int* moff = p.csr;
+  OKRG_HIP(g, hipMemcpyAsync(p.sup, lsup.data(), sizeof(int) * n, hipMemcpyHostToDevice, st));
   OKRG_HIP(g, hipMemcpyAsync(moff, csr.data(), sizeof(int) * csr.size(), hipMemcpyHostToDevice, st));
   const size_t c3 = (size_t)S * n * 3;
   hipLaunchKernelGGL(k_greedy_aggregate, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
@@ -1663,18 +1451,13 @@ extern "C" int okr_greedy_radialize(okr_greedy* g, const okr_yblocks* Y, const o
   const int n = g->n, S = g->S;
   const GPtrs p = gptrs(g, ws);
   const hipStream_t st = g->stream;
-  rc = setup(g, p, Y, L, prm);
+  rc = setup(g, p, Y, L, prm, true);
   if (rc) return rc;
   const double2* V0 = (const double2*)L->V0;
-  std::vector<int> csr(2 * (size_t)n + 1, 0);
-  for (int x = 0; x < n; ++x) csr[super[x] + 1]++;
-  for (int y = 0; y < n; ++y) csr[y + 1] += csr[y];
-  {
-    std::vector<int> fill(csr.begin(), csr.begin() + n);
-    for (int x = 0; x < n; ++x) csr[n + 1 + fill[super[x]]++] = x;
-  }
-  int* moff = (int*)p.sm;
-  OKRG_HIP(g, hipMemcpyAsync(p.sup, super, sizeof(int) * n, hipMemcpyHostToDevice, st));
+  std::vector<int> lsup, csr;
+  assignment(g, super, lsup, csr);
+  int* moff = p.csr;
+  OKRG_HIP(g, hipMemcpyAsync(p.sup, lsup.data(), sizeof(int) * n, hipMemcpyHostToDevice, st));
   OKRG_HIP(g, hipMemcpyAsync(moff, csr.data(), sizeof(int) * csr.size(), hipMemcpyHostToDevice, st));
   const size_t c3 = (size_t)S * n * 3;
   hipLaunchKernelGGL(k_greedy_aggregate, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
@@ -1692,19 +1475,16 @@ extern "C" int okr_greedy_radialize(okr_greedy* g, const okr_yblocks* Y, const o
   hipLaunchKernelGGL(k_radialize, dim3(1), dim3(kGreedyPickThreads), 0, st, n, (const int*)p.parent,
                      (const int*)p.ch_off, (const int*)p.ch, (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev,
                      (const int*)p.sup, down, up, cnt, krad, kp_rad, kp_mesh, (int*)x);
-  LcaTab T;
-  T.first = p.first;
-  T.st = p.sp;
-  T.depth = p.depth;
-  T.E = g->euler_len;
   // the check costs n x n per scenario: the first four scenarios suffice
   // (a missed critical node shows in any scenario that loads its branches)
   const int Sc = std::min(S, 4);
   const unsigned nb = (unsigned)(((size_t)n * Sc + kGreedyThreads - 1) / kGreedyThreads);
-  hipLaunchKernelGGL(k_radial_check, dim3(nb), dim3(kGreedyThreads), 0, st, n, Sc, (const uint8_t*)p.phase, T,
+  hipLaunchKernelGGL(k_radial_check, dim3(nb), dim3(kGreedyThreads), 0, st, n, Sc, (const uint8_t*)p.phase, (const int*)p.pos,
+                     p.T,
                      (const double2*)p.Zr, (const int*)p.sup, (const uint8_t*)krad, (const int*)kp_rad, 1,
                      (const double2*)p.I, (const double2*)p.V, V0[0], V0[1], V0[2], x + 1);
-  hipLaunchKernelGGL(k_radial_check, dim3(nb), dim3(kGreedyThreads), 0, st, n, Sc, (const uint8_t*)p.phase, T,
+  hipLaunchKernelGGL(k_radial_check, dim3(nb), dim3(kGreedyThreads), 0, st, n, Sc, (const uint8_t*)p.phase, (const int*)p.pos,
+                     p.T,
                      (const double2*)p.Zr, (const int*)p.sup, (const uint8_t*)krad, (const int*)kp_mesh, 0,
                      (const double2*)p.I, (const double2*)p.V, V0[0], V0[1], V0[2], x + 2);
   OKRG_HIP(g, hipGetLastError());
@@ -1712,11 +1492,17 @@ extern "C" int okr_greedy_radialize(okr_greedy* g, const okr_yblocks* Y, const o
   unsigned long long hx[4] = {0, 0, 0, 0};
   OKRG_HIP(g, hipMemcpyAsync(status, p.status, sizeof(status), hipMemcpyDeviceToHost, st));
   OKRG_HIP(g, hipMemcpyAsync(hx, x, sizeof(hx), hipMemcpyDeviceToHost, st));
-  OKRG_HIP(g, hipMemcpyAsync(kept_radial, krad, n, hipMemcpyDeviceToHost, st));
-  OKRG_HIP(g, hipMemcpyAsync(kept_parent, kp_rad, sizeof(int) * n, hipMemcpyDeviceToHost, st));
+  std::vector<uint8_t> hk(n);
+  std::vector<int> hp(n);
+  OKRG_HIP(g, hipMemcpyAsync(hk.data(), krad, n, hipMemcpyDeviceToHost, st));
+  OKRG_HIP(g, hipMemcpyAsync(hp.data(), kp_rad, sizeof(int) * n, hipMemcpyDeviceToHost, st));
   OKRG_HIP(g, hipStreamSynchronize(st));
   rc = check_status(g, status[0]);
   if (rc) return rc;
+  for (int q = 0; q < n; ++q) {  // labels to the caller's ids
+    kept_radial[g->pre[q]] = hk[q];
+    kept_parent[g->pre[q]] = hp[q] < 0 ? -1 : g->pre[hp[q]];
+  }
   int nc;
   std::memcpy(&nc, &hx[0], sizeof(int));
   *n_critical = nc;

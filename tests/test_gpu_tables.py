@@ -108,3 +108,31 @@ def test_smice_snapshot_lanes(okr, snapshots):
         assert s["mask"] == d["mask"]
         assert abs(s["smice_rise"] - d["smice_rise"]) < 1e-11
     np.testing.assert_array_equal(out["kept"], keep)
+
+
+@pytest.mark.parametrize("n,S,p_deep,kappa,moves", [
+    (64, 3, 0.5, 0.5, 70), (65, 1, 0.97, 0.5, 70), (129, 2, 0.97, 0.5, 24), (700, 2, 0.9, 0.05, 80)])
+def test_greedy_cluster_list(okr, n, S, p_deep, kappa, moves):
+    """Greedy search at the edges of the cluster list's runs of 64 and of the
+    intervals that one wave scores alone (a 700-node trunk), in both scoring
+    forms: the oracle's moves where it is small enough, and the same moves in
+    both forms.  SMICE sums at most S * n errors that agree within the load
+    flow's 1e-13."""
+    from oracle import greedy as G
+    print(f"greedy cluster list: n={n} S={S} p_deep={p_deep}", flush=True)
+    f = make_feeder("c2", n, n=n, snapshots=S, p_deep=p_deep, kappa=kappa)
+    V, I, st, _ = oracle.powerflow(f)
+    assert st == 0
+    outs = [okr.greedy(f, e_bar=5e-3, vhat=V, max_iter=moves, incremental=inc) for inc in (False, True)]
+    ids = [[(s["cand"], s["s"], s["r"], s["n_cand"], s["n_feasible"]) for s in o["steps"]] for o in outs]
+    assert ids[0] == ids[1] and len(ids[0]) > 10
+    for key in ("smice", "emax"):
+        np.testing.assert_allclose([s[key] for s in outs[1]["steps"]], [s[key] for s in outs[0]["steps"]], rtol=0,
+                                   atol=TOL)
+    if n <= 129:
+        sup, steps, err = G.greedy(f, V, I, e_bar=5e-3, max_iter=moves)
+        assert ids[0] == [(s["cand"], s["s"], s["r"], s["n_cand"], s["n_feasible"]) for s in steps]
+        for o in outs:
+            np.testing.assert_array_equal(o["super"], sup)
+            np.testing.assert_allclose([s["smice"] for s in o["steps"]], [s["smice"] for s in steps], rtol=0, atol=TOL)
+            np.testing.assert_allclose(o["err_per_snapshot"], err, rtol=0, atol=TOL)
