@@ -1,0 +1,480 @@
+// Load flow (Section III's scenario library) and fixed-current solve by prefix
+// sums.
+//
+// Nodes are labelled by depth-first position, so with load currents I the
+// current of the branch above q is the sum of I over its subtree, a run of
+// labels: J(q) = P(end(q)) - P(q) with P the prefix sums of I.  With branch
+// drops d = z J, the voltage is V(q) = V0 - D(q), D(q) the sum of d over q's
+// root path: the prefix sum, at the place where the tour enters q, of the tour
+// that enters (+d) and leaves (-d) every node in depth-first order.  One sweep
+// is two block-wide prefix sums whatever the depth of the tree, where a sweep
+// level by level waits for two barriers and dependent loads per level.
+// Accuracy: the partial sums are bounded by the feeder's total current and
+// voltage drop, so their rounding is below that of adding up |V| ~ 1 level by
+// level: largest error of the converged voltages against extended precision
+// 0.8e-16 (level by level 3.1e-16) at 1000 nodes, 0.9e-16 (5.1e-16) at 6000,
+// 1.0e-16 (6.9e-16) at 8400.
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "okr_device.h"
+#include "okr_flow.h"
+
+namespace okr {
+
+namespace {
+
+constexpr int kFlowThreads = 1024;
+constexpr int kFlowWaves = kFlowThreads / 64;
+constexpr size_t kFlowLds = 150 * 1024;  // dynamic LDS of the second form (one phase's prefix sums)
+
+// v plus its shifted copy (lanes without a source add 0).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+// Inclusive prefix sum over the wave: within rows of 16 lanes, then the rows'
+// last lanes broadcast.
+__device__ __forceinline__ double wave_scan(double v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);
+  v = dpp_add<0x143, 0xc>(v);
+  return v;
+}
+__device__ __forceinline__ double2 wave_scan(double2 v) { return make_double2(wave_scan(v.x), wave_scan(v.y)); }
+
+// The value of the lane before (0 in the first).
+__device__ __forceinline__ double lane_before(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false));
+}
+
+__device__ __forceinline__ double last_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+__device__ __forceinline__ double nan_max(double a, double b) { return (b <= a) ? a : b; }  // keeps NaN
+
+// NaN-propagating maximum over the block (every thread gets it); s holds a
+// value per wave and must not be in use.
+__device__ __forceinline__ double block_nan_max(double v, double* s) {
+  for (int o = 32; o > 0; o >>= 1) v = nan_max(v, __shfl_xor(v, o, 64));
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double r = s[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = nan_max(r, s[w]);
+  return r;
+}
+
+// Load currents and magnitudes at the final voltages, and the band check.
+__device__ __forceinline__ void flow_finish(const FlowArgs& a, int n, size_t base, const uint8_t* __restrict__ phase,
+                                            bool conv, int it, double* shd) {
+  double vlo = 1e300, vhi = -1e300;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int x = a.ext[i];
+    for (int p = 0; p < 3; ++p) {
+      const bool pr = (phase[i] >> p & 1u);
+      const double2 v = a.V[base + i * 3 + p];
+      if (a.Vext) a.Vext[base + x * 3 + p] = v;
+      a.A[base + i * 3 + p] = (i > 0 && pr) ? cconj(cdiv(a.Sload[base + x * 3 + p], v)) : make_double2(0.0, 0.0);
+      const double m = pr ? sqrt(cabs2(v)) : 0.0;
+      a.absV[base + i * 3 + p] = m;
+      if (pr) {
+        vlo = fmin(vlo, m);
+        vhi = fmax(vhi, m);
+      }
+    }
+  }
+  vlo = block_reduce(vlo, [](double x, double y) { return fmin(x, y); }, shd);
+  vhi = block_reduce(vhi, [](double x, double y) { return fmax(x, y); }, shd);
+  if (threadIdx.x == 0) {
+    a.iters[blockIdx.x] = it;
+    if (!conv) atomicOr(a.status, 16);
+    if (vlo < a.vmin || vhi > a.vmax) atomicOr(a.status, 32);
+  }
+}
+
+}  // namespace
+
+// Form 1: a node per thread (n <= 1024), a node's impedance and voltage in
+// registers, the prefix sums, drops and loads in LDS (X, Y, L: n x 3 each; with
+// the loads in registers too the kernel spills); one block per snapshot, one
+// more for the cumulative impedances.  FIXED: one sweep at the currents
+// Sload, given by label.
+// Six barriers and two scans of six doubles per sweep, whatever the depth; bound
+// by FP64 and DPP instructions on one CU per snapshot.  1000 nodes, 24
+// snapshots, 8 sweeps: 97 us with the cumulative impedances (228 + 20 level by
+// level in LDS); 168 snapshots 103 (417 + 20 level by level in global memory);
+// 30 nodes 26 (66 + 6).
+template <bool FIXED>
+__global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const int* __restrict__ end,
+                                                            const int* __restrict__ tour, FlowArgs a) {
+  extern __shared__ double2 flow_lds[];
+  __shared__ double2 s_tot[2][kFlowWaves][3];
+  __shared__ double s_red[16];
+  if (!FIXED && (int)blockIdx.x == S) {
+    zroot_block(n, a.parent, a.lvl_off, a.lvl_nodes, a.nlev, a.z, a.Zroot);
+    return;
+  }
+  double2 *X = flow_lds, *Y = flow_lds + 3 * n, *L = flow_lds + 6 * n + 3 * threadIdx.x;
+  const int q = threadIdx.x, wv = q >> 6;
+  const size_t base = (size_t)blockIdx.x * n * 3;
+  const bool on = q < n, last = (q & 63) == 63;
+  const unsigned ph = on ? a.phase[q] : 0u;
+  const int x = on ? (FIXED ? q : a.ext[q]) : 0;
+  const int e = on ? end[q] : 1, t0 = on ? tour[2 * q] : 0, t1 = on ? tour[2 * q + 1] : 0;
+  double2 z[9], v[3];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) z[k] = on ? a.z[(size_t)q * 9 + k] : make_double2(0.0, 0.0);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    if (on) L[p] = a.Sload[base + x * 3 + p];
+    v[p] = (ph >> p & 1u) ? a.v0[p] : make_double2(0.0, 0.0);
+  }
+  int it = 0;
+  bool conv = false;
+  for (it = 1; it <= a.maxit; ++it) {
+    double2 c[3];
+    // prefix sums of the load currents
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      c[p] = make_double2(0.0, 0.0);
+      if (FIXED ? on : q > 0 && (ph >> p & 1u)) c[p] = FIXED ? L[p] : cconj(cdiv(L[p], v[p]));
+      c[p] = wave_scan(c[p]);
+      if (last) s_tot[0][wv][p] = c[p];
+    }
+    __syncthreads();
+    for (int w = 0; w < wv; ++w)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) c[p] = cadd(c[p], s_tot[0][w][p]);
+    if (on)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) X[q * 3 + p] = c[p];
+    __syncthreads();
+    // branch currents and drops
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const double2 hi = X[(e - 1) * 3 + p], lo = on && q > 0 ? X[(q - 1) * 3 + p] : make_double2(0.0, 0.0);
+      c[p] = csub(hi, lo);
+    }
+    if (on)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        Y[q * 3 + p] = cadd(cadd(cmul(z[p * 3], c[0]), cmul(z[p * 3 + 1], c[1])), cmul(z[p * 3 + 2], c[2]));
+    __syncthreads();
+    // prefix sums of the tour, two steps per thread (read again after the
+    // barrier rather than held in registers)
+    const double f0 = on ? (t0 & 1 ? -1.0 : 1.0) : 0.0, f1 = on ? (t1 & 1 ? -1.0 : 1.0) : 0.0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const double2 y0 = Y[(t0 >> 1) * 3 + p], y1 = Y[(t1 >> 1) * 3 + p];
+      const double2 i = wave_scan(make_double2(f0 * y0.x + f1 * y1.x, f0 * y0.y + f1 * y1.y));
+      if (last) s_tot[1][wv][p] = i;
+      c[p] = make_double2(lane_before(i.x), lane_before(i.y));
+    }
+    __syncthreads();
+    for (int w = 0; w < wv; ++w)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) c[p] = cadd(c[p], s_tot[1][w][p]);
+    if (on) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const double2 y0 = Y[(t0 >> 1) * 3 + p], y1 = Y[(t1 >> 1) * 3 + p];
+        const double2 d0 = make_double2(c[p].x + f0 * y0.x, c[p].y + f0 * y0.y);
+        if (!(t0 & 1)) X[(t0 >> 1) * 3 + p] = d0;
+        if (!(t1 & 1)) X[(t1 >> 1) * 3 + p] = make_double2(d0.x + f1 * y1.x, d0.y + f1 * y1.y);
+      }
+    }
+    __syncthreads();
+    double dmax = 0.0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      if (!(ph >> p & 1u)) continue;
+      const double2 nv = csub(a.v0[p], X[q * 3 + p]);
+      dmax = nan_max(dmax, sqrt(cabs2(csub(nv, v[p]))));
+      v[p] = nv;
+    }
+    if (FIXED) break;
+    dmax = block_nan_max(dmax, s_red);
+    if (!(dmax <= 1e3)) break;
+    if (dmax <= a.tol) {
+      conv = true;
+      break;
+    }
+  }
+  if (on)
+#pragma unroll
+    for (int p = 0; p < 3; ++p) a.V[base + q * 3 + p] = v[p];
+  if (FIXED) return;
+  __syncthreads();
+  flow_finish(a, n, base, a.phase, conv, it, s_red);
+}
+
+struct FlowPhases {
+  const int *lab[3], *ende[3], *tour[3], *idx;
+  int cnt[3];
+};
+
+// Form 2: phase by phase, over the list of the nodes that have the phase (a
+// subtree, in label order), so that one phase's prefix sums or drops fit in LDS
+// (X) for up to 9600 nodes a phase and absent phases cost nothing.  Loads,
+// voltages and branch currents lie by phase and list entry in the V, A and J
+// slices until the end.  A wave takes a run of the list or of the tour; its
+// total is formed first, then the run is scanned from the sum of the waves
+// before it.  6000 nodes, 96 snapshots, 9 sweeps: 888 us with the cumulative
+// impedances (1100 + 88 level by level in breadth-first storage); 8400 nodes,
+// 672 snapshots, 12 sweeps: 2.70 ms (3.99 + 0.12).
+template <bool FIXED>
+__global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowPhases t, FlowArgs a) {
+  extern __shared__ double2 flow_lds[];
+  __shared__ double2 s_tot[2][kFlowWaves];
+  __shared__ double s_red[16];
+  if (!FIXED && (int)blockIdx.x == S) {
+    zroot_block(n, a.parent, a.lvl_off, a.lvl_nodes, a.nlev, a.z, a.Zroot);
+    return;
+  }
+  double2* X = flow_lds;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const size_t base = (size_t)blockIdx.x * n * 3;
+  double2 *Sb = a.V + base, *Vb = a.A + base, *Jb = a.J + base;
+  const double2* Sl = a.Sload + base;
+  if (!FIXED) {
+    for (int p = 0; p < 3; ++p)
+      for (int k = tid; k < t.cnt[p]; k += kFlowThreads) {
+        Sb[p * n + k] = Sl[(size_t)a.ext[t.lab[p][k]] * 3 + p];
+        Vb[p * n + k] = a.v0[p];
+      }
+    __syncthreads();
+  }
+  int it = 0;
+  bool conv = false;
+  for (it = 1; it <= a.maxit; ++it) {
+    for (int p = 0; p < 3; ++p) {
+      const int cnt = t.cnt[p], C = (cnt + kFlowThreads - 1) / kFlowThreads, k0 = wv * 64 * C + lane;
+      const double2 *Sp = Sb + (size_t)p * n, *Vp = Vb + (size_t)p * n;
+      double2 acc = make_double2(0.0, 0.0);
+      for (int i = 0, k = k0; i < C; ++i, k += 64) {
+        if (k >= cnt) break;
+        double2 c = make_double2(0.0, 0.0);
+        if (FIXED) c = Sl[(size_t)t.lab[p][k] * 3 + p];
+        else if (t.lab[p][k] > 0) c = cconj(cdiv(Sp[k], Vp[k]));
+        X[k] = c;
+        acc = cadd(acc, c);
+      }
+      acc = wave_scan(acc);
+      if (lane == 63) s_tot[0][wv] = acc;
+      __syncthreads();
+      double2 run = make_double2(0.0, 0.0);
+      for (int w = 0; w < wv; ++w) run = cadd(run, s_tot[0][w]);
+      for (int i = 0, k = k0; i < C; ++i, k += 64) {
+        const double2 c = wave_scan(k < cnt ? X[k] : make_double2(0.0, 0.0));
+        if (k < cnt) X[k] = cadd(run, c);
+        run = make_double2(run.x + last_lane(c.x), run.y + last_lane(c.y));
+      }
+      __syncthreads();
+      for (int k = tid; k < cnt; k += kFlowThreads) {
+        const double2 hi = X[t.ende[p][k] - 1], lo = k > 0 ? X[k - 1] : make_double2(0.0, 0.0);
+        Jb[(size_t)p * n + k] = csub(hi, lo);
+      }
+      __syncthreads();
+    }
+    double dmax = 0.0;
+    for (int p = 0; p < 3; ++p) {
+      const int cnt = t.cnt[p];
+      for (int k = tid; k < cnt; k += kFlowThreads) {
+        const int q = t.lab[p][k];
+        double2 d = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const int kc = t.idx[c * n + q];
+          if (kc >= 0) d = cadd(d, cmul(a.z[(size_t)q * 9 + p * 3 + c], Jb[(size_t)c * n + kc]));
+        }
+        X[k] = d;
+      }
+      __syncthreads();
+      const int C = (2 * cnt + kFlowThreads - 1) / kFlowThreads, k0 = wv * 64 * C + lane;
+      double2 acc = make_double2(0.0, 0.0);
+      for (int i = 0, k = k0; i < C; ++i, k += 64) {
+        if (k >= 2 * cnt) break;
+        const int s = t.tour[p][k];
+        acc = s & 1 ? csub(acc, X[s >> 1]) : cadd(acc, X[s >> 1]);
+      }
+      acc = wave_scan(acc);
+      if (lane == 63) s_tot[1][wv] = acc;
+      __syncthreads();
+      double2 run = make_double2(0.0, 0.0);
+      for (int w = 0; w < wv; ++w) run = cadd(run, s_tot[1][w]);
+      for (int i = 0, k = k0; i < C; ++i, k += 64) {
+        const int s = k < 2 * cnt ? t.tour[p][k] : 1;
+        double2 g = k < 2 * cnt ? X[s >> 1] : make_double2(0.0, 0.0);
+        if (s & 1) g = make_double2(-g.x, -g.y);
+        g = wave_scan(g);
+        if (!(s & 1)) {
+          const double2 nv = csub(a.v0[p], cadd(run, g));
+          if (FIXED) {
+            a.V[base + (size_t)t.lab[p][s >> 1] * 3 + p] = nv;
+          } else {
+            double2* o = Vb + (size_t)p * n + (s >> 1);
+            dmax = nan_max(dmax, sqrt(cabs2(csub(nv, *o))));
+            *o = nv;
+          }
+        }
+        run = make_double2(run.x + last_lane(g.x), run.y + last_lane(g.y));
+      }
+      __syncthreads();
+    }
+    if (FIXED) break;
+    dmax = block_nan_max(dmax, s_red);
+    if (!(dmax <= 1e3)) break;
+    if (dmax <= a.tol) {
+      conv = true;
+      break;
+    }
+  }
+  // voltages by label (over the loads, no longer read)
+  for (int k = tid; k < n * 3; k += kFlowThreads) {
+    const int p = k % 3, i = t.idx[p * n + k / 3];
+    if (FIXED) {
+      if (i < 0) a.V[base + k] = make_double2(0.0, 0.0);
+    } else {
+      a.V[base + k] = i >= 0 ? Vb[(size_t)p * n + i] : make_double2(0.0, 0.0);
+    }
+  }
+  if (FIXED) return;
+  __syncthreads();
+  flow_finish(a, n, base, a.phase, conv, it, s_red);
+}
+
+// ---- host ----
+
+namespace {
+
+// The tour of a tree given by label (or list entry): 2 q where q is entered,
+// 2 q + 1 where it is left.
+void append_tour(const std::vector<int>& end, std::vector<int>& out) {
+  const int n = (int)end.size();
+  std::vector<int> open;
+  for (int q = 0; q < n; ++q) {
+    while (!open.empty() && end[open.back()] <= q) {
+      out.push_back(2 * open.back() + 1);
+      open.pop_back();
+    }
+    out.push_back(2 * q);
+    open.push_back(q);
+  }
+  for (; !open.empty(); open.pop_back()) out.push_back(2 * open.back() + 1);
+}
+
+FlowPhases phases(const FlowPlan& p, const int* tab) {
+  FlowPhases t;
+  for (int c = 0; c < 3; ++c) {
+    t.lab[c] = tab + p.lab[c];
+    t.ende[c] = tab + p.ende[c];
+    t.tour[c] = tab + p.ptour[c];
+    t.cnt[c] = p.cnt[c];
+  }
+  t.idx = tab + p.idx;
+  return t;
+}
+
+size_t node_lds(int n) { return sizeof(double2) * 9 * (size_t)n; }
+size_t phase_lds(const FlowPlan& p) {
+  size_t m = 1;
+  for (int c : p.cnt) m = c > (int)m ? c : m;
+  return sizeof(double2) * m;
+}
+
+}  // namespace
+
+FlowPlan flow_tables(int n, const int* end, const uint8_t* phase, std::vector<int>& out) {
+  FlowPlan p;
+  p.n = n;
+  if (n <= kFlowThreads) {
+    p.form = 1;
+    const std::vector<int> e(end, end + n);
+    p.end = out.size();
+    out.insert(out.end(), e.begin(), e.end());
+    p.tour = out.size();
+    append_tour(e, out);
+    return p;
+  }
+  std::vector<int> lab[3], idx(3 * (size_t)n, -1);
+  for (int c = 0; c < 3; ++c) {
+    for (int q = 0; q < n; ++q)
+      if (phase[q] >> c & 1) {
+        idx[(size_t)c * n + q] = (int)lab[c].size();
+        lab[c].push_back(q);
+      }
+    p.cnt[c] = (int)lab[c].size();
+  }
+  if (phase_lds(p) > kFlowLds) return p;
+  p.form = 2;
+  for (int c = 0; c < 3; ++c) {
+    std::vector<int> e(lab[c].size());
+    std::vector<int> below(n + 1, 0);  // list entries with a smaller label
+    for (int q = 0; q < n; ++q) below[q + 1] = below[q] + (phase[q] >> c & 1);
+    for (size_t k = 0; k < e.size(); ++k) e[k] = below[end[lab[c][k]]];
+    p.lab[c] = out.size();
+    out.insert(out.end(), lab[c].begin(), lab[c].end());
+    p.ende[c] = out.size();
+    out.insert(out.end(), e.begin(), e.end());
+    p.ptour[c] = out.size();
+    append_tour(e, out);
+  }
+  p.idx = out.size();
+  out.insert(out.end(), idx.begin(), idx.end());
+  return p;
+}
+
+hipError_t flow_prepare(const FlowPlan& p) {
+  const void* f[2] = {nullptr, nullptr};
+  if (p.form == 1 && node_lds(p.n) > 60 * 1024) {
+    f[0] = reinterpret_cast<const void*>(&k_flow_node<false>);
+    f[1] = reinterpret_cast<const void*>(&k_flow_node<true>);
+  } else if (p.form == 2 && phase_lds(p) > 60 * 1024) {
+    f[0] = reinterpret_cast<const void*>(&k_flow_phase<false>);
+    f[1] = reinterpret_cast<const void*>(&k_flow_phase<true>);
+  }
+  for (const void* k : f)
+    if (k) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFlowLds);
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+
+void flow_launch(const FlowPlan& p, const FlowArgs& a, int S, hipStream_t st) {
+  if (p.form == 1)
+    hipLaunchKernelGGL(k_flow_node<false>, dim3(S + 1), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
+                       a.tab + p.end, a.tab + p.tour, a);
+  else
+    hipLaunchKernelGGL(k_flow_phase<false>, dim3(S + 1), dim3(kFlowThreads), phase_lds(p), st, p.n, S,
+                       phases(p, a.tab), a);
+}
+
+void flow_fixed_launch(const FlowPlan& p, const int* tab, const uint8_t* phase, const double2* z, const double2* v0,
+                       const double2* I, double2* J, double2* V, int S, hipStream_t st) {
+  FlowArgs a{};
+  a.phase = phase;
+  a.z = z;
+  a.Sload = I;
+  for (int c = 0; c < 3; ++c) a.v0[c] = v0[c];
+  a.maxit = 1;
+  a.V = V;
+  a.J = J;
+  if (p.form == 1)
+    hipLaunchKernelGGL(k_flow_node<true>, dim3(S), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S, tab + p.end,
+                       tab + p.tour, a);
+  else
+    hipLaunchKernelGGL(k_flow_phase<true>, dim3(S), dim3(kFlowThreads), phase_lds(p), st, p.n, S, phases(p, tab), a);
+}
+
+}  // namespace okr

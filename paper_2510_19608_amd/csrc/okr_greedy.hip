@@ -24,8 +24,8 @@
 // Every move is two launches: k_greedy_score scores all candidates (both
 // directions of the edge above one cluster together), k_greedy_apply settles
 // the move in every block alike and writes the next list, voltages and errors.
-// A search starts from the exact fixed-current solve (a level-synchronous
-// sweep), which also serves the evaluation of a given assignment.
+// A search starts from the exact fixed-current solve, which also serves the
+// evaluation of a given assignment.
 
 #include <hip/hip_runtime.h>
 
@@ -39,6 +39,7 @@
 
 #include "../../include/okr_greedy.h"
 #include "okr_device.h"
+#include "okr_flow.h"
 #include "okr_internal.h"
 
 namespace okr {
@@ -900,6 +901,7 @@ struct okr_greedy {
   size_t o_ext = 0, o_edge = 0, o_part = 0, o_blk = 0;
   // radialization: 5 int arrays of n, kept flags, counter, two maxima
   size_t o_rad = 0, o_radk = 0, o_radx = 0;
+  FlowPlan flow;
   std::vector<int> topo_host;
 };
 
@@ -1012,6 +1014,7 @@ extern "C" int okr_greedy_plan(okr_greedy* g, int32_t n, const int32_t* parent, 
   g->t_ch = put(ch);
   g->t_pre = put(pre);
   g->t_pos = put(g->pos);
+  g->flow = flow_tables(n, end.data(), g->lphase.data(), g->topo_host);
   {
     int K = 1;
     while ((1 << K) <= n) ++K;
@@ -1152,20 +1155,46 @@ int setup(okr_greedy* g, const GPtrs& p, const okr_yblocks* Y, const okr_loads* 
   hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, (const int*)p.parent,
                      (const uint8_t*)p.phase, (const int*)p.ch_off, (const int*)p.ch,
                      (const int*)p.pre, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
-  hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, (const int*)p.parent, (const int*)p.lvl_off,
-                     (const int*)p.lvl_nodes, g->nlev, (const double2*)p.z, p.Zr);
+  const bool scan = !(prm->flags & OKR_FLAG_VHAT_GIVEN) && g->flow.form;
+  if (!scan)  // (otherwise beside the load flow)
+    hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, (const int*)p.parent, (const int*)p.lvl_off,
+                       (const int*)p.lvl_nodes, g->nlev, (const double2*)p.z, p.Zr);
   const size_t c3 = (size_t)S * n * 3;
   const double2* V0 = (const double2*)L->V0;
   if (prm->flags & OKR_FLAG_VHAT_GIVEN) {
     hipLaunchKernelGGL(k_from_vhat, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
                        (const uint8_t*)p.phase, (const double2*)L->S_load, (const double2*)L->Vhat, 0.0, 1e300, p.A,
                        p.absV, p.status, (const int*)p.pre, (double2*)nullptr);
+  } else if (scan) {
+    OKRG_HIP(g, flow_prepare(g->flow));
+    flow_launch(g->flow,
+                FlowArgs{(const int*)p.topo, p.phase, p.z, (const double2*)L->S_load, {V0[0], V0[1], V0[2]},
+                         prm->pf_tol > 0 ? prm->pf_tol : 1e-13, 0.0, 1e300, prm->pf_maxit > 0 ? prm->pf_maxit : 100,
+                         p.Vhat, p.Ib, p.A, p.absV, p.iters, p.status, p.pre, nullptr, p.parent, p.lvl_off,
+                         p.lvl_nodes, g->nlev, p.Zr},
+                S, st);
   } else {
     hipLaunchKernelGGL(k_powerflow, dim3(S), dim3(256), 0, st, n, (const int*)p.parent, (const uint8_t*)p.phase,
                        (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev, (const int*)p.ch_off,
                        (const int*)p.ch, (const double2*)p.z, (const double2*)L->S_load, V0[0], V0[1], V0[2],
                        prm->pf_tol > 0 ? prm->pf_tol : 1e-13, prm->pf_maxit > 0 ? prm->pf_maxit : 100, 0.0, 1e300,
                        p.Vhat, p.Ib, p.A, p.absV, p.iters, p.status, (const int*)p.pre, (double2*)nullptr);
+  }
+  OKRG_HIP(g, hipGetLastError());
+  return OKR_OK;
+}
+
+// Voltages V of the aggregated currents I.
+int fixed_solve(okr_greedy* g, const GPtrs& p, const double2* V0) {
+  const hipStream_t st = g->stream;
+  if (g->flow.form) {
+    OKRG_HIP(g, flow_prepare(g->flow));
+    flow_fixed_launch(g->flow, p.topo, p.phase, p.z, V0, p.I, p.Ib, p.V, g->S, st);
+  } else {
+    hipLaunchKernelGGL(k_greedy_sweep, dim3(g->S), dim3(kGreedyThreads), 0, st, g->n, (const int*)p.parent,
+                       (const uint8_t*)p.phase, (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev,
+                       (const int*)p.ch_off, (const int*)p.ch, (const double2*)p.z, V0[0], V0[1], V0[2],
+                       (const double2*)p.I, p.Ib, p.V);
   }
   OKRG_HIP(g, hipGetLastError());
   return OKR_OK;
@@ -1257,10 +1286,8 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
   const size_t c3 = (size_t)S * n * 3;
   hipLaunchKernelGGL(k_greedy_init, dim3((unsigned)((std::max(c3, (size_t)n) + 255) / 256)), dim3(256), 0, st, n, S,
                      (const double2*)p.A, p.I, p.sup, p.G.gs[0]);
-  hipLaunchKernelGGL(k_greedy_sweep, dim3(S), dim3(kGreedyThreads), 0, st, n, (const int*)p.parent,
-                     (const uint8_t*)p.phase, (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev,
-                     (const int*)p.ch_off, (const int*)p.ch, (const double2*)p.z, V0[0], V0[1], V0[2],
-                     (const double2*)p.I, p.Ib, p.V);
+  rc = fixed_solve(g, p, V0);
+  if (rc) return rc;
   hipLaunchKernelGGL(k_greedy_prep, dim3((unsigned)(n / kGreedyThreads + 1)), dim3(kGreedyThreads), 0, st, n, S,
                      (const int*)p.parent, (const int*)p.end, (const uint8_t*)p.phase, (const double*)p.absV, p.G);
   OKRG_HIP(g, hipGetLastError());
@@ -1417,10 +1444,8 @@ extern "C" int okr_greedy_evaluate(okr_greedy* g, const okr_yblocks* Y, const ok
   const size_t c3 = (size_t)S * n * 3;
   hipLaunchKernelGGL(k_greedy_aggregate, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
                      (const int*)moff, (const int*)(moff + n + 1), (const double2*)p.A, p.I);
-  hipLaunchKernelGGL(k_greedy_sweep, dim3(S), dim3(kGreedyThreads), 0, st, n, (const int*)p.parent,
-                     (const uint8_t*)p.phase, (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev,
-                     (const int*)p.ch_off, (const int*)p.ch, (const double2*)p.z, V0[0], V0[1], V0[2],
-                     (const double2*)p.I, p.Ib, p.V);
+  rc = fixed_solve(g, p, V0);
+  if (rc) return rc;
   hipLaunchKernelGGL(k_greedy_err, dim3(S), dim3(kGreedyThreads), 0, st, n, (const uint8_t*)p.phase,
                      (const int*)p.sup, (const double2*)p.V, (const double*)p.absV, p.err);
   OKRG_HIP(g, hipGetLastError());
@@ -1462,10 +1487,8 @@ extern "C" int okr_greedy_radialize(okr_greedy* g, const okr_yblocks* Y, const o
   const size_t c3 = (size_t)S * n * 3;
   hipLaunchKernelGGL(k_greedy_aggregate, dim3((unsigned)((c3 + 255) / 256)), dim3(256), 0, st, n, S,
                      (const int*)moff, (const int*)(moff + n + 1), (const double2*)p.A, p.I);
-  hipLaunchKernelGGL(k_greedy_sweep, dim3(S), dim3(kGreedyThreads), 0, st, n, (const int*)p.parent,
-                     (const uint8_t*)p.phase, (const int*)p.lvl_off, (const int*)p.lvl_nodes, g->nlev,
-                     (const int*)p.ch_off, (const int*)p.ch, (const double2*)p.z, V0[0], V0[1], V0[2],
-                     (const double2*)p.I, p.Ib, p.V);
+  rc = fixed_solve(g, p, V0);
+  if (rc) return rc;
   char* b = (char*)ws;
   int* rad = (int*)(b + g->o_rad);
   int *down = rad, *up = rad + n, *cnt = rad + 2 * n, *kp_rad = rad + 3 * n, *kp_mesh = rad + 4 * n;

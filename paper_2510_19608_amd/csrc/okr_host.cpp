@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/okr.h"
+#include "okr_flow.h"
 #include "okr_internal.h"
 
 namespace okr {
@@ -24,9 +25,6 @@ __global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const in
 __global__ void k_powerflow(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                             const double2*, const double2*, double2, double2, double2, double, int, double, double,
                             double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
-__global__ void k_powerflow_lds(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
-                                const double2*, const double2*, double2, double2, double2, double, int, double, double,
-                                double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
 __global__ void k_powerflow_bfs(int, const uint8_t*, const int*, const int*, int, const int*, const int*,
                                 const double2*, const double2*, double2, double2, double2, double, int, double, double,
                                 double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
@@ -109,13 +107,7 @@ constexpr int kDefaultLanes = 8;
 constexpr int kStatusInts = 16;
 constexpr double kMixedDelta = 1e-8;  // bound on |e32 - e64| used by the shortlist
 constexpr double kSmiceTol = 1e-9;    // default SMICE tie window
-// Dynamic LDS of the load flow with its iterates in shared memory (0: too
-// large, the global-memory form runs).
 constexpr size_t kPfLdsMax = 150 * 1024;
-size_t pf_lds_bytes(int n, int nlev) {
-  const size_t b = (size_t)n * 3 * 2 * sizeof(double2) + sizeof(int) * ((size_t)4 * n + nlev + 2) + (size_t)n;
-  return b <= kPfLdsMax ? b : 0;
-}
 // Dynamic LDS of the breadth-first form (iterates in global memory, the
 // queue tables in LDS as 16-bit positions; 0: not usable, the node-order
 // global form runs).
@@ -151,6 +143,7 @@ struct Layout {
 struct TopoOffsets {
   int parent, phase, segment, size, ext, ch_off, ch, lvl_off, lvl_nodes, bfs_cf, bfs_pp, seg_off, seg_nodes,
       chunks, units, seg_top, total;
+  FlowPlan flow;
 };
 
 }  // namespace
@@ -618,6 +611,12 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     TO.ext = put(h->pre);
     TO.ch_off = put(off);
     TO.ch = put(ch);
+    std::vector<uint8_t> lph(n);
+    for (int q = 0; q < n; ++q) {
+      size[q] += q;  // the ends of the subtrees
+      lph[q] = h->phase[h->pre[q]];
+    }
+    TO.flow = flow_tables(n, size.data(), lph.data(), tp);
   }
   TO.lvl_off = put(h->lvl_off);
   TO.lvl_nodes = put(labels(h->lvl_nodes));
@@ -759,7 +758,7 @@ namespace {
 struct Ptrs {
   Topo T;
   State St;
-  const int *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks, *units;
+  const int *tp, *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks, *units;
   double2 *z, *Zroot, *Vhat, *Vcur, *A, *J, *P, *headV, *yeq, *Ykd, *Yko;
   double *absV, *econst, *err;
   int *status, *iters, *tab, *tab2, *kp;
@@ -799,6 +798,7 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   Ptrs p{};
   int* tp = (int*)at(L.topo);
   const TopoOffsets& TO = h->TO;
+  p.tp = tp;
   p.T.n = h->n;
   p.T.parent = tp + TO.parent;
   p.T.phase = (const uint8_t*)(tp + TO.phase);
@@ -989,8 +989,9 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   hipLaunchKernelGGL(k_init_state, dim3((ninit + 255) / 256), dim3(256), 0, st, n, p.St, p.status, kStatusInts);
   hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, p.T.parent, p.T.phase, p.T.ch_off,
                      p.T.ch, p.T.ext, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
-  hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev,
-                     (const double2*)p.z, p.Zroot);
+  if (vhat_given || !h->TO.flow.form)  // (otherwise beside the load flow)
+    hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev,
+                       (const double2*)p.z, p.Zroot);
   const size_t c3 = (size_t)S * n * 3;
   if (vhat_given) {
     hipLaunchKernelGGL(k_copy2, dim3(1024), dim3(256), 0, st, (const double2*)loads->Vhat, p.Vhat, c3);
@@ -999,17 +1000,20 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
                        p.status, p.T.ext, p.Vcur);
   } else {
     const double2* V0 = (const double2*)loads->V0;
-    // iterates and tree in LDS where both fit, else the breadth-first form
-    // with the queue tables in LDS, else everything in global memory (one
-    // block per snapshot in each form; the breadth-first form's block of 512
-    // takes most levels of the large feeders in one round: 1.23 -> 1.08 ms
-    // on the 6000-node and 4.12 -> 3.85 ms on the 8400-node feeder against
-    // 256)
-    const size_t pf_lds = pf_lds_bytes(n, h->nlev), pf_bfs = pf_bfs_lds_bytes(n, h->nlev);
+    // by prefix sums while one phase's fit in LDS (any feeder of up to 9600
+    // nodes), else level by level: the breadth-first form with the queue tables
+    // in LDS, or everything in global memory (one block per snapshot in each)
+    const size_t pf_bfs = pf_bfs_lds_bytes(n, h->nlev);
     const double tol = mg->pf_tol > 0 ? mg->pf_tol : 1e-13;
     const int maxit = mg->pf_maxit > 0 ? mg->pf_maxit : 100;
-    if (pf_lds || !pf_bfs)
-      hipLaunchKernelGGL(pf_lds ? k_powerflow_lds : k_powerflow, dim3(S), dim3(256), pf_lds, st, n, p.T.parent,
+    if (h->TO.flow.form)
+      flow_launch(h->TO.flow,
+                  FlowArgs{(const int*)p.tp, p.T.phase, p.z, (const double2*)loads->S_load, {V0[0], V0[1], V0[2]}, tol,
+                           mg->v_min, mg->v_max, maxit, p.Vcur, p.J, p.A, p.absV, p.iters, p.status, p.T.ext, p.Vhat,
+                           p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev, p.Zroot},
+                  S, st);
+    else if (!pf_bfs)
+      hipLaunchKernelGGL(k_powerflow, dim3(S), dim3(256), 0, st, n, p.T.parent,
                          p.T.phase, p.lvl_off, p.lvl_nodes, h->nlev, p.T.ch_off, p.T.ch, (const double2*)p.z,
                          (const double2*)loads->S_load, V0[0], V0[1], V0[2], tol, maxit, mg->v_min, mg->v_max,
                          p.Vcur, p.J, p.A, p.absV, p.iters, p.status, p.T.ext, p.Vhat);
@@ -1310,10 +1314,8 @@ static int reduce_feeder_impl(okr_handle* h, const okr_yblocks* Y, const okr_top
   hipStream_t st = h->stream;
   const Ptrs p = pointers(h, d_workspace);
   if (!(mg->flags & OKR_FLAG_VHAT_GIVEN)) {  // (set before any capture)
-    if (pf_lds_bytes(n, h->nlev) > 64 * 1024)
-      OKR_HIP(h, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_powerflow_lds),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPfLdsMax));
-    else if (!pf_lds_bytes(n, h->nlev) && pf_bfs_lds_bytes(n, h->nlev) > 64 * 1024)
+    OKR_HIP(h, flow_prepare(h->TO.flow));
+    if (!h->TO.flow.form && pf_bfs_lds_bytes(n, h->nlev) > 64 * 1024)
       OKR_HIP(h, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_powerflow_bfs),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPfLdsMax));
   }

@@ -15,6 +15,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "okr_flow.h"
 #include "okr_internal.h"
 #include "okr_device.h"
 
@@ -144,60 +145,20 @@ __device__ __forceinline__ void forward_node(int i, const int* __restrict__ pare
   }
 }
 
-// Where the sweep's data lives: kPfGlobal reads everything from global
-// memory, kPfAll holds the iterates and the tree arrays in LDS.
-enum { kPfGlobal = 0, kPfAll = 1 };
-
-template <int MODE>
-__device__ __forceinline__ void powerflow_body(
-    int n, const int* __restrict__ gparent, const uint8_t* __restrict__ gphase,
-    const int* __restrict__ glvl_off, const int* __restrict__ glvl_nodes, int nlev,
-    const int* __restrict__ gch_off, const int* __restrict__ gch, const double2* __restrict__ z,
+// Level by level from global memory, for feeders beyond the other forms.
+__global__ __launch_bounds__(256) void k_powerflow(
+    int n, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
+    const int* __restrict__ lvl_off, const int* __restrict__ lvl_nodes, int nlev,
+    const int* __restrict__ ch_off, const int* __restrict__ ch, const double2* __restrict__ z,
     const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
     double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
     double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
-    const int* __restrict__ ext, double2* __restrict__ Vext,
-    double2* sbuf, double* shd) {
-  constexpr bool LDS = MODE == kPfAll;
+    const int* __restrict__ ext, double2* __restrict__ Vext) {
+  __shared__ double shd[16];
   const int l = blockIdx.x;
   const size_t base = (size_t)l * n * 3;
-  // (with LDS the iterates, and the tree arrays the sweeps index, live in
-  // shared memory: every level step then waits on LDS instead of global
-  // memory; only the branch impedances are read from global memory)
-  double2* Vl = LDS ? sbuf : V + base;
-  double2* Jl = LDS ? sbuf + (size_t)n * 3 : J + base;
-  const int *parent, *lvl_nodes, *ch_off, *ch;
-  const int* lvl_off;
-  const uint8_t* phase;
-  if constexpr (MODE == kPfGlobal) {
-    parent = gparent;
-    lvl_nodes = glvl_nodes;
-    ch_off = gch_off;
-    ch = gch;
-    lvl_off = glvl_off;
-    phase = gphase;
-  } else {
-    int* s_lvl_off = (int*)(sbuf + (LDS ? (size_t)n * 6 : 0));
-    int* s_lvl_nodes = s_lvl_off + nlev + 1;
-    int* s_ch_off = s_lvl_nodes + n;
-    int* s_ch = s_ch_off + n + 1;
-    int* s_parent = s_ch + n;
-    uint8_t* s_phase = (uint8_t*)(s_parent + n);
-    for (int i = threadIdx.x; i <= nlev; i += blockDim.x) s_lvl_off[i] = glvl_off[i];
-    for (int i = threadIdx.x; i <= n; i += blockDim.x) s_ch_off[i] = gch_off[i];
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-      s_lvl_nodes[i] = glvl_nodes[i];
-      s_ch[i] = i < n - 1 ? gch[i] : 0;
-      s_parent[i] = gparent[i];
-      s_phase[i] = gphase[i];
-    }
-    lvl_off = s_lvl_off;
-    lvl_nodes = s_lvl_nodes;
-    ch_off = s_ch_off;
-    ch = s_ch;
-    parent = s_parent;
-    phase = s_phase;
-  }
+  double2* Vl = V + base;
+  double2* Jl = J + base;
   const double2* Sl = Sload + base;
   const double2 v0[3] = {v0a, v0b, v0c};
   for (int i = threadIdx.x; i < n; i += blockDim.x)
@@ -262,15 +223,7 @@ __device__ __forceinline__ void powerflow_body(
         for (int e = 0; e < 9; ++e) zi[e] = z[(size_t)i * 9 + e];
         forward_node(i, parent, phase, zi, Jl, Vl, dmax);
       }
-      if (LDS) {
-        // the iterates are in LDS: order LDS only, so the next level's
-        // impedance loads stay in flight across the barrier
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-      } else {
-        __syncthreads();
-      }
+      __syncthreads();
     }
     dmax = block_reduce(dmax, [](double a, double b) { return (b <= a) ? a : b; }, shd);
     if (!(dmax <= 1e3)) break;
@@ -282,7 +235,6 @@ __device__ __forceinline__ void powerflow_body(
     for (int p = 0; p < 3; ++p) {
       const bool pr = (phase[i] >> p & 1u);
       const double2 v = Vl[i * 3 + p];
-      if (LDS) V[base + i * 3 + p] = v;
       if (Vext) Vext[base + x * 3 + p] = v;
       A[base + i * 3 + p] = (i > 0 && pr) ? cconj(cdiv(Sl[x * 3 + p], v)) : make_double2(0.0, 0.0);
       const double m = pr ? sqrt(cabs2(v)) : 0.0;
@@ -299,38 +251,7 @@ __device__ __forceinline__ void powerflow_body(
   }
 }
 
-
-__global__ __launch_bounds__(256) void k_powerflow(
-    int n, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
-    const int* __restrict__ lvl_off, const int* __restrict__ lvl_nodes, int nlev,
-    const int* __restrict__ ch_off, const int* __restrict__ ch, const double2* __restrict__ z,
-    const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
-    double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
-    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
-    const int* __restrict__ ext, double2* __restrict__ Vext) {
-  __shared__ double shd[16];
-  powerflow_body<kPfGlobal>(n, parent, phase, lvl_off, lvl_nodes, nlev, ch_off, ch, z, Sload, v0a, v0b, v0c, tol, maxit,
-                            vmin, vmax, V, J, A, absV, iters, status, ext, Vext, nullptr, shd);
-}
-
-// The same with the voltage and current iterates in dynamic LDS (2 x n x 3
-// double2), followed by the level offsets and nodes, child offsets and
-// lists, parents and phases (for feeders small enough to fit).
-__global__ __launch_bounds__(256) void k_powerflow_lds(
-    int n, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
-    const int* __restrict__ lvl_off, const int* __restrict__ lvl_nodes, int nlev,
-    const int* __restrict__ ch_off, const int* __restrict__ ch, const double2* __restrict__ z,
-    const double2* __restrict__ Sload, double2 v0a, double2 v0b, double2 v0c, double tol, int maxit,
-    double vmin, double vmax, double2* __restrict__ V, double2* __restrict__ J,
-    double2* __restrict__ A, double* __restrict__ absV, int* __restrict__ iters, int* __restrict__ status,
-    const int* __restrict__ ext, double2* __restrict__ Vext) {
-  extern __shared__ double2 pf_lds[];
-  __shared__ double shd[16];
-  powerflow_body<kPfAll>(n, parent, phase, lvl_off, lvl_nodes, nlev, ch_off, ch, z, Sload, v0a, v0b, v0c, tol, maxit,
-                         vmin, vmax, V, J, A, absV, iters, status, ext, Vext, pf_lds, shd);
-}
-
-// The same for feeders whose iterates do not fit in LDS (n < 65536): every
+// Breadth-first storage, for feeders beyond the prefix sums' LDS (n < 65536): every
 // per-node quantity of the sweep is stored by breadth-first queue position
 // (each level a contiguous run, the children of position q at positions
 // cf[q] .. cf[q+1]-1 in child-list order, pp[q] the parent's position), so
@@ -476,24 +397,11 @@ __global__ __launch_bounds__(512) void k_powerflow_bfs(
   }
 }
 
-// Cumulative series impedance from the root, Zroot(v) = Zroot(parent) + z(v)
-// (3x3 blocks, zero on absent phases), level by level; the impedance of the
-// path between an ancestor s and r is Zroot(r) - Zroot(s).  One block.
+// Cumulative impedances by a launch of their own (one block; see zroot_block).
 __global__ __launch_bounds__(1024) void k_zroot(int n, const int* __restrict__ parent,
                                                 const int* __restrict__ lvl_off, const int* __restrict__ lvl_nodes,
                                                 int nlev, const double2* __restrict__ z, double2* __restrict__ Zroot) {
-  for (int e = threadIdx.x; e < 9; e += blockDim.x) Zroot[e] = make_double2(0.0, 0.0);  // node 0, level 0
-  __syncthreads();
-  for (int L = 1; L < nlev; ++L) {
-    const int a = lvl_off[L], b = lvl_off[L + 1];
-    for (int t = a * 9 + threadIdx.x; t < b * 9; t += blockDim.x) {
-      const int v = lvl_nodes[t / 9], e = t % 9;
-      const double2 up = Zroot[(size_t)parent[v] * 9 + e], zv = z[(size_t)v * 9 + e];
-      Zroot[(size_t)v * 9 + e] = make_double2(up.x + zv.x, up.y + zv.y);
-    }
-    __threadfence_block();
-    __syncthreads();
-  }
+  zroot_block(n, parent, lvl_off, lvl_nodes, nlev, z, Zroot);
 }
 
 // Given V^ (caller supplied): load currents and magnitudes, band check; with

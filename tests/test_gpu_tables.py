@@ -136,3 +136,37 @@ def test_greedy_cluster_list(okr, n, S, p_deep, kappa, moves):
             np.testing.assert_array_equal(o["super"], sup)
             np.testing.assert_allclose([s["smice"] for s in o["steps"]], [s["smice"] for s in steps], rtol=0, atol=TOL)
             np.testing.assert_allclose(o["err_per_snapshot"], err, rtol=0, atol=TOL)
+
+
+@pytest.mark.parametrize("n,p_deep", [(2, 0.5), (64, 0.5), (65, 0.9), (1023, 0.5), (1024, 0.5), (1025, 0.5), (2100, 0.6)])
+def test_prefix_sum_load_flow(okr, n, p_deep):
+    """Load flow and fixed-current solve by prefix sums at the edges of the
+    waves and of the two forms (up to 1024 nodes, a node per thread; above,
+    phase by phase), 3 snapshots.  The oracle's load flow stops at the same
+    1e-13, so the voltages differ by less than ten times that; the identity
+    assignment solved at the load flow's own currents gives its voltages back
+    within the same bound."""
+    print(f"load flow: n={n} p_deep={p_deep}", flush=True)
+    f = make_feeder("c2", n, n=n, snapshots=3, p_deep=p_deep, kappa=0.2)
+    V, I, st, it = oracle.powerflow(f)
+    assert st == 0
+    out = okr.reduce_feeder(f, want_vhat=True)
+    np.testing.assert_allclose(out["Vhat"], V, rtol=0, atol=1e-12)
+    err, mx = okr.evaluate_assignment(f, np.arange(n))
+    assert mx == err.max() and mx < 1e-12
+
+
+def test_load_flow_beyond_prefix_sums(okr):
+    """An 18,000-node feeder (over 9600 nodes on a phase): the breadth-first
+    load flow of the search, and the level-by-level load flow and fixed-current
+    solve of an evaluation (bounds as above; a wide band keeps the heavily
+    loaded feeder valid)."""
+    print("load flow: n=18000", flush=True)
+    f = make_feeder("c3", 0, n=18000, snapshots=2, v_min=0.5, v_max=1.5)
+    assert max(int((f["phase"] >> p & 1).sum()) for p in range(3)) > 9600
+    V, I, st, _ = oracle.powerflow(f)
+    assert st == 0
+    out = okr.reduce_feeder(f, want_vhat=True)
+    np.testing.assert_allclose(out["Vhat"], V, rtol=0, atol=1e-12)
+    err, _ = okr.evaluate_assignment(f, np.arange(f["n"]))
+    assert err.max() < 1e-12
