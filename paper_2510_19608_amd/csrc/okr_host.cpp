@@ -458,10 +458,12 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
   // segment nodes of any segment: every node that a chain of the segment can
   // ever pass lies there) and at the heads above them (moved currents land
   // there).  Segments that share none of that are independent, so their
-  // order does not matter.  Every segment gets a level one above the highest
-  // level of the earlier segments it conflicts with; each level's segments
-  // (largest first) are cut into chunks of at most nlanes, and the chunks
-  // run level by level: conflicting segments keep their order.
+  // order does not matter.  A segment waits for the earlier segments that it
+  // conflicts with; each chunk takes up to nlanes of those that wait for
+  // nothing any more, the ones at the head of the longest runs of conflicts
+  // first (then the largest): conflicting segments keep their order, and few
+  // chunks are cut beyond the longest run (level by level the 1000-, 6000- and
+  // 8400-node feeders took 20, 61 and 76 chunks against 18, 48 and 59).
   {
     const int want = mg->lanes > 0 ? std::min(mg->lanes, kMaxLanes) : kDefaultLanes;
     h->nlanes = std::max(1, std::min(want, nseg));
@@ -484,57 +486,77 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
       std::sort(heads[g].begin(), heads[g].end());
       heads[g].erase(std::unique(heads[g].begin(), heads[g].end()), heads[g].end());
     }
-    auto inside = [&](int v, const std::vector<std::pair<int, int>>& R) {
-      if (v < 0) return false;
-      const int pv = h->pos[v];
-      for (auto& r : R)
-        if (r.first <= pv && pv < r.second) return true;
-      return false;
-    };
-    auto conflict = [&](int a, int b) {
-      size_t i = 0, j = 0;
-      while (i < iv[a].size() && j < iv[b].size()) {
-        if (iv[a][i].first < iv[b][j].second && iv[b][j].first < iv[a][i].second) return true;
-        if (iv[a][i].second <= iv[b][j].second) ++i;
-        else ++j;
+    // Conflicts: overlapping regions, a head in another's region, a common
+    // head.  The regions' ranges are subtrees, so a sweep over the preorder
+    // positions holds those around the current one on a stack.
+    std::vector<std::vector<int>> later(nseg);  // the segments that wait for g
+    {
+      struct Point {
+        int at, end, g;  // a range [at, end) of g's region; end < 0: a head
+      };
+      std::vector<Point> pts, open;
+      std::vector<std::pair<int, int>> hd;  // (head, segment)
+      for (int g = 0; g < nseg; ++g) {
+        for (auto& r : iv[g]) pts.push_back({r.first, r.second, g});
+        for (int v : heads[g])
+          if (v >= 0) {
+            pts.push_back({h->pos[v], -1, g});
+            hd.push_back({v, g});
+          }
       }
-      for (int x : heads[a])
-        if (inside(x, iv[b]) || std::binary_search(heads[b].begin(), heads[b].end(), x)) return true;
-      for (int x : heads[b])
-        if (inside(x, iv[a])) return true;
-      return false;
-    };
-    std::vector<int> level(nseg, 0);
-    int nlev_seg = 0;
-    for (int g = 0; g < nseg; ++g) {
-      for (int b = g - 1; b >= 0; --b)
-        if (level[b] + 1 > level[g] && conflict(g, b)) level[g] = level[b] + 1;
-      nlev_seg = std::max(nlev_seg, level[g] + 1);
+      std::sort(pts.begin(), pts.end(), [](const Point& a, const Point& b) {
+        if (a.at != b.at) return a.at < b.at;
+        return a.end != b.end ? a.end > b.end : a.g < b.g;
+      });
+      auto pair = [&](int a, int b) {
+        if (a != b) later[std::min(a, b)].push_back(std::max(a, b));
+      };
+      for (const Point& p : pts) {
+        while (!open.empty() && open.back().end <= p.at) open.pop_back();
+        for (const Point& o : open) pair(o.g, p.g);
+        if (p.end >= 0) open.push_back(p);
+      }
+      std::sort(hd.begin(), hd.end());
+      for (size_t a = 0; a < hd.size(); ++a)
+        for (size_t b = a + 1; b < hd.size() && hd[b].first == hd[a].first; ++b) pair(hd[a].second, hd[b].second);
+      for (auto& l : later) {
+        std::sort(l.begin(), l.end());
+        l.erase(std::unique(l.begin(), l.end()), l.end());
+      }
     }
-    std::vector<int> order(nseg);
-    for (int g = 0; g < nseg; ++g) order[g] = g;
+    // wait[g]: how many segments g waits for; height[g]: chunks from g to the
+    // end of its longest run of conflicts
+    std::vector<int> wait(nseg, 0), height(nseg, 1), ready, next;
+    for (int g = 0; g < nseg; ++g)
+      for (int x : later[g]) ++wait[x];
+    for (int g = nseg - 1; g >= 0; --g)
+      for (int x : later[g]) height[g] = std::max(height[g], height[x] + 1);
     auto ksz = [&](int g) { return h->seg_off[g + 1] - h->seg_off[g]; };
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
-      if (level[a] != level[b]) return level[a] < level[b];
-      if (ksz(a) != ksz(b)) return ksz(a) > ksz(b);
-      return a < b;
-    });
     h->chunk_off.assign(1, 0);
     h->chunk_segs.clear();
     h->chunk_k.clear();
-    for (int i = 0; i < nseg; ++i) {
-      const int g = order[i];
-      const int c0 = h->chunk_off.back();
-      const int m = (int)h->chunk_segs.size() - c0;
-      if (m > 0 && (m == h->nlanes || level[h->chunk_segs[c0]] != level[g])) {
-        h->chunk_off.push_back((int)h->chunk_segs.size());
-        h->chunk_k.push_back(0);
+    for (int g = 0; g < nseg; ++g)
+      if (!wait[g]) ready.push_back(g);
+    while (!ready.empty()) {
+      std::sort(ready.begin(), ready.end(), [&](int a, int b) {
+        if (height[a] != height[b]) return height[a] > height[b];
+        if (ksz(a) != ksz(b)) return ksz(a) > ksz(b);
+        return a < b;
+      });
+      const int m = std::min((int)ready.size(), h->nlanes);
+      next.assign(ready.begin() + m, ready.end());
+      int k = 0;
+      for (int i = 0; i < m; ++i) {
+        const int g = ready[i];
+        h->chunk_segs.push_back(g);
+        k = std::max(k, ksz(g));
+        for (int x : later[g])
+          if (--wait[x] == 0) next.push_back(x);
       }
-      if (h->chunk_k.empty()) h->chunk_k.push_back(0);
-      h->chunk_segs.push_back(g);
-      h->chunk_k.back() = std::max(h->chunk_k.back(), ksz(g));
+      h->chunk_k.push_back(k);
+      h->chunk_off.push_back((int)h->chunk_segs.size());
+      ready.swap(next);
     }
-    if (!h->chunk_segs.empty()) h->chunk_off.push_back((int)h->chunk_segs.size());
     // Work units of the table kernel.  A chain's terms depend on the segment
     // nodes above and in it, so a segment has at most the sum over its nodes
     // of 2^(segment nodes on the node's root path) patterns; one unit per 4096
