@@ -13,7 +13,7 @@ namespace okr {
 struct FlowPlan {
   int n = 0, form = 0;     // 1: a node per thread, 2: phase by phase
   size_t end = 0, tour = 0;  // form 1: ends of the labels' subtrees; the tour
-  size_t lab[3] = {}, ende[3] = {}, ptour[3] = {}, idx = 0;  // form 2, by phase: labels, ends, tour; entries [3][n]
+  size_t lab[3] = {}, ende[3] = {}, ptour[3] = {}, idx = 0;  // form 2, by phase: labels << 3 | phases, ends, tour; entries [3][n]
   int cnt[3] = {};           // nodes that have the phase
 };
 

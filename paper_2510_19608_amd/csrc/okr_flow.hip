@@ -27,51 +27,72 @@ namespace {
 
 constexpr int kFlowThreads = 1024;
 constexpr int kFlowWaves = kFlowThreads / 64;
+constexpr int kFlowAhead = 4;  // entries whose loads a thread issues together
 constexpr size_t kFlowLds = 150 * 1024;  // dynamic LDS of the second form (one phase's prefix sums)
 
-// v plus its shifted copy (lanes without a source add 0).
+// A copy shifted along the lanes (DPP control); lanes without a source get 0.
 template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
-  return v + __hiloint2double(hi, lo);
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, ROWS == 0xf);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, ROWS == 0xf);
+  return __hiloint2double(hi, lo);
 }
 
-// Inclusive prefix sum over the wave: within rows of 16 lanes, then the rows'
-// last lanes broadcast.
+// Inclusive prefix sums over rows of 16 lanes, and over the wave (the rows'
+// last lanes broadcast).
+__device__ __forceinline__ double row_scan(double v) {
+  v += dpp<0x111, 0xf>(v);
+  v += dpp<0x112, 0xf>(v);
+  v += dpp<0x114, 0xf>(v);
+  v += dpp<0x118, 0xf>(v);
+  return v;
+}
 __device__ __forceinline__ double wave_scan(double v) {
-  v = dpp_add<0x111, 0xf>(v);
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  v = dpp_add<0x118, 0xf>(v);
-  v = dpp_add<0x142, 0xa>(v);
-  v = dpp_add<0x143, 0xc>(v);
+  v = row_scan(v);
+  v += dpp<0x142, 0xa>(v);
+  v += dpp<0x143, 0xc>(v);
   return v;
 }
 __device__ __forceinline__ double2 wave_scan(double2 v) { return make_double2(wave_scan(v.x), wave_scan(v.y)); }
 
 // The value of the lane before (0 in the first).
-__device__ __forceinline__ double lane_before(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false));
-}
+__device__ __forceinline__ double lane_before(double v) { return dpp<0x138, 0xf>(v); }
 
-__device__ __forceinline__ double last_lane(double v) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
-                          __builtin_amdgcn_readlane(__double2loint(v), 63));
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ __forceinline__ double last_lane(double v) { return read_lane(v, 63); }
+
+// Sum of the waves' totals before wave wv (t: a total per wave, written before
+// the last barrier).
+__device__ __forceinline__ double2 waves_before(const double2* t, int stride, int wv) {
+  const int lane = threadIdx.x & 15;
+  double2 v = lane < (int)(blockDim.x >> 6) ? t[lane * stride] : make_double2(0.0, 0.0);
+  v = make_double2(row_scan(v.x), row_scan(v.y));
+  return wv > 0 ? make_double2(read_lane(v.x, wv - 1), read_lane(v.y, wv - 1)) : make_double2(0.0, 0.0);
 }
 
 __device__ __forceinline__ double nan_max(double a, double b) { return (b <= a) ? a : b; }  // keeps NaN
 
-// NaN-propagating maximum over the block (every thread gets it); s holds a
-// value per wave and must not be in use.
+// NaN-propagating maximum of non-negative values over the block (every thread
+// gets it); s holds a value per wave and must not be in use.
 __device__ __forceinline__ double block_nan_max(double v, double* s) {
-  for (int o = 32; o > 0; o >>= 1) v = nan_max(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = v;
+  v = nan_max(v, dpp<0x111, 0xf>(v));
+  v = nan_max(v, dpp<0x112, 0xf>(v));
+  v = nan_max(v, dpp<0x114, 0xf>(v));
+  v = nan_max(v, dpp<0x118, 0xf>(v));
+  v = nan_max(v, dpp<0x142, 0xa>(v));
+  v = nan_max(v, dpp<0x143, 0xc>(v));
+  if ((threadIdx.x & 63) == 63) s[threadIdx.x >> 6] = v;
   __syncthreads();
-  double r = s[0];
-  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = nan_max(r, s[w]);
-  return r;
+  const int lane = threadIdx.x & 15;
+  v = lane < (int)(blockDim.x >> 6) ? s[lane] : 0.0;
+  v = nan_max(v, dpp<0x111, 0xf>(v));
+  v = nan_max(v, dpp<0x112, 0xf>(v));
+  v = nan_max(v, dpp<0x114, 0xf>(v));
+  v = nan_max(v, dpp<0x118, 0xf>(v));
+  return read_lane(v, 15);
 }
 
 // Load currents and magnitudes at the final voltages, and the band check.
@@ -111,8 +132,9 @@ __device__ __forceinline__ void flow_finish(const FlowArgs& a, int n, size_t bas
 // Sload, given by label.
 // Six barriers and two scans of six doubles per sweep, whatever the depth; bound
 // by FP64 and DPP instructions on one CU per snapshot.  1000 nodes, 24
-// snapshots, 8 sweeps: 97 us with the cumulative impedances (228 + 20 level by
-// level in LDS); 168 snapshots 103 (417 + 20 level by level in global memory);
+// snapshots, 8 sweeps: 75 us with the cumulative impedances (228 + 20 level by
+// level in LDS; 98 with the waves' totals added one by one and three square
+// roots per node); 168 snapshots 80 (417 + 20 level by level in global memory);
 // 30 nodes 26 (66 + 6).
 template <bool FIXED>
 __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const int* __restrict__ end,
@@ -125,7 +147,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
     return;
   }
   double2 *X = flow_lds, *Y = flow_lds + 3 * n, *L = flow_lds + 6 * n + 3 * threadIdx.x;
-  const int q = threadIdx.x, wv = q >> 6;
+  const int q = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(q >> 6);
   const size_t base = (size_t)blockIdx.x * n * 3;
   const bool on = q < n, last = (q & 63) == 63;
   const unsigned ph = on ? a.phase[q] : 0u;
@@ -152,9 +174,8 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
       if (last) s_tot[0][wv][p] = c[p];
     }
     __syncthreads();
-    for (int w = 0; w < wv; ++w)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) c[p] = cadd(c[p], s_tot[0][w][p]);
+    for (int p = 0; p < 3; ++p) c[p] = cadd(c[p], waves_before(&s_tot[0][0][p], 3, wv));
     if (on)
 #pragma unroll
       for (int p = 0; p < 3; ++p) X[q * 3 + p] = c[p];
@@ -181,9 +202,8 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
       c[p] = make_double2(lane_before(i.x), lane_before(i.y));
     }
     __syncthreads();
-    for (int w = 0; w < wv; ++w)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) c[p] = cadd(c[p], s_tot[1][w][p]);
+    for (int p = 0; p < 3; ++p) c[p] = cadd(c[p], waves_before(&s_tot[1][0][p], 3, wv));
     if (on) {
 #pragma unroll
       for (int p = 0; p < 3; ++p) {
@@ -199,11 +219,11 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
     for (int p = 0; p < 3; ++p) {
       if (!(ph >> p & 1u)) continue;
       const double2 nv = csub(a.v0[p], X[q * 3 + p]);
-      dmax = nan_max(dmax, sqrt(cabs2(csub(nv, v[p]))));
+      dmax = nan_max(dmax, cabs2(csub(nv, v[p])));
       v[p] = nv;
     }
     if (FIXED) break;
-    dmax = block_nan_max(dmax, s_red);
+    dmax = sqrt(block_nan_max(dmax, s_red));  // (squares up to here)
     if (!(dmax <= 1e3)) break;
     if (dmax <= a.tol) {
       conv = true;
@@ -225,13 +245,15 @@ struct FlowPhases {
 
 // Form 2: phase by phase, over the list of the nodes that have the phase (a
 // subtree, in label order), so that one phase's prefix sums or drops fit in LDS
-// (X) for up to 9600 nodes a phase and absent phases cost nothing.  Loads,
-// voltages and branch currents lie by phase and list entry in the V, A and J
-// slices until the end.  A wave takes a run of the list or of the tour; its
+// (X) for up to 9600 nodes a phase and absent phases cost nothing.  Loads and
+// voltages lie by phase and list entry in the V and A slices until the end,
+// branch currents by phase and label in the J slice.  A wave takes a run of the list or of the tour; its
 // total is formed first, then the run is scanned from the sum of the waves
-// before it.  6000 nodes, 96 snapshots, 9 sweeps: 888 us with the cumulative
-// impedances (1100 + 88 level by level in breadth-first storage); 8400 nodes,
-// 672 snapshots, 12 sweeps: 2.70 ms (3.99 + 0.12).
+// before it.  6000 nodes, 96 snapshots, 9 sweeps: 709 us with the cumulative
+// impedances (1100 + 88 level by level in breadth-first storage; 826 without
+// loads issued kFlowAhead at a time), bound by latency on 96 CUs.  8400 nodes,
+// 672 snapshots, 12 sweeps: 2.45 ms (3.99 + 0.12; 2.53): about 13 GB, 5.4 TB/s.
+// (64 registers, for two blocks per CU: 852 us and 3.02 ms, spilled.)
 template <bool FIXED>
 __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowPhases t, FlowArgs a) {
   extern __shared__ double2 flow_lds[];
@@ -249,7 +271,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
   if (!FIXED) {
     for (int p = 0; p < 3; ++p)
       for (int k = tid; k < t.cnt[p]; k += kFlowThreads) {
-        Sb[p * n + k] = Sl[(size_t)a.ext[t.lab[p][k]] * 3 + p];
+        Sb[p * n + k] = Sl[(size_t)a.ext[t.lab[p][k] >> 3] * 3 + p];
         Vb[p * n + k] = a.v0[p];
       }
     __syncthreads();
@@ -261,78 +283,133 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
       const int cnt = t.cnt[p], C = (cnt + kFlowThreads - 1) / kFlowThreads, k0 = wv * 64 * C + lane;
       const double2 *Sp = Sb + (size_t)p * n, *Vp = Vb + (size_t)p * n;
       double2 acc = make_double2(0.0, 0.0);
-      for (int i = 0, k = k0; i < C; ++i, k += 64) {
-        if (k >= cnt) break;
-        double2 c = make_double2(0.0, 0.0);
-        if (FIXED) c = Sl[(size_t)t.lab[p][k] * 3 + p];
-        else if (t.lab[p][k] > 0) c = cconj(cdiv(Sp[k], Vp[k]));
-        X[k] = c;
-        acc = cadd(acc, c);
+      for (int i = 0; i < C; i += kFlowAhead) {
+        double2 sv[kFlowAhead], vv[kFlowAhead];
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          const int k = min(k0 + (i + u) * 64, cnt - 1);
+          if (FIXED) {
+            sv[u] = Sl[(size_t)(t.lab[p][k] >> 3) * 3 + p];
+          } else {
+            sv[u] = Sp[k];
+            vv[u] = Vp[k];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          const int k = k0 + (i + u) * 64;
+          if (i + u >= C || k >= cnt) break;
+          double2 c = make_double2(0.0, 0.0);
+          if (FIXED) c = sv[u];
+          else if (k > 0) c = cconj(cdiv(sv[u], vv[u]));  // (entry 0 is the root)
+          X[k] = c;
+          acc = cadd(acc, c);
+        }
       }
       acc = wave_scan(acc);
       if (lane == 63) s_tot[0][wv] = acc;
       __syncthreads();
-      double2 run = make_double2(0.0, 0.0);
-      for (int w = 0; w < wv; ++w) run = cadd(run, s_tot[0][w]);
+      double2 run = waves_before(s_tot[0], 1, wv);
       for (int i = 0, k = k0; i < C; ++i, k += 64) {
         const double2 c = wave_scan(k < cnt ? X[k] : make_double2(0.0, 0.0));
         if (k < cnt) X[k] = cadd(run, c);
         run = make_double2(run.x + last_lane(c.x), run.y + last_lane(c.y));
       }
       __syncthreads();
-      for (int k = tid; k < cnt; k += kFlowThreads) {
-        const double2 hi = X[t.ende[p][k] - 1], lo = k > 0 ? X[k - 1] : make_double2(0.0, 0.0);
-        Jb[(size_t)p * n + k] = csub(hi, lo);
+      for (int k1 = tid; k1 < cnt; k1 += kFlowAhead * kFlowThreads) {
+        int e[kFlowAhead], q[kFlowAhead];
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          const int k = min(k1 + u * kFlowThreads, cnt - 1);
+          e[u] = t.ende[p][k];
+          q[u] = t.lab[p][k] >> 3;
+        }
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          const int k = k1 + u * kFlowThreads;
+          if (k >= cnt) break;
+          const double2 lo = k > 0 ? X[k - 1] : make_double2(0.0, 0.0);
+          Jb[(size_t)p * n + q[u]] = csub(X[e[u] - 1], lo);
+        }
       }
       __syncthreads();
     }
     double dmax = 0.0;
     for (int p = 0; p < 3; ++p) {
       const int cnt = t.cnt[p];
-      for (int k = tid; k < cnt; k += kFlowThreads) {
-        const int q = t.lab[p][k];
-        double2 d = make_double2(0.0, 0.0);
+      for (int k1 = tid; k1 < cnt; k1 += 2 * kFlowThreads) {
+        int q[2];
+        double2 d[2], zz[2][3], jj[2][3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const int kc = t.idx[c * n + q];
-          if (kc >= 0) d = cadd(d, cmul(a.z[(size_t)q * 9 + p * 3 + c], Jb[(size_t)c * n + kc]));
+        for (int u = 0; u < 2; ++u) q[u] = t.lab[p][min(k1 + u * kFlowThreads, cnt - 1)];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            zz[u][c] = a.z[(size_t)(q[u] >> 3) * 9 + p * 3 + c];
+            jj[u][c] = Jb[(size_t)c * n + (q[u] >> 3)];
+          }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          d[u] = make_double2(0.0, 0.0);
+#pragma unroll
+          for (int c = 0; c < 3; ++c)
+            if (q[u] >> c & 1) d[u] = cadd(d[u], cmul(zz[u][c], jj[u][c]));
+          if (k1 + u * kFlowThreads < cnt) X[k1 + u * kFlowThreads] = d[u];
         }
-        X[k] = d;
       }
       __syncthreads();
       const int C = (2 * cnt + kFlowThreads - 1) / kFlowThreads, k0 = wv * 64 * C + lane;
       double2 acc = make_double2(0.0, 0.0);
-      for (int i = 0, k = k0; i < C; ++i, k += 64) {
-        if (k >= 2 * cnt) break;
-        const int s = t.tour[p][k];
-        acc = s & 1 ? csub(acc, X[s >> 1]) : cadd(acc, X[s >> 1]);
+      for (int i = 0; i < C; i += kFlowAhead) {
+        int s[kFlowAhead];
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) s[u] = t.tour[p][min(k0 + (i + u) * 64, 2 * cnt - 1)];
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          if (i + u >= C || k0 + (i + u) * 64 >= 2 * cnt) break;
+          acc = s[u] & 1 ? csub(acc, X[s[u] >> 1]) : cadd(acc, X[s[u] >> 1]);
+        }
       }
       acc = wave_scan(acc);
       if (lane == 63) s_tot[1][wv] = acc;
       __syncthreads();
-      double2 run = make_double2(0.0, 0.0);
-      for (int w = 0; w < wv; ++w) run = cadd(run, s_tot[1][w]);
-      for (int i = 0, k = k0; i < C; ++i, k += 64) {
-        const int s = k < 2 * cnt ? t.tour[p][k] : 1;
-        double2 g = k < 2 * cnt ? X[s >> 1] : make_double2(0.0, 0.0);
-        if (s & 1) g = make_double2(-g.x, -g.y);
-        g = wave_scan(g);
-        if (!(s & 1)) {
-          const double2 nv = csub(a.v0[p], cadd(run, g));
-          if (FIXED) {
-            a.V[base + (size_t)t.lab[p][s >> 1] * 3 + p] = nv;
-          } else {
-            double2* o = Vb + (size_t)p * n + (s >> 1);
-            dmax = nan_max(dmax, sqrt(cabs2(csub(nv, *o))));
-            *o = nv;
-          }
+      double2 run = waves_before(s_tot[1], 1, wv);
+      for (int i = 0; i < C; i += kFlowAhead) {
+        int s[kFlowAhead];
+        double2 old[kFlowAhead];
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          const int k = k0 + (i + u) * 64;
+          s[u] = t.tour[p][min(k, 2 * cnt - 1)];
+          if (i + u >= C || k >= 2 * cnt) s[u] = 1;  // (nothing)
         }
-        run = make_double2(run.x + last_lane(g.x), run.y + last_lane(g.y));
+        if (!FIXED)
+#pragma unroll
+          for (int u = 0; u < kFlowAhead; ++u)
+            if (!(s[u] & 1)) old[u] = Vb[(size_t)p * n + (s[u] >> 1)];
+#pragma unroll
+        for (int u = 0; u < kFlowAhead; ++u) {
+          if (i + u >= C) break;
+          double2 g = k0 + (i + u) * 64 < 2 * cnt ? X[s[u] >> 1] : make_double2(0.0, 0.0);
+          if (s[u] & 1) g = make_double2(-g.x, -g.y);
+          g = wave_scan(g);
+          if (!(s[u] & 1)) {
+            const double2 nv = csub(a.v0[p], cadd(run, g));
+            if (FIXED) {
+              a.V[base + (size_t)(t.lab[p][s[u] >> 1] >> 3) * 3 + p] = nv;
+            } else {
+              dmax = nan_max(dmax, cabs2(csub(nv, old[u])));
+              Vb[(size_t)p * n + (s[u] >> 1)] = nv;
+            }
+          }
+          run = make_double2(run.x + last_lane(g.x), run.y + last_lane(g.y));
+        }
       }
       __syncthreads();
     }
     if (FIXED) break;
-    dmax = block_nan_max(dmax, s_red);
+    dmax = sqrt(block_nan_max(dmax, s_red));  // (squares up to here)
     if (!(dmax <= 1e3)) break;
     if (dmax <= a.tol) {
       conv = true;
@@ -423,7 +500,7 @@ FlowPlan flow_tables(int n, const int* end, const uint8_t* phase, std::vector<in
     for (int q = 0; q < n; ++q) below[q + 1] = below[q] + (phase[q] >> c & 1);
     for (size_t k = 0; k < e.size(); ++k) e[k] = below[end[lab[c][k]]];
     p.lab[c] = out.size();
-    out.insert(out.end(), lab[c].begin(), lab[c].end());
+    for (int q : lab[c]) out.push_back(q << 3 | phase[q]);
     p.ende[c] = out.size();
     out.insert(out.end(), e.begin(), e.end());
     p.ptour[c] = out.size();
