@@ -219,39 +219,73 @@ __device__ __forceinline__ void score_chain(const int* __restrict__ chains, cons
 }
 
 // ---------------------------------------------------------- state update --
-// The structural part of applying mask m to segment H (one block, called by
+// The structural part of applying a mask to segment H (one block, called by
 // every thread): kept flags and super-nodes over Omega_g, and the node -> slot
 // and zone-entry maps cleared for the next segment.  Run by the kernel that
 // settles the decision, so that the next chunk's table build can start while
 // the voltages and currents of this one are still being moved.
-__device__ __forceinline__ void update_state(const SegHdr& H, const int* tab, const Topo& T, const State& St,
-                                             uint32_t m) {
-  const int* slots = tab + H.o_slot;
-  if ((int)threadIdx.x < H.nslots) {
-    const int* sr = slots + threadIdx.x * kSlotInts;
-    if ((m >> sr[SL_BIT]) & 1u) St.kept[sr[SL_NODE]] = 0;
-    St.slot_of[sr[SL_NODE]] = -1;
-  }
-  for (int q = threadIdx.x; q < H.nz; q += blockDim.x) {
-    const int* ze = tab + H.o_zent + q * 3;
-    St.zent_of[ze[0] * 3 + ze[1]] = -1;
-  }
-  __syncthreads();
-  const int* rg = tab + H.o_range;
-  for (int q = threadIdx.x; q < H.nomega; q += blockDim.x) {
+// Before the decision (load): a slot is a kept node, its nearest kept proper
+// ancestor is another slot or stays kept, and a node's super-node is a slot or
+// stays.  After it (store): a reduced slot's super-node is found over the slots
+// in LDS, and each node takes its old super-node's.  Climbing the tree in
+// memory after the decision took 2.3 us of the 10.1 us arg-min at 1000 nodes.
+struct StateUpdate {
+  int up[kMaxK], upnode[kMaxK], node[kMaxK], bit[kMaxK];  // (LDS)
+  __device__ __forceinline__ static int omega_node(const SegHdr& H, const int* rg, int q) {
     int r = 0;
     while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
-    const int i = rg[3 * r] + (q - rg[3 * r + 2]);
-    // up through reduced nodes; a reduced node's recorded super (before or
-    // after this update) is an ancestor with only reduced nodes in between
-    int v = i;
-    while (!St.kept[v]) {
-      const int s = St.sup[v];
-      v = (s >= 0 && s != v) ? s : T.parent[v];
-    }
-    St.sup[i] = v;
+    return rg[3 * r] + (q - rg[3 * r + 2]);
   }
-}
+  // i, s, js: this thread's first node of Omega_g, its super-node and that
+  // one's slot.  Ends with the map reads done (before the caller's barrier).
+  __device__ __forceinline__ void load(const SegHdr& H, const int* tab, const Topo& T, const State& St, int& i, int& s,
+                                       int& js) {
+    const int* slots = tab + H.o_slot;
+    i = s = js = -1;
+    if ((int)threadIdx.x < H.nomega) {
+      i = omega_node(H, tab + H.o_range, threadIdx.x);
+      s = St.sup[i];
+      js = St.slot_of[s];
+    }
+    if ((int)threadIdx.x < H.nslots) {
+      const int* sr = slots + threadIdx.x * kSlotInts;
+      node[threadIdx.x] = sr[SL_NODE];
+      bit[threadIdx.x] = sr[SL_BIT];
+      const int a = St.sup[T.parent[sr[SL_NODE]]];  // (the slack is no slot)
+      upnode[threadIdx.x] = a;
+      up[threadIdx.x] = St.slot_of[a];
+    }
+  }
+  // Slot j's super-node under mask m (after a barrier behind load).
+  __device__ __forceinline__ int super_of(int j, uint32_t m) const {
+    int v = node[j];
+    while (j >= 0 && ((m >> bit[j]) & 1u)) {
+      v = upnode[j];
+      j = up[j];
+    }
+    return v;
+  }
+  __device__ __forceinline__ void store(const SegHdr& H, const int* tab, const State& St, uint32_t m, int i, int s,
+                                        int js) const {
+    if (i >= 0 && js >= 0) {
+      const int v = super_of(js, m);
+      if (v != s) St.sup[i] = v;
+    }
+    for (int q = threadIdx.x + blockDim.x; q < H.nomega; q += blockDim.x) {
+      const int x = omega_node(H, tab + H.o_range, q), y = St.sup[x], j = St.slot_of[y];
+      if (j >= 0) St.sup[x] = super_of(j, m);
+    }
+    __syncthreads();  // the slot map is read
+    if ((int)threadIdx.x < H.nslots) {
+      if ((m >> bit[threadIdx.x]) & 1u) St.kept[node[threadIdx.x]] = 0;
+      St.slot_of[node[threadIdx.x]] = -1;
+    }
+    for (int q = threadIdx.x; q < H.nz; q += blockDim.x) {
+      const int* ze = tab + H.o_zent + q * 3;
+      St.zent_of[ze[0] * 3 + ze[1]] = -1;
+    }
+  }
+};
 
 // ------------------------------------------------------------ block reduce --
 template <typename T, typename Op>

@@ -435,6 +435,11 @@ __global__ void k_from_vhat(int n, int S, const uint8_t* __restrict__ phase, con
 // and then every feasible mask of the chosen level, in any order (the listed
 // masks are a few hundred of 65,536 on the 1000-node workload; scoring them
 // from a dense list keeps every lane busy).
+// One block per segment, bound by latency: the tile records in one round of
+// loads, level and error in one reduction, what the state update reads loaded
+// before the decision.  Per chunk 8.3 us at 1000 nodes (10.2 with the records
+// read in three rounds of 1024 and the update's loads after the decision), 8.4
+// at 6000 (11.9), 9.5 at 8400 (19.8).
 __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
                                                  size_t lstride, const MaskScore* __restrict__ fin,
                                                  const TileRec* __restrict__ tiles, SelParams sp,
@@ -444,16 +449,24 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
                                                  State St) {
   // one slot per wave for each reduction (each its own array, so no
   // reduction's slots are written while another's are still being read)
-  __shared__ int s_best[16], s_amb[16], s_amb2[16];
+  __shared__ int s_best[16], s_near[16], s_amb[16];
   __shared__ double s_emin[16], s_run[16];
   __shared__ unsigned s_pick[16];
   __shared__ int ncand, nlist;
   __shared__ int cand[1024];
+  __shared__ StateUpdate su;
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
   tab = lane_ptr(tab, lstride);
+  const int tid = threadIdx.x, bd = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = bd >> 6;
+  const bool upd = tab && H.valid;
+  int ui = -1, us = -1, uj = -1;
   if (gates && gates[g] == 0) {  // decided without the full enumeration
-    if (tab && H.valid) update_state(H, tab, T, St, decs[g].mask);
+    if (upd) {
+      su.load(H, tab, T, St, ui, us, uj);
+      __syncthreads();
+      su.store(H, tab, St, decs[g].mask, ui, us, uj);
+    }
     return;
   }
   slist = lane_ptr(slist, lstride);
@@ -464,8 +477,12 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   // nothing is reduced when the full network violates the band, the load
   // flow failed, or the segment's tables are inconsistent
   if (!H.valid || (*status & (16 | 32))) {
-    if (tab && H.valid) update_state(H, tab, T, St, 0u);
-    if (threadIdx.x == 0) {
+    if (upd) {
+      su.load(H, tab, T, St, ui, us, uj);
+      __syncthreads();
+      su.store(H, tab, St, 0u, ui, us, uj);
+    }
+    if (tid == 0) {
       DevDecision d;
       d.mask = 0; d.popcount = 0; d.e_loc = 0.0; d.e_min = 0.0; d.ambiguous = 0; d.found = 0;
       d.key_gap = INFINITY;
@@ -475,70 +492,61 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
     }
     return;
   }
-  const int tid = threadIdx.x, bd = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = bd >> 6;
   const int k = H.k;
   const uint32_t nm = 1u << k;
   const int lb = tile_bits(k);
   const int ntiles = (int)(nm >> lb);
-  // up to one tile per thread (segments of up to 16 nodes): its record is
-  // read once and kept in registers
-  const bool one = ntiles <= bd;
-  TileRec r0;
-  r0.best = -1;
-  r0.near = -1;
-  r0.emin = INFINITY;
-  int best = -1;
-  for (int t = tid; t < ntiles; t += bd) {
-    const TileRec r = tiles[t];
-    if (t == tid) r0 = r;
-    best = max(best, r.best);
+  // the first kTileRegs tiles of each thread (all of them for segments of up
+  // to 20 nodes) are read once, together, and kept in registers
+  constexpr int kTileRegs = 16;
+  TileRec rt[kTileRegs];
+#pragma unroll
+  for (int u = 0; u < kTileRegs; ++u) {
+    if (u * bd >= ntiles) break;
+    if (tid + u * bd < ntiles) rt[u] = tiles[tid + u * bd];
+    else rt[u] = TileRec{-1, -1, INFINITY};
   }
-  for (int o = 32; o > 0; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
-  if (lane == 0) s_best[wv] = best;
-  __syncthreads();
-  best = s_best[0];
-  for (int w = 1; w < nw; ++w) best = max(best, s_best[w]);
-  // the smallest error at the chosen level, and masks near the boundary
-  double emin = INFINITY;
-  int amb = 0;
-  if (best >= 0)
-    for (int t = tid; t < ntiles; t += bd) {
-      const TileRec r = one ? r0 : tiles[t];
-      if (r.best == best) emin = fmin(emin, r.emin);
-      if (r.near >= best) amb = 1;
+  auto each_tile = [&](auto f) {
+#pragma unroll
+    for (int u = 0; u < kTileRegs; ++u) {
+      if (u * bd >= ntiles) break;
+      if (tid + u * bd < ntiles) f(rt[u], tid + u * bd);
     }
-  for (int o = 32; o > 0; o >>= 1) {
-    emin = fmin(emin, __shfl_xor(emin, o, 64));
-    amb |= __shfl_xor(amb, o, 64);
-  }
+    for (int t = tid + kTileRegs * bd; t < ntiles; t += bd) f(tiles[t], t);
+  };
+  if (tid == 0) ncand = 0;
+  // the best level, the smallest error there, and the best level near the boundary
+  int best = -1, near = -1;
+  double emin = INFINITY;
+  auto join = [&](int b, double e, int c) {
+    emin = b > best ? e : b == best ? fmin(emin, e) : emin;
+    best = max(best, b);
+    near = max(near, c);
+  };
+  each_tile([&](const TileRec& r, int) { join(r.best, r.emin, r.near); });
+  for (int o = 32; o > 0; o >>= 1) join(__shfl_xor(best, o, 64), __shfl_xor(emin, o, 64), __shfl_xor(near, o, 64));
   if (lane == 0) {
+    s_best[wv] = best;
     s_emin[wv] = emin;
-    s_amb[wv] = amb;
+    s_near[wv] = near;
   }
+  if (upd) su.load(H, tab, T, St, ui, us, uj);
   __syncthreads();
-  emin = s_emin[0];
-  amb = s_amb[0];
-  for (int w = 1; w < nw; ++w) {
-    emin = fmin(emin, s_emin[w]);
-    amb |= s_amb[w];
+  {
+    const int w = lane & (nw - 1);
+    best = s_best[w];
+    emin = s_emin[w];
+    near = s_near[w];
+    for (int o = nw / 2; o > 0; o >>= 1)
+      join(__shfl_xor(best, o, 64), __shfl_xor(emin, o, 64), __shfl_xor(near, o, 64));
   }
+  int amb = best >= 0 && near >= best;
   unsigned pick = 0xffffffffu;
   const double thr = emin + sp.tie;
   // runner-up: the smallest error above the tie window at the chosen level
   // (a tile not rescanned holds it at its own minimum)
   double runner = INFINITY;
-  // candidate tiles, processed in chunks of one tile per thread
-  for (int base = 0; base < ntiles && best >= 0; base += bd) {
-    if (tid == 0) ncand = 0;
-    __syncthreads();
-    const int t = base + tid;
-    if (t < ntiles) {
-      const TileRec r = one ? r0 : tiles[t];
-      if (r.best == best && r.emin <= thr + sp.amb) cand[atomicAdd(&ncand, 1)] = t;
-      else if (r.best == best) runner = fmin(runner, r.emin);
-    }
-    __syncthreads();
-    const int nc = ncand;
+  auto rescan = [&](int nc) {
     for (int q = tid; q < nc * 64; q += bd) {
       if ((q & 63) >> lb) continue;
       const uint32_t mm = (uint32_t)cand[q >> 6] << lb | (uint32_t)(q & 63);
@@ -549,7 +557,36 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
       if (r.e <= thr) pick = min(pick, mm);
       else runner = fmin(runner, r.e);
     }
+  };
+  if (best >= 0) {
+    // candidate tiles: all of them at once, or (more than the list holds) one
+    // tile per thread at a time
+    each_tile([&](const TileRec& r, int t) {
+      if (r.best != best) return;
+      if (r.emin <= thr + sp.amb) {
+        const int at = atomicAdd(&ncand, 1);
+        if (at < 1024) cand[at] = t;
+      } else {
+        runner = fmin(runner, r.emin);
+      }
+    });
     __syncthreads();
+    const int nc = ncand;
+    if (nc <= 1024) {
+      rescan(nc);
+    } else {
+      for (int base = 0; base < ntiles; base += bd) {
+        __syncthreads();
+        if (tid == 0) ncand = 0;
+        __syncthreads();
+        if (base + tid < ntiles) {
+          const TileRec r = tiles[base + tid];
+          if (r.best == best && r.emin <= thr + sp.amb) cand[atomicAdd(&ncand, 1)] = base + tid;
+        }
+        __syncthreads();
+        rescan(ncand);
+      }
+    }
   }
   for (int o = 32; o > 0; o >>= 1) {
     pick = min(pick, (unsigned)__shfl_xor((int)pick, o, 64));
@@ -558,14 +595,19 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   }
   if (lane == 0) {
     s_pick[wv] = pick;
-    s_amb2[wv] = amb;
+    s_amb[wv] = amb;
     s_run[wv] = runner;
   }
   __syncthreads();
+  {
+    const int w = lane & (nw - 1);
+    pick = s_pick[w];
+    for (int o = nw / 2; o > 0; o >>= 1) pick = min(pick, (unsigned)__shfl_xor((int)pick, o, 64));
+  }
+  if (upd) su.store(H, tab, St, best < 0 ? 0u : pick, ui, us, uj);  // this decision is final
   if (tid == 0) {
-    for (int w = 1; w < nw; ++w) {
-      pick = min(pick, s_pick[w]);
-      amb |= s_amb2[w];
+    for (int w = 0; w < nw; ++w) {
+      amb |= s_amb[w];
       runner = fmin(runner, s_run[w]);
     }
     DevDecision d;
@@ -579,11 +621,6 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
       d.smice_rise = 0.0;
     }
     *dec = d;
-    s_pick[0] = d.mask;
-  }
-  if (tab) {  // this decision is final
-    __syncthreads();
-    update_state(H, tab, T, St, s_pick[0]);
   }
   if (!slist) return;
   if (tid == 0) {
@@ -594,7 +631,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
     if (tid == 0) ncand = 0;
     __syncthreads();
     const int t = base + tid;
-    if (t < ntiles && (one ? r0 : tiles[t]).best == best) cand[atomicAdd(&ncand, 1)] = t;
+    if (t < ntiles && tiles[t].best == best) cand[atomicAdd(&ncand, 1)] = t;
     __syncthreads();
     const int nc = ncand;
     for (int q = tid; q < nc * 64; q += bd) {

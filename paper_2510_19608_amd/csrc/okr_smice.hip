@@ -351,8 +351,12 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
   if (!H.valid) return;
   DevDecision d = decs[g];
   tab = lane_ptr(tab, lstride);
+  __shared__ StateUpdate su;
+  int ui, us, uj;
+  su.load(H, tab, T, St, ui, us, uj);
+  __syncthreads();
   if (!d.found) {
-    update_state(H, tab, T, St, d.mask);
+    su.store(H, tab, St, d.mask, ui, us, uj);
     return;
   }
   fin = lane_ptr(fin, lstride);
@@ -395,7 +399,7 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
     d.smice_rise = smv[at] - smv[0];
     decs[g] = d;
   }
-  update_state(H, tab, T, St, pick != 0xffffffffu ? pick : d.mask);
+  su.store(H, tab, St, pick != 0xffffffffu ? pick : d.mask, ui, us, uj);
 }
 
 }  // namespace okr
