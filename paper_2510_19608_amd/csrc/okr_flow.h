@@ -36,12 +36,22 @@ struct FlowArgs {
   double2* Zroot;
 };
 
+// An assignment to evaluate, by label: members of every cluster (CSR), every
+// node's super-node; err [S].
+struct FlowEval {
+  const int *moff, *mem, *sup;
+  double* err;
+};
+
 // Appends the tables of a tree given by label (subtree ends, phases).
 FlowPlan flow_tables(int n, const int* end, const uint8_t* phase, std::vector<int>& out);
 // Kernel attributes (before any capture).
 hipError_t flow_prepare(const FlowPlan& p);
 // Load flow of S snapshots and the cumulative impedances (form 1 or 2).
 void flow_launch(const FlowPlan& p, const FlowArgs& a, int S, hipStream_t st);
+// Load flow, fixed-current solve of the clusters' currents and largest errors
+// (form 1; of a's outputs only the status is written).
+void flow_eval_launch(const FlowPlan& p, const FlowArgs& a, const FlowEval& e, int S, hipStream_t st);
 // Voltages of the fixed currents I [S][n][3] by label (form 1 or 2).
 void flow_fixed_launch(const FlowPlan& p, const int* tab, const uint8_t* phase, const double2* z, const double2* v0,
                        const double2* I, double2* J, double2* V, int S, hipStream_t st);

@@ -128,21 +128,26 @@ __device__ __forceinline__ void flow_finish(const FlowArgs& a, int n, size_t bas
 // Form 1: a node per thread (n <= 1024), a node's impedance and voltage in
 // registers, the prefix sums, drops and loads in LDS (X, Y, L: n x 3 each; with
 // the loads in registers too the kernel spills); one block per snapshot, one
-// more for the cumulative impedances.  FIXED: one sweep at the currents
-// Sload, given by label.
+// more for the cumulative impedances.  kFixed: one sweep at the currents Sload,
+// given by label.  kEval: after the load flow, one sweep at the currents
+// aggregated over the clusters of an assignment, and each snapshot's largest
+// difference of |V^| to the super-node's |V|; nothing else is written.
 // Six barriers and two scans of six doubles per sweep, whatever the depth; bound
 // by FP64 and DPP instructions on one CU per snapshot.  1000 nodes, 24
 // snapshots, 8 sweeps: 75 us with the cumulative impedances (228 + 20 level by
 // level in LDS; 98 with the waves' totals added one by one and three square
 // roots per node); 168 snapshots 80 (417 + 20 level by level in global memory);
 // 30 nodes 26 (66 + 6).
-template <bool FIXED>
+enum { kLoadFlow = 0, kFixed = 1, kEval = 2 };
+
+template <int MODE>
 __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const int* __restrict__ end,
-                                                            const int* __restrict__ tour, FlowArgs a) {
+                                                            const int* __restrict__ tour, FlowArgs a, FlowEval ev) {
+  constexpr bool FIXED = MODE == kFixed;
   extern __shared__ double2 flow_lds[];
   __shared__ double2 s_tot[2][kFlowWaves][3];
   __shared__ double s_red[16];
-  if (!FIXED && (int)blockIdx.x == S) {
+  if (MODE == kLoadFlow && (int)blockIdx.x == S) {
     zroot_block(n, a.parent, a.lvl_off, a.lvl_nodes, a.nlev, a.z, a.Zroot);
     return;
   }
@@ -154,6 +159,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
   const int x = on ? (FIXED ? q : a.ext[q]) : 0;
   const int e = on ? end[q] : 1, t0 = on ? tour[2 * q] : 0, t1 = on ? tour[2 * q + 1] : 0;
   double2 z[9], v[3];
+  double mag[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int k = 0; k < 9; ++k) z[k] = on ? a.z[(size_t)q * 9 + k] : make_double2(0.0, 0.0);
 #pragma unroll
@@ -162,14 +168,18 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
     v[p] = (ph >> p & 1u) ? a.v0[p] : make_double2(0.0, 0.0);
   }
   int it = 0;
-  bool conv = false;
-  for (it = 1; it <= a.maxit; ++it) {
+  bool conv = false, fixed = FIXED;  // fixed: at the currents L
+  for (it = 1; fixed || it <= a.maxit; ++it) {
     double2 c[3];
     // prefix sums of the load currents
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       c[p] = make_double2(0.0, 0.0);
-      if (FIXED ? on : q > 0 && (ph >> p & 1u)) c[p] = FIXED ? L[p] : cconj(cdiv(L[p], v[p]));
+      if (fixed) {
+        if (on) c[p] = L[p];
+      } else if (q > 0 && (ph >> p & 1u)) {
+        c[p] = cconj(cdiv(L[p], v[p]));
+      }
       c[p] = wave_scan(c[p]);
       if (last) s_tot[0][wv][p] = c[p];
     }
@@ -222,13 +232,59 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
       dmax = nan_max(dmax, cabs2(csub(nv, v[p])));
       v[p] = nv;
     }
-    if (FIXED) break;
+    if (fixed) break;
     dmax = sqrt(block_nan_max(dmax, s_red));  // (squares up to here)
-    if (!(dmax <= 1e3)) break;
-    if (dmax <= a.tol) {
-      conv = true;
-      break;
+    conv = dmax <= a.tol;
+    const bool stop = !(dmax <= 1e3) || conv;
+    if (MODE != kEval) {
+      if (stop) break;
+      continue;
     }
+    if (!stop && it < a.maxit) continue;
+    // the load currents and magnitudes at the final voltages, and the currents
+    // summed over the clusters: prefix sums over the member list
+    if (q == 0 && !conv) atomicOr(a.status, 16);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const bool pr = ph >> p & 1u;
+      if (on) L[p] = q > 0 && pr ? cconj(cdiv(L[p], v[p])) : make_double2(0.0, 0.0);
+      mag[p] = pr ? sqrt(cabs2(v[p])) : 0.0;
+    }
+    __syncthreads();
+    const int mq = on ? ev.mem[q] : 0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      c[p] = wave_scan(on ? flow_lds[6 * n + 3 * mq + p] : make_double2(0.0, 0.0));
+      if (last) s_tot[0][wv][p] = c[p];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      c[p] = cadd(c[p], waves_before(&s_tot[0][0][p], 3, wv));
+      if (on) X[q * 3 + p] = c[p];
+    }
+    __syncthreads();
+    const int m0 = on ? ev.moff[q] : 0, m1 = on ? ev.moff[q + 1] : 0;
+    if (on)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const double2 hi = m1 > 0 ? X[(m1 - 1) * 3 + p] : make_double2(0.0, 0.0);
+        const double2 lo = m0 > 0 ? X[(m0 - 1) * 3 + p] : make_double2(0.0, 0.0);
+        L[p] = csub(hi, lo);
+      }
+    fixed = true;  // (a barrier precedes the next write of X)
+  }
+  if (MODE == kEval) {
+    double e = 0.0;
+    if (on) {
+      const int s = ev.sup[q];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        if (ph >> p & 1u) e = fmax(e, fabs(mag[p] - sqrt(cabs2(csub(a.v0[p], X[s * 3 + p])))));
+    }
+    e = block_reduce(e, [](double x, double y) { return fmax(x, y); }, s_red);
+    if (q == 0) ev.err[blockIdx.x] = e;
+    return;
   }
   if (on)
 #pragma unroll
@@ -512,10 +568,11 @@ FlowPlan flow_tables(int n, const int* end, const uint8_t* phase, std::vector<in
 }
 
 hipError_t flow_prepare(const FlowPlan& p) {
-  const void* f[2] = {nullptr, nullptr};
+  const void* f[3] = {nullptr, nullptr, nullptr};
   if (p.form == 1 && node_lds(p.n) > 60 * 1024) {
-    f[0] = reinterpret_cast<const void*>(&k_flow_node<false>);
-    f[1] = reinterpret_cast<const void*>(&k_flow_node<true>);
+    f[0] = reinterpret_cast<const void*>(&k_flow_node<kLoadFlow>);
+    f[1] = reinterpret_cast<const void*>(&k_flow_node<kFixed>);
+    f[2] = reinterpret_cast<const void*>(&k_flow_node<kEval>);
   } else if (p.form == 2 && phase_lds(p) > 60 * 1024) {
     f[0] = reinterpret_cast<const void*>(&k_flow_phase<false>);
     f[1] = reinterpret_cast<const void*>(&k_flow_phase<true>);
@@ -530,11 +587,16 @@ hipError_t flow_prepare(const FlowPlan& p) {
 
 void flow_launch(const FlowPlan& p, const FlowArgs& a, int S, hipStream_t st) {
   if (p.form == 1)
-    hipLaunchKernelGGL(k_flow_node<false>, dim3(S + 1), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
-                       a.tab + p.end, a.tab + p.tour, a);
+    hipLaunchKernelGGL(k_flow_node<kLoadFlow>, dim3(S + 1), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
+                       a.tab + p.end, a.tab + p.tour, a, FlowEval{});
   else
     hipLaunchKernelGGL(k_flow_phase<false>, dim3(S + 1), dim3(kFlowThreads), phase_lds(p), st, p.n, S,
                        phases(p, a.tab), a);
+}
+
+void flow_eval_launch(const FlowPlan& p, const FlowArgs& a, const FlowEval& e, int S, hipStream_t st) {
+  hipLaunchKernelGGL(k_flow_node<kEval>, dim3(S), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
+                     a.tab + p.end, a.tab + p.tour, a, e);
 }
 
 void flow_fixed_launch(const FlowPlan& p, const int* tab, const uint8_t* phase, const double2* z, const double2* v0,
@@ -548,8 +610,8 @@ void flow_fixed_launch(const FlowPlan& p, const int* tab, const uint8_t* phase, 
   a.V = V;
   a.J = J;
   if (p.form == 1)
-    hipLaunchKernelGGL(k_flow_node<true>, dim3(S), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S, tab + p.end,
-                       tab + p.tour, a);
+    hipLaunchKernelGGL(k_flow_node<kFixed>, dim3(S), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
+                       tab + p.end, tab + p.tour, a, FlowEval{});
   else
     hipLaunchKernelGGL(k_flow_phase<true>, dim3(S), dim3(kFlowThreads), phase_lds(p), st, p.n, S, phases(p, tab), a);
 }

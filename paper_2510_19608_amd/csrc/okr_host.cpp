@@ -21,7 +21,7 @@
 namespace okr {
 // kernels (okr_kernels.hip, okr_build.hip)
 __global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const int*, const double2*,
-                           const double2*, double2*, int*);
+                           const double2*, double2*, int*, State);
 __global__ void k_powerflow(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                             const double2*, const double2*, double2, double2, double2, double, int, double, double,
                             double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
@@ -50,11 +50,10 @@ __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, con
                               const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*, int, int);
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
                          DevDecision*, const int*, uint32_t*, int*, const int*, Topo, State);
-__global__ void k_init_state(int, State, int*, int);
 __global__ void k_copy2(const double2*, double2*, size_t);
-__global__ void k_final_err(int, const uint8_t*, const int*, const double2*, const double*, double*);
-__global__ void k_kron_yeq(Topo, State, const double2*, double2*, double2*, int*, int*);
-__global__ void k_kron_diag(Topo, State, const double2*, double2*);
+__global__ void k_final(Topo, State, int, const double2*, double2*, double2*, int*, int*, const double2*, const double*,
+                        double*);
+__global__ void k_kron_diag(Topo, State, const double2*, double2*, const int*, int*, int);
 __global__ void k_sqrt_selftest(const double*, double*, int);
 __global__ void k_pat32(const SegHdr*, const int*, size_t, const int*, const int*, const double2*, const TargetRec*,
                         const double2*, const TargetRec*, double, double, TermsCaps, int2*, int*);
@@ -142,7 +141,7 @@ struct Layout {
 // offsets (in int32) of the static topology arrays inside the topology buffer
 struct TopoOffsets {
   int parent, phase, segment, size, ext, ch_off, ch, lvl_off, lvl_nodes, bfs_cf, bfs_pp, seg_off, seg_nodes,
-      chunks, units, seg_top, total;
+      chunks, units, seg_top, status, total;
   FlowPlan flow;
 };
 
@@ -670,6 +669,7 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
     uint8_t* ph = reinterpret_cast<uint8_t*>(tp.data() + TO.phase);
     for (int q = 0; q < n; ++q) ph[q] = h->phase[h->pre[q]];
   }
+  TO.status = put(std::vector<int>(kStatusInts, 0));  // (cleared by the upload; the results get a copy)
   TO.total = (int)tp.size();
   // table capacity of one segment (layout written by build_struct)
   h->tab_cap = kMaxK * kChainInts + kMaxK * kMaxK + n + kMaxK * kSlotInts + kMaxPairs * kPairInts + 3 * kMaxK +
@@ -783,7 +783,7 @@ struct Ptrs {
   const int *tp, *lvl_off, *lvl_nodes, *bfs_cf, *bfs_pp, *chunks, *units;
   double2 *z, *Zroot, *Vhat, *Vcur, *A, *J, *P, *headV, *yeq, *Ykd, *Yko;
   double *absV, *econst, *err;
-  int *status, *iters, *tab, *tab2, *kp;
+  int *status, *status_out, *iters, *tab, *tab2, *kp;
   SegHdr* hdrs;
   DevDecision* decs;
   TargetRec *srec, *zrec;
@@ -849,7 +849,8 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   p.A = (double2*)at(L.A);
   p.J = (double2*)at(L.J);
   p.absV = (double*)at(L.absV);
-  p.status = (int*)at(L.status);
+  p.status = tp + TO.status;
+  p.status_out = (int*)at(L.status);
   p.iters = (int*)at(L.iters);
   p.hdrs = (SegHdr*)at(L.hdrs);
   p.decs = (DevDecision*)at(L.decs);
@@ -1007,10 +1008,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   std::vector<Ptrs> lp(h->nlanes);
   for (int l = 0; l < h->nlanes; ++l) lp[l] = pointers(h, ws, l);
   const bool vhat_given = (mg->flags & OKR_FLAG_VHAT_GIVEN) != 0;
-  const int ninit = std::max(n, kStatusInts);
-  hipLaunchKernelGGL(k_init_state, dim3((ninit + 255) / 256), dim3(256), 0, st, n, p.St, p.status, kStatusInts);
-  hipLaunchKernelGGL(k_branch_z, dim3((n + 127) / 128), dim3(128), 0, st, n, p.T.parent, p.T.phase, p.T.ch_off,
-                     p.T.ch, p.T.ext, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status);
+  hipLaunchKernelGGL(k_branch_z, dim3((n + 63) / 64), dim3(64), 0, st, n, p.T.parent, p.T.phase, p.T.ch_off,
+                     p.T.ch, p.T.ext, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status, p.St);
   if (vhat_given || !h->TO.flow.form)  // (otherwise beside the load flow)
     hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev,
                        (const double2*)p.z, p.Zroot);
@@ -1233,11 +1232,12 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
                        (const int*)q.tab, (const DevDecision*)q.decs, (const double2*)q.P, (const TargetRec*)q.srec,
                        (const TargetRec*)q.zrec, q.Vcur, q.A);
   }
-  hipLaunchKernelGGL(k_kron_yeq, dim3((n + 127) / 128), dim3(128), 0, st, p.T, p.St, (const double2*)p.z, p.yeq,
-                     p.Yko, p.kp, p.status);
-  hipLaunchKernelGGL(k_kron_diag, dim3((n + 127) / 128), dim3(128), 0, st, p.T, p.St, (const double2*)p.yeq, p.Ykd);
-  hipLaunchKernelGGL(k_final_err, dim3(S), dim3(256), 0, st, n, p.T.phase, (const int*)p.St.sup,
-                     (const double2*)p.Vcur, (const double*)p.absV, p.err);
+  const int ny = (n + 63) / 64;
+  hipLaunchKernelGGL(k_final, dim3(ny + S), dim3(512), 0, st, p.T, p.St, ny, (const double2*)p.z, p.yeq, p.Yko, p.kp,
+                     p.status, (const double2*)p.Vcur, (const double*)p.absV, p.err);
+  const int nd = std::max(n, kStatusInts);
+  hipLaunchKernelGGL(k_kron_diag, dim3((nd + 127) / 128), dim3(128), 0, st, p.T, p.St, (const double2*)p.yeq, p.Ykd,
+                     (const int*)p.status, p.status_out, kStatusInts);
 }
 
 uint64_t bits(double x) {

@@ -24,31 +24,36 @@ namespace okr {
 // Restricted inverse of a 3x3 block on the phases in `mask` (zero-padded):
 // for blocks supported on the present-phase principal submatrix this is the
 // Moore-Penrose pseudo-inverse (Section II.B footnote).  Closed forms for
-// 1x1, 2x2 (adjugate) and 3x3 (cofactors).  Returns false if singular.
-__device__ bool inv_restricted(const double2* A, unsigned mask, double2* out) {
-  int idx[3];
-  int m = 0;
-  for (int p = 0; p < 3; ++p)
-    if (mask >> p & 1u) idx[m++] = p;
+// 1x1, 2x2 (adjugate) and 3x3 (cofactors), with constant indices so that the
+// blocks stay in registers.  Returns false if singular.
+template <int I>
+__device__ __forceinline__ bool inv_one(const double2* A, double2* out) {
+  const double2 a = A[I * 4];
+  if (cabs2(a) == 0.0) return false;
+  out[I * 4] = cdiv(make_double2(1.0, 0.0), a);
+  return true;
+}
+template <int I, int J>
+__device__ __forceinline__ bool inv_two(const double2* A, double2* out) {
+  const double2 a = A[I * 3 + I], b = A[I * 3 + J], c = A[J * 3 + I], d = A[J * 3 + J];
+  const double2 det = csub(cmul(a, d), cmul(b, c));
+  if (cabs2(det) == 0.0) return false;
+  out[I * 3 + I] = cdiv(d, det);
+  out[I * 3 + J] = cdiv(make_double2(-b.x, -b.y), det);
+  out[J * 3 + I] = cdiv(make_double2(-c.x, -c.y), det);
+  out[J * 3 + J] = cdiv(a, det);
+  return true;
+}
+__device__ __forceinline__ bool inv_restricted(const double2* A, unsigned mask, double2* out) {
+#pragma unroll
   for (int q = 0; q < 9; ++q) out[q] = make_double2(0.0, 0.0);
-  if (m == 1) {
-    const double2 a = A[idx[0] * 4];
-    if (cabs2(a) == 0.0) return false;
-    out[idx[0] * 4] = cdiv(make_double2(1.0, 0.0), a);
-    return true;
-  }
-  if (m == 2) {
-    const int i = idx[0], j = idx[1];
-    const double2 a = A[i * 3 + i], b = A[i * 3 + j], c = A[j * 3 + i], d = A[j * 3 + j];
-    const double2 det = csub(cmul(a, d), cmul(b, c));
-    if (cabs2(det) == 0.0) return false;
-    out[i * 3 + i] = cdiv(d, det);
-    out[i * 3 + j] = cdiv(make_double2(-b.x, -b.y), det);
-    out[j * 3 + i] = cdiv(make_double2(-c.x, -c.y), det);
-    out[j * 3 + j] = cdiv(a, det);
-    return true;
-  }
-  if (m == 3) {
+  if (mask == 1) return inv_one<0>(A, out);
+  if (mask == 2) return inv_one<1>(A, out);
+  if (mask == 4) return inv_one<2>(A, out);
+  if (mask == 3) return inv_two<0, 1>(A, out);
+  if (mask == 5) return inv_two<0, 2>(A, out);
+  if (mask == 6) return inv_two<1, 2>(A, out);
+  if (mask == 7) {
     double2 cof[9];
     for (int r = 0; r < 3; ++r)
       for (int c = 0; c < 3; ++c) {
@@ -61,27 +66,37 @@ __device__ bool inv_restricted(const double2* A, unsigned mask, double2* out) {
       for (int c = 0; c < 3; ++c) out[r * 3 + c] = cdiv(cof[c * 3 + r], det);
     return true;
   }
-  return m == 0;
+  return mask == 0;
 }
 
+// Largest |A_q| (one square root: it is monotone).
 __device__ __forceinline__ double blk_maxabs(const double2* A) {
   double mx = 0.0;
-  for (int q = 0; q < 9; ++q) mx = fmax(mx, sqrt(cabs2(A[q])));
-  return mx;
+  for (int q = 0; q < 9; ++q) mx = fmax(mx, cabs2(A[q]));
+  return sqrt(mx);
 }
 
 // ---------------------------------------------------------- validation + z --
 // One thread per node: branch impedance z_i = (-Y_{i,parent})^+ and checks of
 // the admittance input (symmetry, zero absent-phase entries, no shunts).  ext
 // (or null: the same) maps the labels of the tree arrays and z to the input's
-// node ids.
+// node ids.  With a search state it also resets that node's (every node kept and
+// its own super-node, the maps empty).
 // status bits: 1 singular, 2 absent-phase entry, 4 asymmetric, 8 shunt.
-__global__ void k_branch_z(int n, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
+// Bound by the latency of one wave's FP64 chain and its instruction fetch: the
+// comparisons take one square root each, of the largest square.
+__global__ __launch_bounds__(64) void k_branch_z(int n, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
                            const int* __restrict__ ch_off, const int* __restrict__ ch, const int* __restrict__ ext,
                            const double2* __restrict__ Ydiag, const double2* __restrict__ Yoff,
-                           double2* __restrict__ z, int* __restrict__ status) {
+                           double2* __restrict__ z, int* __restrict__ status, State St) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
+  if (St.kept) {
+    St.kept[i] = 1;
+    St.sup[i] = i;
+    St.slot_of[i] = -1;
+    for (int p = 0; p < 3; ++p) St.zent_of[i * 3 + p] = -1;
+  }
   const unsigned ph = phase[i];
   int bad = 0;
   const int x = ext ? ext[i] : i;
@@ -94,13 +109,14 @@ __global__ void k_branch_z(int n, const int* __restrict__ parent, const uint8_t*
     const double2* Yo = Yoff + (size_t)x * 9;
     for (int q = 0; q < 9; ++q) acc[q] = cadd(acc[q], Yo[q]);
     const double oscale = blk_maxabs(Yo);
+    double asym = 0.0;
     for (int r = 0; r < 3; ++r)
       for (int c = 0; c < 3; ++c) {
-        const double2 d = csub(Yo[r * 3 + c], Yo[c * 3 + r]);
-        if (sqrt(cabs2(d)) > 1e-12 * oscale) bad |= 4;
+        asym = fmax(asym, cabs2(csub(Yo[r * 3 + c], Yo[c * 3 + r])));
         const bool absent = !((ph >> r) & 1u) || !((ph >> c) & 1u);
         if (absent && cabs2(Yo[r * 3 + c]) != 0.0) bad |= 2;
       }
+    if (sqrt(asym) > 1e-12 * oscale) bad |= 4;
     double2 y[9];
     for (int q = 0; q < 9; ++q) y[q] = make_double2(-Yo[q].x, -Yo[q].y);
     if (!inv_restricted(y, ph, z + (size_t)i * 9)) bad |= 1;
@@ -651,49 +667,18 @@ __global__ void k_sqrt_selftest(const double* __restrict__ x, double* __restrict
   if (i < n) y[i] = sqrt_nr(x[i]);
 }
 
-// Reset of the search state at the start of a call (no memset nodes, so the
-// sequence can be captured in a graph).
-__global__ void k_init_state(int n, State St, int* __restrict__ status, int nstatus) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    St.kept[i] = 1;
-    St.sup[i] = i;
-    St.slot_of[i] = -1;
-    St.zent_of[3 * i] = St.zent_of[3 * i + 1] = St.zent_of[3 * i + 2] = -1;
-  }
-  if (i < nstatus) status[i] = 0;
-}
-
 __global__ void k_copy2(const double2* __restrict__ a, double2* __restrict__ b, size_t count) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
     b[i] = a[i];
 }
 
 // ---------------------------------------------------------- final outputs --
-// Per-snapshot max error of the final reduction over every node-phase.
-__global__ __launch_bounds__(256) void k_final_err(int n, const uint8_t* __restrict__ phase,
-                                                   const int* __restrict__ sup, const double2* __restrict__ Vcur,
-                                                   const double* __restrict__ absV, double* __restrict__ err) {
-  __shared__ double shd[16];
-  const int l = blockIdx.x;
-  double e = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
-    for (int p = 0; p < 3; ++p) {
-      if (!(phase[i] >> p & 1u)) continue;
-      const double m = sqrt(cabs2(Vcur[((size_t)l * n + sup[i]) * 3 + p]));
-      e = fmax(e, fabs(m - absV[((size_t)l * n + i) * 3 + p]));
-    }
-  e = block_reduce(e, [](double a, double b) { return fmax(a, b); }, shd);
-  if (threadIdx.x == 0) err[l] = e;
-}
-
 // Kron-reduced branch of every kept node: the eliminated path up to its kept
 // parent is a series chain, so y_eq = (sum of z on the path, restricted to
 // the node's phases)^-1 (eq. Y_kron for degree-2 and leaf eliminations).
-__global__ void k_kron_yeq(Topo T, State St, const double2* __restrict__ z, double2* __restrict__ yeq,
-                           double2* __restrict__ Yk_off, int* __restrict__ kp_out, int* __restrict__ status) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= T.n) return;
+__device__ __forceinline__ void kron_yeq(int x, const Topo& T, const State& St, const double2* __restrict__ z,
+                                         double2* __restrict__ yeq, double2* __restrict__ Yk_off,
+                                         int* __restrict__ kp_out, int* __restrict__ status) {
   const int xe = T.ext[x];  // (the outputs go by the caller's node ids)
   double2* yo = Yk_off + (size_t)xe * 9;
   double2* ye = yeq + (size_t)x * 9;
@@ -717,8 +702,41 @@ __global__ void k_kron_yeq(Topo T, State St, const double2* __restrict__ z, doub
 // Y_Kron(x,x) = y_eq of x's own branch plus those of its reduced-network
 // children, found by following each tree child down through reduced nodes
 // (which have at most one child) to the first kept node.
-__global__ void k_kron_diag(Topo T, State St, const double2* __restrict__ yeq, double2* __restrict__ Yk_diag) {
+
+// Final outputs that wait for nothing but the search: the first ny blocks form
+// the admittances of the kept branches (one wave of nodes each, for their long
+// FP64 chains to run on many CUs), each other block one snapshot's largest error
+// of the final reduction over every node-phase.  (As two launches 10 and 7.4 us
+// at 1000 nodes; the errors with 256 threads a block 42 us at 6000 nodes.)
+__global__ __launch_bounds__(512) void k_final(Topo T, State St, int ny, const double2* __restrict__ z,
+                                               double2* __restrict__ yeq, double2* __restrict__ Yk_off,
+                                               int* __restrict__ kp_out, int* __restrict__ status,
+                                               const double2* __restrict__ Vcur, const double* __restrict__ absV,
+                                               double* __restrict__ err) {
+  __shared__ double shd[16];
+  if ((int)blockIdx.x < ny) {
+    const int x = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x < 64 && x < T.n) kron_yeq(x, T, St, z, yeq, Yk_off, kp_out, status);
+    return;
+  }
+  const int l = blockIdx.x - ny, n = T.n;
+  double e = 0.0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const unsigned ph = T.phase[i];
+    const size_t at = ((size_t)l * n + i) * 3, as = ((size_t)l * n + St.sup[i]) * 3;
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      if (ph >> p & 1u) e = fmax(e, fabs(sqrt(cabs2(Vcur[as + p])) - absV[at + p]));
+  }
+  e = block_reduce(e, [](double a, double b) { return fmax(a, b); }, shd);
+  if (threadIdx.x == 0) err[l] = e;
+}
+
+// Diagonal blocks of the reduced network; the status word joins the results.
+__global__ void k_kron_diag(Topo T, State St, const double2* __restrict__ yeq, double2* __restrict__ Yk_diag,
+                            const int* __restrict__ status, int* __restrict__ status_out, int nstatus) {
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
+  if (x < nstatus) status_out[x] = status[x];
   if (x >= T.n) return;
   double2 D[9];
   for (int q = 0; q < 9; ++q) D[q] = make_double2(0.0, 0.0);
