@@ -14,6 +14,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include "okr_device.h"
 #include "okr_internal.h"
 
 namespace okr {
@@ -30,27 +31,6 @@ __device__ __forceinline__ int child_toward(const Topo& T, int h, int v) {
   }
   return -1;
 }
-
-// Orders a wave's own LDS accesses (no other wave takes part).
-__device__ __forceinline__ void wave_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Inclusive prefix sum of an int over the first 32 lanes, or the whole wave.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_add(int v) {
-  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, ROWS == 0xf);
-}
-__device__ __forceinline__ int scan32(int v) {
-  v = dpp_add<0x111, 0xf>(v);
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  v = dpp_add<0x118, 0xf>(v);
-  return dpp_add<0x142, 0xa>(v);
-}
-__device__ __forceinline__ int scan64(int v) { return dpp_add<0x143, 0xc>(scan32(v)); }
 
 // Structural tables of segment segs[z] (one block).  Wave 0 finds the chains on
 // its own: a lane per segment node, then per chain, comparisons over readlane

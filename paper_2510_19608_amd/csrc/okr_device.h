@@ -218,6 +218,139 @@ __device__ __forceinline__ void score_chain(const int* __restrict__ chains, cons
     }
 }
 
+// Orders a wave's own LDS accesses (no other wave takes part).
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Inclusive prefix sum of an int over the first 32 lanes, or the whole wave.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, ROWS == 0xf);
+}
+__device__ __forceinline__ int scan32(int v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  return dpp_add<0x142, 0xa>(v);
+}
+__device__ __forceinline__ int scan64(int v) { return dpp_add<0x143, 0xc>(scan32(v)); }
+
+// ------------------------------------------------------------- SMICE prep --
+// Node of Omega_g with flattened index q (ranges: start, end, cumulative).
+__device__ __forceinline__ int omega_node(const int* rg, int nr, int q) {
+  int r = 0;
+  while (r + 1 < nr && rg[3 * (r + 1) + 2] <= q) ++r;
+  return rg[3 * r] + (q - rg[3 * r + 2]);
+}
+
+// Zone entry of the lowest present phase of node i, or -1 if i is not a
+// zone target of this segment.
+__device__ __forceinline__ int sm_first_entry(const Topo& T, const State& St, int i, int nz) {
+  const unsigned ph = T.phase[i];
+  for (int p = 0; p < 3; ++p)
+    if (ph >> p & 1u) {
+      const int e = St.zent_of[i * 3 + p];
+      return (e >= 0 && e < nz) ? e : -1;
+    }
+  return -1;
+}
+
+// A segment's SMICE tables (one block of up to 1024 threads): distinct heads in
+// chain order, zone targets grouped by anchor chain in Omega_g order, head
+// maxima zeroed.  A second block of the arg-min's launch: the two read nothing
+// of each other's (as a launch of its own, with one thread's loop over the heads
+// and a serial sum over 256 threads' counts, 11 us per chunk at 1000 nodes).
+__device__ __forceinline__ void smice_prep(const SegHdr& H, const int* tab, const Topo& T, const State& St, int* stab,
+                                           double* hK, int S) {
+  __shared__ int s_hnode[kMaxK], s_nh, s_cnt[kMaxK], s_run[kMaxK], s_w[16][kMaxK];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
+  if (!H.valid) {
+    if (tid == 0) {
+      stab[SM_NH] = 0;
+      stab[SM_NZN] = 0;
+    }
+    return;
+  }
+  const int nch = H.nchains, nom = H.nomega;
+  if (wv == 0) {
+    int head = -1, outer = -1, first = lane;
+    if (lane < nch) {
+      head = tab[H.o_chain + lane * kChainInts + C_HEAD];
+      outer = tab[H.o_chain + lane * kChainInts + C_OUTER];
+    }
+    for (int q = nch - 1; q >= 0; --q)
+      if (q < lane && __builtin_amdgcn_readlane(head, q) == head) first = q;
+    const uint32_t firsts = (uint32_t)__ballot(lane < nch && first == lane);
+    const int x = __popc(firsts & ((1u << (first & 31)) - 1u));  // the head's number
+    if (lane < nch) {
+      stab[SM_CHX + lane] = x;
+      s_cnt[lane] = 0;
+      if (first == lane) {
+        s_hnode[x] = head;
+        stab[SM_HNODE + x] = head;
+        stab[SM_HIN + x] = outer >= 0 ? 1 : 0;
+      }
+    }
+    if (lane == 0) s_nh = stab[SM_NH] = __popc(firsts);
+  }
+  __syncthreads();
+  const int nh = s_nh;
+  for (int t = tid; t < nh * S; t += blockDim.x) hK[t] = 0.0;
+  const int* rg = tab + H.o_range;
+  auto anchor = [&](int q, int& i) {  // anchor chain of Omega_g node q, -1: no target
+    i = omega_node(rg, H.nrange, q);
+    const int e = sm_first_entry(T, St, i, H.nz);
+    return e >= 0 ? tab[H.o_zent + 3 * e + 2] : -1;
+  };
+  int node = 0, at = tid < nom ? anchor(tid, node) : -1;
+  for (int q = tid; q < nom; q += blockDim.x) {
+    int i = node;
+    const int c = q == tid ? at : anchor(q, i);
+    if (c >= 0) atomicAdd(&s_cnt[c], 1);
+  }
+  __syncthreads();
+  if (wv == 0) {
+    const int v = lane < nch ? s_cnt[lane] : 0, x = scan32(v);
+    if (lane < nch) stab[SM_ZOFF + lane] = s_run[lane] = x - v;
+    if (lane == nch - 1) stab[SM_ZOFF + nch] = stab[SM_NZN] = x;
+  }
+  __syncthreads();
+  for (int q = tid; q - tid < nom; q += blockDim.x) {  // (rounds of the whole block, in order)
+    int c = -1;
+    if (q < nom) c = q == tid ? at : anchor(q, node);
+    int rank = 0;
+    for (int y = 0; y < nch; ++y) {
+      const unsigned long long b = __ballot(c == y);
+      if (c == y) rank = __popcll(b & ((1ull << lane) - 1ull));
+      if (lane == 0) s_w[wv][y] = __popcll(b);
+    }
+    __syncthreads();
+    if (c >= 0) {
+      int to = s_run[c] + rank;
+      for (int w = 0; w < wv; ++w) to += s_w[w][c];
+      int* zr = stab + SM_ZREC + to * kZrecInts;
+      zr[0] = node;
+      const unsigned ph = T.phase[node];
+      for (int p = 0; p < 3; ++p) {
+        const int ep = St.zent_of[node * 3 + p];
+        zr[1 + p] = ((ph >> p & 1u) && ep >= 0 && ep < H.nz) ? ep : -1;
+      }
+      int hx = -1;
+      for (int x = 0; x < nh; ++x)
+        if (s_hnode[x] == node) hx = x;
+      zr[4] = hx;
+    }
+    __syncthreads();
+    if (tid < nch)
+      for (int w = 0; w < nw; ++w) s_run[tid] += s_w[w][tid];
+    __syncthreads();
+  }
+}
+
 // ---------------------------------------------------------- state update --
 // The structural part of applying a mask to segment H (one block, called by
 // every thread): kept flags and super-nodes over Omega_g, and the node -> slot
@@ -231,11 +364,6 @@ __device__ __forceinline__ void score_chain(const int* __restrict__ chains, cons
 // memory after the decision took 2.3 us of the 10.1 us arg-min at 1000 nodes.
 struct StateUpdate {
   int up[kMaxK], upnode[kMaxK], node[kMaxK], bit[kMaxK];  // (LDS)
-  __device__ __forceinline__ static int omega_node(const SegHdr& H, const int* rg, int q) {
-    int r = 0;
-    while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
-    return rg[3 * r] + (q - rg[3 * r + 2]);
-  }
   // i, s, js: this thread's first node of Omega_g, its super-node and that
   // one's slot.  Ends with the map reads done (before the caller's barrier).
   __device__ __forceinline__ void load(const SegHdr& H, const int* tab, const Topo& T, const State& St, int& i, int& s,
@@ -243,7 +371,7 @@ struct StateUpdate {
     const int* slots = tab + H.o_slot;
     i = s = js = -1;
     if ((int)threadIdx.x < H.nomega) {
-      i = omega_node(H, tab + H.o_range, threadIdx.x);
+      i = omega_node(tab + H.o_range, H.nrange, threadIdx.x);
       s = St.sup[i];
       js = St.slot_of[s];
     }
@@ -272,7 +400,7 @@ struct StateUpdate {
       if (v != s) St.sup[i] = v;
     }
     for (int q = threadIdx.x + blockDim.x; q < H.nomega; q += blockDim.x) {
-      const int x = omega_node(H, tab + H.o_range, q), y = St.sup[x], j = St.slot_of[y];
+      const int x = omega_node(tab + H.o_range, H.nrange, q), y = St.sup[x], j = St.slot_of[y];
       if (j >= 0) St.sup[x] = super_of(j, m);
     }
     __syncthreads();  // the slot map is read

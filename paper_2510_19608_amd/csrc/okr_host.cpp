@@ -49,7 +49,7 @@ __global__ void k_surr_rank(const SegHdr*, int, const int*, const float*, const 
 __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, const unsigned long long*,
                               const unsigned long long*, SelParams, MaskScore*, TileRec*, const int*, int, int);
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
-                         DevDecision*, const int*, uint32_t*, int*, const int*, Topo, State);
+                         DevDecision*, const int*, uint32_t*, int*, const int*, Topo, State, SmicePrep);
 __global__ void k_copy2(const double2*, double2*, size_t);
 __global__ void k_final(Topo, State, int, const double2*, double2*, double2*, int*, int*, const double2*, const double*,
                         double*);
@@ -87,7 +87,6 @@ __global__ void k_topk(const SegHdr*, int, const uint32_t*, const uint32_t*, int
 __global__ void k_surr_decide(const SegHdr*, int, SelParams, const int*, const uint32_t*, const int*,
                               const MaskScore*, DevDecision*, int*);
 __global__ void k_zero_f32(float*, int);
-__global__ void k_smice_prep(const SegHdr*, const int*, size_t, const int*, Topo, State, int*, double*, int);
 __global__ void k_smice_hconst(const SegHdr*, const int*, size_t, Topo, State, const double2*, const double*,
                                const int*, double*, int);
 __global__ void k_smice_score(const SegHdr*, const int*, size_t, const int*, const double2*, const TargetRec*,
@@ -1147,14 +1146,13 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       else pattern_tables(h, q, c, st);
       pattern_combine(h, q, c, sp, gates, dump || feat_out, st);
       if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
-      hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
+      hipLaunchKernelGGL(k_argmin, dim3(smice ? 2 : 1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates,
                          smice ? q.smlist : (uint32_t*)nullptr, smice ? q.smcount : (int*)nullptr,
-                         smice ? (const int*)nullptr : (const int*)q.tab, q.T, q.St);
+                         smice ? (const int*)nullptr : (const int*)q.tab, q.T, q.St,
+                         SmicePrep{(const int*)q.tab, q.stab, q.hK, S});
       if (smice) {
         // SMICE of the feasible masks of the chosen level, and the decision under it
-        hipLaunchKernelGGL(k_smice_prep, dim3(1, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
-                           (const int*)q.tab, q.T, q.St, q.stab, q.hK, S);
         hipLaunchKernelGGL(k_smice_hconst, dim3(members_blocks, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs,
                            lstride, q.T, q.St, (const double2*)q.Vcur, (const double*)q.absV, (const int*)q.stab,
                            q.hK, S);
@@ -1214,7 +1212,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       pattern_combine(h, q, c, sp, q.sgates, false, st);
       hipLaunchKernelGGL(k_argmin, dim3(1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs,
-                         (const int*)q.sgates, (uint32_t*)nullptr, (int*)nullptr, (const int*)q.tab, q.T, q.St);
+                         (const int*)q.sgates, (uint32_t*)nullptr, (int*)nullptr, (const int*)q.tab, q.T, q.St,
+                         SmicePrep{});
       if (dump)
         for (int z = 0; z < nz; ++z) {
           const int g = h->chunk_segs[c0 + z];

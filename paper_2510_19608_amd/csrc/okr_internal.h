@@ -239,6 +239,14 @@ enum { SM_NH = 0, SM_NZN = 1, SM_CHX = 2, SM_HNODE = SM_CHX + kMaxK, SM_HIN = SM
        SM_ZOFF = SM_HIN + kMaxK, SM_ZREC = SM_ZOFF + kMaxK + 1 };
 constexpr int kZrecInts = 5;
 
+// What the SMICE tables of a chunk need besides the state (null: not the key).
+struct SmicePrep {
+  const int* tab;
+  int* stab;
+  double* hK;
+  int S;
+};
+
 struct MixedState {  // per segment: the screening levels and shortlist sizes
   int lo_level, hi_level, best, nA, nB, pad;
   double e_up;

@@ -462,7 +462,7 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
                                                  const int* __restrict__ status, DevDecision* __restrict__ decs,
                                                  const int* __restrict__ gates, uint32_t* __restrict__ slist,
                                                  int* __restrict__ scount, const int* __restrict__ tab, Topo T,
-                                                 State St) {
+                                                 State St, SmicePrep pp) {
   // one slot per wave for each reduction (each its own array, so no
   // reduction's slots are written while another's are still being read)
   __shared__ int s_best[16], s_near[16], s_amb[16];
@@ -473,6 +473,10 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   __shared__ StateUpdate su;
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
+  if (blockIdx.x == 1) {  // (SMICE as the key: the segment's tables for it)
+    smice_prep(H, lane_ptr(pp.tab, lstride), T, St, lane_ptr(pp.stab, lstride), lane_ptr(pp.hK, lstride), pp.S);
+    return;
+  }
   tab = lane_ptr(tab, lstride);
   const int tid = threadIdx.x, bd = blockDim.x, lane = tid & 63, wv = tid >> 6, nw = bd >> 6;
   const bool upd = tab && H.valid;

@@ -12,10 +12,11 @@
 // groups' extreme |V^|), so each group enters once per phase, as in the
 // per-mask scoring.
 //
-//   k_smice_prep   (1 block)  distinct heads, zone targets grouped by their
-//                             anchor chain in Omega_g order, head maxima zeroed
+//   (k_argmin)                lists mask 0 and the candidate masks; its second
+//                             block, smice_prep: distinct heads, zone targets
+//                             grouped by their anchor chain in Omega_g order,
+//                             head maxima zeroed
 //   k_smice_hconst (grid)     fixed error of each outside head's cluster
-//   (k_argmin)                lists mask 0 and the candidate masks
 //   k_smice_score  (grid)     SMICE of every listed mask
 //   k_smice_argmin (1 block)  the smallest SMICE, tie rule, margin, flags
 #include <hip/hip_runtime.h>
@@ -26,124 +27,6 @@
 #include "okr_internal.h"
 
 namespace okr {
-
-// Node of Omega_g with flattened index q (ranges: start, end, cumulative).
-__device__ __forceinline__ int sm_omega_node(const Topo& T, const int* rg, int nr, int q) {
-  int r = 0;
-  while (r + 1 < nr && rg[3 * (r + 1) + 2] <= q) ++r;
-  return rg[3 * r] + (q - rg[3 * r + 2]);
-}
-
-// Zone entry of the lowest present phase of node i, or -1 if i is not a
-// zone target of this segment.
-__device__ __forceinline__ int sm_first_entry(const Topo& T, const State& St, int i, int nz) {
-  const unsigned ph = T.phase[i];
-  for (int p = 0; p < 3; ++p)
-    if (ph >> p & 1u) {
-      const int e = St.zent_of[i * 3 + p];
-      return (e >= 0 && e < nz) ? e : -1;
-    }
-  return -1;
-}
-
-__global__ __launch_bounds__(256) void k_smice_prep(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
-                                                    size_t lstride, const int* __restrict__ tab, Topo T, State St,
-                                                    int* __restrict__ stab, double* __restrict__ hK, int S) {
-  __shared__ int s_cnt[256][kMaxK];  // per thread: zone targets of its Omega range per anchor chain
-  __shared__ int s_tot[kMaxK + 1];
-  __shared__ int s_hnode[kMaxK], s_hin[kMaxK], s_chx[kMaxK], s_nh;
-  const int g = segs[blockIdx.z];
-  const SegHdr H = load_hdr_g(hdrs, g);
-  tab = lane_ptr(tab, lstride);
-  stab = lane_ptr(stab, lstride);
-  hK = lane_ptr(hK, lstride);
-  const int tid = threadIdx.x;
-  if (!H.valid) {
-    if (tid == 0) {
-      stab[SM_NH] = 0;
-      stab[SM_NZN] = 0;
-    }
-    return;
-  }
-  const int nch = H.nchains;
-  const int* chains = tab + H.o_chain;
-  if (tid == 0) {  // distinct heads in chain order
-    int nh = 0;
-    for (int c = 0; c < nch; ++c) {
-      const int hd = chains[c * kChainInts + C_HEAD];
-      int x = 0;
-      while (x < nh && s_hnode[x] != hd) ++x;
-      if (x == nh) {
-        s_hnode[nh] = hd;
-        s_hin[nh] = chains[c * kChainInts + C_OUTER] >= 0 ? 1 : 0;
-        ++nh;
-      }
-      s_chx[c] = x;
-    }
-    s_nh = nh;
-  }
-  for (int c = 0; c < nch; ++c) s_cnt[tid][c] = 0;
-  __syncthreads();
-  const int nh = s_nh;
-  for (int t = tid; t < nh * S; t += blockDim.x) hK[t] = 0.0;
-  // zone targets in Omega_g order: thread tid owns a contiguous range of it
-  const int* rg = tab + H.o_range;
-  const int nom = H.nomega, per = (nom + 255) / 256;
-  const int q0 = min(nom, tid * per), q1 = min(nom, q0 + per);
-  for (int q = q0; q < q1; ++q) {
-    const int i = sm_omega_node(T, rg, H.nrange, q);
-    const int e = sm_first_entry(T, St, i, H.nz);
-    if (e >= 0) s_cnt[tid][tab[H.o_zent + 3 * e + 2]]++;
-  }
-  __syncthreads();
-  if (tid < nch) {  // exclusive scan over threads, per chain
-    int acc = 0;
-    for (int t = 0; t < 256; ++t) {
-      const int v = s_cnt[t][tid];
-      s_cnt[t][tid] = acc;
-      acc += v;
-    }
-    s_tot[tid] = acc;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int acc = 0;
-    for (int c = 0; c < nch; ++c) {
-      const int v = s_tot[c];
-      s_tot[c] = acc;
-      stab[SM_ZOFF + c] = acc;
-      acc += v;
-    }
-    s_tot[nch] = acc;
-    stab[SM_ZOFF + nch] = acc;
-    stab[SM_NZN] = acc;
-    stab[SM_NH] = nh;
-  }
-  if (tid < nch) stab[SM_CHX + tid] = s_chx[tid];
-  if (tid < nh) {
-    stab[SM_HNODE + tid] = s_hnode[tid];
-    stab[SM_HIN + tid] = s_hin[tid];
-  }
-  __syncthreads();
-  for (int q = q0; q < q1; ++q) {
-    const int i = sm_omega_node(T, rg, H.nrange, q);
-    const int e = sm_first_entry(T, St, i, H.nz);
-    if (e < 0) continue;
-    const int c = tab[H.o_zent + 3 * e + 2];
-    const int at = s_tot[c] + s_cnt[tid][c]++;
-    int* zr = stab + SM_ZREC + at * kZrecInts;
-    zr[0] = i;
-    const unsigned ph = T.phase[i];
-    for (int p = 0; p < 3; ++p) {
-      const int ep = St.zent_of[i * 3 + p];
-      zr[1 + p] = ((ph >> p & 1u) && ep >= 0 && ep < H.nz) ? ep : -1;
-    }
-    int hx = -1;
-    for (int x = 0; x < nh; ++x)
-      if (s_hnode[x] == i) hx = x;
-    zr[4] = hx;
-  }
-}
 
 // Fixed error of the cluster of every head outside Omega_g, per snapshot:
 // the largest error over its members (every node whose super-node it is,
