@@ -416,10 +416,15 @@ struct StateUpdate {
 };
 
 // ------------------------------------------------------------ block reduce --
+template <typename T>
+__device__ __forceinline__ T shfl_xor_of(T v, int o) {
+  return __shfl_xor(v, o, 64);
+}
+
 template <typename T, typename Op>
 __device__ T block_reduce(T v, Op op, T* sh) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
-  for (int o = 32; o > 0; o >>= 1) v = op(v, __shfl_xor(v, o, 64));
+  for (int o = 32; o > 0; o >>= 1) v = op(v, shfl_xor_of(v, o));
   __syncthreads();
   if (lane == 0) sh[wid] = v;
   __syncthreads();

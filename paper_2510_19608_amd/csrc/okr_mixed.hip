@@ -18,7 +18,9 @@
 // A listed mask's FP64 score is one pattern entry per chain, so the selections,
 // the scores of both lists and the decision are one launch (ten before: three
 // selections and the lists' chain walks, 100 us per chunk on the 6000-node
-// feeder).
+// feeder).  One block per segment, bound by latency: 17 us per chunk there, 21
+// with the tile records read again for each of four passes and every maximum
+// reduced by itself.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -27,6 +29,23 @@
 #include "okr_internal.h"
 
 namespace okr {
+
+struct Levels {
+  int lo, hi;
+};
+struct Verdict {
+  double dev, runner;
+  unsigned pick;
+  int amb;
+};
+
+__device__ __forceinline__ Levels shfl_xor_of(const Levels& v, int o) {
+  return Levels{__shfl_xor(v.lo, o, 64), __shfl_xor(v.hi, o, 64)};
+}
+__device__ __forceinline__ Verdict shfl_xor_of(const Verdict& v, int o) {
+  return Verdict{__shfl_xor(v.dev, o, 64), __shfl_xor(v.runner, o, 64), (unsigned)__shfl_xor((int)v.pick, o, 64),
+                 __shfl_xor(v.amb, o, 64)};
+}
 
 __device__ __forceinline__ bool skip_segment(const SegHdr& H, const int* status) {
   return !H.valid || (*status & (16 | 32));
@@ -40,7 +59,8 @@ __global__ __launch_bounds__(1024) void k_mixed_decide(
     MaskScore* scoreB, DevDecision* __restrict__ decs, int* __restrict__ redo) {
   __shared__ double shd[16];
   __shared__ int shi[16];
-  __shared__ unsigned shu[16];
+  __shared__ Levels shv[16];
+  __shared__ Verdict shr[16];
   __shared__ int s_pm[kMaxK], s_pb[kMaxK];
   __shared__ int cand[1024], ncand, nlist;
   const int g = segs[blockIdx.z];
@@ -97,32 +117,69 @@ __global__ __launch_bounds__(1024) void k_mixed_decide(
   const double dd = sp.delta + sp.amb;
   auto is_sure = [&](const MaskScore32& r) { return (double)r.e <= sp.e_bar - dd && (double)r.slack >= dd; };
   auto is_poss = [&](const MaskScore32& r) { return (double)r.e <= sp.e_bar + dd && (double)r.slack >= -dd; };
-  // visit(mask, its FP32 score) of every mask of the tiles that `want`
+  // the first kTileRegs tile records of each thread (all of them for segments of
+  // up to 20 nodes) are read once, together, and kept in registers
+  constexpr int kTileRegs = 16;
+  TileRec32 rt[kTileRegs];
+#pragma unroll
+  for (int u = 0; u < kTileRegs; ++u) {
+    if (u * bd >= ntiles) break;
+    if (tid + u * bd < ntiles) rt[u] = tiles[tid + u * bd];
+  }
+  auto each_tile = [&](auto f) {
+#pragma unroll
+    for (int u = 0; u < kTileRegs; ++u) {
+      if (u * bd >= ntiles) break;
+      if (tid + u * bd < ntiles) f(rt[u], tid + u * bd);
+    }
+    for (int t = tid + kTileRegs * bd; t < ntiles; t += bd) f(tiles[t], t);
+  };
+  // visit(mask, its FP32 score) of every mask of the tiles that `want`: of all of
+  // them at once, or (more than the list holds) a tile per thread at a time.
+  // ncand is 0 at the start and again at the end.
+  auto visit_all = [&](auto visit) {
+    for (int q = tid, nc = ncand; q < nc * 64; q += bd)
+      if (((q & 63) >> lb) == 0) {
+        const uint32_t m = (uint32_t)cand[q >> 6] << lb | (uint32_t)(q & 63);
+        visit(m, fin[m]);
+      }
+  };
   auto scan = [&](auto want, auto visit) {
-    for (int base = 0; base < ntiles; base += bd) {
-      if (tid == 0) ncand = 0;
-      __syncthreads();
+    each_tile([&](const TileRec32& t, int at) {
+      if (want(t)) {
+        const int i = atomicAdd(&ncand, 1);
+        if (i < 1024) cand[i] = at;
+      }
+    });
+    __syncthreads();
+    const bool all = ncand <= 1024;
+    if (all) visit_all(visit);
+    __syncthreads();
+    if (tid == 0) ncand = 0;
+    __syncthreads();
+    for (int base = 0; !all && base < ntiles; base += bd) {
       if (base + tid < ntiles && want(tiles[base + tid])) cand[atomicAdd(&ncand, 1)] = base + tid;
       __syncthreads();
-      for (int q = tid, nc = ncand; q < nc * 64; q += bd)
-        if (((q & 63) >> lb) == 0) {
-          const uint32_t m = (uint32_t)cand[q >> 6] << lb | (uint32_t)(q & 63);
-          visit(m, fin[m]);
-        }
+      visit_all(visit);
+      __syncthreads();
+      if (tid == 0) ncand = 0;
       __syncthreads();
     }
   };
   // list A: masks whose FP32 verdict is uncertain, at or above the best level
   // holding a surely feasible mask
   int lo = -1, hi = -1;
-  for (int t = tid; t < ntiles; t += bd) {
-    lo = max(lo, tiles[t].sure);
-    hi = max(hi, tiles[t].poss);
+  each_tile([&](const TileRec32& t, int) {
+    lo = max(lo, t.sure);
+    hi = max(hi, t.poss);
+  });
+  if (tid == 0) ncand = nlist = 0;
+  {
+    const Levels v = block_reduce(
+        Levels{lo, hi}, [](const Levels& a, const Levels& b) { return Levels{max(a.lo, b.lo), max(a.hi, b.hi)}; }, shv);
+    lo = v.lo;
+    hi = v.hi;
   }
-  lo = block_reduce(lo, [](int a, int b) { return max(a, b); }, shi);
-  hi = block_reduce(hi, [](int a, int b) { return max(a, b); }, shi);
-  if (tid == 0) nlist = 0;
-  __syncthreads();
   scan([&](const TileRec32& t) { return t.unc >= lo && t.unc >= 0; },
        [&](uint32_t m, const MaskScore32& r) {
          if (is_poss(r) && !is_sure(r) && __popc(m) >= lo) listA[atomicAdd(&nlist, 1)] = m;
@@ -193,10 +250,19 @@ __global__ __launch_bounds__(1024) void k_mixed_decide(
     if (__popc(listA[q]) >= best && near_boundary(r, sp.e_bar, sp.amb)) amb = 1;
     if (r.e <= 2.0 * sp.e_bar) dev = fmax(dev, fabs((double)fin[listA[q]].e - r.e));
   }
-  pick = block_reduce(pick, [](unsigned a, unsigned b) { return min(a, b); }, shu);
-  amb = block_reduce(amb, [](int a, int b) { return a | b; }, shi);
-  dev = block_reduce(dev, [](double a, double b) { return fmax(a, b); }, shd);
-  runner = block_reduce(runner, [](double a, double b) { return fmin(a, b); }, shd);
+  {
+    const Verdict v = block_reduce(Verdict{dev, runner, pick, amb},
+                                   [](const Verdict& a, const Verdict& b) {
+                                     return Verdict{fmax(a.dev, b.dev), fmin(a.runner, b.runner),
+                                                    (unsigned)min(a.pick, b.pick),
+                                                    a.amb | b.amb};
+                                   },
+                                   shr);
+    pick = v.pick;
+    amb = v.amb;
+    dev = v.dev;
+    runner = v.runner;
+  }
   if (tid == 0) {
     DevDecision d;
     const bool found = pick != 0xffffffffu;
