@@ -237,6 +237,69 @@ __global__ __launch_bounds__(kTermsBlock * NS) void k_seg_terms(
     const double2* Al = A + (size_t)l * n * 3;
     const double* av = absV + (size_t)l * n * 3;
     if (tid == 0) s_ec = 0.0;
+    // members: every node of Omega_g contributes |V^| to the cluster of its
+    // current super-node (a slot, a zone target, or a head outside Omega_g,
+    // whose error is mask-independent and folds into the constant error).  The
+    // last threads take the first nodes, so that their chain of loads (node,
+    // super-node, its slot or entry) runs beside the pairs' of the first ones.
+    const int* rg = tab + H.o_range;
+    struct Member {
+      int to[3];    // -1: nothing; slot record; kMZone | zone entry; kMConst
+      double a[3];  // |V^|, or the error against a head outside
+    };
+    constexpr int kMZone = 1 << 28, kMConst = 1 << 29;
+    auto member = [&](int q) {
+      Member m;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) m.to[p] = -1;
+      if (q >= H.nomega) return m;
+      int r = 0;
+      while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
+      const int i = rg[3 * r] + (q - rg[3 * r + 2]);
+      const int sp = St.sup[i];
+      const unsigned ph = T.phase[i];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) m.a[p] = av[(size_t)i * 3 + p];
+      const int sg = T.segment[sp], s = St.slot_of[sp];
+      int zi[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) zi[p] = St.zent_of[sp * 3 + p];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        if (!(ph >> p & 1u)) continue;
+        if (sg == g) {
+          if (s >= 0 && s < H.nslots) m.to[p] = s * 3 + p;
+        } else if (zi[p] >= 0) {
+          if (zi[p] < H.nz) m.to[p] = kMZone | zi[p];
+        } else {
+          const double2 v = Vl[(size_t)sp * 3 + p];
+          m.to[p] = kMConst;
+          m.a[p] = fabs(sqrt(v.x * v.x + v.y * v.y) - m.a[p]);
+        }
+      }
+      return m;
+    };
+    auto fold = [](TargetRec* r, double v) {
+      atomicMin((unsigned long long*)&r->lo, (unsigned long long)__double_as_longlong(v));
+      atomicMax((unsigned long long*)&r->hi, (unsigned long long)__double_as_longlong(v));
+    };
+    auto fold_member = [&](const Member& m) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        if (m.to[p] < 0) continue;
+        if (m.to[p] == kMConst) {
+          atomicMax((unsigned long long*)&s_ec, (unsigned long long)__double_as_longlong(m.a[p]));
+        } else if (m.to[p] & kMZone) {
+          const int zi = m.to[p] & ~kMZone;
+          if (zi < zst) fold(&sZ[zi], m.a[p]);
+          else fold(&gZ[zi], m.a[p]);
+        } else {
+          fold(&sS[m.to[p]], m.a[p]);
+        }
+      }
+    };
+    const int q0 = on ? kTermsBlock - 1 - tid : INT_MAX;
+    const Member m0 = member(q0);
     // one index space over pairs, slot-phases, chains and zone entries
     const int nP = H.npairs, nS = H.nslots * 3, nC = H.nchains * 3;
     for (int x = on ? tid : INT_MAX; x < nP + nS + nC + H.nz; x += kTermsBlock) {
@@ -273,44 +336,8 @@ __global__ __launch_bounds__(kTermsBlock * NS) void k_seg_terms(
       }
     }
     __syncthreads();
-    // members: every node of Omega_g contributes |V^| to the cluster of its
-    // current super-node (a slot, a zone target, or a head outside Omega_g,
-    // whose error is mask-independent and folds into the constant error)
-    const int* rg = tab + H.o_range;
-    auto fold = [](TargetRec* r, double v) {
-      atomicMin((unsigned long long*)&r->lo, (unsigned long long)__double_as_longlong(v));
-      atomicMax((unsigned long long*)&r->hi, (unsigned long long)__double_as_longlong(v));
-    };
-    for (int q = on ? tid : INT_MAX; q < H.nomega; q += kTermsBlock) {
-      int r = 0;
-      while (r + 1 < H.nrange && rg[3 * (r + 1) + 2] <= q) ++r;
-      const int i = rg[3 * r] + (q - rg[3 * r + 2]);
-      const int sp = St.sup[i];
-      const unsigned ph = T.phase[i];
-      if (T.segment[sp] == g) {
-        const int s = St.slot_of[sp];
-        if (s < 0 || s >= H.nslots) continue;
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-          if (ph >> p & 1u) fold(&sS[s * 3 + p], av[(size_t)i * 3 + p]);
-      } else {
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          if (!(ph >> p & 1u)) continue;
-          const double a = av[(size_t)i * 3 + p];
-          const int zi = St.zent_of[sp * 3 + p];
-          if (zi >= H.nz) continue;
-          if (zi >= 0) {
-            if (zi < zst) fold(&sZ[zi], a);
-            else fold(&gZ[zi], a);
-          } else {
-            const double2 v = Vl[(size_t)sp * 3 + p];
-            atomicMax((unsigned long long*)&s_ec,
-                      (unsigned long long)__double_as_longlong(fabs(sqrt(v.x * v.x + v.y * v.y) - a)));
-          }
-        }
-      }
-    }
+    fold_member(m0);
+    for (int q = on ? q0 + kTermsBlock : INT_MAX; q < H.nomega; q += kTermsBlock) fold_member(member(q));
     __syncthreads();
     if (part == 0 && on) {
       uint4 *dP = (uint4*)gP, *dS = (uint4*)gS, *dH = (uint4*)gH, *dZ = (uint4*)gZ;
