@@ -374,8 +374,7 @@ class Reducer:
         """One pass of the whole search (planning included when replan).  With
         want_features the per-mask surrogate features and FP64 targets of every
         segment are left in ``self.features`` / ``self.targets`` (device).
-        With autotune the scoring launch shape is tuned first (kept in the
-        handle for later runs)."""
+        autotune passes the library's autotuning flag (accepted, no effect)."""
         # inputs written on the caller's stream are complete before the search
         self.stream.wait_stream(self.torch.cuda.current_stream(self.device))
         if replan:

@@ -308,12 +308,13 @@ struct FlowPhases {
 // before it.  6000 nodes, 96 snapshots, 9 sweeps: 709 us with the cumulative
 // impedances (1100 + 88 level by level in breadth-first storage; 826 without
 // loads issued kFlowAhead at a time), bound by latency on 96 CUs.  8400 nodes,
-// 672 snapshots, 12 sweeps: 2.45 ms (3.99 + 0.12; 2.53): about 13 GB, 5.4 TB/s.
+// 288 snapshots, 12 sweeps: 2.29 ms in blocks of 512, two on a compute unit (3.99
+// + 0.12 level by level; 2.44 in blocks of 1024, 256 of them and then 33).
 // (64 registers, for two blocks per CU: 852 us and 3.02 ms, spilled.)
-template <bool FIXED>
-__global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowPhases t, FlowArgs a) {
+template <bool FIXED, int BT>
+__global__ __launch_bounds__(BT) void k_flow_phase(int n, int S, FlowPhases t, FlowArgs a) {
   extern __shared__ double2 flow_lds[];
-  __shared__ double2 s_tot[2][kFlowWaves];
+  __shared__ double2 s_tot[2][BT / 64];
   __shared__ double s_red[16];
   if (!FIXED && (int)blockIdx.x == S) {
     zroot_block(n, a.parent, a.lvl_off, a.lvl_nodes, a.nlev, a.z, a.Zroot);
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
   const double2* Sl = a.Sload + base;
   if (!FIXED) {
     for (int p = 0; p < 3; ++p)
-      for (int k = tid; k < t.cnt[p]; k += kFlowThreads) {
+      for (int k = tid; k < t.cnt[p]; k += BT) {
         Sb[p * n + k] = Sl[(size_t)a.ext[t.lab[p][k] >> 3] * 3 + p];
         Vb[p * n + k] = a.v0[p];
       }
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
   bool conv = false;
   for (it = 1; it <= a.maxit; ++it) {
     for (int p = 0; p < 3; ++p) {
-      const int cnt = t.cnt[p], C = (cnt + kFlowThreads - 1) / kFlowThreads, k0 = wv * 64 * C + lane;
+      const int cnt = t.cnt[p], C = (cnt + BT - 1) / BT, k0 = wv * 64 * C + lane;
       const double2 *Sp = Sb + (size_t)p * n, *Vp = Vb + (size_t)p * n;
       double2 acc = make_double2(0.0, 0.0);
       for (int i = 0; i < C; i += kFlowAhead) {
@@ -372,17 +373,17 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
         run = make_double2(run.x + last_lane(c.x), run.y + last_lane(c.y));
       }
       __syncthreads();
-      for (int k1 = tid; k1 < cnt; k1 += kFlowAhead * kFlowThreads) {
+      for (int k1 = tid; k1 < cnt; k1 += kFlowAhead * BT) {
         int e[kFlowAhead], q[kFlowAhead];
 #pragma unroll
         for (int u = 0; u < kFlowAhead; ++u) {
-          const int k = min(k1 + u * kFlowThreads, cnt - 1);
+          const int k = min(k1 + u * BT, cnt - 1);
           e[u] = t.ende[p][k];
           q[u] = t.lab[p][k] >> 3;
         }
 #pragma unroll
         for (int u = 0; u < kFlowAhead; ++u) {
-          const int k = k1 + u * kFlowThreads;
+          const int k = k1 + u * BT;
           if (k >= cnt) break;
           const double2 lo = k > 0 ? X[k - 1] : make_double2(0.0, 0.0);
           Jb[(size_t)p * n + q[u]] = csub(X[e[u] - 1], lo);
@@ -393,11 +394,11 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
     double dmax = 0.0;
     for (int p = 0; p < 3; ++p) {
       const int cnt = t.cnt[p];
-      for (int k1 = tid; k1 < cnt; k1 += 2 * kFlowThreads) {
+      for (int k1 = tid; k1 < cnt; k1 += 2 * BT) {
         int q[2];
         double2 d[2], zz[2][3], jj[2][3];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) q[u] = t.lab[p][min(k1 + u * kFlowThreads, cnt - 1)];
+        for (int u = 0; u < 2; ++u) q[u] = t.lab[p][min(k1 + u * BT, cnt - 1)];
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -411,11 +412,11 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
 #pragma unroll
           for (int c = 0; c < 3; ++c)
             if (q[u] >> c & 1) d[u] = cadd(d[u], cmul(zz[u][c], jj[u][c]));
-          if (k1 + u * kFlowThreads < cnt) X[k1 + u * kFlowThreads] = d[u];
+          if (k1 + u * BT < cnt) X[k1 + u * BT] = d[u];
         }
       }
       __syncthreads();
-      const int C = (2 * cnt + kFlowThreads - 1) / kFlowThreads, k0 = wv * 64 * C + lane;
+      const int C = (2 * cnt + BT - 1) / BT, k0 = wv * 64 * C + lane;
       double2 acc = make_double2(0.0, 0.0);
       for (int i = 0; i < C; i += kFlowAhead) {
         int s[kFlowAhead];
@@ -473,7 +474,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_phase(int n, int S, FlowP
     }
   }
   // voltages by label (over the loads, no longer read)
-  for (int k = tid; k < n * 3; k += kFlowThreads) {
+  for (int k = tid; k < n * 3; k += BT) {
     const int p = k % 3, i = t.idx[p * n + k / 3];
     if (FIXED) {
       if (i < 0) a.V[base + k] = make_double2(0.0, 0.0);
@@ -525,6 +526,12 @@ size_t phase_lds(const FlowPlan& p) {
   return sizeof(double2) * m;
 }
 
+// Blocks of 512 threads, two on a compute unit, where blocks of 1024 would leave
+// a second round of them (more snapshots than compute units) and two blocks' sums
+// fit in a unit's LDS.
+constexpr int kComputeUnits = 256;
+bool pairs_of_blocks(const FlowPlan& p, int S) { return S > kComputeUnits && phase_lds(p) <= 78 * 1024; }
+
 }  // namespace
 
 FlowPlan flow_tables(int n, const int* end, const uint8_t* phase, std::vector<int>& out) {
@@ -574,8 +581,9 @@ hipError_t flow_prepare(const FlowPlan& p) {
     f[1] = reinterpret_cast<const void*>(&k_flow_node<kFixed>);
     f[2] = reinterpret_cast<const void*>(&k_flow_node<kEval>);
   } else if (p.form == 2 && phase_lds(p) > 60 * 1024) {
-    f[0] = reinterpret_cast<const void*>(&k_flow_phase<false>);
-    f[1] = reinterpret_cast<const void*>(&k_flow_phase<true>);
+    f[0] = reinterpret_cast<const void*>(&k_flow_phase<false, kFlowThreads>);
+    f[1] = reinterpret_cast<const void*>(&k_flow_phase<true, kFlowThreads>);
+    f[2] = reinterpret_cast<const void*>(&k_flow_phase<false, kFlowThreads / 2>);
   }
   for (const void* k : f)
     if (k) {
@@ -590,8 +598,9 @@ void flow_launch(const FlowPlan& p, const FlowArgs& a, int S, hipStream_t st) {
     hipLaunchKernelGGL(k_flow_node<kLoadFlow>, dim3(S + 1), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
                        a.tab + p.end, a.tab + p.tour, a, FlowEval{});
   else
-    hipLaunchKernelGGL(k_flow_phase<false>, dim3(S + 1), dim3(kFlowThreads), phase_lds(p), st, p.n, S,
-                       phases(p, a.tab), a);
+    hipLaunchKernelGGL((pairs_of_blocks(p, S) ? k_flow_phase<false, kFlowThreads / 2> : k_flow_phase<false, kFlowThreads>),
+                       dim3(S + 1), dim3(pairs_of_blocks(p, S) ? kFlowThreads / 2 : kFlowThreads), phase_lds(p), st, p.n,
+                       S, phases(p, a.tab), a);
 }
 
 void flow_eval_launch(const FlowPlan& p, const FlowArgs& a, const FlowEval& e, int S, hipStream_t st) {
@@ -613,7 +622,7 @@ void flow_fixed_launch(const FlowPlan& p, const int* tab, const uint8_t* phase, 
     hipLaunchKernelGGL(k_flow_node<kFixed>, dim3(S), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
                        tab + p.end, tab + p.tour, a, FlowEval{});
   else
-    hipLaunchKernelGGL(k_flow_phase<true>, dim3(S), dim3(kFlowThreads), phase_lds(p), st, p.n, S, phases(p, tab), a);
+    hipLaunchKernelGGL((k_flow_phase<true, kFlowThreads>), dim3(S), dim3(kFlowThreads), phase_lds(p), st, p.n, S, phases(p, tab), a);
 }
 
 }  // namespace okr

@@ -160,7 +160,7 @@ struct DevDecision {
   double smice_rise;  // with SMICE as the key: SMICE of the chosen mask minus SMICE of mask 0
 };
 
-// Per-mask partial score: max error and min band slack over a snapshot group.
+// A mask's score: largest error and smallest band slack over the snapshots.
 struct MaskScore {
   double e;
   double slack;
@@ -173,8 +173,7 @@ struct PatScore {
   double e, qmin, qmax;
 };
 
-// Per-tile (64 consecutive masks) summary written by the last scoring block
-// of the tile: best feasible level, smallest error at that level, highest
+// Per-tile (64 consecutive masks) summary: best feasible level, smallest error at that level, highest
 // level of a near-boundary mask.
 struct TileRec {
   int32_t best;   // max popcount of a feasible mask, -1 if none

@@ -10,14 +10,14 @@
 //                      label too
 //   absV[S][n][3]      |Vhat|
 //   per segment        P[S][npairs][3], slot/zone TargetRec[S][..][3], headV
-//   scores             MaskScore[snapshot group][2^k]
+//   scores             MaskScore[2^k]
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include "okr_device.h"
 #include "okr_flow.h"
 #include "okr_internal.h"
-#include "okr_device.h"
 
 namespace okr {
 

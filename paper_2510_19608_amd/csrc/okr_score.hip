@@ -1,6 +1,6 @@
-// Candidate scoring kernels: every mask of a segment (FP64, and the FP32
-// difference-form screen of the mixed-precision search) and FP64 rescoring of
-// a mask list.  Built with NaNs excluded (no input or intermediate here is
+// Candidate scoring kernels: a segment's numeric tables and chain patterns, every
+// mask's score from them (FP64, and the FP32 difference-form screen of the
+// mixed-precision search), and FP64 scores of a mask list.  Built with NaNs excluded (no input or intermediate here is
 // NaN), which lets max/min compile to single instructions.
 #include <hip/hip_runtime.h>
 #include <limits.h>
@@ -53,6 +53,11 @@ namespace okr {
 // 8400-node feeder, whose chains carry up to 1,115 entries).  Its entries are
 // evaluated by whole waves instead: one wave per pattern walks the chain for
 // its exit value and takes an entry per lane.
+//
+// Per launch (chunks of up to 8 segments): 11.1 us at 1000 nodes and 24
+// snapshots, 21.5 at 6000 and 96, 58.4 at 8400 and 288 (with k_fac_combine 18,
+// 31 and 74), where the tables took 13, 20 and 26 us in two launches and scoring
+// mask by mask 79, 577 and 4412.
 struct ChainState {
   double2 S[3];   // voltage shift
   double sm[3];   // magnitude of the current super

@@ -170,3 +170,23 @@ def test_load_flow_beyond_prefix_sums(okr):
     np.testing.assert_allclose(out["Vhat"], V, rtol=0, atol=1e-12)
     err, _ = okr.evaluate_assignment(f, np.arange(f["n"]))
     assert err.max() < 1e-12
+
+
+def test_load_flow_more_snapshots_than_compute_units(okr):
+    """257 snapshots of a 1100-node feeder: the phase-by-phase load flow in
+    blocks of 512 threads, two on a compute unit (bound as above)."""
+    print("load flow: n=1100, 257 snapshots", flush=True)
+    f = make_feeder("c2", 3, n=1100, snapshots=257, kappa=0.2, seg_size=(6, 8))
+    V, I, st, _ = oracle.powerflow(f)
+    assert st == 0
+    out = okr.reduce_feeder(f, want_vhat=True)
+    np.testing.assert_allclose(out["Vhat"], V, rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("S", [255, 257])
+def test_snapshot_pairs_with_a_remainder(okr, S):
+    """Two snapshots per block of the table kernel with one block's second
+    half empty, and the lists' and patterns' folds over both."""
+    print(f"tables: {S} snapshots", flush=True)
+    f = make_feeder("c1", 5, n=30, snapshots=S, e_bar=5e-4, kappa=0.25)
+    check(okr, f, per_segment=64)
