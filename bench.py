@@ -6,9 +6,9 @@ arg-min, state update, Y_Kron and final errors) with the inputs resident in
 HBM and the topology planned beforehand.
 
 Prints ONE JSON line.  `value` = candidates scored per second by the plain
-FP64 search (every mask scored exactly).  `roofline` describes the dominant
-kernel (the FP64 scoring kernel) from HIP-event timings recorded on the
-library's stream inside the timed region.  `modes` gives the time-to-optimal
+FP64 search (every mask scored exactly).  `roofline` describes the scoring
+launches (the pattern tables and the combine) from HIP-event timings recorded
+on the library's stream inside the timed region.  `modes` gives the time-to-optimal
 (median of repeated whole searches, graph-captured) of the plain, mixed
 precision and surrogate-pruned forms and their agreement with the plain
 decisions.  `cpu_baseline` is the FP64 CPU oracle on a bounded sample.
@@ -31,15 +31,15 @@ sys.path.insert(0, ROOT)
 FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X FP64 vector (256 CUs x 2.4 GHz x 128 flop/clk)
 BF16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense BF16 matrix peak
 
-# HBM bytes per launch of the FP64 scoring kernel on this workload, from the
-# FETCH_SIZE / WRITE_SIZE counters scaled by a known-size copy (see
-# profiles/k_score_fp64_c2_1000node_24snap.md), valid only for the sources
-# they were taken with: any change to them reports null.
+HBM_PEAK_TBPS = 8.0              # MI355X HBM3E
+
+# HBM bytes per chunk of the two scoring launches on this workload, from the
+# FETCH_SIZE / WRITE_SIZE counters (see profiles/search_kernels.md), valid only
+# for the sources they were taken with: any change to them reports null.
 TRAFFIC_SOURCES = ["paper_2510_19608_amd/csrc/okr_score.hip", "paper_2510_19608_amd/csrc/okr_device.h",
-                   "paper_2510_19608_amd/csrc/okr_internal.h", "paper_2510_19608_amd/csrc/okr_host.cpp",
-                   "paper_2510_19608_amd/csrc/okr_build.hip"]
-TRAFFIC_SHA1 = "d4e106bf619241fea9a9d0c6e71a8725af23265d"
-TRAFFIC_BYTES_PER_LAUNCH = 1923167
+                   "paper_2510_19608_amd/csrc/okr_internal.h", "paper_2510_19608_amd/csrc/okr_build.hip"]
+TRAFFIC_SHA1 = "ca08e2576f82a2729f99a3860dd1ce13bc6de31f"
+TRAFFIC_BYTES_PER_LAUNCH = 1187000
 
 
 def measured_traffic():
@@ -112,11 +112,10 @@ def cpu_baseline_all_cores(seed, seconds=10.0):
                 sample=f"{done} masks of segment 0 of the 1000-node 24-snapshot feeder, {k} processes, {dt:.1f} s")
 
 
-def timed_runs(R, reps, autotune=True):
-    """Median wall time (ms) of `reps` whole searches after one warm-up (the
-    warm-up tunes the scoring launch shape unless autotune is off)."""
+def timed_runs(R, reps):
+    """Median wall time (ms) of `reps` whole searches after two warm-ups."""
     import torch
-    R.run(replan=False, autotune=autotune)
+    R.run(replan=False)
     R.run(replan=False)
     torch.cuda.synchronize()
     ts = []
@@ -181,7 +180,7 @@ def surrogate_mode(f, args, plain_ms, ref, ncand, trained):
     from paper_2510_19608_amd import Reducer
     params, margin, info = trained
     R = Reducer(f, device="cuda:0", graph=True, surrogate=params, top_k=args.top_k, surrogate_margin=margin)
-    ms = timed_runs(R, args.reps, True)
+    ms = timed_runs(R, args.reps)
     masks, pops, res = decisions(R)
     fallback = sum(1 for s in res["segments"] if s["n_scored"] > s["n_refined"])
     R.close()
@@ -198,7 +197,7 @@ def modes_section(f, args, trained):
     modes = {}
     Rg = Reducer(f, device="cuda:0", graph=True)
     ncand = int(Rg.sizes.n_candidates)
-    plain_ms = timed_runs(Rg, args.reps, True)
+    plain_ms = timed_runs(Rg, args.reps)
     ref_masks, ref_pops, res = decisions(Rg)
     Rg.close()
     below = sum(1 for s in res["segments"] if s["popcount"] < s["k"])
@@ -209,7 +208,7 @@ def modes_section(f, args, trained):
     wanted = set(args.modes.split(","))
     if "mixed" in wanted:
         Rm = Reducer(f, device="cuda:0", graph=True, precision="mixed")
-        ms = timed_runs(Rm, args.reps, True)
+        ms = timed_runs(Rm, args.reps)
         m, p, res = decisions(Rm)
         refined = sum(s["n_refined"] for s in res["segments"])
         dev = max(s["fp32_dev"] for s in res["segments"])
@@ -221,7 +220,7 @@ def modes_section(f, args, trained):
     if "factored" in wanted:
         # exact per-mask scores assembled from per-chain pattern tables
         Rf = Reducer(f, device="cuda:0", graph=True, precision="factored")
-        ms = timed_runs(Rf, args.reps, False)
+        ms = timed_runs(Rf, args.reps)
         m, p, res = decisions(Rf)
         Rf.close()
         modes["factored_fp64"] = mode_entry("factored", ms, plain_ms, m, p, res, ref_masks, ref_pops, ncand)
@@ -232,9 +231,7 @@ def fullsize_section(seed, reps=3):
     """Time-to-optimal of the whole search on the 6000-node feeder (96
     snapshots, segments of 8-18 eligible nodes) and the 8400-node feeder (288
     snapshots, segments of 8-20), plain FP64, mixed precision and the factored
-    FP64 form, each as one captured graph (launch shapes from the library's
-    defaults); with the
-    launch structure of the search (chunks of independent segments, one
+    FP64 form, each as one captured graph; with the launch structure of the search (chunks of independent segments, one
     scoring launch each) and, from a stream-launched timed run, the wall time
     of the search against the time inside its scoring launches."""
     import torch
@@ -247,7 +244,7 @@ def fullsize_section(seed, reps=3):
         ref = None
         for prec in ("fp64", "mixed", "factored"):
             R = Reducer(f, device="cuda:0", graph=True, precision=prec)
-            ms = timed_runs(R, reps, False)
+            ms = timed_runs(R, reps)
             masks, pops, res = decisions(R)
             ncand = int(R.sizes.n_candidates)
             R.close()
@@ -426,9 +423,7 @@ def main():
     ap.add_argument("--lanes", type=int, default=0,
                     help="segments per launch chunk of the timed searches (0 = the library default, 8)")
     ap.add_argument("--autotune", action="store_true",
-                    help="tune the headline search's scoring launch shape before its warm-up (default: the "
-                         "library's default rule, so that a profile of this command sees only timed shapes; the "
-                         "time-to-optimal sections always tune, once per handle)")
+                    help="pass the autotuning flag to the first run (accepted by the library, no effect)")
     ap.add_argument("--copy-probe-mib", type=int, default=0,
                     help="first run one device-to-device copy of this many MiB (a known-size reference "
                          "for hardware byte counters)")
@@ -462,23 +457,22 @@ def main():
     for _ in range(args.warmup):
         R.run(replan=False)
     torch.cuda.synchronize()
-    kern_ms, flops, kflops = 0.0, 0.0, 0.0
+    kern_ms, flops = 0.0, 0.0
     t0 = time.perf_counter()
     for _ in range(args.steps):
         R.run(replan=False)
         r = R.res
         kern_ms += r.score_kernel_ms
         flops += r.algorithmic_flops
-        kflops += r.kernel_form_flops
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     ref_masks, ref_pops, out = decisions(R)
     R.close()
-    shapes = sorted({(s["k"], s["score_groups"], s["score_mpl"]) for s in out["segments"]})
     ms_per_step = dt * 1e3 / args.steps
     launches = out["n_score_launches"] * args.steps
-    achieved = flops / (kern_ms * 1e-3) / 1e12 if kern_ms > 0 else None
-    k_achieved = kflops / (kern_ms * 1e-3) / 1e12 if kern_ms > 0 else None
+    traffic = measured_traffic()
+    chunk_s = kern_ms * 1e-3 / max(launches, 1)
+    achieved = traffic / chunk_s / 1e12 if traffic and chunk_s > 0 else None
     line = {
         "metric": "candidate reductions scored/sec (1000-node, 24 snaps); time-to-optimal vs plain",
         "value": ncand * args.steps / dt,
@@ -497,21 +491,19 @@ def main():
                    "seed": args.seed, "n_candidates": ncand, "segments": int(out["n_score_launches"]),
                    "precision": "fp64", "e_bar": f["e_bar"], "n_kept": int(out["n_kept"]),
                    "max_err": out["max_err"], "parallelism": "single GPU"},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": (achieved / FP64_VECTOR_PEAK_TFLOPS) if achieved else None,
-                     "traffic": measured_traffic(), "kernel": "okr::k_score_fp64",
-                     "avg_launch_us": kern_ms * 1e3 / max(launches, 1),
-                     "flops_per_launch": flops / max(launches, 1),
-                     "flop_count": "the method's work per candidate and snapshot: 2|phi| per reduced node and "
-                                   "hop to its super-node, 8|phi|^2 + 2|phi| per edge carrying the moved current, "
-                                   "2|phi| per segment node, 10 per affected node-phase; 18 per reduced node per "
-                                   "candidate; exact averages over the masks",
-                     "kernel_form": {"flops_per_launch": kflops / max(launches, 1), "achieved": k_achieved,
-                                     "frac": (k_achieved / FP64_VECTOR_PEAK_TFLOPS) if k_achieved else None,
-                                     "note": "the arithmetic the scoring kernel itself does: shared per-segment "
-                                             "tables replace the per-candidate voltage-change products"},
-                     "whole_step_tflops": flops / dt / 1e12,
-                     "launch_shapes_k_groups_mpl": shapes},
+        "roofline": {"bound": "latency", "achieved": achieved, "peak": HBM_PEAK_TBPS, "unit": "TB/s",
+                     "frac": (achieved / HBM_PEAK_TBPS) if achieved else None, "traffic": traffic,
+                     "kernel": "okr::k_seg_terms + okr::k_fac_combine",
+                     "avg_chunk_us": chunk_s * 1e6,
+                     "note": "every mask's score is assembled from its chains' pattern tables, so the arithmetic of "
+                             "scoring mask by mask is not performed; its rate is given for comparison only",
+                     "mask_by_mask_equivalent": {
+                         "flops_per_chunk": flops / max(launches, 1),
+                         "equivalent_tflops": flops / (kern_ms * 1e-3) / 1e12 if kern_ms > 0 else None,
+                         "flop_count": "the method's work per candidate and snapshot: 2|phi| per reduced node and "
+                                       "hop to its super-node, 8|phi|^2 + 2|phi| per edge carrying the moved "
+                                       "current, 2|phi| per segment node, 10 per affected node-phase; 18 per "
+                                       "reduced node per candidate; exact averages over the masks"}},
     }
     if not args.no_modes:
         trained = train_surrogate(args) if "surrogate" in args.modes.split(",") else None
