@@ -137,7 +137,7 @@ __device__ __forceinline__ void flow_finish(const FlowArgs& a, int n, size_t bas
 // snapshots, 8 sweeps: 75 us with the cumulative impedances (228 + 20 level by
 // level in LDS; 98 with the waves' totals added one by one and three square
 // roots per node); 168 snapshots 80 (417 + 20 level by level in global memory);
-// 30 nodes 26 (66 + 6).
+// 30 nodes 25 (66 + 6), where k_flow_small takes 17.
 enum { kLoadFlow = 0, kFixed = 1, kEval = 2 };
 
 template <int MODE>
@@ -290,6 +290,82 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_node(int n, int S, const 
 #pragma unroll
     for (int p = 0; p < 3; ++p) a.V[base + q * 3 + p] = v[p];
   if (FIXED) return;
+  __syncthreads();
+  flow_finish(a, n, base, a.phase, conv, it, s_red);
+}
+
+// Form 1 for small feeders (n <= kFlowSmall): a thread per node and phase, so
+// that a node's three phases run in three waves side by side instead of one
+// after the other (a single wave issues one FP64 instruction in about 8 cycles
+// here).  The load flow and the cumulative impedances.  30 nodes: 16.7 us a
+// launch against 25.
+constexpr int kFlowSmall = 320;
+__global__ __launch_bounds__(kFlowThreads) void k_flow_small(int n, int S, const int* __restrict__ end,
+                                                             const int* __restrict__ tour, FlowArgs a) {
+  __shared__ double2 X[3][kFlowSmall], Y[3][kFlowSmall];
+  __shared__ double2 s_tot[2][16];
+  __shared__ double s_red[16];
+  if ((int)blockIdx.x == S) {
+    zroot_block(n, a.parent, a.lvl_off, a.lvl_nodes, a.nlev, a.z, a.Zroot);
+    return;
+  }
+  const int W = (n + 63) >> 6, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int p = wv / W, w0 = p * W, q = (wv - w0) * 64 + (threadIdx.x & 63);
+  const size_t base = (size_t)blockIdx.x * n * 3;
+  const bool on = q < n, last = (threadIdx.x & 63) == 63;
+  const unsigned ph = on ? a.phase[q] : 0u;
+  const bool pr = ph >> p & 1u;
+  const int e = on ? end[q] : 1, t0 = on ? tour[2 * q] : 0, t1 = on ? tour[2 * q + 1] : 0;
+  double2 z[3], s = make_double2(0.0, 0.0), v = pr ? a.v0[p] : s;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) z[c] = on ? a.z[(size_t)q * 9 + p * 3 + c] : make_double2(0.0, 0.0);
+  if (on) s = a.Sload[base + (size_t)a.ext[q] * 3 + p];
+  const double f0 = on ? (t0 & 1 ? -1.0 : 1.0) : 0.0, f1 = on ? (t1 & 1 ? -1.0 : 1.0) : 0.0;
+  int it = 0;
+  bool conv = false;
+  for (it = 1; it <= a.maxit; ++it) {
+    double2 c = q > 0 && pr ? cconj(cdiv(s, v)) : make_double2(0.0, 0.0);
+    c = wave_scan(c);
+    if (last) s_tot[0][wv] = c;
+    __syncthreads();
+    for (int w = w0; w < wv; ++w) c = cadd(c, s_tot[0][w]);
+    if (on) X[p][q] = c;
+    __syncthreads();
+    double2 d = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double2 hi = X[k][e - 1], lo = on && q > 0 ? X[k][q - 1] : make_double2(0.0, 0.0);
+      const double2 j = cmul(z[k], csub(hi, lo));
+      d = k ? cadd(d, j) : j;
+    }
+    if (on) Y[p][q] = d;
+    __syncthreads();
+    const double2 y0 = Y[p][t0 >> 1], y1 = Y[p][t1 >> 1];
+    const double2 g = wave_scan(make_double2(f0 * y0.x + f1 * y1.x, f0 * y0.y + f1 * y1.y));
+    if (last) s_tot[1][wv] = g;
+    c = make_double2(lane_before(g.x), lane_before(g.y));
+    __syncthreads();
+    for (int w = w0; w < wv; ++w) c = cadd(c, s_tot[1][w]);
+    if (on) {
+      const double2 d0 = make_double2(c.x + f0 * y0.x, c.y + f0 * y0.y);
+      if (!(t0 & 1)) X[p][t0 >> 1] = d0;
+      if (!(t1 & 1)) X[p][t1 >> 1] = make_double2(d0.x + f1 * y1.x, d0.y + f1 * y1.y);
+    }
+    __syncthreads();
+    double dmax = 0.0;
+    if (pr) {
+      const double2 nv = csub(a.v0[p], X[p][q]);
+      dmax = nan_max(dmax, cabs2(csub(nv, v)));
+      v = nv;
+    }
+    dmax = sqrt(block_nan_max(dmax, s_red));
+    if (!(dmax <= 1e3)) break;
+    if (dmax <= a.tol) {
+      conv = true;
+      break;
+    }
+  }
+  if (on) a.V[base + q * 3 + p] = v;
   __syncthreads();
   flow_finish(a, n, base, a.phase, conv, it, s_red);
 }
@@ -594,7 +670,10 @@ hipError_t flow_prepare(const FlowPlan& p) {
 }
 
 void flow_launch(const FlowPlan& p, const FlowArgs& a, int S, hipStream_t st) {
-  if (p.form == 1)
+  if (p.form == 1 && p.n <= kFlowSmall)
+    hipLaunchKernelGGL(k_flow_small, dim3(S + 1), dim3((p.n + 63) / 64 * 192), 0, st, p.n, S, a.tab + p.end,
+                       a.tab + p.tour, a);
+  else if (p.form == 1)
     hipLaunchKernelGGL(k_flow_node<kLoadFlow>, dim3(S + 1), dim3((p.n + 63) / 64 * 64), node_lds(p.n), st, p.n, S,
                        a.tab + p.end, a.tab + p.tour, a, FlowEval{});
   else

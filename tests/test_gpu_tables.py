@@ -138,11 +138,11 @@ def test_greedy_cluster_list(okr, n, S, p_deep, kappa, moves):
             np.testing.assert_allclose(o["err_per_snapshot"], err, rtol=0, atol=TOL)
 
 
-@pytest.mark.parametrize("n,p_deep", [(2, 0.5), (64, 0.5), (65, 0.9), (1023, 0.5), (1024, 0.5), (1025, 0.5), (2100, 0.6)])
+@pytest.mark.parametrize("n,p_deep", [(2, 0.5), (64, 0.5), (65, 0.9), (320, 0.5), (321, 0.5), (1023, 0.5), (1024, 0.5), (1025, 0.5), (2100, 0.6)])
 def test_prefix_sum_load_flow(okr, n, p_deep):
     """Load flow and fixed-current solve by prefix sums at the edges of the
-    waves and of the two forms (up to 1024 nodes, a node per thread; above,
-    phase by phase), 3 snapshots.  The oracle's load flow stops at the same
+    waves and of the forms (up to 320 nodes a thread per node and phase, up to
+    1024 a thread per node; above, phase by phase), 3 snapshots.  The oracle's load flow stops at the same
     1e-13, so the voltages differ by less than ten times that; the identity
     assignment solved at the load flow's own currents gives its voltages back
     within the same bound."""
