@@ -16,6 +16,7 @@
 
 #include "okr_device.h"
 #include "okr_internal.h"
+#include "okr_kron.h"
 
 namespace okr {
 
@@ -554,6 +555,9 @@ __device__ __forceinline__ void apply_values(const SegHdr& H, const int* tab, in
 // One step between two chunks' scorings: blocks [0, nz) build the structural
 // tables of the next chunk's segments, the others move the voltages and
 // currents of the previous chunk's decided segments (4 snapshots per block).
+// After the last chunk, the first ny blocks form the admittances of the kept
+// branches instead, which need only the structure (a wave of nodes each: long
+// FP64 chains).
 // The two share nothing: the kept set and super-nodes are final when the
 // previous decision is, the build reads and writes no voltage or current, and
 // the chunks' tables alternate between two buffers.  As launches of their own
@@ -567,19 +571,26 @@ __global__ __launch_bounds__(256) void k_step(Topo T, State St, const int* __res
                                               const int* __restrict__ psegs, const int* __restrict__ ptab,
                                               const DevDecision* __restrict__ decs, const double2* __restrict__ P,
                                               const TargetRec* __restrict__ srec, const TargetRec* __restrict__ zrec,
-                                              double2* __restrict__ Vcur, double2* __restrict__ A) {
+                                              double2* __restrict__ Vcur, double2* __restrict__ A, int ny,
+                                              const double2* __restrict__ z, double2* __restrict__ yeq,
+                                              double2* __restrict__ Yk_off, int* __restrict__ kp_out) {
+  if ((int)blockIdx.x < ny) {
+    const int x = blockIdx.x * 64 + threadIdx.x;
+    if (threadIdx.x < 64 && x < T.n) kron_yeq(x, T, St, z, yeq, Yk_off, kp_out, status);
+    return;
+  }
   if ((int)blockIdx.x < nz) {
     build_struct(T, St, segs, blockIdx.x, lstride, S, hdrs, tab, tab_cap, status, pat, ecmax, pat32);
     return;
   }
   __shared__ ApplyLds s_apply[4];
-  const int per = (S + 3) / 4, x = (int)blockIdx.x - nz, z = x / per;
-  const int l = (x - z * per) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int g = *as_cint(psegs + z);
+  const int per = (S + 3) / 4, x = (int)blockIdx.x - nz - ny, pz = x / per;
+  const int l = (x - pz * per) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = *as_cint(psegs + pz);
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid) return;
-  apply_values(H, lane_ptr_z(ptab, lstride, z), T.n, l, l < S, *as_cint((const int*)&decs[g].mask),
-               lane_ptr_z(P, lstride, z), lane_ptr_z(srec, lstride, z), lane_ptr_z(zrec, lstride, z), Vcur, A,
+  apply_values(H, lane_ptr_z(ptab, lstride, pz), T.n, l, l < S, *as_cint((const int*)&decs[g].mask),
+               lane_ptr_z(P, lstride, pz), lane_ptr_z(srec, lstride, pz), lane_ptr_z(zrec, lstride, pz), Vcur, A,
                s_apply[threadIdx.x >> 6]);
 }
 

@@ -32,7 +32,7 @@ __global__ void k_from_vhat(int, int, const uint8_t*, const double2*, const doub
                             double*, int*, const int*, double2*);
 __global__ void k_step(Topo, State, const int*, int, size_t, int, SegHdr*, int*, int, int*, unsigned long long*,
                        unsigned long long*, int2*, const int*, const int*, const DevDecision*, const double2*,
-                       const TargetRec*, const TargetRec*, double2*, double2*);
+                       const TargetRec*, const TargetRec*, double2*, double2*, int, const double2*, double2*, double2*, int*);
 __global__ void k_zroot(int, const int*, const int*, const int*, int, const double2*, double2*);
 template <bool BUILD, bool PAT, int NS, bool DEEP>
 __global__ void k_seg_terms(const SegHdr*, const int*, size_t, const int*, const int*, Topo, State, const double2*,
@@ -51,9 +51,8 @@ __global__ void k_fac_combine(const SegHdr*, const int*, size_t, const int*, con
 __global__ void k_argmin(const SegHdr*, const int*, size_t, const MaskScore*, const TileRec*, SelParams, const int*,
                          DevDecision*, const int*, uint32_t*, int*, const int*, Topo, State, SmicePrep);
 __global__ void k_copy2(const double2*, double2*, size_t);
-__global__ void k_final(Topo, State, int, const double2*, double2*, double2*, int*, int*, const double2*, const double*,
+__global__ void k_final(Topo, State, int, const double2*, double2*, const int*, int*, int, const double2*, const double*,
                         double*);
-__global__ void k_kron_diag(Topo, State, const double2*, double2*, const int*, int*, int);
 __global__ void k_sqrt_selftest(const double*, double*, int);
 __global__ void k_pat32(const SegHdr*, const int*, size_t, const int*, const int*, const double2*, const TargetRec*,
                         const double2*, const TargetRec*, double, double, TermsCaps, int2*, int*);
@@ -1073,7 +1072,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
     hipLaunchKernelGGL(k_step, dim3(nz + pz * ((S + 3) / 4)), dim3(256), 0, st, q.T, q.St, segs, nz, lstride, S, q.hdrs,
                        q.tab, h->tab_cap, q.status, q.pat, q.ecmax, mixed ? q.pat32 : (int2*)nullptr, segs - pz,
                        (const int*)q.tab2, (const DevDecision*)q.decs, (const double2*)q.P, (const TargetRec*)q.srec,
-                       (const TargetRec*)q.zrec, q.Vcur, q.A);
+                       (const TargetRec*)q.zrec, q.Vcur, q.A, 0, (const double2*)nullptr, (double2*)nullptr,
+                       (double2*)nullptr, (int*)nullptr);
     // the tables come with the scoring, or first where something reads them before
     const bool tables_first = surr || feat_out;
     if (tables_first) launch_terms(h, q, c, true, false, nullptr, st);
@@ -1223,20 +1223,19 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
         }
     }
   }
-  if (nchunk > 0) {  // the last chunk's voltages and currents
+  {  // the last chunk's voltages and currents, the kept branches' admittances
     const Ptrs& q = lp[0];
-    const int c0 = h->chunk_off[nchunk - 1], pz = h->chunk_off[nchunk] - c0;
-    hipLaunchKernelGGL(k_step, dim3(pz * ((S + 3) / 4)), dim3(256), 0, st, q.T, q.St, (const int*)nullptr, 0, lstride, S,
-                       q.hdrs, q.tab2, h->tab_cap, q.status, q.pat, q.ecmax, (int2*)nullptr, p.chunks + c0,
+    const int c0 = nchunk > 0 ? h->chunk_off[nchunk - 1] : 0, pz = nchunk > 0 ? h->chunk_off[nchunk] - c0 : 0;
+    const int ny = (n + 63) / 64;
+    hipLaunchKernelGGL(k_step, dim3(ny + pz * ((S + 3) / 4)), dim3(256), 0, st, q.T, q.St, (const int*)nullptr, 0,
+                       lstride, S, q.hdrs, q.tab2, h->tab_cap, q.status, q.pat, q.ecmax, (int2*)nullptr, p.chunks + c0,
                        (const int*)q.tab, (const DevDecision*)q.decs, (const double2*)q.P, (const TargetRec*)q.srec,
-                       (const TargetRec*)q.zrec, q.Vcur, q.A);
+                       (const TargetRec*)q.zrec, q.Vcur, q.A, ny, (const double2*)p.z, p.yeq, p.Yko, p.kp);
   }
-  const int ny = (n + 63) / 64;
-  hipLaunchKernelGGL(k_final, dim3(ny + S), dim3(512), 0, st, p.T, p.St, ny, (const double2*)p.z, p.yeq, p.Yko, p.kp,
-                     p.status, (const double2*)p.Vcur, (const double*)p.absV, p.err);
-  const int nd = std::max(n, kStatusInts);
-  hipLaunchKernelGGL(k_kron_diag, dim3((nd + 127) / 128), dim3(128), 0, st, p.T, p.St, (const double2*)p.yeq, p.Ykd,
-                     (const int*)p.status, p.status_out, kStatusInts);
+  const int nd = (std::max(n, kStatusInts) + 63) / 64;
+  hipLaunchKernelGGL(k_final, dim3(nd + S), dim3(512), 0, st, p.T, p.St, nd, (const double2*)p.yeq, p.Ykd,
+                     (const int*)p.status, p.status_out, kStatusInts, (const double2*)p.Vcur, (const double*)p.absV,
+                     p.err);
 }
 
 uint64_t bits(double x) {
