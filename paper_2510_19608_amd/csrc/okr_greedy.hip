@@ -44,8 +44,8 @@
 
 namespace okr {
 
-__global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const int*, const double2*,
-                           const double2*, double2*, int*, State);
+__global__ void k_branch_z(int, int, const uint8_t*, const int*, const int*, const int*, const double2*, const double2*,
+                           double2*, int*, State);
 __global__ void k_powerflow(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                             const double2*, const double2*, double2, double2, double2, double, int, double, double,
                             double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
@@ -1154,7 +1154,7 @@ int setup(okr_greedy* g, const GPtrs& p, const okr_yblocks* Y, const okr_loads* 
   const int n = g->n, S = g->S;
   OKRG_HIP(g, hipMemcpyAsync(p.topo, g->topo_host.data(), sizeof(int) * (lca ? g->topo_host.size() : g->t_lca),
                              hipMemcpyHostToDevice, st));
-  hipLaunchKernelGGL(k_branch_z, dim3((n + 63) / 64), dim3(64), 0, st, n, (const int*)p.parent,
+  hipLaunchKernelGGL(k_branch_z, dim3((n + 63) / 64 + (n + 3) / 4), dim3(64), 0, st, n, (n + 63) / 64,
                      (const uint8_t*)p.phase, (const int*)p.ch_off, (const int*)p.ch,
                      (const int*)p.pre, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status, State{});
   const bool scan = !(prm->flags & OKR_FLAG_VHAT_GIVEN) && g->flow.form;

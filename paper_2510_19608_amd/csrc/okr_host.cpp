@@ -20,8 +20,8 @@
 
 namespace okr {
 // kernels (okr_kernels.hip, okr_build.hip)
-__global__ void k_branch_z(int, const int*, const uint8_t*, const int*, const int*, const int*, const double2*,
-                           const double2*, double2*, int*, State);
+__global__ void k_branch_z(int, int, const uint8_t*, const int*, const int*, const int*, const double2*, const double2*,
+                           double2*, int*, State);
 __global__ void k_powerflow(int, const int*, const uint8_t*, const int*, const int*, int, const int*, const int*,
                             const double2*, const double2*, double2, double2, double2, double, int, double, double,
                             double2*, double2*, double2*, double*, int*, int*, const int*, double2*);
@@ -1006,7 +1006,7 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
   std::vector<Ptrs> lp(h->nlanes);
   for (int l = 0; l < h->nlanes; ++l) lp[l] = pointers(h, ws, l);
   const bool vhat_given = (mg->flags & OKR_FLAG_VHAT_GIVEN) != 0;
-  hipLaunchKernelGGL(k_branch_z, dim3((n + 63) / 64), dim3(64), 0, st, n, p.T.parent, p.T.phase, p.T.ch_off,
+  hipLaunchKernelGGL(k_branch_z, dim3((n + 63) / 64 + (n + 3) / 4), dim3(64), 0, st, n, (n + 63) / 64, p.T.phase, p.T.ch_off,
                      p.T.ch, p.T.ext, (const double2*)Y->Y_diag, (const double2*)Y->Y_off, p.z, p.status, p.St);
   if (vhat_given || !h->TO.flow.form)  // (otherwise beside the load flow)
     hipLaunchKernelGGL(k_zroot, dim3(1), dim3(1024), 0, st, n, p.T.parent, p.lvl_off, p.lvl_nodes, h->nlev,
