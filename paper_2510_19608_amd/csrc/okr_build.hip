@@ -20,6 +20,7 @@
 
 namespace okr {
 
+constexpr uint8_t kNoKey = 255;
 constexpr int kOmegaLds = 4096;  // Omega_g nodes whose zone classification is kept in shared memory
 // structural part of a segment's tables (chains, nesting, slots, pairs, ranges)
 constexpr int kTabLds = kMaxK * kChainInts + kMaxK * kMaxK + kMaxK * kSlotInts + kMaxPairs * kPairInts + 3 * kMaxK;
@@ -54,7 +55,8 @@ __device__ __forceinline__ void build_struct(Topo T, State St, const int* __rest
   __shared__ int s_keycnt[kMaxK * 3], s_keyoff[kMaxK * 3], s_keycur[kMaxK * 3];
   __shared__ SegHdr s_h;
   __shared__ int s_err, s_nch;
-  __shared__ int s_zi[kOmegaLds], s_zk[kOmegaLds];  // zone pass: node and key of Omega index q
+  __shared__ int s_zi[kOmegaLds];      // zone pass: node of Omega index q
+  __shared__ uint8_t s_zk[kOmegaLds];  // its key (chain * 8 | phases: below 192), kNoKey: no target
   __shared__ int s_tab[kTabLds];                     // structural tables before they are written out
   const int g = segs[z];
   tab = lane_ptr_z(tab, lstride, z);
@@ -350,7 +352,7 @@ __device__ __forceinline__ void build_struct(Topo T, State St, const int* __rest
     const int key = classify(zi, zseg, zkept, zph);
     if (q < kOmegaLds) {
       s_zi[q] = zi;
-      s_zk[q] = key;
+      s_zk[q] = key < 0 ? kNoKey : (uint8_t)key;
     }
     if (key < 0) continue;
     for (int p = 0; p < 3; ++p)
@@ -406,7 +408,7 @@ __device__ __forceinline__ void build_struct(Topo T, State St, const int* __rest
       int i, key;
       if (q < kOmegaLds) {
         i = s_zi[q];
-        key = s_zk[q];
+        key = s_zk[q] == kNoKey ? -1 : s_zk[q];
       } else {
         i = omega(q);
         key = classify(i, T.segment[i], St.kept[i], T.phase[i]);
