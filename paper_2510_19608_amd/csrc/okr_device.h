@@ -259,14 +259,65 @@ __device__ __forceinline__ int sm_first_entry(const Topo& T, const State& St, in
   return -1;
 }
 
+// The chains' distinct heads in chain order, by wave 0: hnode, hin (1: the head
+// lies below another chain) and their number; returns the head number of the
+// lane's chain.  (LDS outputs; a barrier is up to the caller.)
+__device__ __forceinline__ int distinct_heads(const SegHdr& H, const int* tab, int* hnode, int* hin, int* nh) {
+  const int lane = threadIdx.x & 63, nch = H.nchains;
+  int head = -1, outer = -1, first = lane;
+  if (lane < nch) {
+    head = tab[H.o_chain + lane * kChainInts + C_HEAD];
+    outer = tab[H.o_chain + lane * kChainInts + C_OUTER];
+  }
+  for (int q = nch - 1; q >= 0; --q)
+    if (q < lane && __builtin_amdgcn_readlane(head, q) == head) first = q;
+  const uint32_t firsts = (uint32_t)__ballot(lane < nch && first == lane);
+  const int x = __popc(firsts & ((1u << (first & 31)) - 1u));  // the head's number
+  if (lane < nch && first == lane) {
+    hnode[x] = head;
+    hin[x] = outer >= 0 ? 1 : 0;
+  }
+  if (lane == 0) *nh = __popc(firsts);
+  return x;
+}
+
+// Fixed error of the cluster of every head outside Omega_g in snapshot l (one
+// block): the largest error over its members (every node whose super-node it is,
+// itself included) and their phases, against its unchanging voltage.
+__device__ __forceinline__ void smice_hconst(const SegHdr& H, const int* tab, const Topo& T, const State& St,
+                                             const double2* Vcur, const double* absV, double* hK, int S, int l) {
+  __shared__ int c_hnode[kMaxK], c_hin[kMaxK], c_nh;
+  __shared__ unsigned long long c_max[kMaxK];
+  if (!H.valid) return;
+  if (threadIdx.x < 64) distinct_heads(H, tab, c_hnode, c_hin, &c_nh);
+  if (threadIdx.x < kMaxK) c_max[threadIdx.x] = 0ull;
+  __syncthreads();
+  const int n = T.n, nh = c_nh;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int sp = St.sup[i];
+    int x = -1;
+    for (int y = 0; y < nh; ++y)
+      if (c_hnode[y] == sp && !c_hin[y]) x = y;
+    if (x < 0) continue;
+    const unsigned ph = T.phase[i];
+    double e = 0.0;
+    for (int p = 0; p < 3; ++p)
+      if (ph >> p & 1u)
+        e = fmax(e, fabs(vmag(Vcur[((size_t)l * n + sp) * 3 + p]) - absV[((size_t)l * n + i) * 3 + p]));
+    atomicMax(&c_max[x], (unsigned long long)__double_as_longlong(e));
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < nh) hK[threadIdx.x * S + l] = __longlong_as_double((long long)c_max[threadIdx.x]);
+}
+
 // A segment's SMICE tables (one block of up to 1024 threads): distinct heads in
-// chain order, zone targets grouped by anchor chain in Omega_g order, head
-// maxima zeroed.  A second block of the arg-min's launch: the two read nothing
-// of each other's (as a launch of its own, with one thread's loop over the heads
-// and a serial sum over 256 threads' counts, 11 us per chunk at 1000 nodes).
-__device__ __forceinline__ void smice_prep(const SegHdr& H, const int* tab, const Topo& T, const State& St, int* stab,
-                                           double* hK, int S) {
-  __shared__ int s_hnode[kMaxK], s_nh, s_cnt[kMaxK], s_run[kMaxK], s_w[16][kMaxK];
+// chain order, zone targets grouped by anchor chain in Omega_g order.  With the
+// heads' fixed errors, further blocks of the arg-min's launch: they read nothing
+// of each other's (as launches of their own, one thread looping over the heads, a
+// serial sum over 256 threads' counts and atomics into memory, 11 and 4.6 us per
+// chunk at 1000 nodes).
+__device__ __forceinline__ void smice_prep(const SegHdr& H, const int* tab, const Topo& T, const State& St, int* stab) {
+  __shared__ int s_hnode[kMaxK], s_hin[kMaxK], s_nh, s_cnt[kMaxK], s_run[kMaxK], s_w[16][kMaxK];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
   if (!H.valid) {
     if (tid == 0) {
@@ -277,29 +328,19 @@ __device__ __forceinline__ void smice_prep(const SegHdr& H, const int* tab, cons
   }
   const int nch = H.nchains, nom = H.nomega;
   if (wv == 0) {
-    int head = -1, outer = -1, first = lane;
-    if (lane < nch) {
-      head = tab[H.o_chain + lane * kChainInts + C_HEAD];
-      outer = tab[H.o_chain + lane * kChainInts + C_OUTER];
-    }
-    for (int q = nch - 1; q >= 0; --q)
-      if (q < lane && __builtin_amdgcn_readlane(head, q) == head) first = q;
-    const uint32_t firsts = (uint32_t)__ballot(lane < nch && first == lane);
-    const int x = __popc(firsts & ((1u << (first & 31)) - 1u));  // the head's number
+    const int x = distinct_heads(H, tab, s_hnode, s_hin, &s_nh);
     if (lane < nch) {
       stab[SM_CHX + lane] = x;
       s_cnt[lane] = 0;
-      if (first == lane) {
-        s_hnode[x] = head;
-        stab[SM_HNODE + x] = head;
-        stab[SM_HIN + x] = outer >= 0 ? 1 : 0;
-      }
     }
-    if (lane == 0) s_nh = stab[SM_NH] = __popc(firsts);
   }
   __syncthreads();
   const int nh = s_nh;
-  for (int t = tid; t < nh * S; t += blockDim.x) hK[t] = 0.0;
+  if (tid == 0) stab[SM_NH] = nh;
+  if (tid < nh) {
+    stab[SM_HNODE + tid] = s_hnode[tid];
+    stab[SM_HIN + tid] = s_hin[tid];
+  }
   const int* rg = tab + H.o_range;
   auto anchor = [&](int q, int& i) {  // anchor chain of Omega_g node q, -1: no target
     i = omega_node(rg, H.nrange, q);

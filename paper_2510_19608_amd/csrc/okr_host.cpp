@@ -86,8 +86,6 @@ __global__ void k_topk(const SegHdr*, int, const uint32_t*, const uint32_t*, int
 __global__ void k_surr_decide(const SegHdr*, int, SelParams, const int*, const uint32_t*, const int*,
                               const MaskScore*, DevDecision*, int*);
 __global__ void k_zero_f32(float*, int);
-__global__ void k_smice_hconst(const SegHdr*, const int*, size_t, Topo, State, const double2*, const double*,
-                               const int*, double*, int);
 __global__ void k_smice_score(const SegHdr*, const int*, size_t, const int*, const double2*, const TargetRec*,
                               const double2*, const TargetRec*, const int*, const double*, const uint32_t*,
                               const int*, double*);
@@ -1056,7 +1054,6 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
     hipLaunchKernelGGL(k_refresh_weights, dim3((kSurrH * kSurrH + 255) / 256), dim3(256), 0, st, mg->surrogate,
                        p.sW1b, p.sW2b, (__bf16*)nullptr);
   const bool smice = mg->secondary == OKR_SECONDARY_SMICE && !surr;
-  const int members_blocks = std::min(2048, std::max(1, (int)(((size_t)n * S + 255) / 256)));
   // per-mask feature rows of segment g start at foff[g] (segments in id order)
   std::vector<size_t> foff(h->nseg + 1, 0);
   for (int g = 0; g < h->nseg; ++g) foff[g + 1] = foff[g] + ((size_t)1 << (h->seg_off[g + 1] - h->seg_off[g]));
@@ -1146,16 +1143,13 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
       else pattern_tables(h, q, c, st);
       pattern_combine(h, q, c, sp, gates, dump || feat_out, st);
       if (ev) (void)hipEventRecord((*ev)[2 * c + 1], st);
-      hipLaunchKernelGGL(k_argmin, dim3(smice ? 2 : 1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
+      hipLaunchKernelGGL(k_argmin, dim3(smice ? 2 + S : 1, 1, nz), dim3(1024), 0, st, (const SegHdr*)q.hdrs, segs, lstride,
                          (const MaskScore*)q.fin, (const TileRec*)q.tiles, sp, (const int*)q.status, q.decs, gates,
                          smice ? q.smlist : (uint32_t*)nullptr, smice ? q.smcount : (int*)nullptr,
                          smice ? (const int*)nullptr : (const int*)q.tab, q.T, q.St,
-                         SmicePrep{(const int*)q.tab, q.stab, q.hK, S});
+                         SmicePrep{(const int*)q.tab, q.stab, q.hK, (const double2*)q.Vcur, (const double*)q.absV, S});
       if (smice) {
         // SMICE of the feasible masks of the chosen level, and the decision under it
-        hipLaunchKernelGGL(k_smice_hconst, dim3(members_blocks, 1, nz), dim3(256), 0, st, (const SegHdr*)q.hdrs, segs,
-                           lstride, q.T, q.St, (const double2*)q.Vcur, (const double*)q.absV, (const int*)q.stab,
-                           q.hK, S);
         // (as many blocks as fill the chip, or take every mask of the largest level at 4 per block)
         const int sb = std::max(1, std::min((int)(nmask / 4), 2048 / nz));
         hipLaunchKernelGGL(k_smice_score, dim3(sb, 1, nz), dim3(kSmiceThreadsHost), 0, st, (const SegHdr*)q.hdrs, segs,

@@ -243,6 +243,8 @@ struct SmicePrep {
   const int* tab;
   int* stab;
   double* hK;
+  const double2* Vcur;
+  const double* absV;
   int S;
 };
 

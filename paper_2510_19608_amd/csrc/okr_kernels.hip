@@ -444,7 +444,12 @@ __global__ __launch_bounds__(1024) void k_argmin(const SegHdr* __restrict__ hdrs
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
   if (blockIdx.x == 1) {  // (SMICE as the key: the segment's tables for it)
-    smice_prep(H, lane_ptr(pp.tab, lstride), T, St, lane_ptr(pp.stab, lstride), lane_ptr(pp.hK, lstride), pp.S);
+    smice_prep(H, lane_ptr(pp.tab, lstride), T, St, lane_ptr(pp.stab, lstride));
+    return;
+  }
+  if (blockIdx.x > 1) {  // (the fixed errors of its heads, a snapshot per block)
+    smice_hconst(H, lane_ptr(pp.tab, lstride), T, St, pp.Vcur, pp.absV, lane_ptr(pp.hK, lstride), pp.S,
+                 (int)blockIdx.x - 2);
     return;
   }
   tab = lane_ptr(tab, lstride);

@@ -14,9 +14,9 @@
 //
 //   (k_argmin)                lists mask 0 and the candidate masks; its second
 //                             block, smice_prep: distinct heads, zone targets
-//                             grouped by their anchor chain in Omega_g order,
-//                             head maxima zeroed
-//   k_smice_hconst (grid)     fixed error of each outside head's cluster
+//                             grouped by their anchor chain in Omega_g order;
+//                             a block per snapshot, smice_hconst: fixed error of
+//                             each outside head's cluster
 //   k_smice_score  (grid)     SMICE of every listed mask
 //   k_smice_argmin (1 block)  the smallest SMICE, tie rule, margin, flags
 #include <hip/hip_runtime.h>
@@ -27,46 +27,6 @@
 #include "okr_internal.h"
 
 namespace okr {
-
-// Fixed error of the cluster of every head outside Omega_g, per snapshot:
-// the largest error over its members (every node whose super-node it is,
-// itself included) and their phases, against its unchanging voltage.
-__global__ __launch_bounds__(256) void k_smice_hconst(const SegHdr* __restrict__ hdrs, const int* __restrict__ segs,
-                                                      size_t lstride, Topo T, State St,
-                                                      const double2* __restrict__ Vcur,
-                                                      const double* __restrict__ absV,
-                                                      const int* __restrict__ stab, double* __restrict__ hK, int S) {
-  __shared__ int s_hnode[kMaxK], s_hin[kMaxK];
-  const int g = segs[blockIdx.z];
-  const SegHdr H = load_hdr_g(hdrs, g);
-  if (!H.valid) return;
-  stab = lane_ptr(stab, lstride);
-  hK = lane_ptr(hK, lstride);
-  const int nh = stab[SM_NH];
-  if (threadIdx.x < nh) {
-    s_hnode[threadIdx.x] = stab[SM_HNODE + threadIdx.x];
-    s_hin[threadIdx.x] = stab[SM_HIN + threadIdx.x];
-  }
-  __syncthreads();
-  const int n = T.n;
-  const long total = (long)n * S;
-  for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < total; t += (long)gridDim.x * blockDim.x) {
-    const int l = (int)(t / n), i = (int)(t % n);
-    const int sp = St.sup[i];
-    int x = -1;
-    for (int y = 0; y < nh; ++y)
-      if (s_hnode[y] == sp && !s_hin[y]) x = y;
-    if (x < 0) continue;
-    const unsigned ph = T.phase[i];
-    double e = 0.0;
-    for (int p = 0; p < 3; ++p)
-      if (ph >> p & 1u) {
-        const double2 v = Vcur[((size_t)l * n + sp) * 3 + p];
-        e = fmax(e, fabs(vmag(v) - absV[((size_t)l * n + i) * 3 + p]));
-      }
-    atomicMax((unsigned long long*)&hK[x * S + l], (unsigned long long)__double_as_longlong(e));
-  }
-}
 
 // Voltage shift at the bottom of one chain for mask m (the currents its
 // reduced slots move to their super-nodes), added to B.
