@@ -174,6 +174,15 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
   }
 }
 
+struct SmicePick {
+  double runner;
+  unsigned pick;
+  int amb;
+};
+__device__ __forceinline__ SmicePick shfl_xor_of(const SmicePick& v, int o) {
+  return SmicePick{__shfl_xor(v.runner, o, 64), (unsigned)__shfl_xor((int)v.pick, o, 64), __shfl_xor(v.amb, o, 64)};
+}
+
 // The decision under SMICE: the smallest SMICE among the candidates, the
 // lowest mask within tol of it, the margin to the next one outside, and the
 // ambiguity flags (a candidate within tol/100 of the tie-window edge, or a
@@ -187,8 +196,7 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
                                                        DevDecision* __restrict__ decs, const int* __restrict__ tab,
                                                        Topo T, State St) {
   __shared__ double shd[16];
-  __shared__ int shi[16];
-  __shared__ unsigned shu[16];
+  __shared__ SmicePick shp[16];
   const int g = segs[blockIdx.z];
   const SegHdr H = load_hdr_g(hdrs, g);
   if (!H.valid) return;
@@ -210,6 +218,9 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
   const int ntiles = (int)((1u << H.k) >> tile_bits(H.k));
   // (the list's first entry is mask 0, a candidate at level 0 only)
   const int count = *scount, first = d.popcount == 0 ? 0 : 1;
+  int amb = 0;
+  for (int t = threadIdx.x; t < ntiles; t += blockDim.x)
+    if (tiles[t].near >= d.popcount) amb = 1;
   double smin = INFINITY;
   for (int i = first + threadIdx.x; i < count; i += blockDim.x) smin = fmin(smin, smv[i]);
   smin = block_reduce(smin, [](double a, double b) { return fmin(a, b); }, shd);
@@ -217,7 +228,6 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
   unsigned pick = 0xffffffffu;
   int at = -1;  // list position of this thread's pick
   double runner = INFINITY;
-  int amb = 0;
   for (int i = first + threadIdx.x; i < count; i += blockDim.x) {
     const double v = smv[i];
     if (fabs(v - thr) <= atol) amb = 1;
@@ -229,11 +239,17 @@ __global__ __launch_bounds__(1024) void k_smice_argmin(const SegHdr* __restrict_
     }
   }
   const unsigned mine = pick;
-  for (int t = threadIdx.x; t < ntiles; t += blockDim.x)
-    if (tiles[t].near >= d.popcount) amb = 1;
-  pick = block_reduce(pick, [](unsigned a, unsigned b) { return min(a, b); }, shu);
-  amb = block_reduce(amb, [](int a, int b) { return a | b; }, shi);
-  runner = block_reduce(runner, [](double a, double b) { return fmin(a, b); }, shd);
+  {
+    const SmicePick v = block_reduce(SmicePick{runner, pick, amb},
+                                     [](const SmicePick& a, const SmicePick& b) {
+                                       return SmicePick{fmin(a.runner, b.runner), (unsigned)min(a.pick, b.pick),
+                                                        a.amb | b.amb};
+                                     },
+                                     shp);
+    runner = v.runner;
+    pick = v.pick;
+    amb = v.amb;
+  }
   if (at >= 0 && mine == pick) {  // one thread: the list holds a mask once
     d.mask = pick;
     d.e_loc = fin[pick].e;
