@@ -156,6 +156,19 @@ def test_prefix_sum_load_flow(okr, n, p_deep):
     assert mx == err.max() and mx < 1e-12
 
 
+@pytest.mark.parametrize("n", [65, 1025])
+def test_evaluation_of_given_voltages(okr, n):
+    """An evaluation with V^ given takes the aggregate, fixed solve and errors
+    as launches of their own: the identity assignment gives the oracle's V^
+    back (bound as above)."""
+    print(f"evaluation, V^ given: n={n}", flush=True)
+    f = make_feeder("c2", n, n=n, snapshots=3, kappa=0.2)
+    V, I, st, _ = oracle.powerflow(f)
+    assert st == 0
+    err, mx = okr.evaluate_assignment(f, np.arange(n), vhat=V)
+    assert mx == err.max() and mx < 1e-12
+
+
 def test_load_flow_beyond_prefix_sums(okr):
     """An 18,000-node feeder (over 9600 nodes on a phase): the breadth-first
     load flow of the search, and the level-by-level load flow and fixed-current
