@@ -110,7 +110,7 @@ size_t pf_bfs_lds_bytes(int n, int nlev) {
   const size_t b = sizeof(int) * ((size_t)nlev + 1) + sizeof(uint16_t) * ((size_t)3 * n + 1) + (size_t)n;
   return (n < 65536 && b <= kPfLdsMax) ? b : 0;
 }
-constexpr int kSmiceThreadsHost = 128;  // threads per block of the SMICE scoring (4 masks a round)
+constexpr int kSmiceThreadsHost = 128;  // threads per block of the SMICE scoring (2 masks a round)
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -1150,8 +1150,8 @@ void enqueue_search(okr_handle* h, void* ws, const okr_yblocks* Y, const okr_loa
                          SmicePrep{(const int*)q.tab, q.stab, q.hK, (const double2*)q.Vcur, (const double*)q.absV, S});
       if (smice) {
         // SMICE of the feasible masks of the chosen level, and the decision under it
-        // (as many blocks as fill the chip, or take every mask of the largest level at 4 per block)
-        const int sb = std::max(1, std::min((int)(nmask / 4), 2048 / nz));
+        // (as many blocks as fill the chip, or take every mask of the largest level at 2 per block)
+        const int sb = std::max(1, std::min((int)(nmask / 2), 2048 / nz));
         hipLaunchKernelGGL(k_smice_score, dim3(sb, 1, nz), dim3(kSmiceThreadsHost), 0, st, (const SegHdr*)q.hdrs, segs,
                            lstride, (const int*)q.tab, (const double2*)q.P, (const TargetRec*)q.srec,
                            (const double2*)q.headV, (const TargetRec*)q.zrec, (const int*)q.stab, (const double*)q.hK,

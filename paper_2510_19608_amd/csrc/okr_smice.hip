@@ -39,9 +39,10 @@ __device__ __forceinline__ void sm_shift_chain(const cint* cr, const double2* Pl
       const int w = r < 8 ? phw0 : (r < 16 ? phw1 : phw2);
       const int ph = (w >> (3 * (r & 7))) & 7;
       const double2* pr = Pl + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3;
+      const double2 d[3] = {pr[0], pr[1], pr[2]};
 #pragma unroll
       for (int p = 0; p < 3; ++p)
-        if (ph >> p & 1) B[p] = cadd(B[p], pr[p]);  // the slot's present phases only
+        if (ph >> p & 1) B[p] = cadd(B[p], d[p]);  // the slot's present phases only
     } else {
       sidx = r + 1;
     }
@@ -54,12 +55,14 @@ __device__ __forceinline__ double sm_group(double mag, double lo, double hi) { r
 
 // SMICE over the clusters a mask can touch, summed over the snapshots, for
 // every listed mask (mask 0 first, then the feasible masks of the chosen
-// level).  kSmiceLanes lanes per mask, each taking every kSmiceLanes-th
-// snapshot, their sums folded in a fixed order; per-lane head maxima in LDS.
-// The walk of one (mask, snapshot) is a serial chain of table reads of about
-// 1.2 us per chain, so one lane per mask over the 24 snapshots of the
-// 1000-node workload took 320-420 us per launch; 30 us with 32 lanes.
-constexpr int kSmiceThreads = 128, kSmiceLanes = 32;
+// level).  A wave per mask, its lanes the snapshots, their sums folded in a
+// fixed order; per-lane head maxima in LDS.  The walk of one (mask, snapshot) is
+// a serial chain of table reads, bound by their latency: with one mask in a wave
+// its branches are scalar and the tables' indices scalar loads, and the next
+// record is read while one is worked on.  26 us a launch at 1000 nodes, 24
+// snapshots (30 with two masks in a wave, each record read when it is needed;
+// 320-420 with one lane per mask).
+constexpr int kSmiceThreads = 128;
 __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
     const SegHdr* __restrict__ hdrs, const int* __restrict__ segs, size_t lstride, const int* __restrict__ tab,
     const double2* __restrict__ P, const TargetRec* __restrict__ srec, const double2* __restrict__ headV,
@@ -71,7 +74,7 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
   if (!H.valid) return;
   slist = lane_ptr(slist, lstride);
   scount = lane_ptr(scount, lstride);
-  constexpr int kMasks = kSmiceThreads / kSmiceLanes;  // masks per block and round
+  constexpr int kMasks = kSmiceThreads / 64;  // masks per block and round
   const int count = *as_cint(scount);
   tab = lane_ptr(tab, lstride);
   P = lane_ptr(P, lstride);
@@ -81,20 +84,21 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
   stab = lane_ptr(stab, lstride);
   hK = lane_ptr(hK, lstride);
   smv = lane_ptr(smv, lstride);
-  const int tid = threadIdx.x, sl = tid % kSmiceLanes;
-  const int S = H.S, nh = stab[SM_NH];
+  const int tid = threadIdx.x, sl = tid & 63;
+  const cint* sm = as_cint(stab);
+  const int S = H.S, nh = sm[SM_NH];
   const cint* chains = as_cint(tab + H.o_chain);
   const cint* nest = as_cint(tab + H.o_nest);
-  const int* zr0 = stab + SM_ZREC;
-  for (int i = blockIdx.x * kMasks + tid / kSmiceLanes; i < count; i += gridDim.x * kMasks) {
-  const uint32_t m = slist[i];
+  const cint* zr0 = sm + SM_ZREC;
+  for (int i = blockIdx.x * kMasks + __builtin_amdgcn_readfirstlane(tid >> 6); i < count; i += gridDim.x * kMasks) {
+  const uint32_t m = (uint32_t)as_cint((const int*)slist)[i];
   double total = 0.0;
-  for (int l = sl; l < S; l += kSmiceLanes) {
+  for (int l = sl; l < S; l += 64) {
     const double2* Pl = P + (size_t)l * H.npairs * 3;
     const TargetRec* Tl = srec + (size_t)l * H.nslots * 3;
     const double2* Hl = headV + (size_t)l * H.nchains * 3;
     const TargetRec* Zl = zrec + (size_t)l * H.nz;
-    for (int x = 0; x < nh; ++x) s_acc[x][tid] = stab[SM_HIN + x] ? 0.0 : hK[x * S + l];
+    for (int x = 0; x < nh; ++x) s_acc[x][tid] = sm[SM_HIN + x] ? 0.0 : hK[x * S + l];
     double tot = 0.0;
     for (int c = 0; c < H.nchains; ++c) {
       const cint* cr = chains + c * kChainInts;
@@ -112,56 +116,70 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
         const double2 v = inner ? cadd(Hl[c * 3 + p], B[p]) : Hl[c * 3 + p];
         smag[p] = (hph >> p & 1) ? vmag(v) : 0.0;
       }
-      const int hx = stab[SM_CHX + c];
+      const int hx = sm[SM_CHX + c];
       const int ns = cr[C_NSLOT], s0 = cr[C_SLOT0], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
       const int phw0 = cr[C_PHW0], phw1 = cr[C_PHW1], phw2 = cr[C_PHW2];
       int sidx = 0;
       bool open = false;
-      double cl = 0.0;
+      double cl = 0.0, hd = 0.0;
+      TargetRec nt[3];
+      double2 np[3];
+      // record of slot r and, if it is reduced, the rise of moving it to slot sidx
+      auto fetch = [&](int r) {
+        const TargetRec* tr = Tl + (s0 + r) * 3;
+        const double2* pr = Pl + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) nt[p] = tr[p];
+        if ((m >> (bit0 + r)) & 1u) {
+#pragma unroll
+          for (int p = 0; p < 3; ++p) np[p] = pr[p];
+        }
+      };
+      if (ns > 0) fetch(0);
       for (int r = 0; r < ns; ++r) {
         const int w = r < 8 ? phw0 : (r < 16 ? phw1 : phw2);
         const int ph = (w >> (3 * (r & 7))) & 7;
-        const TargetRec* tr = Tl + (s0 + r) * 3;
-        if ((m >> (bit0 + r)) & 1u) {  // reduced: its group joins the current super-node's cluster
-          const double2* pr = Pl + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3;
-          double er = 0.0;
+        const TargetRec t[3] = {nt[0], nt[1], nt[2]};
+        const double2 pr[3] = {np[0], np[1], np[2]};
+        const bool red = (m >> (bit0 + r)) & 1u, top = sidx == 0;
+        if (!red) sidx = r + 1;
+        if (r + 1 < ns) fetch(r + 1);
+        double er = 0.0;
+        if (red) {  // its group joins the current super-node's cluster
 #pragma unroll
           for (int p = 0; p < 3; ++p) {
             if (!(ph >> p & 1)) continue;
             B[p] = cadd(B[p], pr[p]);
-            er = fmax(er, sm_group(smag[p], tr[p].lo, tr[p].hi));
+            er = fmax(er, sm_group(smag[p], t[p].lo, t[p].hi));
           }
-          if (sidx == 0) s_acc[hx][tid] = fmax(s_acc[hx][tid], er);
+          if (top) hd = fmax(hd, er);
           else cl = fmax(cl, er);
         } else {  // kept: closes the cluster above, opens its own
           if (open) tot += cl;
-          double er = 0.0;
 #pragma unroll
           for (int p = 0; p < 3; ++p) {
             if (!(ph >> p & 1)) continue;
-            const double mg = vmag(cadd(tr[p].W, B[p]));
-            smag[p] = mg;
-            er = fmax(er, sm_group(mg, tr[p].lo, tr[p].hi));
+            smag[p] = vmag(cadd(t[p].W, B[p]));
+            er = fmax(er, sm_group(smag[p], t[p].lo, t[p].hi));
           }
           cl = er;
           open = true;
-          sidx = r + 1;
         }
       }
+      s_acc[hx][tid] = fmax(s_acc[hx][tid], hd);
       if (open) tot += cl;
       // zone targets anchored at this chain: their voltage moves with the
       // chain's bottom shift; a target that heads chains below keeps the
       // maximum for the head's cluster
-      for (int z = stab[SM_ZOFF + c], ze = stab[SM_ZOFF + c + 1]; z < ze; ++z) {
-        const int* zr = zr0 + z * kZrecInts;
+      for (int z = sm[SM_ZOFF + c], ze = sm[SM_ZOFF + c + 1]; z < ze; ++z) {
+        const cint* zr = zr0 + z * kZrecInts;
+        TargetRec t[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) t[p] = Zl[max(zr[1 + p], 0)];
         double ez = 0.0;
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-          const int e = zr[1 + p];
-          if (e < 0) continue;
-          const TargetRec t = Zl[e];
-          ez = fmax(ez, sm_group(vmag(cadd(t.W, B[p])), t.lo, t.hi));
-        }
+        for (int p = 0; p < 3; ++p)
+          if (zr[1 + p] >= 0) ez = fmax(ez, sm_group(vmag(cadd(t[p].W, B[p])), t[p].lo, t[p].hi));
         if (zr[4] >= 0) s_acc[zr[4]][tid] = fmax(s_acc[zr[4]][tid], ez);
         else tot += ez;
       }
@@ -169,7 +187,7 @@ __global__ __launch_bounds__(kSmiceThreads) void k_smice_score(
     for (int x = 0; x < nh; ++x) tot += s_acc[x][tid];
     total += tot;
   }
-  for (int o = kSmiceLanes / 2; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
+  for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
   if (sl == 0) smv[i] = total;
   }
 }
