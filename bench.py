@@ -38,7 +38,7 @@ HBM_PEAK_TBPS = 8.0              # MI355X HBM3E
 # for the sources they were taken with: any change to them reports null.
 TRAFFIC_SOURCES = ["paper_2510_19608_amd/csrc/okr_score.hip", "paper_2510_19608_amd/csrc/okr_device.h",
                    "paper_2510_19608_amd/csrc/okr_internal.h", "paper_2510_19608_amd/csrc/okr_build.hip"]
-TRAFFIC_SHA1 = "ca08e2576f82a2729f99a3860dd1ce13bc6de31f"
+TRAFFIC_SHA1 = "3d19a479946badcaf6a7f3e7ec5a80490845425a"
 TRAFFIC_BYTES_PER_LAUNCH = 1187000
 
 
