@@ -50,7 +50,7 @@ hipError_t flow_prepare(const FlowPlan& p);
 // Load flow of S snapshots and the cumulative impedances (form 1 or 2).
 void flow_launch(const FlowPlan& p, const FlowArgs& a, int S, hipStream_t st);
 // Load flow, fixed-current solve of the clusters' currents and largest errors
-// (form 1; of a's outputs only the status is written).
+// (form 1; of a's outputs only the status and absV are written).
 void flow_eval_launch(const FlowPlan& p, const FlowArgs& a, const FlowEval& e, int S, hipStream_t st);
 // Voltages of the fixed currents I [S][n][3] by label (form 1 or 2).
 void flow_fixed_launch(const FlowPlan& p, const int* tab, const uint8_t* phase, const double2* z, const double2* v0,
