@@ -457,6 +457,12 @@ struct StateUpdate {
 };
 
 // ------------------------------------------------------------ block reduce --
+// The larger of two non-negative values, NaN if either is (the bit patterns
+// order like the values, with every NaN above infinity).
+__device__ __forceinline__ double nan_max(double a, double b) {
+  return (unsigned long long)__double_as_longlong(a) > (unsigned long long)__double_as_longlong(b) ? a : b;
+}
+
 template <typename T>
 __device__ __forceinline__ T shfl_xor_of(T v, int o) {
   return __shfl_xor(v, o, 64);

@@ -103,8 +103,6 @@ __device__ __forceinline__ double l1(double2 a) { return fabs(a.x) + fabs(a.y); 
 // Bound on the magnitude of the current that load s draws at voltage v.
 __device__ __forceinline__ double current_bound(double2 s, double2 v) { return l1(s) / fmax(fabs(v.x), fabs(v.y)); }
 
-__device__ __forceinline__ double nan_max(double a, double b) { return (b <= a) ? a : b; }  // keeps NaN
-
 // NaN-propagating maximum of non-negative values over the block (every thread
 // gets it); s holds a value per wave and must not be in use.
 __device__ __forceinline__ double block_nan_max(double v, double* s) {

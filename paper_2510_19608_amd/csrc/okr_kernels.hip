@@ -126,7 +126,7 @@ __device__ __forceinline__ void forward_node(int i, const int* __restrict__ pare
     const double2 d = cadd(cadd(cmul(zi[p * 3], j0), cmul(zi[p * 3 + 1], j1)), cmul(zi[p * 3 + 2], j2));
     const double2 nv = csub(Vl[pv * 3 + p], d);
     const double dd = sqrt(cabs2(csub(nv, Vl[i * 3 + p])));
-    dmax = (dd <= dmax) ? dmax : dd;
+    dmax = nan_max(dmax, dd);
     Vl[i * 3 + p] = nv;
   }
 }
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void k_powerflow(
       }
       __syncthreads();
     }
-    dmax = block_reduce(dmax, [](double a, double b) { return (b <= a) ? a : b; }, shd);
+    dmax = block_reduce(dmax, [](double a, double b) { return nan_max(a, b); }, shd);
     if (!(dmax <= 1e3)) break;
     if (dmax <= tol) { conv = true; break; }
   }
@@ -343,13 +343,13 @@ __global__ __launch_bounds__(512) void k_powerflow_bfs(
           const double2 d = cadd(cadd(cmul(zi[p * 3], j[0]), cmul(zi[p * 3 + 1], j[1])), cmul(zi[p * 3 + 2], j[2]));
           const double2 nv = csub(vp[p], d);
           const double dd = sqrt(cabs2(csub(nv, vo[p])));
-          dmax = (dd <= dmax) ? dmax : dd;
+          dmax = nan_max(dmax, dd);
           Vb[q * 3 + p] = nv;
         }
       }
       __syncthreads();
     }
-    dmax = block_reduce(dmax, [](double a, double b) { return (b <= a) ? a : b; }, shd);
+    dmax = block_reduce(dmax, [](double a, double b) { return nan_max(a, b); }, shd);
     if (!(dmax <= 1e3)) break;
     if (dmax <= tol) { conv = true; break; }
   }

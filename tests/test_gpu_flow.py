@@ -151,3 +151,35 @@ def test_light_branches_keep_their_bits(okr, n, S, p_deep):
     assert worst <= TOL
     assert np.abs(err - want).max() <= TOL_STOP
     assert np.abs(given - want_given).max() <= TOL
+
+
+def without_phase_a(n, S, nan_at):
+    """A feeder of phases b and c alone whose loads are NaN at one node."""
+    f = make_feeder("c2", n, n=n, snapshots=S, p_single=0.0, p_two=0.0, kappa=2.0 ** -6, seg_size=(6, 8), v_min=0.5,
+                    v_max=1.5)
+    parent, Yo, S_load = np.asarray(f["parent"]), np.array(f["Y_off"]), np.array(f["S_load"])
+    for i in range(1, n):
+        z = np.linalg.inv(-Yo[i])[1:, 1:]
+        Yo[i] = 0
+        Yo[i, 1:, 1:] = -np.linalg.inv(z)
+    Yd = np.zeros_like(Yo)
+    for i in range(1, n):
+        Yd[i] -= Yo[i]
+        Yd[parent[i]] -= Yo[i]
+    S_load[:, :, 0] = 0
+    S_load[-1, nan_at, 2] = np.nan
+    return dict(f, phase=np.full(n, 6, np.uint8), Y_off=Yo, Y_diag=Yd, S_load=S_load)
+
+
+@pytest.mark.parametrize("n", [30, 320, 1000, 1100, 18000])
+def test_nan_load_is_no_convergence(okr, n):
+    """A load flow that turns NaN is reported as diverged in every form, also
+    where the lanes of an absent phase hold zeros beside the NaN ones."""
+    print(f"NaN load: n={n}", flush=True)
+    f = without_phase_a(n, 2, n - 1)
+    with pytest.raises(okr.OkrError) as e:
+        okr.reduce_feeder(f, want_vhat=False)
+    assert "converge" in str(e.value)
+    with pytest.raises(okr.OkrError) as e:
+        okr.evaluate_assignment(f, np.arange(n))
+    assert "converge" in str(e.value)
