@@ -68,8 +68,9 @@ struct GStep {  // layout of okr_greedy_step
 constexpr int kGreedyThreads = 256;
 constexpr int kGreedyPickThreads = 1024;
 constexpr int kGreedyMaxS = 64;      // scenarios of a search (moved currents staged in LDS)
-constexpr int kGreedyMaxN = 12288;   // nodes of an incremental search
-constexpr int kGreedyFullSN = 6144;  // S x n up to which every candidate sums every cluster
+constexpr int kGreedyMaxN = 12288;   // nodes that an incremental search accepts (its counts' 20 bits would hold 2^19)
+constexpr int kGreedyFullSN = 6144;  // S x n up to which every candidate sums every cluster ...
+constexpr int kGreedyFullSNL = 7680;  // ... and S x n + 3 x levels
 
 // Lowest common ancestors of labels (depth-first positions): the smallest
 // (parent, last position) over power-of-two runs of labels, level k at
@@ -1277,9 +1278,13 @@ extern "C" int okr_greedy_run(okr_greedy* g, const okr_yblocks* Y, const okr_loa
   if (S > kGreedyMaxS) OKRG_FAIL(g, OKR_E_UNSUPPORTED, "the search takes at most %d scenarios", kGreedyMaxS);
   // every candidate sums every cluster while there are few (1000 nodes, 2
   // scenarios: 9.5 us a scoring against 10.7); beyond that, or when asked, only
-  // the clusters a move can change
+  // the clusters a move can change.  A level counts as three errors, so that
+  // deep feeders near the limit go by the changed clusters too: us per move of
+  // the first 320, every cluster against the changed ones, 6000 nodes x 1
+  // scenario with 949 levels 80 and 39, 3000 x 2 with 820 levels 50 and 39,
+  // 1500 x 4 with 1196 levels 45 and 49
   const bool incremental = (prm->flags & OKR_GREEDY_INCREMENTAL) || (size_t)S * n > kGreedyFullSN ||
-                           8 * (size_t)S * n + 24 * (size_t)g->nlev > 60 * 1024;
+                           (size_t)S * n + 3 * (size_t)g->nlev > kGreedyFullSNL;
   if (incremental && n > kGreedyMaxN)
     OKRG_FAIL(g, OKR_E_UNSUPPORTED, "the search takes at most %d nodes", kGreedyMaxN);
   const hipStream_t st = g->stream;
