@@ -46,105 +46,55 @@ __device__ __forceinline__ double sqrt_nr(double x) {
 // through it, so all scoring forms round alike).
 __device__ __forceinline__ double mag2(double2 a) { return fma(a.x, a.x, a.y * a.y); }
 __device__ __forceinline__ double vmag(double2 a) { return sqrt_nr(mag2(a)); }
-// Magnitude of a chain head's voltage (mask-independent for chains that are
-// not nested below another chain), one fixed evaluation order.
-__device__ __forceinline__ double hmag(double2 a) { return sqrt_nr(fma(a.x, a.x, a.y * a.y)); }
 
-// Walk one chain for M masks at once (one lane holds M masks; every
-// wave-uniform quantity -- chain record, slot records, targets, head
-// magnitude -- is shared by the M independent arithmetic chains): super-node
-// slots top to bottom; a reduced slot adds the voltage rise of moving its
-// aggregated current to its current super (P from LDS); a kept slot becomes
-// the super of the slots below it.  With ERR, every slot cluster's error
-// against its super's magnitude is folded into el, and the squared
-// magnitudes of kept slots into (qmin, qmax) for the band (the slack is
-// formed once per mask: sqrt is monotone, so min(|V| - vmin) =
+// Walk one chain for one mask: super-node slots top to bottom; a reduced slot
+// adds the voltage rise of moving its aggregated current to its current super
+// (P from LDS); a kept slot becomes the super of the slots below it.  With ERR,
+// every slot cluster's error against its super's magnitude is folded into el, and
+// the squared magnitudes of kept slots into (qmin, qmax) for the band (the slack
+// is formed once per mask: sqrt is monotone, so min(|V| - vmin) =
 // sqrt(min |V|^2) - vmin exactly).  Slot r of the chain has mask bit
-// C_BIT0 + r, pairs from C_PAIR0 + r(r+1)/2 and its phases in the C_PHW
-// words, so the slot loop issues no scalar loads.  The arithmetic of each
-// mask is the same whatever M.
-template <bool ERR, int M>
+// C_BIT0 + r, pairs from C_PAIR0 + r(r+1)/2 and its phases in the C_PHW words.
+template <bool ERR>
 __device__ __forceinline__ void walk_chain(const int* __restrict__ cr, const double2* Ps, const TargetRec* Ss,
-                                           const double2* Hs, const double* Hm, int c, const uint32_t (&m)[M],
-                                           double2 (&B)[M][3], double (&el)[M], double (&qmin)[M],
-                                           double (&qmax)[M]) {
-  double2 S[M][3];
-  double sm[M][3];
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) {
-      S[i][p] = B[i][p];
-      sm[i][p] = 0.0;
-    }
+                                           const double2* Hs, int c, uint32_t m, double2 (&B)[3], double& el,
+                                           double& qmin, double& qmax) {
+  double sm[3] = {0.0, 0.0, 0.0};
   if (ERR) {
     const int hph = cr[C_PHASE];
-    const double2* hv = Hs + c * 3;
-    if (cr[C_OUTER] < 0) {  // head unaffected by the mask
+    const bool inner = cr[C_OUTER] >= 0;  // (else the head is unaffected by the mask)
 #pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        double h = 0.0;
-        if (Hm) h = Hm[c * 3 + p];
-        else if (hph >> p & 1) h = hmag(hv[p]);
-#pragma unroll
-        for (int i = 0; i < M; ++i) sm[i][p] = h;
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < 3; ++p)
-        if (hph >> p & 1) {
-          const double2 h = hv[p];
-#pragma unroll
-          for (int i = 0; i < M; ++i) sm[i][p] = vmag(cadd(h, B[i][p]));
-        }
-    }
+    for (int p = 0; p < 3; ++p)
+      if (hph >> p & 1) sm[p] = vmag(inner ? cadd(Hs[c * 3 + p], B[p]) : Hs[c * 3 + p]);
   }
   const int ns = cr[C_NSLOT], s0 = cr[C_SLOT0], pair0 = cr[C_PAIR0], bit0 = cr[C_BIT0];
   const int phw0 = cr[C_PHW0], phw1 = cr[C_PHW1], phw2 = cr[C_PHW2];
-  int sidx[M];
-#pragma unroll
-  for (int i = 0; i < M; ++i) sidx[i] = 0;
+  int sidx = 0;
   for (int r = 0; r < ns; ++r) {
     const int w = r < 8 ? phw0 : (r < 16 ? phw1 : phw2);
     const int ph = (w >> (3 * (r & 7))) & 7;
-    const int prow = pair0 + ((r * (r + 1)) >> 1);
     const TargetRec* tr = Ss + (s0 + r) * 3;
-    bool red[M];
-    double rf[M];
-    const double2* pp[M];
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      red[i] = (m[i] >> (bit0 + r)) & 1u;
-      rf[i] = red[i] ? 1.0 : 0.0;
-      pp[i] = Ps + (prow + sidx[i]) * 3;
-    }
+    const bool red = (m >> (bit0 + r)) & 1u;
+    const double rf = red ? 1.0 : 0.0;
+    const double2* pr = Ps + (pair0 + ((r * (r + 1)) >> 1) + sidx) * 3;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       if (!(ph >> p & 1)) continue;
-      TargetRec t;
-      if (ERR) t = tr[p];
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const double2 pv = pp[i][p];
-        S[i][p].x = fma(rf[i], pv.x, S[i][p].x);
-        S[i][p].y = fma(rf[i], pv.y, S[i][p].y);
-        if (ERR) {
-          const double vx = t.W.x + S[i][p].x, vy = t.W.y + S[i][p].y;
-          const double q = fma(vx, vx, vy * vy);
-          if (!red[i]) sm[i][p] = sqrt_nr(q);
-          qmin[i] = fmin(qmin[i], red[i] ? INFINITY : q);
-          qmax[i] = fmax(qmax[i], red[i] ? -INFINITY : q);
-          el[i] = fmax(el[i], fmax(sm[i][p] - t.lo, t.hi - sm[i][p]));
-        }
+      const double2 pv = pr[p];
+      B[p].x = fma(rf, pv.x, B[p].x);
+      B[p].y = fma(rf, pv.y, B[p].y);
+      if (ERR) {
+        const TargetRec t = tr[p];
+        const double vx = t.W.x + B[p].x, vy = t.W.y + B[p].y;
+        const double q = fma(vx, vx, vy * vy);
+        if (!red) sm[p] = sqrt_nr(q);
+        qmin = fmin(qmin, red ? INFINITY : q);
+        qmax = fmax(qmax, red ? -INFINITY : q);
+        el = fmax(el, fmax(sm[p] - t.lo, t.hi - sm[p]));
       }
     }
-#pragma unroll
-    for (int i = 0; i < M; ++i) sidx[i] = red[i] ? sidx[i] : r + 1;
+    sidx = red ? sidx : r + 1;
   }
-#pragma unroll
-  for (int i = 0; i < M; ++i)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) B[i][p] = S[i][p];
 }
 
 // The mask's bits at pm's positions, gathered (run by run).
@@ -177,44 +127,35 @@ __device__ __forceinline__ bool near_boundary(const MaskScore& r, double e_bar, 
   return !rin && !rout;
 }
 
-// Terms of chain c for M masks and one snapshot folded into el, kept squared
+// Terms of chain c for one mask and one snapshot folded into el, kept squared
 // magnitudes into (qmin, qmax): the nesting path walked to the chain's head
 // (voltage rises only), the chain's own slots, then the zone entries anchored
-// below it (the first zcap of them from the LDS stage Zs when STAGED, the
-// rest from global memory).  They depend on the mask bits in C_PMASK only.
-template <bool STAGED, int M>
+// below it (the first zcap of them from the LDS stage Zs, the rest from global
+// memory).  They depend on the mask bits in C_PMASK only.
 __device__ __forceinline__ void score_chain(const int* __restrict__ chains, const int* __restrict__ nest, int c,
                                             const double2* Ps, const TargetRec* Ss, const double2* Hs,
-                                            const double* Hm, const TargetRec* Zs, int zcap,
-                                            const TargetRec* __restrict__ zrec_l, const uint32_t (&m)[M],
-                                            double (&el)[M], double (&qmin)[M], double (&qmax)[M]) {
+                                            const TargetRec* Zs, int zcap, const TargetRec* __restrict__ zrec_l,
+                                            uint32_t m, double& el, double& qmin, double& qmax) {
   const int* cr = chains + c * kChainInts;
-  double2 B[M][3];
+  double2 B[3];
 #pragma unroll
-  for (int i = 0; i < M; ++i)
-#pragma unroll
-    for (int p = 0; p < 3; ++p) B[i][p] = make_double2(0.0, 0.0);
+  for (int p = 0; p < 3; ++p) B[p] = make_double2(0.0, 0.0);
   const int nl = cr[C_NEST_LEN], no = cr[C_NEST_OFF];
-  for (int q = 0; q + 1 < nl; ++q) {
-    const int oc = nest[no + q];
-    walk_chain<false, M>(chains + oc * kChainInts, Ps, Ss, Hs, Hm, oc, m, B, el, qmin, qmax);
-  }
-  walk_chain<true, M>(cr, Ps, Ss, Hs, Hm, c, m, B, el, qmin, qmax);
+  for (int q = 0; q + 1 < nl; ++q)
+    walk_chain<false>(chains + nest[no + q] * kChainInts, Ps, Ss, Hs, nest[no + q], m, B, el, qmin, qmax);
+  walk_chain<true>(cr, Ps, Ss, Hs, c, m, B, el, qmin, qmax);
 #pragma unroll
   for (int p = 0; p < 3; ++p)
     for (int q = cr[C_ZOFF0 + p], qe = q + cr[C_ZCNT0 + p]; q < qe; ++q) {
       TargetRec t;
-      if (STAGED && q < zcap) t = Zs[q];
+      if (q < zcap) t = Zs[q];
       else t = zrec_l[q];
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const double vx = t.W.x + B[i][p].x, vy = t.W.y + B[i][p].y;
-        const double q2 = fma(vx, vx, vy * vy);
-        const double mag = sqrt_nr(q2);
-        el[i] = fmax(el[i], fmax(mag - t.lo, t.hi - mag));
-        qmin[i] = fmin(qmin[i], q2);
-        qmax[i] = fmax(qmax[i], q2);
-      }
+      const double vx = t.W.x + B[p].x, vy = t.W.y + B[p].y;
+      const double q2 = fma(vx, vx, vy * vy);
+      const double mag = sqrt_nr(q2);
+      el = fmax(el, fmax(mag - t.lo, t.hi - mag));
+      qmin = fmin(qmin, q2);
+      qmax = fmax(qmax, q2);
     }
 }
 
@@ -479,22 +420,6 @@ __device__ T block_reduce(T v, Op op, T* sh) {
   for (int w = 1; w < nw; ++w) r = op(r, sh[w]);
   __syncthreads();
   return r;
-}
-
-// Exclusive prefix sum of one int per thread over the block (Hillis-Steele in
-// `sh`, which holds blockDim.x ints).
-__device__ __forceinline__ int block_exclusive_scan(int v, int* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int o = 1; o < (int)blockDim.x; o <<= 1) {
-    const int x = threadIdx.x >= (unsigned)o ? sh[threadIdx.x - o] : 0;
-    __syncthreads();
-    sh[threadIdx.x] += x;
-    __syncthreads();
-  }
-  const int incl = sh[threadIdx.x];
-  __syncthreads();
-  return incl - v;
 }
 
 }  // namespace okr

@@ -2,7 +2,6 @@
 // of the plan, workspace layout, and the launch sequence of a search (one
 // stream of kernels, optionally replayed as a captured hipGraph; one host
 // synchronisation at the end).
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -906,12 +905,10 @@ Ptrs pointers(okr_handle* h, void* d_workspace, int lane = 0) {
   return p;
 }
 
-// FP64 scores of list[0 .. *count) (at most cap masks) of one segment into
-// out: one lane per (listed mask, chain, snapshot), folded by atomics.  w
-// holds the segment's scratch pointers and segp its id in device memory.
-// FP64 scores of a mask list per chunk position (list, count and out in each
-// position's scratch block; cap bounds every list): accumulators, chain
-// terms of every (listed mask, chain), final scores.
+// FP64 scores of a mask list per chunk position (list[0 .. *count), count and out
+// in each position's scratch block, w the first one's; cap bounds every list;
+// segp: the positions' segment ids in device memory): accumulators, the terms of
+// every (listed mask, chain, snapshot) folded by atomics, final scores.
 void list_score(const okr_handle* h, const Ptrs& w, const int* segp, int nz, int k, const uint32_t* list,
                 const int* count, int cap, MaskScore* out, const SelParams& sp, hipStream_t st) {
   const size_t ls = h->L.lane_stride;

@@ -8,7 +8,6 @@ namespace okr {
 
 constexpr int kMaxK = 24;                    // eligible nodes per segment
 constexpr int kMaxPairs = kMaxK * (kMaxK + 1) / 2;  // (super slot, reduced slot) pairs
-constexpr int kScoreBlock = 64;              // masks per tile record (one wave)
 
 // status bit set when a structural invariant of a segment's tables fails (the
 // segment is then skipped by the scoring path and the call reports an error)

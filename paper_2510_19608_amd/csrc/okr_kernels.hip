@@ -31,10 +31,9 @@ __device__ __forceinline__ double blk_maxabs(const double2* A) {
 
 // ---------------------------------------------------------- validation + z --
 // Branch impedances z_i = (-Y_{i,parent})^+ and checks of the admittance input
-// (symmetry, zero absent-phase entries, no shunts).  ext (or null: the same) maps
-// the labels of the tree arrays and z to the input's node ids.  With a search
-// state it also resets every node's (kept and its own super-node, the maps
-// empty).
+// (symmetry, zero absent-phase entries, no shunts).  ext maps the labels of the
+// tree arrays and z to the input's node ids.  With a search state it also resets
+// every node's (kept and its own super-node, the maps empty).
 // status bits: 1 singular, 2 absent-phase entry, 4 asymmetric, 8 shunt.
 // The first nz blocks take a node per thread (inverse, symmetry, reset), the
 // others the row sums, 16 lanes per node (9 entries; the children's ids loaded
@@ -62,7 +61,7 @@ __global__ __launch_bounds__(64) void k_branch_z(int n, int nz, const uint8_t* _
       return;
     }
     const unsigned ph = phase[i];
-    const double2* Yo = Yoff + (size_t)(ext ? ext[i] : i) * 9;
+    const double2* Yo = Yoff + (size_t)ext[i] * 9;
     const double oscale = blk_maxabs(Yo);
     double asym = 0.0;
     double2 y[9];
@@ -82,7 +81,7 @@ __global__ __launch_bounds__(64) void k_branch_z(int n, int nz, const uint8_t* _
     const int i = ((int)blockIdx.x - nz) * 4 + (tid >> 4), k = tid & 15;
     const bool in = i < n, on = in && k < 9;
     const int r = k / 3, c = k - 3 * r;
-    const int x = in ? (ext ? ext[i] : i) : 0, e0 = in ? ch_off[i] : 0, nc = in ? ch_off[i + 1] - e0 : 0;
+    const int x = in ? ext[i] : 0, e0 = in ? ch_off[i] : 0, nc = in ? ch_off[i + 1] - e0 : 0;
     const unsigned ph = in ? phase[i] : 0u;
     double2 acc = make_double2(0.0, 0.0);
     if (on) acc = Ydiag[(size_t)x * 9 + k];
@@ -91,7 +90,7 @@ __global__ __launch_bounds__(64) void k_branch_z(int n, int nz, const uint8_t* _
     if (on && absent && dmax != 0.0) bad |= 2;
     if (on && i > 0) acc = cadd(acc, Yoff[(size_t)x * 9 + k]);
     for (int b = 0; __ballot(b < nc); b += 16) {
-      const int id = b + k < nc ? (ext ? ext[ch[e0 + b + k]] : ch[e0 + b + k]) : 0;
+      const int id = b + k < nc ? ext[ch[e0 + b + k]] : 0;
       for (int j = 0; j < 16 && __ballot(b + j < nc); ++j) {
         const int y = __shfl(id, (tid & 48) + j, 64);
         if (on && b + j < nc) acc = cadd(acc, Yoff[(size_t)y * 9 + c * 3 + r]);
@@ -112,8 +111,7 @@ __global__ __launch_bounds__(64) void k_branch_z(int n, int nz, const uint8_t* _
 // sweep on the radial tree, one block per snapshot, level-synchronous.
 // status bit 16: not converged; bit 32: base network outside the band.
 // The tree arrays, V, J, A and absV go by label, Sload by the caller's node
-// ids (ext[label], or null: the same); Vext, where given, takes the voltages
-// by the caller's ids.
+// ids (ext[label]); Vext, where given, takes the voltages by the caller's ids.
 // Forward-sweep update of node i: V(i) = V(parent) - z(i) J(i) on its
 // present phases, and the largest change into dmax (NaN-propagating).
 __device__ __forceinline__ void forward_node(int i, const int* __restrict__ parent, const uint8_t* __restrict__ phase,
@@ -158,7 +156,7 @@ __global__ __launch_bounds__(256) void k_powerflow(
     // steps' latency chain), then the backward sweep adds each level's
     // children into their parents, deepest level first
     for (int i = tid; i < n; i += bd) {
-      const int x = ext ? ext[i] : i;
+      const int x = ext[i];
       for (int p = 0; p < 3; ++p)
         Jl[i * 3 + p] = (i > 0 && (phase[i] >> p & 1u)) ? cconj(cdiv(Sl[x * 3 + p], Vl[i * 3 + p]))
                                                         : make_double2(0.0, 0.0);
@@ -217,7 +215,7 @@ __global__ __launch_bounds__(256) void k_powerflow(
   }
   double vlo = 1e300, vhi = -1e300;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const int x = ext ? ext[i] : i;
+    const int x = ext[i];
     for (int p = 0; p < 3; ++p) {
       const bool pr = (phase[i] >> p & 1u);
       const double2 v = Vl[i * 3 + p];
@@ -390,8 +388,8 @@ __global__ __launch_bounds__(1024) void k_zroot(int n, const int* __restrict__ p
   zroot_block(n, parent, lvl_off, lvl_nodes, nlev, z, Zroot);
 }
 
-// Given V^ (caller supplied): load currents and magnitudes, band check; with
-// ext (label -> the caller's node id) the voltages by label too.
+// Given V^ (caller supplied, by the caller's node ids ext[label]): load currents
+// and magnitudes, band check; with Vlab the voltages by label too.
 __global__ void k_from_vhat(int n, int S, const uint8_t* __restrict__ phase, const double2* __restrict__ Sload,
                             const double2* __restrict__ V, double vmin, double vmax, double2* __restrict__ A,
                             double* __restrict__ absV, int* __restrict__ status, const int* __restrict__ ext,
@@ -399,7 +397,7 @@ __global__ void k_from_vhat(int n, int S, const uint8_t* __restrict__ phase, con
   const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= (size_t)S * n * 3) return;
   const int p = q % 3, i = (q / 3) % n;
-  const size_t x = ext ? q + ((long)ext[i] - i) * 3 : q;
+  const size_t x = q + ((long)ext[i] - i) * 3;
   const bool pr = (phase[i] >> p & 1u);
   const double2 v = V[x];
   if (Vlab) Vlab[q] = v;
@@ -654,7 +652,10 @@ __global__ void k_copy2(const double2* __restrict__ a, double2* __restrict__ b, 
 // ---------------------------------------------------------- final outputs --
 // Final outputs: the first nd blocks form the diagonal blocks of the reduced
 // network (and the status word joins the results), each other block one
-// snapshot's largest error of the final reduction over every node-phase.  (As
+// snapshot's largest error of the final reduction over every node-phase.
+// Y_Kron(x,x) = y_eq of x's own branch plus those of its reduced-network
+// children, found by following each tree child down through reduced nodes
+// (which have at most one child) to the first kept node.  (As
 // launches of their own 11 and 7.4 us at 1000 nodes; the errors with 256 threads
 // a block 42 us at 6000 nodes.)
 __global__ __launch_bounds__(512) void k_final(Topo T, State St, int nd, const double2* __restrict__ yeq,

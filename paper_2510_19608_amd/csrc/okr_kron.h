@@ -83,8 +83,4 @@ __device__ __forceinline__ void kron_yeq(int x, const Topo& T, const State& St, 
   for (int q = 0; q < 9; ++q) yo[q] = make_double2(-ye[q].x, -ye[q].y);
 }
 
-// Y_Kron(x,x) = y_eq of x's own branch plus those of its reduced-network
-// children, found by following each tree child down through reduced nodes
-// (which have at most one child) to the first kept node.
-
 }  // namespace okr

@@ -615,14 +615,12 @@ __global__ __launch_bounds__(kTermsBlock) void k_chain_terms(
     const int it = base + threadIdx.x;
     if (it < items) {
       const int q = it / nch, c = it - q * nch;
-      const uint32_t mm[1] = {list[q]};
-      double el[1] = {ec}, qn[1] = {INFINITY}, qx[1] = {0.0};
-      score_chain<true, 1>(chains, nest, c, sP, sS, sH, (const double*)nullptr, sZ, zst, zrec + (size_t)l * H.nz,
-                           mm, el, qn, qx);
+      double el = ec, qn = INFINITY, qx = 0.0;
+      score_chain(chains, nest, c, sP, sS, sH, sZ, zst, zrec + (size_t)l * H.nz, list[q], el, qn, qx);
       unsigned long long* a = s_acc + 3 * (q - q0);
-      atomicMax(&a[0], (unsigned long long)__double_as_longlong(el[0]));
-      if (qn[0] < INFINITY) atomicMin(&a[1], (unsigned long long)__double_as_longlong(qn[0]));
-      if (qx[0] > 0.0) atomicMax(&a[2], (unsigned long long)__double_as_longlong(qx[0]));
+      atomicMax(&a[0], (unsigned long long)__double_as_longlong(el));
+      if (qn < INFINITY) atomicMin(&a[1], (unsigned long long)__double_as_longlong(qn));
+      if (qx > 0.0) atomicMax(&a[2], (unsigned long long)__double_as_longlong(qx));
     }
     __syncthreads();
     for (int i = threadIdx.x; i <= q1 - q0; i += blockDim.x) {

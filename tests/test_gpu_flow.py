@@ -133,8 +133,8 @@ def test_light_branches_keep_their_bits(okr, n, S, p_deep):
     x = Exact(f)
     V = x.flow()
     assert np.abs(V - x.V0 * x.on).max() < 0.1
-    even = okr.reduce_feeder(make_feeder("c2", n, n=n, snapshots=S, p_deep=p_deep, seg_size=(6, 8), v_min=0.5, v_max=1.5,
-                                         kappa=f["kappa"]), want_vhat=False)
+    even = okr.reduce_feeder(make_feeder("c2", n, n=n, snapshots=S, p_deep=p_deep, seg_size=(6, 8), v_min=0.5,
+                                         v_max=1.5, kappa=f["kappa"]), want_vhat=False)
     out = okr.reduce_feeder(f, want_vhat=False)
     assert out["pf_iterations"] <= even["pf_iterations"]
     out = okr.reduce_feeder(f, pf_tol=1e-15)
