@@ -38,7 +38,7 @@ HBM_PEAK_TBPS = 8.0              # MI355X HBM3E
 # for the sources they were taken with: any change to them reports null.
 TRAFFIC_SOURCES = ["paper_2510_19608_amd/csrc/okr_score.hip", "paper_2510_19608_amd/csrc/okr_device.h",
                    "paper_2510_19608_amd/csrc/okr_internal.h", "paper_2510_19608_amd/csrc/okr_build.hip"]
-TRAFFIC_SHA1 = "3d19a479946badcaf6a7f3e7ec5a80490845425a"
+TRAFFIC_SHA1 = "f34615d747e860791bacc267cf195009feb07d56"
 TRAFFIC_BYTES_PER_LAUNCH = 1187000
 
 
@@ -488,7 +488,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": "c2: 1000-node synthetic three-phase feeder, 24 snapshots, "
                                "segments of 16 eligible nodes, exhaustive 2^16 masks per segment",
-                   "seed": args.seed, "n_candidates": ncand, "segments": int(out["n_score_launches"]),
+                   "seed": args.seed, "n_candidates": ncand, "segments": len(out["segments"]),
+                   "chunks": int(out["n_score_launches"]),
                    "precision": "fp64", "e_bar": f["e_bar"], "n_kept": int(out["n_kept"]),
                    "max_err": out["max_err"], "parallelism": "single GPU"},
         "roofline": {"bound": "latency", "achieved": achieved, "peak": HBM_PEAK_TBPS, "unit": "TB/s",

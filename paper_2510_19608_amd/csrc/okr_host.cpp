@@ -459,7 +459,7 @@ extern "C" int okr_plan(okr_handle* h, const okr_topology* topo, const okr_margi
   // nothing any more, the ones at the head of the longest runs of conflicts
   // first (then the largest): conflicting segments keep their order, and few
   // chunks are cut beyond the longest run (level by level the 1000-, 6000- and
-  // 8400-node feeders took 20, 61 and 76 chunks against 18, 48 and 59).
+  // 8400-node feeders took 20, 61 and 76 chunks against 18, 47 and 59).
   {
     const int want = mg->lanes > 0 ? std::min(mg->lanes, kMaxLanes) : kDefaultLanes;
     h->nlanes = std::max(1, std::min(want, nseg));
