@@ -183,3 +183,21 @@ def test_nan_load_is_no_convergence(okr, n):
     with pytest.raises(okr.OkrError) as e:
         okr.evaluate_assignment(f, np.arange(n))
     assert "converge" in str(e.value)
+
+
+@pytest.mark.parametrize("n,S", [(9600, 2), (9601, 2), (4902, 257), (4903, 257)])
+def test_phase_lists_at_the_edges_of_lds(okr, n, S):
+    """Three-phase feeders at the largest list that a block's LDS holds (9600
+    entries and their rows' sums), one more (level by level), and at the largest
+    that two blocks share a compute unit with (4902).  The oracle's load flow
+    stops at the same 1e-13, so the voltages differ by less than ten times that."""
+    import oracle
+    print(f"phase lists: n={n} S={S}", flush=True)
+    f = make_feeder("c2", 1, n=n, snapshots=S, p_single=0.0, p_two=0.0, p_deep=0.5, kappa=2.0 ** -7, seg_size=(4, 6),
+                    v_min=0.5, v_max=1.5)
+    V, _, st, _ = oracle.powerflow(f)
+    assert st == 0
+    out = okr.reduce_feeder(f, want_vhat=True)
+    np.testing.assert_allclose(out["Vhat"], V, rtol=0, atol=1e-12)
+    err, _ = okr.evaluate_assignment(f, np.arange(n))
+    assert err.max() < 1e-12
